@@ -116,8 +116,9 @@ typedef struct {
                                0 unless timing is enabled with treepm_set_timing          */
     int64_t evaluated;      /* pairs the last force call evaluated: both force kernels
                                skip list entries whose source lies at least r_cut from
-                               the group's bounding box (every pair they form adds
-                               exactly zero), so this is at most interactions            */
+                               the bounding box of the group (FP32: of the run of its
+                               particles that is evaluated together; every pair they
+                               form adds exactly zero), so this is at most interactions  */
     double latency_ms;      /* ensemble results only: completion minus submission (ms)    */
     double queue_ms;        /* ensemble results only: start of service minus submission,
                                the part of latency_ms spent queued (ms)                  */
@@ -184,10 +185,11 @@ int treepm_walk(treepm_ctx *ctx, void *hip_stream, treepm_stats *stats);
 /* Short-range force on every particle from its group's list (eq. 1, 2), written in the
  * caller's original particle order.  TREEPM_FP32 boxes work in lengths of r_cut, relative to
  * the group's cube centre: with s = (r / r_cut)^2 the pair law
- * G(s) = g_P3M(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) is G = (1 - s)^4 H(u), u = min(s + c, 1),
- * c a power of two at most (eps/r_cut)^2 / 64, and H comes from a table of cubic pieces built
- * on the host for the box (32 per octave of u, relative least-squares fits, zero at u = 1);
- * the rest of the pair arithmetic is FP32.  ax, ay, az: n values each of type out_prec
+ * G(s) = g_P3M(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) is G = p(u)^5, u = min(c + (1 - c) s, 1),
+ * c a power of two at most (eps/r_cut)^2 / 2, and p comes from a table of quadratic pieces built
+ * on the host for the box (64 per octave of u, relative least-squares fits, zero at u = 1);
+ * the rest of the pair arithmetic is FP32, with the sums over at most 192 list entries added up
+ * in FP64.  ax, ay, az: n values each of type out_prec
  * (TREEPM_FP32 = float, TREEPM_FP64 = double) and kind mem_kind.  Requires a walk
  * (ERR_STATE).  Uses no memory beyond what the build and walk allocated (device outputs). */
 int treepm_force_short(treepm_ctx *ctx, void *ax, void *ay, void *az, int out_prec,
@@ -196,7 +198,7 @@ int treepm_force_short(treepm_ctx *ctx, void *ax, void *ay, void *az, int out_pr
 /* Walk (as treepm_walk) and FP32 short-range force (as treepm_force_short with float outputs)
  * of n_boxes built boxes at once, with shared launches (Section 2.2 steps 5 and 6 for every
  * box): one traversal launch over the (box, group) pairs of all boxes, and one persistent
- * force launch per size class over all of them.  Each box keeps its own particles, tree,
+ * force launch over all boxes of equal eps / r_cut.  Each box keeps its own particles, tree,
  * lists and pair-law table, and its results equal, bit for bit, those of treepm_walk followed
  * by treepm_force_short on that box alone.  ctxs: n_boxes (1 .. 16) distinct contexts on one
  * device, each built (ERR_STATE) with precision TREEPM_FP32 (ERR_ARG); ax[b], ay[b], az[b]:
@@ -338,7 +340,7 @@ int treepm_ens_create(int device, size_t hbm_budget, int max_inflight, treepm_en
  * worker that has built a box hands it to a ready list instead of walking it, and whenever no
  * batch is running the next free worker takes every ready box (up to 16) and runs their walks
  * and forces with treepm_force_short_batch (Section 2.2 steps 5 and 6 for all of them in one
- * traversal launch and one force launch per size class) while the other workers build the
+ * traversal launch and one force launch per eps / r_cut) while the other workers build the
  * next boxes.  Results are those of the boxes alone, bit for bit.  Takes effect for boxes
  * built after the call.  ERR_ARG for a NULL server or another value of enable. */
 int treepm_ens_set_batching(treepm_ens *ens, int enable);

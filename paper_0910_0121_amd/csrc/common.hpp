@@ -212,55 +212,48 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n)
 
 struct ForceParams {
     double L, eps2, inv_eta, eta, rc2, rc;
-    uint32_t *kept; // per group, list entries that survived the cutoff cull
+    unsigned long long *pairs; // per group, the pairs left by the cutoff cull
 };
 
 // The FP32 pair law G(s) = g(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) (s = r^2 in units of
-// r_cut^2) as cubic pieces in u = min(s + c, 1): 2^kTabSegBits pieces per octave of u,
-// located by the bit pattern of u (index = (bits >> kTabShift) - base, position = the low
-// kTabShift bits), from u = c up to u = 1 (R = 2); the last entry is zero and takes u = 1.
-constexpr int kTabSegBits = 5;
+// r_cut^2) as quadratic pieces of p = G^(1/5) in u = min(c + (1 - c) s, 1): 2^kTabSegBits pieces
+// per octave of u, located by the bit pattern of u, from u = c up to u = 1 (R = 2); the last
+// entry is zero and takes u = 1.
+constexpr int kTabSegBits = 6;
 constexpr int kTabShift = 23 - kTabSegBits;
-constexpr uint32_t kTabMaxEntries = 1025; // 32 octaves: eps / r_cut down to 2^-13
+constexpr int kTabAddrShift = kTabShift - 2; // bits(edge) >> this = byte address of its entry
+constexpr int kTabMinExp = -27;              // c >= 2^-27: eps / r_cut down to 2^-13
 struct ForceTable {
-    const float4 *coef; // entries x (c0, c1, c2, c3), device
+    const float *coef;  // device: entries constant terms, then the linear, then the quadratic
     uint32_t entries;
-    uint32_t base;      // (bit pattern of c) >> kTabShift
-    float c;            // a power of two at most (eps/r_cut)^2 / 64
+    uint32_t base;      // byte address of the first entry: bits(c) >> kTabAddrShift
+    float c;            // a power of two at most (eps/r_cut)^2 / 2
 };
-// Fills the table for eps / r_cut (host, FP64 fit, rounded to float); false if eps / r_cut is
-// not positive or too small for kTabMaxEntries entries.
-bool build_force_table(double eps_over_rcut, std::vector<float4> &coef, uint32_t &base, float &c);
+// Fills the table for eps / r_cut (host, FP64 fit, rounded to float) and ft but for its device
+// pointer; false if eps / r_cut is not in [2^-13, 8).
+bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTable &ft);
 
-constexpr int kForceClasses = 8; // FP32 force: one class per blocking factor K = 1..8
-// Layout of the class buffer (u32 words): the class sizes, per class the kXcds + 1 part
-// starts (absolute word positions in the buffer), the per-(class, part) queue counters, the
-// (class, part, cost bucket) cursors, then per class its group ids (stride words apart),
-// each part longest first.
-constexpr uint32_t kClsCounts = 0;
-constexpr uint32_t kClsStarts = kClsCounts + kForceClasses;
-constexpr uint32_t kClsQueue = kClsStarts + kForceClasses * (kXcds + 1);
-constexpr uint32_t kClsBins = kClsQueue + kForceClasses * kXcds;
-constexpr uint32_t kClsLists = kClsBins + kForceClasses * kXcds * 64;
-// Classes, parts and longest-first order of the groups (len: list lengths), into cls.
-void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len, uint32_t *cls,
-                     uint32_t stride, hipStream_t s);
-// Empties the force queues (a fill kernel): on the call's stream before the class launches
-// fork onto the other streams.
-void launch_force_f32_prep(uint32_t *cls, hipStream_t s);
-// class_counts: host copy of the class sizes.  Classes are launched largest blocking factor
-// first, round-robin over the n_streams streams (the caller forks and joins them); each is a
-// persistent kernel of at most n_cu x (its waves per SIMD) workgroups.
-void launch_force_f32(NodeArrays nd, GroupArrays gr, uint32_t *cls, const uint32_t *class_counts,
-                      const uint64_t *off, const uint32_t *len, const uint32_t *entries,
-                      const double4 *ps, const uint32_t *pidx, ForceParams fp, ForceTable ft,
-                      void *rec, int rec64, int n_cu, const hipStream_t *streams,
-                      int n_streams);
-// The FP32 force of several boxes in one persistent launch per class: box b's class buffer,
-// lists and records as launch_force_f32 takes them for that box alone (queues zeroed by
-// launch_force_f32_prep).  Boxes whose tables have equal tab_id share one LDS copy; a
-// workgroup reloads the table when the next box's differs.  class_totals[K - 1] is the sum
-// over boxes of class K's size, max_entries the largest table.  float4 records only.
+// Layout of the queue buffer (u32 words): the kXcds + 1 part starts and the kXcds ends of the
+// parts' runs of split groups (absolute word positions in the buffer), the queue counters of
+// the split and of the other groups, the (part, cost bucket) cursors, then the group ids, each
+// part's longest first.
+// Queue counters lie 256 bytes apart: atomics on one cache line from all XCDs are served one
+// at a time, about 55 ns each.
+constexpr uint32_t kQueueStride = 64;
+constexpr uint32_t kClsStarts = 0;
+constexpr uint32_t kClsHeavyEnd = kClsStarts + kXcds + 1;
+constexpr uint32_t kClsQueue = kClsHeavyEnd + kXcds;
+constexpr uint32_t kClsBins = kClsQueue + 2 * kXcds * kQueueStride;
+constexpr uint32_t kClsLists = kClsBins + kXcds * 64;
+// Parts and longest-first order of the groups (len: list lengths; pairs: the box's
+// interactions, device), into cls (kClsLists + n_groups words).
+void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
+                     const unsigned long long *pairs, uint32_t *cls, hipStream_t s);
+// Empties the force queues and zeroes pairs (n_groups words), which the split groups add to,
+// and *sum, which launch_pair_stats adds to.
+void launch_force_prep(uint32_t *cls, unsigned long long *pairs, uint32_t n_groups,
+                       unsigned long long *sum, hipStream_t s);
+// One box as the FP32 force kernel reads it.
 struct ForceBox {
     NodeArrays nd;
     GroupArrays gr;
@@ -272,11 +265,14 @@ struct ForceBox {
     ForceParams fp;
     ForceTable ft;
     void *rec;
-    uint64_t tab_id;
+    int rec64; // rec holds double4 records
 };
-void launch_force_f32_multi(const ForceBox *boxes, int nb, const uint32_t *class_totals,
-                            uint32_t max_entries, int n_cu, const hipStream_t *streams,
-                            int n_streams);
+// A persistent launch of at most two workgroups per CU over the box's queues.
+void launch_force_f32(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
+// The same over nb <= kMaxBatch boxes with equal tables (descriptors in device memory; the
+// queues of all boxes are taken as one, through the first box's counters; n_groups in all).
+void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_groups, int n_cu,
+                            hipStream_t s);
 // rec of the force launchers: one record per particle in the caller's order (pidx), float4
 // (ax, ay, az, 0) or, with rec64, double4.  launch_force_out then writes them out: mode 0
 // float arrays, 1 double arrays (from float4 / double4 records), 2 kick (v += dt a into double
@@ -287,9 +283,9 @@ void launch_force_out(const void *rec, int mode, int64_t n, void *ax, void *ay, 
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,
                          const double *mj, const double *xg, double eta, ForceTable ft,
                          double *out, hipStream_t s);
-// sum over groups of count * kept (pairs the force kernel evaluated) into *out (device).
-void launch_kept_stats(GroupArrays gr, uint32_t n_groups, const uint32_t *kept,
-                       unsigned long long *out, hipStream_t s);
+// Adds the groups' pairs (pairs the force kernel evaluated) into *sum (device).
+void launch_pair_stats(uint32_t n_groups, const unsigned long long *pairs,
+                       unsigned long long *sum, hipStream_t s);
 void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
                       const uint32_t *len, const uint32_t *entries, const double4 *ps, const uint32_t *pidx,
                       ForceParams fp, void *rec, int rec64, hipStream_t s);

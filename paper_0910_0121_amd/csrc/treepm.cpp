@@ -49,7 +49,7 @@ struct treepm_ctx {
     bool idle_set = false;
     hipStream_t cur = nullptr;
     // The FP32 force's size classes run concurrently on the call's stream and these.
-    static constexpr int kSubStreams = 3;
+    static constexpr int kSubStreams = 1;
     hipStream_t sub[kSubStreams] = {};
     hipEvent_t fork = nullptr, join[kSubStreams] = {};
     std::string err;
@@ -82,7 +82,6 @@ struct treepm_ctx {
     // lists
     Buf off, glen, wctr, scan64, entries, wstats, overflow, gcells, cls, kept, kept_sum, out[3], bnd, runs;
     int last_force_prec = -1;
-    uint32_t class_counts[kForceClasses] = {};
     uint64_t n_entries = 0;
     // From the last walk on this context: total list entries, the longest list and the number
     // of groups, used to size the one-pass walk's pool (0: no walk yet, use two passes).
@@ -826,7 +825,7 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
     if ((e = reserve(c->overflow, 64)) != hipSuccess) return hip_fail(c, e, "flags");
     if ((e = reserve(c->gcells, ((size_t)G + 1) * 4)) != hipSuccess)
         return hip_fail(c, e, "group stats");
-    if ((e = reserve(c->cls, (kClsLists + kForceClasses * ((size_t)G + 1)) * 4)) != hipSuccess)
+    if ((e = reserve(c->cls, (kClsLists + (size_t)G + 1) * 4)) != hipSuccess)
         return hip_fail(c, e, "group classes");
     fill_u32(c->overflow.as<unsigned>(), 1, 0u, s);
     fill_u64(c->wstats.as<uint64_t>(), 4, 0ull, s);
@@ -898,17 +897,14 @@ int post_walk_results(treepm_ctx *c, hipStream_t s, WalkResults &wr)
     GroupArrays gr = groups_view(c);
     uint32_t *len = c->glen.as<uint32_t>(), *cls = c->cls.as<uint32_t>();
     launch_walk_stats(gr, G, len, c->gcells.as<uint32_t>(), c->wstats.as<unsigned long long>(), s);
-    launch_classify(gr, G, len, cls, G + 1, s);
+    launch_classify(gr, G, len, c->wstats.as<unsigned long long>() + 2, cls, s);
     return fetch_post(c, s, &wr.seq, {&wr.hov, c->overflow.p, sizeof wr.hov},
-                      {c->class_counts, cls + kClsCounts, sizeof c->class_counts},
                       {wr.hs, c->wstats.p, sizeof wr.hs});
 }
 
 int wait_walk_results(treepm_ctx *c, hipStream_t s, WalkResults &wr)
 {
     int rc = fetch_wait(c, s, wr.seq, {&wr.hov, c->overflow.p, sizeof wr.hov},
-                        {c->class_counts, c->cls.as<uint32_t>() + kClsCounts,
-                         sizeof c->class_counts},
                         {wr.hs, c->wstats.p, sizeof wr.hs});
     if (rc) return rc;
     if (wr.hov & 3u)
@@ -1265,25 +1261,42 @@ TREEPM_API int treepm_walk(treepm_ctx *c, void *hip_stream, treepm_stats *stats)
 
 namespace {
 
-// The FP32 pair-law table of the context's eps / eta, built on the host and copied to the
+// eps / r_cut to 36 bits: boxes of the same ratio get the same table whatever the rounding of
+// the two lengths, and a change of 2^-36 in eps is far below the table's own rounding.
+double table_key(const treepm_params &P)
+{
+    int e;
+    const double f = std::frexp(P.eps / P.r_cut, &e);
+    return std::ldexp(std::nearbyint(std::ldexp(f, 36)), e - 36);
+}
+
+// The FP32 pair-law table of the context's eps / r_cut, built on the host and copied to the
 // device once per parameter set.
 int ensure_table(treepm_ctx *c, hipStream_t s)
 {
-    const double key = c->prm.eps / c->prm.r_cut;
+    const double key = table_key(c->prm);
     if (c->tab.p && c->tab_key == key) return TREEPM_OK;
-    std::vector<float4> coef;
-    uint32_t base = 0;
-    float cc = 0.f;
-    if (!build_force_table(key, coef, base, cc))
+    std::vector<float> coef;
+    ForceTable ft{};
+    if (!build_force_table(key, coef, ft))
         return fail(c, TREEPM_ERR_ARG, "eps / r_cut = %g is outside the FP32 table's range", key);
-    hipError_t e = reserve(c->tab, coef.size() * sizeof(float4));
+    hipError_t e = reserve(c->tab, coef.size() * sizeof(float));
     if (e != hipSuccess) return hip_fail(c, e, "pair-law table");
-    HIPCHK(c, hipMemcpyAsync(c->tab.p, coef.data(), coef.size() * sizeof(float4),
+    HIPCHK(c, hipMemcpyAsync(c->tab.p, coef.data(), coef.size() * sizeof(float),
                              hipMemcpyHostToDevice, s));
     HIPCHK(c, hipStreamSynchronize(s)); // coef is a host temporary
-    c->ftab = ForceTable{c->tab.as<float4>(), (uint32_t)coef.size(), base, cc};
+    c->ftab = ft;
+    c->ftab.coef = c->tab.as<float>();
     c->tab_key = key;
     return TREEPM_OK;
+}
+
+// The context as the FP32 force kernel reads it (ensure_table has run, kept is reserved).
+ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
+{
+    return ForceBox{nodes_view(c), groups_view(c), c->cls.as<uint32_t>(),
+                    c->off.as<uint64_t>(), c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
+                    c->psrc.as<double4>(), c->idx.as<uint32_t>(), fp, c->ftab, rec, rec64};
 }
 
 } // namespace
@@ -1328,35 +1341,19 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     GroupArrays gr = groups_view(c);
     double eta = 0.5 * P.r_cut;
     {
-        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 4);
+        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
         if (e == hipSuccess) e = reserve(c->kept_sum, 64);
         if (e != hipSuccess) return hip_fail(c, e, "force statistics");
     }
     ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
-                   c->kept.as<uint32_t>()};
+                   c->kept.as<unsigned long long>()};
+    launch_force_prep(c->cls.as<uint32_t>(), fp.pairs, c->n_groups,
+                      c->kept_sum.as<unsigned long long>(), s);
     const int rec64 = out_prec != TREEPM_FP32;
     void *rec = c->rec.p; // n x 32 bytes since the build
     if (P.precision == TREEPM_FP32) {
         if ((rc = ensure_table(c, s))) return rc;
-        hipStream_t streams[1 + treepm_ctx::kSubStreams] = {s};
-        int ns = 1;
-        launch_force_f32_prep(c->cls.as<uint32_t>(), s); // queues, before the fork
-        if (c->fork) {
-            HIPCHK(c, hipEventRecord(c->fork, s));
-            for (int i = 0; i < treepm_ctx::kSubStreams; ++i) {
-                HIPCHK(c, hipStreamWaitEvent(c->sub[i], c->fork, 0));
-                streams[ns++] = c->sub[i];
-            }
-        }
-        launch_force_f32(nd, gr, c->cls.as<uint32_t>(), c->class_counts, c->off.as<uint64_t>(),
-                         c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
-                         c->psrc.as<double4>(), c->idx.as<uint32_t>(), fp, c->ftab, rec, rec64,
-                         c->n_cu, streams, ns);
-        if (c->fork)
-            for (int i = 0; i < treepm_ctx::kSubStreams; ++i) {
-                HIPCHK(c, hipEventRecord(c->join[i], c->sub[i]));
-                HIPCHK(c, hipStreamWaitEvent(s, c->join[i], 0));
-            }
+        launch_force_f32(force_box(c, fp, rec, rec64), c->n_groups, c->n_cu, s);
     } else
         launch_force_f64(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
                          c->entries.as<uint32_t>(),
@@ -1368,7 +1365,7 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     launch_force_out(rec, out_prec, (int64_t)c->n, dst[0], dst[1], dst[2], kick_dt, s);
     HIPCHK(c, hipGetLastError());
     record(c, 5, s);
-    launch_kept_stats(gr, c->n_groups, c->kept.as<uint32_t>(),
+    launch_pair_stats(c->n_groups, c->kept.as<unsigned long long>(),
                           c->kept_sum.as<unsigned long long>(), s);
     c->last_force_prec = P.precision;
     c->ev_valid[2] = c->timing;
@@ -1547,24 +1544,22 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
     return TREEPM_OK;
 }
 
-// The FP32 short-range force of walked boxes with one persistent launch per size class over
-// all of them (forked over the leader's sub-streams), then per box the quadrupole terms, the
-// float outputs and the statistics; host outputs are copied back and waited for.
+// The FP32 short-range force of walked boxes with one persistent launch per pair-law table over
+// all boxes that share it, then per box the quadrupole terms, the float outputs and the
+// statistics; host outputs are copied back and waited for.
 int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *ay,
                 float *const *az, int mem_kind, hipStream_t s)
 {
     treepm_ctx *lead = cs[0];
     int rc;
     std::vector<ForceBox> fb(nb);
-    uint32_t totals[kForceClasses] = {};
-    uint32_t max_entries = 0;
     std::vector<std::array<float *, 3>> dst(nb);
     for (int b = 0; b < nb; ++b) {
         treepm_ctx *c = cs[b];
         Bind bind(c, s);
         const treepm_params &P = c->prm;
         if ((rc = ensure_table(c, s))) return rc;
-        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 4);
+        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
         if (e == hipSuccess) e = reserve(c->kept_sum, 64);
         if (e != hipSuccess) return hip_fail(c, e, "force statistics");
         dst[b] = {ax[b], ay[b], az[b]};
@@ -1575,44 +1570,30 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
                 dst[b][a] = c->out[a].as<float>();
             }
         const double eta = 0.5 * P.r_cut;
-        ForceBox &F = fb[b];
-        F.nd = nodes_view(c);
-        F.gr = groups_view(c);
-        F.cls = c->cls.as<uint32_t>();
-        F.off = c->off.as<uint64_t>();
-        F.len = c->glen.as<uint32_t>();
-        F.entries = c->entries.as<uint32_t>();
-        F.ps = c->psrc.as<double4>();
-        F.pidx = c->idx.as<uint32_t>();
-        F.fp = ForceParams{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
-                           c->kept.as<uint32_t>()};
-        F.ft = c->ftab;
-        F.rec = c->rec.p;
-        uint64_t id;
-        std::memcpy(&id, &c->tab_key, sizeof id);
-        F.tab_id = id;
-        max_entries = std::max(max_entries, c->ftab.entries);
-        for (int k = 0; k < kForceClasses; ++k) totals[k] += c->class_counts[k];
-        launch_force_f32_prep(F.cls, s);
+        const ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
+                             c->kept.as<unsigned long long>()};
+        fb[b] = force_box(c, fp, c->rec.p, 0);
+        launch_force_prep(fb[b].cls, fp.pairs, c->n_groups,
+                          c->kept_sum.as<unsigned long long>(), s);
     }
+    // the boxes by table: each launch's workgroups then load one table
+    std::vector<int> order(nb);
+    for (int b = 0; b < nb; ++b) order[b] = b;
+    std::stable_sort(order.begin(), order.end(),
+                     [&](int x, int y) { return cs[x]->tab_key < cs[y]->tab_key; });
+    std::vector<ForceBox> sorted(nb);
+    for (int k = 0; k < nb; ++k) sorted[k] = fb[order[k]];
     ForceBox *dev = nullptr;
     const size_t at_force = 2 * (size_t)kMaxBatch * sizeof(WalkBox);
-    if ((rc = upload(lead, s, fb, at_force, &dev))) return rc;
-    hipStream_t streams[1 + treepm_ctx::kSubStreams] = {s};
-    int ns = 1;
-    if (lead->fork) {
-        HIPCHK(lead, hipEventRecord(lead->fork, s));
-        for (int i = 0; i < treepm_ctx::kSubStreams; ++i) {
-            HIPCHK(lead, hipStreamWaitEvent(lead->sub[i], lead->fork, 0));
-            streams[ns++] = lead->sub[i];
-        }
+    if ((rc = upload(lead, s, sorted, at_force, &dev))) return rc;
+    for (int k = 0; k < nb;) {
+        int k1 = k;
+        uint32_t groups = 0;
+        for (; k1 < nb && cs[order[k1]]->tab_key == cs[order[k]]->tab_key; ++k1)
+            groups += cs[order[k1]]->n_groups;
+        launch_force_f32_multi(dev + k, k1 - k, groups, lead->n_cu, s);
+        k = k1;
     }
-    launch_force_f32_multi(dev, nb, totals, max_entries, lead->n_cu, streams, ns);
-    if (lead->fork)
-        for (int i = 0; i < treepm_ctx::kSubStreams; ++i) {
-            HIPCHK(lead, hipEventRecord(lead->join[i], lead->sub[i]));
-            HIPCHK(lead, hipStreamWaitEvent(s, lead->join[i], 0));
-        }
     for (int b = 0; b < nb; ++b) {
         treepm_ctx *c = cs[b];
         const ForceBox &F = fb[b];
@@ -1621,7 +1602,7 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
                         c->n_q.as<double>(), F.fp, F.rec, 0, 0, s);
         launch_force_out(F.rec, TREEPM_FP32, (int64_t)c->n, dst[b][0], dst[b][1], dst[b][2],
                          0.0, s);
-        launch_kept_stats(F.gr, c->n_groups, c->kept.as<uint32_t>(),
+        launch_pair_stats(c->n_groups, c->kept.as<unsigned long long>(),
                           c->kept_sum.as<unsigned long long>(), s);
         c->last_force_prec = TREEPM_FP32;
         c->ev_valid[1] = c->ev_valid[2] = false;
@@ -2127,25 +2108,23 @@ TREEPM_API int treepm_pairwise_f32(const treepm_params *params, int device, int6
     if (rc) return rc;
     if (n_i < 1 || n_j < 1 || n_i * n_j > (int64_t)1 << 28 || !xi || !xj || !mj || !xg || !out)
         return TREEPM_ERR_ARG;
-    std::vector<float4> coef;
-    uint32_t tbase = 0;
-    float tc = 0.f;
-    if (!build_force_table(params->eps / params->r_cut, coef, tbase, tc))
-        return TREEPM_ERR_ARG;
+    std::vector<float> coef;
+    ForceTable ft{};
+    if (!build_force_table(table_key(*params), coef, ft)) return TREEPM_ERR_ARG;
     if (hipSetDevice(device) != hipSuccess) return TREEPM_ERR_DEVICE;
-    size_t bt = coef.size() * sizeof(float4), bi = (size_t)n_i * 3 * 8,
+    size_t bt = (coef.size() * sizeof(float) + 15) / 16 * 16, bi = (size_t)n_i * 3 * 8,
            bj = (size_t)n_j * 3 * 8, bm = (size_t)n_j * 8, bo = (size_t)n_i * n_j * 3 * 8;
     char *d = nullptr;
     if (hipMalloc(&d, bt + bi + bj + bm + bo) != hipSuccess) return TREEPM_ERR_OOM;
-    float4 *dtab = (float4 *)d;
+    float *dtab = (float *)d;
     double *dxi = (double *)(d + bt), *dxj = (double *)(d + bt + bi),
            *dmj = (double *)(d + bt + bi + bj), *dout = (double *)(d + bt + bi + bj + bm);
-    hipError_t e = hipMemcpy(dtab, coef.data(), bt, hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(dtab, coef.data(), coef.size() * sizeof(float), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dxi, xi, bi, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dxj, xj, bj, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(dmj, mj, bm, hipMemcpyHostToDevice);
     if (e == hipSuccess) {
-        const ForceTable ft{dtab, (uint32_t)coef.size(), tbase, tc};
+        ft.coef = dtab;
         launch_pairwise_f32(n_i, dxi, n_j, dxj, dmj, xg, 0.5 * params->r_cut, ft, dout,
                             nullptr);
         e = hipGetLastError();
