@@ -57,6 +57,20 @@ struct GroupArrays {
     double *lox, *loy, *loz, *hix, *hiy, *hiz;
 };
 
+// Workgroups are dealt to the 8 XCDs (each with its own L2) round-robin by block index.
+// xcd_block renumbers block b of n so that each XCD takes a contiguous run: neighbouring
+// groups (key order) then share one L2.  A bijection on [0, n).
+constexpr uint32_t kXcds = 8;
+__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n)
+{
+    const uint32_t q = n / kXcds, r = n % kXcds, x = b % kXcds;
+    return x * q + (x < r ? x : r) + b / kXcds;
+}
+
+// Work counters that many waves share lie kQueueStride words (256 bytes) apart: atomics on one
+// cache line from all XCDs are served one at a time, 40 to 55 ns each.
+constexpr uint32_t kQueueStride = 64;
+
 // ------------------------------------------------------------------ launchers (k_scan.hip)
 // Exclusive prefix sum in place over n values; the total is written to *total (device).
 // tmp must hold scan_tmp_elems(n) values of the same type.
@@ -163,7 +177,8 @@ void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, Wal
 // One pass: n_waves waves write the lists into chunks of `chunk` entries taken from the
 // pool entries[0, pool_cap); a group is walked into the wave's current chunk if at least
 // `reserve` entries are left there, else (or if it did not fit) into a fresh chunk.  Sets bit 4 of *overflow if a list or the pool ran out of room
-// (the lists are then incomplete).  counters holds kXcds + 2 words (8-byte aligned).
+// (the lists are then incomplete).  counters holds kWalkCounterWords words (8-byte aligned).
+constexpr uint32_t kWalkCounterWords = (kXcds + 1) * kQueueStride;
 void launch_walk_pool(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
                       uint32_t n_waves, uint64_t pool_cap, uint64_t chunk, uint64_t reserve,
                       uint32_t *counters, uint64_t *off, uint32_t *len, uint32_t *entries,
@@ -193,23 +208,13 @@ struct WalkBox {
 void launch_walk_count_multi(const WalkBox *boxes, int nb, uint32_t total, hipStream_t s);
 void launch_walk_emit_multi(const WalkBox *boxes, int nb, uint32_t total, hipStream_t s);
 // One pass over all items: n_waves waves take items in batches from kXcds counters (zeroed
-// here; counters holds kXcds words) and write each box's lists into chunks of that box's
+// here; counters holds kXcds * kQueueStride words) and write each box's lists into chunks of that box's
 // pool.  A box whose list or pool runs out of room gets bit 4 of its overflow flag; the other
 // boxes are not affected.
 void launch_walk_pool_multi(const WalkBox *boxes, int nb, uint32_t total, uint32_t n_waves,
                             uint32_t *counters, hipStream_t s);
 
 // ------------------------------------------------------------------ launchers (k_force.hip)
-// Workgroups are dealt to the 8 XCDs (each with its own L2) round-robin by block index.
-// xcd_block renumbers block b of n so that each XCD takes a contiguous run: neighbouring
-// groups (key order) then share one L2.  A bijection on [0, n).
-constexpr uint32_t kXcds = 8;
-__device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n)
-{
-    const uint32_t q = n / kXcds, r = n % kXcds, x = b % kXcds;
-    return x * q + (x < r ? x : r) + b / kXcds;
-}
-
 struct ForceParams {
     double L, eps2, inv_eta, eta, rc2, rc;
     unsigned long long *pairs; // per group, the pairs left by the cutoff cull
@@ -237,9 +242,6 @@ bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTabl
 // parts' runs of split groups (absolute word positions in the buffer), the queue counters of
 // the split and of the other groups, the (part, cost bucket) cursors, then the group ids, each
 // part's longest first.
-// Queue counters lie 256 bytes apart: atomics on one cache line from all XCDs are served one
-// at a time, about 55 ns each.
-constexpr uint32_t kQueueStride = 64;
 constexpr uint32_t kClsStarts = 0;
 constexpr uint32_t kClsHeavyEnd = kClsStarts + kXcds + 1;
 constexpr uint32_t kClsQueue = kClsHeavyEnd + kXcds;

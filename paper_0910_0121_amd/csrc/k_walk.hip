@@ -40,7 +40,10 @@ namespace {
 
 constexpr int kStackCap = 1024;
 constexpr int kStackReserve = 7 * kMaxLevel; // a depth-first descent from the root's children
-constexpr uint32_t kWalkBatch = 4;
+// Groups taken per atomic in the one-pass walk, from counters kQueueStride words apart: 1, 2
+// and 4 take 2.01, 1.99 and 2.07 ms on the 256^3 clustered box (4 with the counters and the
+// pool's in one cache line: 2.47 ms, bound by its 88,000 atomics).
+constexpr uint32_t kWalkBatch = 2;
 
 // |wrap(v)| for |v| <= L (both points in [0, L)): min(|v|, L - |v|).  Bit for bit the
 // absolute value of the two-sided wrap (v - L if v >= L/2, v + L if v < -L/2, else v):
@@ -312,7 +315,7 @@ __global__ __launch_bounds__(64) void k_walk_pool(const WalkNode *__restrict__ w
         const uint32_t hi = (uint32_t)((uint64_t)n_groups * (x + 1) / kXcds);
         for (;;) {
             uint32_t t = 0;
-            if (threadIdx.x == 0) t = atomicAdd(&counters[x], kWalkBatch);
+            if (threadIdx.x == 0) t = atomicAdd(&counters[x * kQueueStride], kWalkBatch);
             t = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
             if (t >= hi - lo) break;
             const uint32_t g1 = lo + t + kWalkBatch < hi ? lo + t + kWalkBatch : hi;
@@ -419,7 +422,7 @@ __global__ __launch_bounds__(64) void k_walk_pool_multi(const WalkBox *__restric
         const uint32_t hi = (uint32_t)((uint64_t)total * (x + 1) / kXcds);
         for (;;) {
             uint32_t k = 0;
-            if (threadIdx.x == 0) k = atomicAdd(&counters[x], kWalkBatch);
+            if (threadIdx.x == 0) k = atomicAdd(&counters[x * kQueueStride], kWalkBatch);
             k = (uint32_t)__builtin_amdgcn_readfirstlane((int)k);
             if (k >= hi - lo) break;
             const uint32_t t1 = lo + k + kWalkBatch < hi ? lo + k + kWalkBatch : hi;
@@ -490,25 +493,28 @@ __global__ __launch_bounds__(256) void k_walk_stats(GroupArrays gr, uint32_t n_g
         const unsigned long long o = __shfl_xor(mx, d, 64);
         mx = o > mx ? o : mx;
     }
-    if ((threadIdx.x & 63) == 0) atomicMax(&stats[3], mx);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
         c += __shfl_xor(c, d, 64);
         p += __shfl_xor(p, d, 64);
         it += __shfl_xor(it, d, 64);
     }
-    __shared__ unsigned long long sm[3][4];
+    __shared__ unsigned long long sm[4][4];
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         sm[0][w] = c;
         sm[1][w] = p;
         sm[2][w] = it;
+        sm[3][w] = mx;
     }
     __syncthreads();
     if (threadIdx.x < 3) {
         unsigned long long t = sm[threadIdx.x][0] + sm[threadIdx.x][1] + sm[threadIdx.x][2] +
                                sm[threadIdx.x][3];
         atomicAdd(&stats[threadIdx.x], t);
+    } else if (threadIdx.x == 3) {
+        const unsigned long long a = max(sm[3][0], sm[3][1]), b = max(sm[3][2], sm[3][3]);
+        atomicMax(&stats[3], max(a, b));
     }
 }
 
@@ -545,15 +551,15 @@ void launch_walk_pool(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, Wal
                       unsigned *overflow, uint32_t *gcells, hipStream_t s)
 {
     if (!n_groups) return;
-    fill_u32(counters, kXcds + 2, 0u, s);
+    fill_u32(counters, kWalkCounterWords, 0u, s);
     if (wp.open)
         k_walk_pool<1><<<n_waves, 64, 0, s>>>(wn, gr, n_groups, wp, counters,
-                                              (unsigned long long *)(counters + kXcds),
+                                              (unsigned long long *)(counters + kXcds * kQueueStride),
                                               pool_cap, chunk, reserve, off, len, entries,
                                               overflow, gcells);
     else
         k_walk_pool<0><<<n_waves, 64, 0, s>>>(wn, gr, n_groups, wp, counters,
-                                              (unsigned long long *)(counters + kXcds),
+                                              (unsigned long long *)(counters + kXcds * kQueueStride),
                                               pool_cap, chunk, reserve, off, len, entries,
                                               overflow, gcells);
 }
@@ -572,7 +578,7 @@ void launch_walk_pool_multi(const WalkBox *boxes, int nb, uint32_t total, uint32
                             uint32_t *counters, hipStream_t s)
 {
     if (!total) return;
-    fill_u32(counters, kXcds, 0u, s);
+    fill_u32(counters, kXcds * kQueueStride, 0u, s);
     k_walk_pool_multi<<<n_waves, 64, 0, s>>>(boxes, nb, total, counters);
 }
 
@@ -581,7 +587,7 @@ void launch_walk_stats(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
 {
     if (!n_groups) return;
     unsigned b = (n_groups + 255) / 256;
-    k_walk_stats<<<b < 256 ? b : 256, 256, 0, s>>>(gr, n_groups, len, gcells, stats);
+    k_walk_stats<<<b < 128 ? b : 128, 256, 0, s>>>(gr, n_groups, len, gcells, stats);
 }
 
 } // namespace tpm

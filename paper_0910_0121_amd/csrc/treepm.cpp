@@ -818,7 +818,7 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
     hipError_t e;
     if ((e = reserve(c->off, ((size_t)G + 1) * 8)) != hipSuccess) return hip_fail(c, e, "offsets");
     if ((e = reserve(c->glen, ((size_t)G + 1) * 4)) != hipSuccess) return hip_fail(c, e, "lengths");
-    if ((e = reserve(c->wctr, 128)) != hipSuccess) return hip_fail(c, e, "counters");
+    if ((e = reserve(c->wctr, kWalkCounterWords * 4)) != hipSuccess) return hip_fail(c, e, "counters");
     if ((e = reserve(c->scan64, (scan_tmp_elems((size_t)G + 1) + 64) * 8)) != hipSuccess)
         return hip_fail(c, e, "scan buffer");
     if ((e = reserve(c->wstats, 64)) != hipSuccess) return hip_fail(c, e, "stats");
@@ -1445,7 +1445,7 @@ WalkBox walk_box(treepm_ctx *c, const BoxWalk &bw, uint32_t g0)
     w.len = c->glen.as<uint32_t>();
     w.entries = c->entries.as<uint32_t>();
     w.gcells = c->gcells.as<uint32_t>();
-    w.pool_next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() + kXcds);
+    w.pool_next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() + kXcds * kQueueStride);
     w.pool_cap = bw.pool;
     w.chunk = bw.chunk;
     w.reserve = bw.reserve_len;
@@ -1487,7 +1487,7 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
     {
         Bind bind(lead, s);
         const size_t bytes = (2 * (size_t)kMaxBatch) * sizeof(WalkBox) +
-                             (size_t)kMaxBatch * sizeof(ForceBox) + 256;
+                             (size_t)kMaxBatch * sizeof(ForceBox) + kWalkCounterWords * 4;
         hipError_t e = reserve(lead->bdesc, bytes);
         if (e != hipSuccess) return hip_fail(lead, e, "batch descriptors");
     }
