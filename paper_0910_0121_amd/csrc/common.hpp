@@ -14,8 +14,6 @@ constexpr uint32_t kCellTag = 0x80000000u; // list entry: node index | tag, else
 constexpr int kSortBits = 8;               // radix digit width
 constexpr int kSortBins = 1 << kSortBits;
 constexpr int kSortThreads = 256;
-constexpr int kSortItems = 16;
-constexpr int kSortTile = kSortThreads * kSortItems;
 
 // Flags raised by the validation/key kernel.
 constexpr unsigned kFlagNonFinite = 1u; // non-finite position or mass, or mass <= 0
@@ -97,19 +95,27 @@ void launch_keys(int64_t n, const double *x, const double *y, const double *z, c
 size_t sort_hist_elems(int64_t n);
 void radix_sort(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt, uint32_t *idx_alt,
                 uint32_t *hist, uint32_t *scan_tmp, hipStream_t s);
-// The sort in two steps: stable passes over bits [kRunBits, 64) only, then each run of equal
+// The sort in two steps: stable passes over bits [run_bits, 64) only, then each run of equal
 // high bits sorted by (key, index) in place.  Returns true if the result is in key_alt /
 // idx_alt (an odd number of passes).  long_runs holds long_cap entries; flags (device, two
-// words) ends with flags[1] != 0 if a run could not be sorted this way: the order is then
-// incomplete and radix_sort (on the returned arrays) must follow.
-constexpr int kRunBits = 24;
+// words, zeroed by the caller) ends with flags[1] != 0 if a run could not be sorted this way:
+// the order is then incomplete, and a sort with fewer run_bits (or radix_sort) on the returned
+// arrays must follow (equal keys are still in index order).
+// sort_run_bits: the run_bits to try first, 40, 32 and 24 up to 2^16, 2^21 and more particles
+// (three, four or five passes; cells of level 8, 10.7 or 13.3).  In a clustered box the fullest
+// cell grows about as the square of its side: 43 particles at level 13.3 of the 256^3 box, and
+// so a few hundred at most at these limits, below kLongRun.
+int sort_run_bits(int64_t n);
 constexpr uint32_t kShortRun = 8; // the register sorting network in k_fix_runs has 8 inputs
 constexpr uint32_t kLongRun = 2048;
-bool radix_sort_high(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
+bool radix_sort_high(int64_t n, int run_bits, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
                      uint32_t *idx_alt, uint32_t *hist, uint32_t *scan_tmp, uint2 *long_runs,
                      uint32_t long_cap, unsigned *flags, hipStream_t s);
+// Zeroes flags (6 words) and *mmax and resets the groups' extremes (launch_groups).
+void launch_build_init(unsigned *flags, unsigned long long *mmax, unsigned *min_level,
+                       unsigned *max_count, hipStream_t s);
 // Writes the key-ordered records psrc (x, y, z, m) and the bit pattern of the largest mass
-// into *mmax (the particle mesh scales its fixed-point sums by it).
+// into *mmax, zeroed by the caller (the particle mesh scales its fixed-point sums by it).
 void launch_permute(int64_t n, const uint32_t *idx, const double4 *rec, double4 *psrc,
                     unsigned long long *mmax, hipStream_t s);
 void launch_root(NodeArrays nd, uint32_t n, double L, hipStream_t s);
@@ -122,12 +128,6 @@ void launch_split(NodeArrays nd, const uint64_t *key, uint32_t lo, uint32_t hi, 
 // Emit children of nodes [lo, hi) at base + exclusive prefix in cnt, from the bounds in bnd.
 void launch_emit(NodeArrays nd, const uint32_t *bnd, uint32_t lo, uint32_t hi, int level,
                  uint32_t base, const uint32_t *cnt, double L, hipStream_t s);
-// Moments of the nodes [lo, hi) of one level, deepest level first: mass, position sums S
-// (comx/comy/comz; the centre of mass S / M goes to nsrc and the walk records wn).
-// derive = 1 for a tree from launch_tree_emit: nchild and internal counts are set here, the
-// children of the level's nodes being the nodes [child_first[lo], child_end).
-void launch_moments(NodeArrays nd, const double4 *ps, uint32_t lo, uint32_t hi, int derive,
-                    uint32_t child_end, WalkNode *wn, hipStream_t s);
 // The octree straight from the sorted keys (n >= 1, n_leaf - 1 <= kTreeWin): the same nodes in
 // the same order as the level-by-level split.  launch_tree_levels writes per particle the
 // levels of the nodes that start there and its leaf's count (sl, n words), per block of tree_blocks(n) the counts
@@ -136,24 +136,30 @@ void launch_moments(NodeArrays nd, const double4 *ps, uint32_t lo, uint32_t hi, 
 // writes every node but nchild and the internal counts (left to the moments with derive = 1).
 constexpr int kTreeWin = 256;
 struct TreeOffsets {
-    uint32_t off[kMaxLevel + 3]; // first node of each level; off[22] = off[23] = node count
+    uint32_t off[kMaxLevel + 3]; // first node of each level; past the last, the node count
 };
+// Moments of all nodes, deepest level first (levels 0 .. max_level at to.off): mass, position
+// sums S (comx/comy/comz; the centre of mass S / M goes to nsrc and the walk records wn).
+// derive = 1 for a tree from launch_tree_emit: nchild and internal counts are set here, the
+// children of a level's nodes being the next level's from child_first on.
+void launch_moments(NodeArrays nd, const double4 *ps, const TreeOffsets &to, int max_level,
+                    int derive, WalkNode *wn, hipStream_t s);
 uint32_t tree_blocks(int64_t n);
+// It also zeroes gstart (n words) and gflag (n + 1) for launch_group_mark.
 void launch_tree_levels(const uint64_t *key, uint32_t n, int n_leaf, uint32_t *sl, uint32_t *blk,
-                        uint32_t *tot, hipStream_t s);
+                        uint32_t *tot, uint32_t *gstart, uint32_t *gflag, hipStream_t s);
 void launch_tree_emit(NodeArrays nd, const uint64_t *key, const uint32_t *sl, const uint32_t *blk,
                       const TreeOffsets &to, uint32_t n, double L, hipStream_t s);
-// Groups: mark in gstart[first] (n values, zeroed here) every maximal node with
-// count <= n_crit or no children; then compact in key order.
+// Groups: mark in gstart[first] and gflag[first] (n and n + 1 words, zeroed here if `clear`)
+// every maximal node with count <= n_crit or no children.  With gpos the prefix sums of gflag
+// and *n_groups their total (device), launch_groups then lists the first cap groups in key
+// order, with their boxes, lowers *min_level to the shallowest group level and raises
+// *max_count to the largest group.
 void launch_group_mark(NodeArrays nd, uint32_t n_nodes, int n_crit, uint32_t *gstart,
-                       uint32_t *gflag, int64_t n, hipStream_t s);
-void launch_group_compact(const uint32_t *gstart, const uint32_t *gpos, int64_t n,
-                          uint32_t *gnode, hipStream_t s);
-// Also lowers *min_level to the shallowest group level and raises *max_count to the
-// largest group.
-void launch_group_bbox(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const double4 *ps,
-                       unsigned *min_level,
-                       unsigned *max_count, hipStream_t s);
+                       uint32_t *gflag, int64_t n, bool clear, hipStream_t s);
+void launch_groups(NodeArrays nd, GroupArrays gr, const uint32_t *gstart, const uint32_t *gpos,
+                   int64_t n, const uint32_t *n_groups, uint32_t cap, const double4 *ps,
+                   unsigned *min_level, unsigned *max_count, hipStream_t s);
 
 // ------------------------------------------------------------------ launchers (k_walk.hip)
 // open = 0: fixed angle, th2 = theta^2.  open = 1: theta(d) of eq. (12) from eta = r_cut/2,

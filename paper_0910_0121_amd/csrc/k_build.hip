@@ -68,6 +68,9 @@ __global__ __launch_bounds__(256) void k_keys(int64_t n, const double *__restric
     if (f) atomicOr(flags, f);
 }
 
+// Digit counts of each tile (kSortThreads x ITEMS keys): by digit then tile for the device-wide
+// scan of many tiles, by tile then digit (FUSED) where k_scatter adds them up itself.
+template <int ITEMS, bool FUSED>
 __global__ __launch_bounds__(kSortThreads) void k_hist(const uint64_t *__restrict__ key,
                                                        int64_t n, int shift,
                                                        uint32_t *__restrict__ hist,
@@ -76,21 +79,28 @@ __global__ __launch_bounds__(kSortThreads) void k_hist(const uint64_t *__restric
     __shared__ uint32_t h[kSortBins];
     h[threadIdx.x] = 0;
     __syncthreads();
-    int64_t base = (int64_t)blockIdx.x * kSortTile;
-    for (int it = 0; it < kSortItems; ++it) {
+    int64_t base = (int64_t)blockIdx.x * (kSortThreads * ITEMS);
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
         int64_t k = base + (int64_t)it * kSortThreads + threadIdx.x;
         if (k < n) atomicAdd(&h[(uint32_t)(key[k] >> shift) & (kSortBins - 1)], 1u);
     }
     __syncthreads();
-    hist[(size_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
+    if (FUSED)
+        hist[(size_t)blockIdx.x * kSortBins + threadIdx.x] = h[threadIdx.x];
+    else
+        hist[(size_t)threadIdx.x * nblocks + blockIdx.x] = h[threadIdx.x];
 }
 
-// Stable scatter of one tile.  Wave w takes elements w * 1024 + it * 64 + lane of the tile
-// (iteration it = 0..15), which is also their order for stability.  Each wave ranks its
+// Stable scatter of one tile.  Wave w takes elements w * 64 ITEMS + it * 64 + lane of the tile
+// (iteration it = 0 .. ITEMS - 1), which is also their order for stability.  Each wave ranks its
 // elements among equal digits with ballots and a wave-private running count per digit (no
 // block barrier inside the loop); the per-wave counts then give each wave's base inside
 // each digit's run.  The tile is reordered by digit in LDS and written out in that order,
-// so elements with equal digits leave as contiguous runs.
+// so elements with equal digits leave as contiguous runs.  FUSED: hist holds the tiles' raw
+// counts, and thread d adds up digit d's over all tiles (at most kSortFusedTiles of them) itself,
+// which saves the scan's launches.
+template <int ITEMS, bool FUSED>
 __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint64_t *__restrict__ key,
                                                           const uint32_t *__restrict__ idx,
                                                           int64_t n, int shift,
@@ -99,32 +109,45 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint64_t *__rest
                                                           uint64_t *__restrict__ key_out,
                                                           uint32_t *__restrict__ idx_out)
 {
-    constexpr int kWaves = kSortThreads / 64;
-    __shared__ uint64_t skey[kSortTile];
-    __shared__ uint32_t sidx[kSortTile];
+    constexpr int kWaves = kSortThreads / 64, kTile = kSortThreads * ITEMS;
+    __shared__ uint64_t skey[kTile];
+    __shared__ uint32_t sidx[kTile];
     __shared__ uint32_t goff[kSortBins];  // global offset of this tile's digit-d run
     __shared__ uint32_t loff[kSortBins];  // local offset of digit d inside the tile
     __shared__ uint32_t wcnt[kWaves][kSortBins]; // per-wave digit counts, then wave bases
     __shared__ uint32_t wsum[kWaves];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int64_t base = (int64_t)blockIdx.x * kSortTile;
-    goff[tid] = hist[(size_t)tid * nblocks + blockIdx.x];
+    const int64_t base = (int64_t)blockIdx.x * kTile;
+    uint32_t digits = 0; // FUSED: keys with digit tid in all tiles
+    if (FUSED) {
+        uint32_t before = 0;
+        const uint32_t *h = hist + tid;
+#pragma unroll 8
+        for (uint32_t b = 0; b < nblocks; ++b) {
+            const uint32_t c = h[(size_t)b * kSortBins];
+            digits += c;
+            before += b < blockIdx.x ? c : 0u;
+        }
+        goff[tid] = before;
+    } else {
+        goff[tid] = hist[(size_t)tid * nblocks + blockIdx.x];
+    }
 #pragma unroll
     for (int q = 0; q < kWaves; ++q) wcnt[q][tid] = 0;
     __syncthreads();
     const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    const int64_t wb = base + (int64_t)w * (kSortItems * 64);
-    uint64_t kv[kSortItems];
-    uint32_t iv[kSortItems], rk[kSortItems];
+    const int64_t wb = base + (int64_t)w * (ITEMS * 64);
+    uint64_t kv[ITEMS];
+    uint32_t iv[ITEMS], rk[ITEMS];
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const int64_t k = wb + it * 64 + lane;
         const bool valid = k < n;
         kv[it] = valid ? key[k] : 0ull;
         iv[it] = valid ? idx[k] : 0u;
     }
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const bool valid = wb + it * 64 + lane < n;
         const uint32_t d = (uint32_t)(kv[it] >> shift) & (kSortBins - 1);
         uint64_t peers = __ballot(valid);
@@ -163,8 +186,21 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint64_t *__rest
         loff[tid] = before + inc - v;
     }
     __syncthreads();
+    if (FUSED) { // the digit's first position: exclusive scan of the totals over the digits
+        uint32_t inc = digits;
 #pragma unroll
-    for (int it = 0; it < kSortItems; ++it) {
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += o;
+        }
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        uint32_t before = 0;
+        for (int q = 0; q < w; ++q) before += wsum[q];
+        goff[tid] += before + inc - digits;
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
         if (wb + it * 64 + lane < n) {
             const uint32_t d = (uint32_t)(kv[it] >> shift) & (kSortBins - 1);
             const uint32_t lp = loff[d] + wcnt[w][d] + rk[it];
@@ -173,7 +209,7 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint64_t *__rest
         }
     }
     __syncthreads();
-    const int64_t cnt = (n - base) < kSortTile ? (n - base) : kSortTile;
+    const int64_t cnt = (n - base) < kTile ? (n - base) : kTile;
     for (int e = tid; e < cnt; e += kSortThreads) {
         const uint64_t kk = skey[e];
         const uint32_t d = (uint32_t)(kk >> shift) & (kSortBins - 1);
@@ -183,14 +219,14 @@ __global__ __launch_bounds__(kSortThreads) void k_scatter(const uint64_t *__rest
     }
 }
 
-// Second half of the sort.  After stable passes over the key bits from kRunBits up, equal
-// high parts form runs (cells of about level 13, rarely more than a few particles) in input
-// order; sorting each run by (key, index) completes the order by (key, index).  One thread
+// Second half of the sort.  After stable passes over the key bits from run_bits up, equal
+// high parts form runs (small cells, rarely more than a few particles) in input order; sorting each run by (key, index) completes the order by (key, index).  One thread
 // per run start sorts a run of up to kShortRun elements in registers; longer runs, up to
 // kLongRun, are listed for k_fix_long_runs; a run longer than that (or a full list) sets
 // *fallback, and the caller then sorts everything by all bits.  Elements of one run share the
 // high part, so reading neighbours while their runs are being reordered is harmless.
-__global__ __launch_bounds__(256) void k_fix_runs(int64_t n, uint64_t *__restrict__ key,
+__global__ __launch_bounds__(256) void k_fix_runs(int64_t n, int run_bits,
+                                                  uint64_t *__restrict__ key,
                                                   uint32_t *__restrict__ idx,
                                                   uint2 *__restrict__ long_runs,
                                                   uint32_t long_cap, unsigned *long_count,
@@ -198,10 +234,10 @@ __global__ __launch_bounds__(256) void k_fix_runs(int64_t n, uint64_t *__restric
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const uint64_t hk = key[i] >> kRunBits;
-        if (i > 0 && (key[i - 1] >> kRunBits) == hk) continue;
+        const uint64_t hk = key[i] >> run_bits;
+        if (i > 0 && (key[i - 1] >> run_bits) == hk) continue;
         int64_t e = i + 1;
-        while (e < n && e - i <= (int64_t)kLongRun && (key[e] >> kRunBits) == hk) ++e;
+        while (e < n && e - i <= (int64_t)kLongRun && (key[e] >> run_bits) == hk) ++e;
         const int64_t len = e - i;
         if (len > (int64_t)kShortRun) {
             const unsigned slot = len <= (int64_t)kLongRun ? atomicAdd(long_count, 1u) : long_cap;
@@ -489,8 +525,6 @@ __global__ __launch_bounds__(256) void k_emit(NodeArrays nd, const uint32_t *__r
 // before i); its first child, if any, is node (l + 1, i); its parent is the last level-(l - 1)
 // node that starts at or before i.
 constexpr int kTreeThreads = 256;
-constexpr int kTreeItems = 16;
-constexpr int kTreeTile = kTreeThreads * kTreeItems;
 constexpr int kTreeLevels = kMaxLevel + 1;
 constexpr uint32_t kTreeLong = 0x3fffffu; // leaf count not found within the window
 
@@ -523,12 +557,17 @@ __device__ __forceinline__ uint32_t tree_word(int s, int Lf, uint32_t cnt)
     return (uint32_t)s | ((uint32_t)Lf << 5) | (cnt << 10);
 }
 
+// It also zeroes the groups' flags of its particles (gstart, gflag, n + 1 words of the latter).
+template <int ITEMS>
 __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__restrict__ key,
                                                              uint32_t n, int n_leaf,
                                                              uint32_t *__restrict__ sl,
                                                              uint32_t *__restrict__ blk,
-                                                             uint32_t nblk)
+                                                             uint32_t nblk,
+                                                             uint32_t *__restrict__ gstart,
+                                                             uint32_t *__restrict__ gflag)
 {
+    constexpr int kTreeItems = ITEMS, kTreeTile = kTreeThreads * ITEMS;
     __shared__ uint8_t ms[kTreeTile + kTreeWin];
     __shared__ uint8_t ss[kTreeTile + kTreeWin];
     __shared__ uint32_t lc[kTreeLevels];
@@ -582,6 +621,9 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_levels(const uint64_t *__
             lm[q] = (2u << Lf) - (1u << s);
         }
         sl[i] = tree_word(s <= Lf ? s : 22, Lf, cnt);
+        gstart[i] = 0u;
+        gflag[i] = 0u;
+        if (i == (int64_t)n - 1) gflag[n] = 0u;
     }
     // nodes per level starting in this tile: one ballot per level and item, one LDS add per
     // level and wave
@@ -655,7 +697,8 @@ __device__ __forceinline__ uint32_t cell_end(const uint64_t *__restrict__ key, u
 // of leaves (internal counts are summed by the moments pass).  Level by level, each wave lists
 // the particles of its tile part at which a node of that level starts (in particle order, so
 // in node order) and then writes 64 consecutive nodes at a time.  msk[l][t]: which of thread
-// t's 16 particles start a level-l node; cur[l][t]: the index of the first of them.
+// t's ITEMS particles start a level-l node; cur[l][t]: the index of the first of them.
+template <int ITEMS>
 __global__ __launch_bounds__(kTreeThreads) void k_tree_emit(NodeArrays nd,
                                                            const uint64_t *__restrict__ key,
                                                            const uint32_t *__restrict__ sl,
@@ -663,6 +706,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_emit(NodeArrays nd,
                                                            uint32_t nblk, TreeOffsets to,
                                                            uint32_t n, double L)
 {
+    constexpr int kTreeItems = ITEMS, kTreeTile = kTreeThreads * ITEMS;
     __shared__ uint32_t cur[kTreeLevels][kTreeThreads];
     __shared__ uint16_t msk[kTreeLevels][kTreeThreads];
     __shared__ uint16_t lst[kTreeThreads / 64][64 * kTreeItems];
@@ -725,7 +769,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_emit(NodeArrays nd,
         const int sh = 3 * (kMaxLevel - l);
         for (uint32_t j = lane; j < total; j += 64) {
             const uint32_t p = my[j];
-            const uint32_t t = p >> 4, q = p & 15u;
+            const uint32_t t = p / kTreeItems, q = p % kTreeItems;
             const uint32_t i = (uint32_t)b0 + p;
             const uint32_t u = base + j;
             const uint64_t k = key[i];
@@ -763,64 +807,88 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_emit(NodeArrays nd,
 // child_first of the next node of its level (child_end after the level's last node), so
 // nchild is set here, and an internal node's count is the sum of its children's.
 template <int DERIVE>
+__device__ __forceinline__ void node_moments(const NodeArrays &nd,
+                                             const double4 *__restrict__ ps, uint32_t u,
+                                             uint32_t hi, uint32_t child_end,
+                                             WalkNode *__restrict__ wn)
+{
+    double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
+    uint32_t nch;
+    if (DERIVE) {
+        const uint32_t nx = u + 1 < hi ? nd.child_first[u + 1] : child_end;
+        nch = nx - nd.child_first[u];
+        nd.nchild[u] = (uint8_t)nch;
+    } else {
+        nch = nd.nchild[u];
+    }
+    const uint32_t f = nd.first[u];
+    uint32_t cnt, cf = 0;
+    if (nch == 0) {
+        cnt = nd.count[u];
+        for (uint32_t k = f; k < f + cnt; ++k) {
+            const double4 r = ps[k];
+            M += r.w;
+            Sx += r.w * r.x;
+            Sy += r.w * r.y;
+            Sz += r.w * r.z;
+        }
+    } else {
+        cf = nd.child_first[u];
+        cnt = 0;
+        for (uint32_t c = cf; c < cf + nch; ++c) {
+            M += nd.mass[c];
+            Sx += nd.comx[c];
+            Sy += nd.comy[c];
+            Sz += nd.comz[c];
+            cnt += nd.count[c];
+        }
+        if (DERIVE) nd.count[u] = cnt;
+    }
+    nd.mass[u] = M;
+    nd.comx[u] = Sx;
+    nd.comy[u] = Sy;
+    nd.comz[u] = Sz;
+    const double c0 = Sx / M, c1 = Sy / M, c2 = Sz / M;
+    nd.nsrc[u] = make_double4(c0, c1, c2, M);
+    WalkNode w;
+    w.cn[0] = nd.cnx[u];
+    w.cn[1] = nd.cny[u];
+    w.cn[2] = nd.cnz[u];
+    w.com[0] = c0;
+    w.com[1] = c1;
+    w.com[2] = c2;
+    w.first = f;
+    w.count = cnt;
+    w.nchild = (uint8_t)nch;
+    w.child_first = cf;
+    w.level = nd.level[u];
+    w.pad0 = w.pad1 = 0;
+    wn[u] = w;
+}
+
+template <int DERIVE>
 __global__ __launch_bounds__(256) void k_moments(NodeArrays nd, const double4 *__restrict__ ps,
                                                  uint32_t lo, uint32_t hi, uint32_t child_end,
                                                  WalkNode *__restrict__ wn)
 {
     for (uint32_t u = lo + blockIdx.x * blockDim.x + threadIdx.x; u < hi;
-         u += gridDim.x * blockDim.x) {
-        double M = 0.0, Sx = 0.0, Sy = 0.0, Sz = 0.0;
-        uint32_t nch;
-        if (DERIVE) {
-            const uint32_t nx = u + 1 < hi ? nd.child_first[u + 1] : child_end;
-            nch = nx - nd.child_first[u];
-            nd.nchild[u] = (uint8_t)nch;
-        } else {
-            nch = nd.nchild[u];
-        }
-        const uint32_t f = nd.first[u];
-        uint32_t cnt, cf = 0;
-        if (nch == 0) {
-            cnt = nd.count[u];
-            for (uint32_t k = f; k < f + cnt; ++k) {
-                const double4 r = ps[k];
-                M += r.w;
-                Sx += r.w * r.x;
-                Sy += r.w * r.y;
-                Sz += r.w * r.z;
-            }
-        } else {
-            cf = nd.child_first[u];
-            cnt = 0;
-            for (uint32_t c = cf; c < cf + nch; ++c) {
-                M += nd.mass[c];
-                Sx += nd.comx[c];
-                Sy += nd.comy[c];
-                Sz += nd.comz[c];
-                cnt += nd.count[c];
-            }
-            if (DERIVE) nd.count[u] = cnt;
-        }
-        nd.mass[u] = M;
-        nd.comx[u] = Sx;
-        nd.comy[u] = Sy;
-        nd.comz[u] = Sz;
-        const double c0 = Sx / M, c1 = Sy / M, c2 = Sz / M;
-        nd.nsrc[u] = make_double4(c0, c1, c2, M);
-        WalkNode w;
-        w.cn[0] = nd.cnx[u];
-        w.cn[1] = nd.cny[u];
-        w.cn[2] = nd.cnz[u];
-        w.com[0] = c0;
-        w.com[1] = c1;
-        w.com[2] = c2;
-        w.first = f;
-        w.count = cnt;
-        w.nchild = (uint8_t)nch;
-        w.child_first = cf;
-        w.level = nd.level[u];
-        w.pad0 = w.pad1 = 0;
-        wn[u] = w;
+         u += gridDim.x * blockDim.x)
+        node_moments<DERIVE>(nd, ps, u, hi, child_end, wn);
+}
+
+// Consecutive levels of few nodes (l1 down to l0) by one workgroup, a barrier between levels:
+// the same operations in the same order as a launch per level, without a launch's latency
+// (about 7 us) for each.
+template <int DERIVE>
+__global__ __launch_bounds__(1024) void k_moments_levels(NodeArrays nd,
+                                                         const double4 *__restrict__ ps,
+                                                         TreeOffsets to, int l1, int l0,
+                                                         WalkNode *__restrict__ wn)
+{
+    for (int l = l1; l >= l0; --l) {
+        for (uint32_t u = to.off[l] + threadIdx.x; u < to.off[l + 1]; u += 1024u)
+            node_moments<DERIVE>(nd, ps, u, to.off[l + 1], to.off[l + 2], wn);
+        __syncthreads();
     }
 }
 
@@ -843,29 +911,38 @@ __global__ __launch_bounds__(256) void k_group_mark(NodeArrays nd, uint32_t n_no
 
 __global__ __launch_bounds__(256) void k_group_compact(const uint32_t *__restrict__ gstart,
                                                        const uint32_t *__restrict__ gpos,
-                                                       int64_t n, uint32_t *__restrict__ gnode)
+                                                       int64_t n, uint32_t cap,
+                                                       uint32_t *__restrict__ gnode)
 {
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
         uint32_t s = gstart[k];
-        if (s) gnode[gpos[k]] = s - 1;
+        if (s && gpos[k] < cap) gnode[gpos[k]] = s - 1;
     }
 }
 
-// Eight lanes per group: exact min/max of its particle positions.
+// Eight lanes per group: exact min/max of its particle positions; also lowers *min_level to the
+// shallowest group level and raises *max_count to the largest group (a block reduction, then an
+// atomic only where it changes the word).  *n_groups groups, of which the first cap are done.
 __global__ __launch_bounds__(256) void k_group_bbox(NodeArrays nd, GroupArrays gr,
-                                                    uint32_t n_groups,
-                                                    const double4 *__restrict__ ps)
+                                                    const uint32_t *__restrict__ n_groups,
+                                                    uint32_t cap,
+                                                    const double4 *__restrict__ ps,
+                                                    unsigned *min_level, unsigned *max_count)
 {
     const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     const uint32_t g = t >> 3;
     const int sub = (int)(t & 7);
-    const bool act = g < n_groups;
+    const uint32_t ng = *n_groups < cap ? *n_groups : cap;
+    if ((blockIdx.x * blockDim.x) >> 3 >= ng) return; // the whole block leaves
+    const bool act = g < ng;
     uint32_t u = 0, f = 0, c = 0;
+    unsigned lv = 255u;
     if (act) {
         u = gr.node[g];
         f = nd.first[u];
         c = nd.count[u];
+        lv = nd.level[u];
     }
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     for (uint32_t k = f + sub; k < f + c; k += 8) {
@@ -901,20 +978,7 @@ __global__ __launch_bounds__(256) void k_group_bbox(NodeArrays nd, GroupArrays g
         gr.xgy[g] = nd.cny[u];
         gr.xgz[g] = nd.cnz[u];
     }
-}
-
-// Shallowest group level and largest group: block reductions, one atomic per block.
-__global__ __launch_bounds__(256) void k_group_extremes(NodeArrays nd, GroupArrays gr,
-                                                        uint32_t n_groups, unsigned *min_level,
-                                                        unsigned *max_count)
-{
-    unsigned lv = 255u, mc = 0u;
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n_groups;
-         g += gridDim.x * blockDim.x) {
-        uint32_t u = gr.node[g];
-        lv = min(lv, (unsigned)nd.level[u]);
-        mc = max(mc, (unsigned)nd.count[u]);
-    }
+    unsigned mc = c;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
         lv = min(lv, (unsigned)__shfl_xor((int)lv, d, 64));
@@ -931,9 +995,20 @@ __global__ __launch_bounds__(256) void k_group_extremes(NodeArrays nd, GroupArra
             lv = min(lv, s_lv[w]);
             mc = max(mc, s_mc[w]);
         }
-        atomicMin(min_level, lv);
-        atomicMax(max_count, mc);
+        if (lv < *(volatile unsigned *)min_level) atomicMin(min_level, lv);
+        if (mc > *(volatile unsigned *)max_count) atomicMax(max_count, mc);
     }
+}
+
+// The words a build starts from: flags (6) and the largest mass zero, the groups' extremes.
+__global__ void k_build_init(unsigned *flags, unsigned long long *mmax, unsigned *min_level,
+                             unsigned *max_count)
+{
+    const int t = threadIdx.x;
+    if (t < 6) flags[t] = 0u;
+    if (t == 6) *mmax = 0ull;
+    if (t == 7) *min_level = 255u;
+    if (t == 8) *max_count = 0u;
 }
 
 inline unsigned grid_for(int64_t n, int threads, int64_t cap = 65536)
@@ -954,42 +1029,70 @@ void launch_keys(int64_t n, const double *x, const double *y, const double *z, c
     k_keys<<<grid_for(n, 256), 256, 0, s>>>(n, x, y, z, m, L, scale, key, idx, flags, rec);
 }
 
-size_t sort_hist_elems(int64_t n)
+// Tiles of 1024 keys up to 2^18 of them (more blocks, each done sooner: a pass over 3,000 keys
+// takes 9 us in the scatter with one tile of 4096), of 4096 above (longer runs per digit in the
+// scatter's writes).
+static int sort_items(int64_t n) { return n <= (1 << 18) ? 4 : 16; }
+
+static uint32_t sort_tiles(int64_t n)
 {
-    size_t nb = (size_t)((n + kSortTile - 1) / kSortTile);
-    if (nb < 1) nb = 1;
-    return nb * kSortBins;
+    const int64_t tile = (int64_t)kSortThreads * sort_items(n);
+    return (uint32_t)((n + tile - 1) / tile);
 }
+
+size_t sort_hist_elems(int64_t n) { return (size_t)(n > 0 ? sort_tiles(n) : 1) * kSortBins; }
+
+int sort_run_bits(int64_t n)
+{
+    return n <= (1 << 16) ? 40 : n <= (1 << 21) ? 32 : 24;
+}
+
+// Up to this many tiles the scatter adds up the tiles' digit counts itself: every block then
+// reads tiles x 1 KB, and two to four launches of a pass fall away.
+constexpr uint32_t kSortFusedTiles = 256;
 
 // Stable LSD passes over bits [lo_bit, 64) of the keys, 8 bits per pass; an even number of
 // passes leaves the result in key / idx.
 static void radix_passes(int64_t n, int lo_bit, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
                          uint32_t *idx_alt, uint32_t *hist, uint32_t *scan_tmp, hipStream_t s)
 {
-    uint32_t nb = (uint32_t)((n + kSortTile - 1) / kSortTile);
+    const uint32_t nb = sort_tiles(n);
+    const bool small = sort_items(n) == 4, fused = nb <= kSortFusedTiles;
     uint64_t *kin = key, *kout = key_alt;
     uint32_t *iin = idx, *iout = idx_alt;
     for (int shift = lo_bit; shift < 64; shift += kSortBits) {
-        k_hist<<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
-        scan_u32(hist, (size_t)nb * kSortBins, scan_tmp, scan_tmp + 1, s);
-        k_scatter<<<nb, kSortThreads, 0, s>>>(kin, iin, n, shift, hist, nb, kout, iout);
+        if (small) { // 2^18 keys are 256 tiles
+            k_hist<4, true><<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
+            k_scatter<4, true><<<nb, kSortThreads, 0, s>>>(kin, iin, n, shift, hist, nb, kout,
+                                                          iout);
+        } else if (fused) {
+            k_hist<16, true><<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
+            k_scatter<16, true><<<nb, kSortThreads, 0, s>>>(kin, iin, n, shift, hist, nb, kout,
+                                                           iout);
+        } else {
+            k_hist<16, false><<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
+            scan_u32(hist, (size_t)nb * kSortBins, scan_tmp, scan_tmp + 1, s);
+            k_scatter<16, false><<<nb, kSortThreads, 0, s>>>(kin, iin, n, shift, hist, nb, kout,
+                                                            iout);
+        }
         uint64_t *tk = kin; kin = kout; kout = tk;
         uint32_t *ti = iin; iin = iout; iout = ti;
     }
 }
 
-bool radix_sort_high(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
+bool radix_sort_high(int64_t n, int run_bits, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
                      uint32_t *idx_alt, uint32_t *hist, uint32_t *scan_tmp, uint2 *long_runs,
                      uint32_t long_cap, unsigned *flags, hipStream_t s)
 {
-    fill_u32(flags, 2, 0u, s); // [0] listed long runs, [1] fallback
     if (n <= 1) return false;
-    radix_passes(n, kRunBits, key, idx, key_alt, idx_alt, hist, scan_tmp, s);
-    const bool odd = ((64 - kRunBits) / kSortBits) % 2 == 1;
+    radix_passes(n, run_bits, key, idx, key_alt, idx_alt, hist, scan_tmp, s);
+    const bool odd = ((64 - run_bits) / kSortBits) % 2 == 1;
     uint64_t *k = odd ? key_alt : key;
     uint32_t *v = odd ? idx_alt : idx;
-    k_fix_runs<<<grid_for(n, 256), 256, 0, s>>>(n, k, v, long_runs, long_cap, flags, flags + 1);
-    k_fix_long_runs<<<256, 256, 0, s>>>(long_runs, flags, long_cap, k, v);
+    k_fix_runs<<<grid_for(n, 256), 256, 0, s>>>(n, run_bits, k, v, long_runs, long_cap, flags,
+                                                flags + 1);
+    const unsigned lb = grid_for((int64_t)long_cap, 1, 256);
+    k_fix_long_runs<<<lb, 256, 0, s>>>(long_runs, flags, long_cap, k, v);
     return odd;
 }
 
@@ -1003,7 +1106,6 @@ void radix_sort(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt, uint
 void launch_permute(int64_t n, const uint32_t *idx, const double4 *rec, double4 *psrc,
                     unsigned long long *mmax, hipStream_t s)
 {
-    fill_u64((uint64_t *)mmax, 1, 0ull, s);
     if (n) k_permute<<<grid_for(n, 256), 256, 0, s>>>(n, idx, rec, psrc, mmax);
 }
 
@@ -1026,23 +1128,52 @@ void launch_emit(NodeArrays nd, const uint32_t *bnd, uint32_t lo, uint32_t hi, i
     k_emit<<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, bnd, lo, hi, level, base, cnt, L);
 }
 
-void launch_moments(NodeArrays nd, const double4 *ps, uint32_t lo, uint32_t hi, int derive,
-                    uint32_t child_end, WalkNode *wn, hipStream_t s)
+// Levels of at most this many nodes next to each other share a launch.
+constexpr uint32_t kFewNodes = 2048;
+
+void launch_moments(NodeArrays nd, const double4 *ps, const TreeOffsets &to, int max_level,
+                    int derive, WalkNode *wn, hipStream_t s)
 {
-    if (hi <= lo) return;
-    if (derive)
-        k_moments<1><<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, ps, lo, hi, child_end, wn);
-    else
-        k_moments<0><<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, ps, lo, hi, child_end, wn);
+    for (int l = max_level; l >= 0;) {
+        const uint32_t lo = to.off[l], hi = to.off[l + 1];
+        int l0 = l;
+        while (l0 >= 0 && to.off[l0 + 1] - to.off[l0] <= kFewNodes) --l0;
+        if (l - l0 >= 2) {
+            if (derive)
+                k_moments_levels<1><<<1, 1024, 0, s>>>(nd, ps, to, l, l0 + 1, wn);
+            else
+                k_moments_levels<0><<<1, 1024, 0, s>>>(nd, ps, to, l, l0 + 1, wn);
+            l = l0;
+            continue;
+        }
+        if (derive)
+            k_moments<1><<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, ps, lo, hi, to.off[l + 2], wn);
+        else
+            k_moments<0><<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, ps, lo, hi, to.off[l + 2], wn);
+        --l;
+    }
 }
 
-uint32_t tree_blocks(int64_t n) { return (uint32_t)((n + kTreeTile - 1) / kTreeTile); }
+// Tiles of 1024 particles up to 2^20 of them, of 4096 above: with 4096 a box of 700,001 has 171
+// blocks for 256 compute units, and one of 3,000 a single one (levels 28 us, emit 17 us).
+static int tree_items(int64_t n) { return n <= (1 << 20) ? 4 : 16; }
+
+uint32_t tree_blocks(int64_t n)
+{
+    const int64_t tile = (int64_t)kTreeThreads * tree_items(n);
+    return (uint32_t)((n + tile - 1) / tile);
+}
 
 void launch_tree_levels(const uint64_t *key, uint32_t n, int n_leaf, uint32_t *sl, uint32_t *blk,
-                        uint32_t *tot, hipStream_t s)
+                        uint32_t *tot, uint32_t *gstart, uint32_t *gflag, hipStream_t s)
 {
     const uint32_t nblk = tree_blocks(n);
-    k_tree_levels<<<nblk, kTreeThreads, 0, s>>>(key, n, n_leaf, sl, blk, nblk);
+    if (tree_items(n) == 4)
+        k_tree_levels<4><<<nblk, kTreeThreads, 0, s>>>(key, n, n_leaf, sl, blk, nblk, gstart,
+                                                      gflag);
+    else
+        k_tree_levels<16><<<nblk, kTreeThreads, 0, s>>>(key, n, n_leaf, sl, blk, nblk, gstart,
+                                                       gflag);
     k_tree_scan<<<kTreeLevels, 1024, 0, s>>>(blk, nblk, tot);
 }
 
@@ -1050,32 +1181,36 @@ void launch_tree_emit(NodeArrays nd, const uint64_t *key, const uint32_t *sl, co
                       const TreeOffsets &to, uint32_t n, double L, hipStream_t s)
 {
     const uint32_t nblk = tree_blocks(n);
-    k_tree_emit<<<nblk, kTreeThreads, 0, s>>>(nd, key, sl, blk, nblk, to, n, L);
+    if (tree_items(n) == 4)
+        k_tree_emit<4><<<nblk, kTreeThreads, 0, s>>>(nd, key, sl, blk, nblk, to, n, L);
+    else
+        k_tree_emit<16><<<nblk, kTreeThreads, 0, s>>>(nd, key, sl, blk, nblk, to, n, L);
 }
 
-
 void launch_group_mark(NodeArrays nd, uint32_t n_nodes, int n_crit, uint32_t *gstart,
-                       uint32_t *gflag, int64_t n, hipStream_t s)
+                       uint32_t *gflag, int64_t n, bool clear, hipStream_t s)
 {
-    fill_u32(gstart, (size_t)n, 0u, s);
-    fill_u32(gflag, (size_t)n + 1, 0u, s);
+    if (clear) {
+        fill_u32(gstart, (size_t)n, 0u, s);
+        fill_u32(gflag, (size_t)n + 1, 0u, s);
+    }
     k_group_mark<<<grid_for(n_nodes, 256), 256, 0, s>>>(nd, n_nodes, n_crit, gstart, gflag);
 }
 
-void launch_group_compact(const uint32_t *gstart, const uint32_t *gpos, int64_t n,
-                          uint32_t *gnode, hipStream_t s)
+void launch_groups(NodeArrays nd, GroupArrays gr, const uint32_t *gstart, const uint32_t *gpos,
+                   int64_t n, const uint32_t *n_groups, uint32_t cap, const double4 *ps,
+                   unsigned *min_level, unsigned *max_count, hipStream_t s)
 {
-    k_group_compact<<<grid_for(n, 256), 256, 0, s>>>(gstart, gpos, n, gnode);
+    if (!cap) return;
+    k_group_compact<<<grid_for(n, 256), 256, 0, s>>>(gstart, gpos, n, cap, gr.node);
+    k_group_bbox<<<(unsigned)(((uint64_t)cap * 8 + 255) / 256), 256, 0, s>>>(
+        nd, gr, n_groups, cap, ps, min_level, max_count);
 }
 
-void launch_group_bbox(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const double4 *ps,
-                       unsigned *min_level, unsigned *max_count, hipStream_t s)
+void launch_build_init(unsigned *flags, unsigned long long *mmax, unsigned *min_level,
+                       unsigned *max_count, hipStream_t s)
 {
-    if (!n_groups) return;
-    k_group_bbox<<<(unsigned)(((uint64_t)n_groups * 8 + 255) / 256), 256, 0, s>>>(nd, gr, n_groups,
-                                                                                ps);
-    k_group_extremes<<<grid_for(n_groups, 256, 256), 256, 0, s>>>(nd, gr, n_groups, min_level,
-                                                                 max_count);
+    k_build_init<<<1, 64, 0, s>>>(flags, mmax, min_level, max_count);
 }
 
 } // namespace tpm

@@ -48,7 +48,7 @@ struct treepm_ctx {
     hipEvent_t idle = nullptr;
     bool idle_set = false;
     hipStream_t cur = nullptr;
-    // The FP32 force's size classes run concurrently on the call's stream and these.
+    // The build's gather runs beside its octree passes on this one.
     static constexpr int kSubStreams = 1;
     hipStream_t sub[kSubStreams] = {};
     hipEvent_t fork = nullptr, join[kSubStreams] = {};
@@ -91,6 +91,8 @@ struct treepm_ctx {
     uint32_t *mbox_h = nullptr, *mbox_d = nullptr;
     uint32_t mseq = 0;
     uint32_t walk_hint_groups = 0;
+    // A sort of this context found runs too long for sort_run_bits: start from 24 bits.
+    bool sort_wide = false;
     int walk_passes = TREEPM_WALK_AUTO; // treepm_set_walk_passes
     uint64_t st[3] = {0, 0, 0};
     // FP32 pair-law table: device copy, and the eps / eta it was built for (0: none)
@@ -587,6 +589,10 @@ void record(treepm_ctx *c, int i, hipStream_t s)
     if (c->timing) hipEventRecord(c->ev[i], s);
 }
 
+// Below this many particles the gather takes less time (40 us at 700,000, beside octree passes
+// of 50) than the events of a second stream.
+constexpr int64_t kSideGather = 1 << 20;
+
 int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const double *z,
              const double *m, int mem_kind, hipStream_t s)
 {
@@ -618,41 +624,54 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
             src[a] = c->in[a].as<double>();
         }
     }
-    unsigned *flags = c->flags.as<unsigned>();
-    fill_u32(flags, 4, 0u, s);
+    {
+        hipError_t e = reserve(c->pm_mx, 8);
+        if (e != hipSuccess) return hip_fail(c, e, "largest-mass word");
+    }
+    unsigned *flags = c->flags.as<unsigned>(), *sflags = flags + 4;
+    unsigned *misc = c->g_misc.as<unsigned>();
+    launch_build_init(flags, c->pm_mx.as<unsigned long long>(), misc, misc + 1, s);
     launch_keys(n, src[0], src[1], src[2], src[3], P.L, c->key.as<uint64_t>(),
                 c->idx.as<uint32_t>(), flags, c->rec.as<double4>(), s);
     uint32_t *scan_tmp = c->scan32.as<uint32_t>();
+    const uint32_t long_cap = (uint32_t)(N / (kShortRun + 1) + 1);
     {
-        // high key bits first, runs of equal high bits sorted in place; all bits if a run is
-        // too long for that
-        unsigned *sflags = c->flags.as<unsigned>() + 4;
-        const uint32_t long_cap = (uint32_t)(N / (kShortRun + 1) + 1);
         hipError_t e = reserve(c->runs, (size_t)long_cap * sizeof(uint2));
         if (e != hipSuccess) return hip_fail(c, e, "sort runs");
-        if (radix_sort_high(n, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
+    }
+    // high key bits first, runs of equal high bits sorted in place
+    auto sort_high = [&](int run_bits) {
+        if (radix_sort_high(n, run_bits, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
                             c->key_alt.as<uint64_t>(), c->idx_alt.as<uint32_t>(),
                             c->hist.as<uint32_t>(), scan_tmp, c->runs.as<uint2>(), long_cap,
                             sflags, s)) {
             std::swap(c->key, c->key_alt);
             std::swap(c->idx, c->idx_alt);
         }
-        // the input checks of k_keys and the sort's fallback flag in one read (sorting
-        // invalid input first is harmless: keys are clamped)
-        unsigned fl[6] = {};
-        if ((rc = fetch(c, s, {fl, flags, sizeof fl}))) return rc;
-        if (fl[0] & kFlagNonFinite)
-            return fail(c, TREEPM_ERR_ARG, "non-finite position or mass, or a mass <= 0");
-        if (fl[0] & kFlagRange)
-            return fail(c, TREEPM_ERR_RANGE, "a position lies outside [0, L); wrap it first");
-        if (fl[5])
+    };
+    // The input checks of k_keys and the sort's fallback flag (sorting invalid input first is
+    // harmless: keys are clamped).  A run too long to be sorted in place means more high bits,
+    // and in the end all of them.
+    int run_bits = c->sort_wide ? 24 : sort_run_bits(n);
+    sort_high(run_bits);
+    unsigned fl[6] = {};
+    if ((rc = fetch(c, s, {fl, flags, sizeof fl}))) return rc;
+    if (fl[0] & kFlagNonFinite)
+        return fail(c, TREEPM_ERR_ARG, "non-finite position or mass, or a mass <= 0");
+    if (fl[0] & kFlagRange)
+        return fail(c, TREEPM_ERR_RANGE, "a position lies outside [0, L); wrap it first");
+    while (fl[5]) {
+        if (run_bits == 24) {
             radix_sort(n, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
                        c->key_alt.as<uint64_t>(), c->idx_alt.as<uint32_t>(),
                        c->hist.as<uint32_t>(), scan_tmp, s);
-    }
-    {
-        hipError_t e = reserve(c->pm_mx, 8);
-        if (e != hipSuccess) return hip_fail(c, e, "largest-mass word");
+            break;
+        }
+        c->sort_wide = true;
+        run_bits = 24;
+        fill_u32(sflags, 2, 0u, s);
+        sort_high(run_bits);
+        if ((rc = fetch(c, s, {fl, flags, sizeof fl}))) return rc;
     }
     // The gather into key order reads only the sort's indices, and the octree passes only the
     // keys: the gather runs on a side stream beside them, and the moments wait for it.
@@ -669,7 +688,7 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
             }
         }
     } side{c, s, s};
-    if (c->fork) {
+    if (c->fork && n >= kSideGather) {
         HIPCHK(c, hipEventRecord(c->fork, s));
         HIPCHK(c, hipStreamWaitEvent(c->sub[0], c->fork, 0));
         side.sp = c->sub[0];
@@ -693,7 +712,8 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
         uint32_t *blk = c->tree_blk.as<uint32_t>();
         uint32_t *tot = blk + (size_t)nblk * (kMaxLevel + 1);
         launch_tree_levels(c->key.as<uint64_t>(), (uint32_t)n, P.n_leaf,
-                           c->tree_sl.as<uint32_t>(), blk, tot, s);
+                           c->tree_sl.as<uint32_t>(), blk, tot, c->gstart.as<uint32_t>(),
+                           c->gflag.as<uint32_t>(), s);
         uint32_t per_level[kMaxLevel + 1] = {};
         if ((rc = fetch(c, s, {per_level, tot, sizeof per_level}))) return rc;
         TreeOffsets to{};
@@ -755,12 +775,10 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     // moments from the deepest level up (a flat-built tree has its nchild and internal counts
     // set here; the children of level l end where level l + 2 starts)
     nd = nodes_view(c);
-    for (int l = c->max_level; l >= 0; --l) {
-        const uint32_t child_end =
-            (size_t)l + 2 < c->lvl.size() ? c->lvl[l + 2] : c->n_nodes;
-        launch_moments(nd, ps, c->lvl[l], c->lvl[l + 1], flat ? 1 : 0, child_end,
-                       c->n_walk.as<WalkNode>(), s);
-    }
+    TreeOffsets levels{};
+    for (int l = 0; l < kMaxLevel + 3; ++l)
+        levels.off[l] = (size_t)l < c->lvl.size() ? c->lvl[l] : c->n_nodes;
+    launch_moments(nd, ps, levels, c->max_level, flat ? 1 : 0, c->n_walk.as<WalkNode>(), s);
     if (P.quadrupole) {
         hipError_t e = reserve(c->n_q, (size_t)c->n_nodes * 6 * sizeof(double));
         if (e != hipSuccess) return hip_fail(c, e, "second moments");
@@ -770,23 +788,25 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     // groups in key order
     int n_crit = P.n_crit > 0 ? P.n_crit : kDefaultNCrit;
     uint32_t *gstart = c->gstart.as<uint32_t>(), *gflag = c->gflag.as<uint32_t>();
-    launch_group_mark(nd, c->n_nodes, n_crit, gstart, gflag, n, s);
+    launch_group_mark(nd, c->n_nodes, n_crit, gstart, gflag, n, !flat, s);
     scan_u32(gflag, N + 1, cnt_total, cnt_tmp, s);
+    // The group arrays left by an earlier build (or, for a small box, room for one group in 16
+    // particles) usually hold this one's groups: then nothing waits for their number.
     uint32_t ng = 0;
-    if ((rc = fetch(c, s, {&ng, cnt_total, sizeof ng}))) return rc;
-    if ((rc = ensure_groups(c, ng))) return rc;
-    GroupArrays gr = groups_view(c);
-    launch_group_compact(gstart, gflag, n, gr.node, s);
-    unsigned *misc = c->g_misc.as<unsigned>();
-    fill_u32(misc, 1, 255u, s);
-    fill_u32(misc + 1, 1, 0u, s);
-    launch_group_bbox(nd, gr, ng, ps, misc, misc + 1, s);
     unsigned hm[2] = {0, 0};
-    if ((rc = fetch(c, s, {hm, misc, sizeof hm}))) return rc;
+    if (n < kSideGather && c->group_cap < N / 16 + 64 && (rc = ensure_groups(c, N / 16 + 64)))
+        return rc;
+    for (;;) {
+        const uint32_t cap = (uint32_t)std::min<size_t>(c->g_node.p ? c->group_cap : 0, N);
+        GroupArrays gr = groups_view(c);
+        launch_groups(nd, gr, gstart, gflag, n, cnt_total, cap, ps, misc, misc + 1, s);
+        if ((rc = fetch(c, s, {&ng, cnt_total, sizeof ng}, {hm, misc, sizeof hm}))) return rc;
+        if (ng <= cap) break;
+        if ((rc = ensure_groups(c, ng))) return rc;
+    }
     c->n_groups = ng;
     c->min_group_level = hm[0];
     c->max_group = hm[1];
-    HIPCHK(c, hipStreamSynchronize(s));
     return TREEPM_OK;
 }
 
