@@ -174,12 +174,13 @@ struct WalkParams {
 };
 // Group g's interaction list is entries[off[g] .. off[g] + len[g]).
 // Two passes: the count pass writes each list length to counts[g]; after the caller's prefix
-// sum (counts -> off) the emit pass writes the lists, len and gcells (cell entries).
+// sum (counts -> off) the emit pass writes the lists, len and gcells (cell entries), and sets bit
+// 4 of *overflow if they need more than entries_cap entries.
 void launch_walk_count(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
                        uint64_t *counts, unsigned *overflow, hipStream_t s);
 void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
-                      const uint64_t *off, uint32_t *len, uint32_t *entries, unsigned *overflow,
-                      uint32_t *gcells, hipStream_t s);
+                      const uint64_t *off, uint32_t *len, uint32_t *entries,
+                      uint64_t entries_cap, unsigned *overflow, uint32_t *gcells, hipStream_t s);
 // One pass: n_waves waves write the lists into chunks of `chunk` entries taken from the
 // pool entries[0, pool_cap); a group is walked into the wave's current chunk if at least
 // `reserve` entries are left there, else (or if it did not fit) into a fresh chunk.  Sets bit 4 of *overflow if a list or the pool ran out of room
@@ -208,7 +209,19 @@ struct WalkBox {
     uint64_t pool_cap, chunk, reserve;
     unsigned *overflow;
     uint32_t g0, n_groups;
+    uint64_t entries_cap;          // two passes: room at entries
+    unsigned long long *stats;     // see launch_walk_stats
+    uint32_t *cls;                 // queue buffer of the force
+    uint32_t *mailbox;             // launch_walk_results_one: where the results go, and
+    uint32_t seq;                  // the sequence number that marks them
 };
+// Clears a walk's flags, statistics, queue bins and the word after its list lengths.
+void launch_walk_init(const WalkBox &box, hipStream_t s);
+void launch_walk_init_multi(const WalkBox *boxes, int nb, hipStream_t s); // device array
+// off[0 .. n_groups] of each box to its exclusive prefix sums, for boxes of at most
+// kOneBlockGroups groups (one workgroup per box).
+constexpr uint32_t kOneBlockGroups = 16384;
+void launch_walk_scan_multi(const WalkBox *boxes, int nb, hipStream_t s);
 // The two passes over all items of the boxes (one wave per item; descriptors in device
 // memory, total = sum of n_groups).
 void launch_walk_count_multi(const WalkBox *boxes, int nb, uint32_t total, hipStream_t s);
@@ -255,12 +268,14 @@ constexpr uint32_t kClsBins = kClsQueue + 2 * kXcds * kQueueStride;
 constexpr uint32_t kClsLists = kClsBins + kXcds * 64;
 // Parts and longest-first order of the groups (len: list lengths; pairs: the box's
 // interactions, device), into cls (kClsLists + n_groups words).
+// The bins have been cleared (launch_walk_init).
 void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
                      const unsigned long long *pairs, uint32_t *cls, hipStream_t s);
-// Empties the force queues and zeroes pairs (n_groups words), which the split groups add to,
-// and *sum, which launch_pair_stats adds to.
-void launch_force_prep(uint32_t *cls, unsigned long long *pairs, uint32_t n_groups,
-                       unsigned long long *sum, hipStream_t s);
+// launch_walk_stats and launch_classify in one launch of a workgroup (boxes of at most
+// kOneBlockGroups groups), which then publishes the overflow word and the four statistics to
+// the box's mailbox.
+void launch_walk_results_one(const WalkBox &box, hipStream_t s);
+void launch_walk_results_multi(const WalkBox *boxes, int nb, hipStream_t s); // device array
 // One box as the FP32 force kernel reads it.
 struct ForceBox {
     NodeArrays nd;
@@ -274,7 +289,15 @@ struct ForceBox {
     ForceTable ft;
     void *rec;
     int rec64; // rec holds double4 records
+    uint32_t n_groups;
+    unsigned long long *pair_sum; // pairs evaluated, over all groups
+    int64_t n;
+    void *out[3]; // launch_force_out_multi: the float outputs
 };
+// Empties a box's force queues and zeroes its pairs (which split groups add to) and *pair_sum
+// (which the output pass adds to).
+void launch_force_prep(const ForceBox &box, hipStream_t s);
+void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s); // device array
 // A persistent launch of at most two workgroups per CU over the box's queues.
 void launch_force_f32(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
 // The same over nb <= kMaxBatch boxes with equal tables (descriptors in device memory; the
@@ -284,16 +307,16 @@ void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_groups, in
 // rec of the force launchers: one record per particle in the caller's order (pidx), float4
 // (ax, ay, az, 0) or, with rec64, double4.  launch_force_out then writes them out: mode 0
 // float arrays, 1 double arrays (from float4 / double4 records), 2 kick (v += dt a into double
-// velocities, double4 records), walking the records in order.
+// velocities, double4 records), walking the records in order; and adds the groups' pairs (the
+// pairs the force kernel evaluated) into *pair_sum.
 void launch_force_out(const void *rec, int mode, int64_t n, void *ax, void *ay, void *az,
-                      double dt, hipStream_t s);
+                      double dt, uint32_t n_groups, const unsigned long long *pairs,
+                      unsigned long long *pair_sum, hipStream_t s);
+void launch_force_out_multi(const ForceBox *boxes, int nb, int64_t most, hipStream_t s);
 // FP32 pair routine on explicit positions, pair by pair (xg: host, 3 values).
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,
                          const double *mj, const double *xg, double eta, ForceTable ft,
                          double *out, hipStream_t s);
-// Adds the groups' pairs (pairs the force kernel evaluated) into *sum (device).
-void launch_pair_stats(uint32_t n_groups, const unsigned long long *pairs,
-                       unsigned long long *sum, hipStream_t s);
 void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
                       const uint32_t *len, const uint32_t *entries, const double4 *ps, const uint32_t *pidx,
                       ForceParams fp, void *rec, int rec64, hipStream_t s);

@@ -725,20 +725,19 @@ __global__ __launch_bounds__(64 * kForceWaves, 4) void k_force_f32_multi(
     force_f32_body<true>(bx, nb);
 }
 
-__global__ __launch_bounds__(256) void k_pair_stats(uint32_t n_groups,
-                                                    const unsigned long long *__restrict__ pairs,
-                                                    unsigned long long *out)
+// Adds the groups' pairs into *sum: blocks b of nb.
+__device__ __forceinline__ void sum_pairs(uint32_t n_groups, const unsigned long long *pairs,
+                                          unsigned long long *sum, uint32_t b, uint32_t nb)
 {
     unsigned long long v = 0;
-    for (uint32_t g = blockIdx.x * blockDim.x + threadIdx.x; g < n_groups;
-         g += gridDim.x * blockDim.x)
+    for (uint32_t g = b * blockDim.x + threadIdx.x; g < n_groups; g += nb * blockDim.x)
         v += pairs[g];
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
     __shared__ unsigned long long sm[4];
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(out, sm[0] + sm[1] + sm[2] + sm[3]);
+    if (threadIdx.x == 0) atomicAdd(sum, sm[0] + sm[1] + sm[2] + sm[3]);
 }
 
 // Pair by pair: out[(i * n_j + j) * 3 + a] = acceleration at x_i from (x_j, m_j) with the
@@ -825,17 +824,16 @@ __global__ __launch_bounds__(256) void k_class_count(GroupArrays gr, uint32_t n_
         if (s_cnt[i]) atomicAdd(&hist[i], s_cnt[i]);
 }
 
-// One wave, lane = cost bucket: bins to cursors (in place), part starts and the ends of the
-// parts' split runs.
-__global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, const unsigned long long *pairs)
+// By one wave, lane = cost bucket: the bins' counts to cursors (in place; bins in global memory
+// or LDS), part starts and the ends of the parts' split runs into cls.
+__device__ __forceinline__ void scan_bins(uint32_t *bins, uint32_t *cls, uint32_t t)
 {
     static_assert(kCostBuckets == 64, "one lane per bucket");
-    const int lane = threadIdx.x;
-    const uint32_t t = split_log2(*pairs);
+    const int lane = __lane_id();
     uint32_t pos = kClsLists;
     uint32_t c[kXcds];
 #pragma unroll
-    for (int p = 0; p < (int)kXcds; ++p) c[p] = cls[kClsBins + p * kCostBuckets + lane];
+    for (int p = 0; p < (int)kXcds; ++p) c[p] = bins[p * kCostBuckets + lane];
 #pragma unroll
     for (int p = 0; p < (int)kXcds; ++p) {
         uint32_t v = c[p];
@@ -844,13 +842,17 @@ __global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, const unsigned
             const uint32_t u = __shfl_up(v, d, 64);
             if (lane >= d) v += u;
         }
-        cls[kClsBins + p * kCostBuckets + lane] = pos + v - c[p];
+        bins[p * kCostBuckets + lane] = pos + v - c[p];
         // bucket lane holds lg = 63 - lane: split for lg >= t
         if (lane == 0) cls[kClsStarts + p] = pos;
         if (lane == 63 - (int)t) cls[kClsHeavyEnd + p] = pos + v;
         pos += (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
     }
     if (lane == 0) cls[kClsStarts + kXcds] = pos;
+}
+__global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, const unsigned long long *pairs)
+{
+    scan_bins(cls + kClsBins, cls, split_log2(*pairs));
 }
 
 __global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t n_groups,
@@ -1020,14 +1022,13 @@ __global__ __launch_bounds__(64) void k_force_f64(
 // The records in the caller's order, split into three arrays or applied as a kick (modes as
 // for store_rec; records are float4 for kOutF32, double4 otherwise).
 template <int MODE>
-__global__ __launch_bounds__(256) void k_force_out(const void *__restrict__ rec, int64_t n,
-                                                   void *ax, void *ay, void *az, double dt)
+__device__ __forceinline__ void write_out(const void *__restrict__ rec, int64_t n, void *ax,
+                                          void *ay, void *az, double dt, uint32_t b, uint32_t nb)
 {
     // the kick's product and sum are rounded separately: no fused multiply-add here (the
     // rest of this file contracts)
 #pragma clang fp contract(off)
-    for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < n;
-         j += (int64_t)gridDim.x * 256) {
+    for (int64_t j = (int64_t)b * 256 + threadIdx.x; j < n; j += (int64_t)nb * 256) {
         if (MODE == kOutF32) {
             const float4 r = ((const float4 *)rec)[j];
             ((float *)ax)[j] = r.x;
@@ -1049,12 +1050,116 @@ __global__ __launch_bounds__(256) void k_force_out(const void *__restrict__ rec,
     }
 }
 
+// The last stat_blocks blocks add up the groups' pairs; the others write the results.
+template <int MODE>
+__global__ __launch_bounds__(256) void k_force_out(const void *__restrict__ rec, int64_t n,
+                                                   void *ax, void *ay, void *az, double dt,
+                                                   uint32_t n_groups,
+                                                   const unsigned long long *__restrict__ pairs,
+                                                   unsigned long long *sum, uint32_t stat_blocks)
+{
+    const uint32_t nb = gridDim.x - stat_blocks;
+    if (blockIdx.x < nb)
+        write_out<MODE>(rec, n, ax, ay, az, dt, blockIdx.x, nb);
+    else
+        sum_pairs(n_groups, pairs, sum, blockIdx.x - nb, stat_blocks);
+}
+
+// Box blockIdx.y's float outputs and pairs.
+__global__ __launch_bounds__(256) void k_force_out_multi(const ForceBox *__restrict__ bx,
+                                                         uint32_t stat_blocks)
+{
+    const ForceBox &B = bx[blockIdx.y];
+    const uint32_t nb = gridDim.x - stat_blocks;
+    if (blockIdx.x < nb)
+        write_out<kOutF32>(B.rec, B.n, B.out[0], B.out[1], B.out[2], 0.0, blockIdx.x, nb);
+    else
+        sum_pairs(B.n_groups, B.fp.pairs, B.pair_sum, blockIdx.x - nb, stat_blocks);
+}
+
+// Statistics, queue bins, queues and their publication by one workgroup (see the class kernels
+// and launch_walk_stats for each part).
+__device__ __forceinline__ void walk_results(const WalkBox &B)
+{
+    constexpr int kThreads = 1024, kWaves = kThreads / 64;
+    __shared__ uint32_t bin[kBins];
+    __shared__ unsigned long long part[4][kWaves], tot[4];
+    const uint32_t tid = threadIdx.x, G = B.n_groups;
+    const int lane = tid & 63, wave = tid >> 6;
+    unsigned long long v[4] = {0, 0, 0, 0}; // cells, particles, pairs, longest list
+    for (uint32_t g = tid; g < G; g += kThreads) {
+        const unsigned long long l = B.len[g], c = B.gcells[g];
+        v[0] += c;
+        v[1] += l - c;
+        v[2] += l * B.gr.count[g];
+        v[3] = l > v[3] ? l : v[3];
+    }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) {
+        for (int k = 0; k < 3; ++k) v[k] += __shfl_xor(v[k], d, 64);
+        const unsigned long long o = __shfl_xor(v[3], d, 64);
+        v[3] = o > v[3] ? o : v[3];
+    }
+    if (lane == 0)
+        for (int k = 0; k < 4; ++k) part[k][wave] = v[k];
+    for (uint32_t i = tid; i < kBins; i += kThreads) bin[i] = 0;
+    __syncthreads();
+    if (tid < 4) {
+        unsigned long long t = 0;
+        for (int w = 0; w < kWaves; ++w)
+            t = tid == 3 ? (part[3][w] > t ? part[3][w] : t) : t + part[tid][w];
+        tot[tid] = t;
+        B.stats[tid] = t;
+    }
+    __syncthreads();
+    const uint32_t t = split_log2(tot[2]);
+    for (uint32_t g = tid; g < G; g += kThreads)
+        atomicAdd(&bin[cost_bin(g, G, B.gr.count[g], B.len[g], t)], 1u);
+    __syncthreads();
+    if (wave == 0) scan_bins(bin, B.cls, t);
+    __syncthreads();
+    for (uint32_t g = tid; g < G; g += kThreads)
+        B.cls[atomicAdd(&bin[cost_bin(g, G, B.gr.count[g], B.len[g], t)], 1u)] = g;
+    if (tid == 0 && B.mailbox) {
+        uint32_t *m = B.mailbox;
+        __hip_atomic_store(&m[1], *(volatile unsigned *)B.overflow, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+        for (int k = 0; k < 4; ++k) {
+            __hip_atomic_store(&m[2 + 2 * k], (uint32_t)tot[k], __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+            __hip_atomic_store(&m[3 + 2 * k], (uint32_t)(tot[k] >> 32), __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __hip_atomic_store(&m[0], B.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+__global__ __launch_bounds__(1024) void k_walk_results(WalkBox box) { walk_results(box); }
+__global__ __launch_bounds__(1024) void k_walk_results_multi(const WalkBox *__restrict__ bx)
+{
+    walk_results(bx[blockIdx.x]);
+}
+
+__device__ __forceinline__ void force_prep(const ForceBox &B, uint32_t b, uint32_t nb)
+{
+    const uint32_t i = b * 256u + threadIdx.x;
+    if (i < 2 * kXcds) B.cls[kClsQueue + i * kQueueStride] = 0;
+    if (i == 0) *B.pair_sum = 0;
+    for (uint32_t k = i; k < B.n_groups; k += nb * 256u) B.fp.pairs[k] = 0;
+}
+__global__ __launch_bounds__(256) void k_force_prep(ForceBox box)
+{
+    force_prep(box, blockIdx.x, gridDim.x);
+}
+__global__ __launch_bounds__(256) void k_force_prep_multi(const ForceBox *__restrict__ bx)
+{
+    force_prep(bx[blockIdx.y], blockIdx.x, gridDim.x);
+}
+
 } // namespace
 
 void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
                      const unsigned long long *pairs, uint32_t *cls, hipStream_t s)
 {
-    fill_u32(cls, kClsLists, 0u, s);
     if (!n_groups) return;
     const unsigned b = (n_groups + 256u * kClassifyItems - 1) / (256u * kClassifyItems);
     k_class_count<<<b, 256, 0, s>>>(gr, n_groups, len, pairs, cls + kClsBins);
@@ -1079,21 +1184,25 @@ void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_groups, in
                                                                                           nb);
 }
 
-__global__ __launch_bounds__(256) void k_force_prep(uint32_t *queue, unsigned long long *pairs,
-                                                    uint32_t n, unsigned long long *sum)
+void launch_force_prep(const ForceBox &box, hipStream_t s)
 {
-    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
-    if (i < 2 * kXcds) queue[i * kQueueStride] = 0;
-    if (i == 0) *sum = 0;
-    for (uint32_t k = i; k < n; k += gridDim.x * 256u) pairs[k] = 0;
+    const uint32_t b = (box.n_groups + 255) / 256;
+    k_force_prep<<<b < 1024 ? (b ? b : 1) : 1024, 256, 0, s>>>(box);
 }
 
-void launch_force_prep(uint32_t *cls, unsigned long long *pairs, uint32_t n_groups,
-                       unsigned long long *sum, hipStream_t s)
+void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s)
 {
-    const uint32_t b = (n_groups + 255) / 256;
-    k_force_prep<<<b < 1024 ? (b ? b : 1) : 1024, 256, 0, s>>>(cls + kClsQueue, pairs, n_groups,
-                                                             sum);
+    k_force_prep_multi<<<dim3(32, nb), 256, 0, s>>>(boxes);
+}
+
+void launch_walk_results_one(const WalkBox &box, hipStream_t s)
+{
+    k_walk_results<<<1, 1024, 0, s>>>(box);
+}
+
+void launch_walk_results_multi(const WalkBox *boxes, int nb, hipStream_t s)
+{
+    if (nb) k_walk_results_multi<<<nb, 1024, 0, s>>>(boxes);
 }
 
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,
@@ -1109,14 +1218,6 @@ void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const doubl
         out);
 }
 
-void launch_pair_stats(uint32_t n_groups, const unsigned long long *pairs,
-                       unsigned long long *sum, hipStream_t s)
-{
-    if (!n_groups) return;
-    const unsigned b = (n_groups + 255) / 256;
-    k_pair_stats<<<b < 256 ? b : 256, 256, 0, s>>>(n_groups, pairs, sum);
-}
-
 void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
                       const uint32_t *len, const uint32_t *entries, const double4 *ps, const uint32_t *pidx,
                       ForceParams fp, void *rec, int rec64, hipStream_t s)
@@ -1130,18 +1231,36 @@ void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const ui
                                               fp, rec);
 }
 
+static uint32_t stat_blocks(uint32_t n_groups)
+{
+    const uint32_t b = (n_groups + 1023) / 1024;
+    return b < 1 ? 1 : b < 64 ? b : 64;
+}
+
 void launch_force_out(const void *rec, int mode, int64_t n, void *ax, void *ay, void *az,
-                      double dt, hipStream_t s)
+                      double dt, uint32_t n_groups, const unsigned long long *pairs,
+                      unsigned long long *pair_sum, hipStream_t s)
 {
     if (n <= 0) return;
     const int64_t want = (n + 255) / 256;
-    const unsigned b = (unsigned)(want < 4096 ? want : 4096);
+    const uint32_t sb = stat_blocks(n_groups);
+    const unsigned b = (unsigned)(want < 4096 ? want : 4096) + sb;
     if (mode == kOutKick)
-        k_force_out<kOutKick><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt);
+        k_force_out<kOutKick><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt, n_groups, pairs,
+                                               pair_sum, sb);
     else if (mode == kOutF64)
-        k_force_out<kOutF64><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt);
+        k_force_out<kOutF64><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt, n_groups, pairs,
+                                              pair_sum, sb);
     else
-        k_force_out<kOutF32><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt);
+        k_force_out<kOutF32><<<b, 256, 0, s>>>(rec, n, ax, ay, az, dt, n_groups, pairs,
+                                              pair_sum, sb);
+}
+
+void launch_force_out_multi(const ForceBox *boxes, int nb, int64_t most, hipStream_t s)
+{
+    const int64_t want = (most + 255) / 256;
+    k_force_out_multi<<<dim3((unsigned)(want < 1024 ? want : 1024) + 4, nb), 256, 0, s>>>(boxes,
+                                                                                         4);
 }
 
 // ------------------------------------------------------------------ the pair-law table

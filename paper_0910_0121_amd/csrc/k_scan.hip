@@ -83,6 +83,48 @@ __global__ __launch_bounds__(kThreads) void k_scan_tile(T *data, size_t n, const
     if (total && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = off + tot;
 }
 
+// Exclusive scan in place by one workgroup, kOneTile values at a time with a carry: for up to
+// kOneScan values one launch of about 2 us a tile is less than the three of the general way.
+constexpr int kOneThreads = 1024;
+constexpr size_t kOneTile = (size_t)kOneThreads * kItems;
+constexpr size_t kOneScan = 4 * kOneTile;
+
+template <typename T>
+__global__ __launch_bounds__(kOneThreads) void k_scan_one(T *data, size_t n, T *total)
+{
+    __shared__ T wsum[kOneThreads / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    T carry = 0;
+    for (size_t t0 = 0; t0 < n; t0 += kOneTile) {
+        const size_t base = t0 + (size_t)threadIdx.x * kItems;
+        T v[kItems];
+        T s = 0;
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            v[i] = base + i < n ? data[base + i] : T(0);
+            s += v[i];
+        }
+        const T inc = wave_incl_scan(s);
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        T before = 0, all = 0;
+#pragma unroll
+        for (int i = 0; i < kOneThreads / 64; ++i) {
+            if (i < w) before += wsum[i];
+            all += wsum[i];
+        }
+        T run = carry + before + inc - s;
+#pragma unroll
+        for (int i = 0; i < kItems; ++i) {
+            if (base + i < n) data[base + i] = run;
+            run += v[i];
+        }
+        carry += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) *total = carry;
+}
+
 template <typename T>
 __global__ void k_set(T *p, size_t n, T v)
 {
@@ -101,6 +143,10 @@ void scan_rec(T *data, size_t n, T *total, T *tmp, hipStream_t s)
     size_t nb = (n + kTile - 1) / kTile;
     if (nb == 1) {
         k_scan_tile<T><<<1, kThreads, 0, s>>>(data, n, nullptr, total);
+        return;
+    }
+    if (n <= kOneScan) {
+        k_scan_one<T><<<1, kOneThreads, 0, s>>>(data, n, total);
         return;
     }
     T *partials = tmp;

@@ -258,27 +258,32 @@ __device__ __forceinline__ uint64_t walk_group(const WalkNode *__restrict__ wn,
 }
 
 // Two passes, one wave per group.  Count: cnt[g] = list length.  Emit: writes the list at
-// entries + off[g], and len[g], gcells[g].
+// entries + off[g], and len[g], gcells[g]; a list that ends past entries_cap sets bit 4 of
+// *overflow (the caller launches the emit pass on the room an earlier walk left, without
+// waiting for the lengths).
 template <int EMIT, int OPEN>
 __global__ __launch_bounds__(64) void k_walk(const WalkNode *__restrict__ wn, GroupArrays gr,
                                              uint32_t n_groups, WalkParams wp,
                                              uint64_t *__restrict__ cnt_off,
                                              uint32_t *__restrict__ len,
                                              uint32_t *__restrict__ entries,
-                                             unsigned *overflow, uint32_t *__restrict__ gcells)
+                                             uint64_t entries_cap, unsigned *overflow,
+                                             uint32_t *__restrict__ gcells)
 {
     __shared__ uint32_t stk[kStackCap];
     __shared__ uint32_t s_mark[64];
     const uint32_t g = xcd_block(blockIdx.x, gridDim.x);
     if (g >= n_groups) return;
     uint64_t ncell = 0;
+    const uint64_t at = EMIT ? min(cnt_off[g], entries_cap) : 0, room = entries_cap - at;
     const uint64_t w = walk_group<EMIT, OPEN>(wn, gr, g, wp, stk, s_mark,
-                                        EMIT ? entries + cnt_off[g] : nullptr, ~0ull, overflow,
-                                        &ncell);
+                                              EMIT ? entries + at : nullptr, room, overflow,
+                                              &ncell);
     if (threadIdx.x == 0) {
         if (!EMIT) {
             cnt_off[g] = w;
         } else {
+            if (w > room) atomicOr(overflow, 4u);
             len[g] = (uint32_t)w;
             gcells[g] = (uint32_t)ncell;
         }
@@ -391,13 +396,14 @@ __global__ __launch_bounds__(64) void k_walk_multi(const WalkBox *__restrict__ b
     const WalkBox &B = bx[box_of(bx, nb, t)];
     const uint32_t g = t - B.g0;
     uint64_t ncell = 0;
+    const uint64_t at = EMIT ? min(B.off[g], B.entries_cap) : 0, room = B.entries_cap - at;
     const uint64_t w =
-        walk_box_group<EMIT>(B, g, stk, s_mark, EMIT ? B.entries + B.off[g] : nullptr, ~0ull,
-                             &ncell);
+        walk_box_group<EMIT>(B, g, stk, s_mark, EMIT ? B.entries + at : nullptr, room, &ncell);
     if (threadIdx.x == 0) {
         if (!EMIT) {
             B.off[g] = w;
         } else {
+            if (w > room) atomicOr(B.overflow, 4u);
             B.len[g] = (uint32_t)w;
             B.gcells[g] = (uint32_t)ncell;
         }
@@ -518,7 +524,64 @@ __global__ __launch_bounds__(256) void k_walk_stats(GroupArrays gr, uint32_t n_g
     }
 }
 
+// What a walk starts from: no flags, statistics and queue bins, and a zero after the list
+// lengths (their prefix sum then ends with the total).
+__device__ __forceinline__ void walk_init(const WalkBox &B)
+{
+    for (uint32_t i = threadIdx.x; i < kClsLists; i += blockDim.x) B.cls[i] = 0u;
+    if (threadIdx.x < 4) B.stats[threadIdx.x] = 0ull;
+    if (threadIdx.x == 4) *B.overflow = 0u;
+    if (threadIdx.x == 5) B.off[B.n_groups] = 0ull;
+}
+__global__ __launch_bounds__(512) void k_walk_init(WalkBox box) { walk_init(box); }
+__global__ __launch_bounds__(512) void k_walk_init_multi(const WalkBox *__restrict__ bx)
+{
+    walk_init(bx[blockIdx.x]);
+}
+
+// The prefix sums of several boxes' list lengths, a workgroup per box (up to kOneBlockGroups).
+__global__ __launch_bounds__(1024) void k_walk_scan_multi(const WalkBox *__restrict__ bx)
+{
+    __shared__ uint64_t wsum[16];
+    const WalkBox &B = bx[blockIdx.x];
+    const uint32_t n = B.n_groups + 1;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    uint64_t carry = 0;
+    for (uint32_t t0 = 0; t0 < n; t0 += 1024u) {
+        const uint32_t g = t0 + threadIdx.x;
+        const uint64_t v = g < n ? B.off[g] : 0ull;
+        uint64_t inc = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint64_t o = __shfl_up(inc, d, 64);
+            if (lane >= d) inc += o;
+        }
+        if (lane == 63) wsum[w] = inc;
+        __syncthreads();
+        uint64_t before = 0, all = 0;
+        for (int q = 0; q < 16; ++q) {
+            if (q < w) before += wsum[q];
+            all += wsum[q];
+        }
+        if (g < n) B.off[g] = carry + before + inc - v;
+        carry += all;
+        __syncthreads();
+    }
+}
+
 } // namespace
+
+void launch_walk_init(const WalkBox &box, hipStream_t s) { k_walk_init<<<1, 512, 0, s>>>(box); }
+
+void launch_walk_init_multi(const WalkBox *boxes, int nb, hipStream_t s)
+{
+    if (nb) k_walk_init_multi<<<nb, 512, 0, s>>>(boxes);
+}
+
+void launch_walk_scan_multi(const WalkBox *boxes, int nb, hipStream_t s)
+{
+    if (nb) k_walk_scan_multi<<<nb, 1024, 0, s>>>(boxes);
+}
 
 void launch_walk_count(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
                        uint64_t *counts, unsigned *overflow, hipStream_t s)
@@ -526,23 +589,23 @@ void launch_walk_count(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, Wa
     if (!n_groups) return;
     if (wp.open)
         k_walk<0, 1><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, counts, nullptr, nullptr,
-                                            overflow, nullptr);
+                                            0, overflow, nullptr);
     else
         k_walk<0, 0><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, counts, nullptr, nullptr,
-                                            overflow, nullptr);
+                                            0, overflow, nullptr);
 }
 
 void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
-                      const uint64_t *off, uint32_t *len, uint32_t *entries, unsigned *overflow,
-                      uint32_t *gcells, hipStream_t s)
+                      const uint64_t *off, uint32_t *len, uint32_t *entries,
+                      uint64_t entries_cap, unsigned *overflow, uint32_t *gcells, hipStream_t s)
 {
     if (!n_groups) return;
     if (wp.open)
         k_walk<1, 1><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, const_cast<uint64_t *>(off),
-                                            len, entries, overflow, gcells);
+                                            len, entries, entries_cap, overflow, gcells);
     else
         k_walk<1, 0><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, const_cast<uint64_t *>(off),
-                                            len, entries, overflow, gcells);
+                                            len, entries, entries_cap, overflow, gcells);
 }
 
 void launch_walk_pool(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,

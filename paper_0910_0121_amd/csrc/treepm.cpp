@@ -847,8 +847,6 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
         return hip_fail(c, e, "group stats");
     if ((e = reserve(c->cls, (kClsLists + (size_t)G + 1) * 4)) != hipSuccess)
         return hip_fail(c, e, "group classes");
-    fill_u32(c->overflow.as<unsigned>(), 1, 0u, s);
-    fill_u64(c->wstats.as<uint64_t>(), 4, 0ull, s);
     const treepm_params &P = c->prm;
     const bool open = P.opening == TREEPM_OPEN_DISTANCE;
     const double th_lo = std::min(P.theta_max, P.theta / std::sqrt(0.46));
@@ -879,28 +877,55 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
     return TREEPM_OK;
 }
 
-// The lists in two passes: counts, their prefix sum, the lists.
-int walk_two_pass(treepm_ctx *c, hipStream_t s, const BoxWalk &bw)
+WalkBox walk_box(treepm_ctx *c, const BoxWalk &bw, uint32_t g0)
+{
+    WalkBox w{};
+    w.wn = c->n_walk.as<WalkNode>();
+    w.gr = groups_view(c);
+    w.wp = bw.wp;
+    w.off = c->off.as<uint64_t>();
+    w.len = c->glen.as<uint32_t>();
+    w.entries = c->entries.as<uint32_t>();
+    w.gcells = c->gcells.as<uint32_t>();
+    w.pool_next =
+        reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() + kXcds * kQueueStride);
+    w.pool_cap = bw.pool;
+    w.chunk = bw.chunk;
+    w.reserve = bw.reserve_len;
+    w.overflow = c->overflow.as<unsigned>();
+    w.g0 = g0;
+    w.n_groups = bw.G;
+    w.entries_cap = c->entries.bytes / 4;
+    w.stats = c->wstats.as<unsigned long long>();
+    w.cls = c->cls.as<uint32_t>();
+    return w;
+}
+
+// The lists in two passes: counts, their prefix sum, the lists.  With ahead, room that an
+// earlier walk left for lists is used without waiting for the lengths; the emit pass sets bit
+// 4 of the flags if it is too small.
+int walk_two_pass(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, bool ahead)
 {
     const uint32_t G = bw.G;
     uint64_t *off = c->off.as<uint64_t>(), *tot = c->scan64.as<uint64_t>();
     unsigned *ovf = c->overflow.as<unsigned>();
     const WalkNode *wn = c->n_walk.as<WalkNode>();
     GroupArrays gr = groups_view(c);
-    fill_u64(off, (size_t)G + 1, 0ull, s);
     launch_walk_count(wn, gr, G, bw.wp, off, ovf, s);
     scan_u64(off, (size_t)G + 1, tot, tot + 1, s);
-    uint64_t total = 0;
-    unsigned ov = 0;
-    int r = fetch(c, s, {&total, tot, sizeof total}, {&ov, ovf, sizeof ov});
-    if (r) return r;
-    if (ov)
-        return fail(c, TREEPM_ERR_OVERFLOW, ov & 2u ? "walk read a bad node index"
-                                                    : "walk stack overflow");
-    hipError_t e = reserve(c->entries, std::max<size_t>(total, 1) * 4);
-    if (e != hipSuccess) return hip_fail(c, e, "interaction lists");
+    if (!ahead || !c->walk_hint || !c->entries.p) {
+        uint64_t total = 0;
+        unsigned ov = 0;
+        int r = fetch(c, s, {&total, tot, sizeof total}, {&ov, ovf, sizeof ov});
+        if (r) return r;
+        if (ov)
+            return fail(c, TREEPM_ERR_OVERFLOW, ov & 2u ? "walk read a bad node index"
+                                                        : "walk stack overflow");
+        hipError_t e = reserve(c->entries, std::max<size_t>(total, 1) * 4);
+        if (e != hipSuccess) return hip_fail(c, e, "interaction lists");
+    }
     launch_walk_emit(wn, gr, G, bw.wp, off, c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
-                     ovf, c->gcells.as<uint32_t>(), s);
+                     c->entries.bytes / 4, ovf, c->gcells.as<uint32_t>(), s);
     return TREEPM_OK;
 }
 
@@ -911,8 +936,25 @@ struct WalkResults {
     uint32_t seq = 0;
 };
 
-int post_walk_results(treepm_ctx *c, hipStream_t s, WalkResults &wr)
+// Whether one workgroup makes and publishes a box's results.
+bool results_by_one(const treepm_ctx *c) { return c->n_groups <= kOneBlockGroups && c->mbox_h; }
+
+uint32_t next_seq(treepm_ctx *c)
 {
+    const uint32_t seq = ++c->mseq;
+    return seq ? seq : ++c->mseq;
+}
+
+int post_walk_results(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr)
+{
+    if (results_by_one(c)) {
+        WalkBox w = walk_box(c, bw, 0);
+        w.mailbox = c->mbox_d;
+        wr.seq = w.seq = next_seq(c);
+        launch_walk_results_one(w, s);
+        HIPCHK(c, hipGetLastError());
+        return TREEPM_OK;
+    }
     const uint32_t G = c->n_groups;
     GroupArrays gr = groups_view(c);
     uint32_t *len = c->glen.as<uint32_t>(), *cls = c->cls.as<uint32_t>();
@@ -939,11 +981,10 @@ int settle_walk(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr
 {
     int rc;
     while (wr.hov) {
-        fill_u32(c->overflow.as<unsigned>(), 1, 0u, s);
-        fill_u64(c->wstats.as<uint64_t>(), 4, 0ull, s);
-        if ((rc = walk_two_pass(c, s, bw))) return rc;
+        launch_walk_init(walk_box(c, bw, 0), s);
+        if ((rc = walk_two_pass(c, s, bw, false))) return rc;
         wr = WalkResults{};
-        if ((rc = post_walk_results(c, s, wr))) return rc;
+        if ((rc = post_walk_results(c, s, bw, wr))) return rc;
         if ((rc = wait_walk_results(c, s, wr))) return rc;
     }
     c->n_entries = wr.hs[0] + wr.hs[1];
@@ -959,15 +1000,16 @@ int do_walk(treepm_ctx *c, hipStream_t s)
     int rc;
     BoxWalk bw;
     if ((rc = prepare_walk(c, s, bw))) return rc;
+    launch_walk_init(walk_box(c, bw, 0), s);
     if (bw.pooled)
         launch_walk_pool(c->n_walk.as<WalkNode>(), groups_view(c), bw.G, bw.wp, bw.waves, bw.pool,
                          bw.chunk, bw.reserve_len, c->wctr.as<uint32_t>(), c->off.as<uint64_t>(),
                          c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
                          c->overflow.as<unsigned>(), c->gcells.as<uint32_t>(), s);
-    else if ((rc = walk_two_pass(c, s, bw)))
+    else if ((rc = walk_two_pass(c, s, bw, true)))
         return rc;
     WalkResults wr;
-    if ((rc = post_walk_results(c, s, wr))) return rc;
+    if ((rc = post_walk_results(c, s, bw, wr))) return rc;
     if ((rc = wait_walk_results(c, s, wr))) return rc;
     return settle_walk(c, s, bw, wr);
 }
@@ -1311,12 +1353,27 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
     return TREEPM_OK;
 }
 
-// The context as the FP32 force kernel reads it (ensure_table has run, kept is reserved).
+// The context as the force launches read it (pairs and pair sums are reserved; for the FP32
+// kernel, ensure_table has run).
 ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
 {
-    return ForceBox{nodes_view(c), groups_view(c), c->cls.as<uint32_t>(),
-                    c->off.as<uint64_t>(), c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
-                    c->psrc.as<double4>(), c->idx.as<uint32_t>(), fp, c->ftab, rec, rec64};
+    ForceBox F{};
+    F.nd = nodes_view(c);
+    F.gr = groups_view(c);
+    F.cls = c->cls.as<uint32_t>();
+    F.off = c->off.as<uint64_t>();
+    F.len = c->glen.as<uint32_t>();
+    F.entries = c->entries.as<uint32_t>();
+    F.ps = c->psrc.as<double4>();
+    F.pidx = c->idx.as<uint32_t>();
+    F.fp = fp;
+    F.ft = c->ftab;
+    F.rec = rec;
+    F.rec64 = rec64;
+    F.n_groups = c->n_groups;
+    F.pair_sum = c->kept_sum.as<unsigned long long>();
+    F.n = c->n;
+    return F;
 }
 
 } // namespace
@@ -1367,13 +1424,13 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     }
     ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
                    c->kept.as<unsigned long long>()};
-    launch_force_prep(c->cls.as<uint32_t>(), fp.pairs, c->n_groups,
-                      c->kept_sum.as<unsigned long long>(), s);
     const int rec64 = out_prec != TREEPM_FP32;
     void *rec = c->rec.p; // n x 32 bytes since the build
+    if (P.precision == TREEPM_FP32 && (rc = ensure_table(c, s))) return rc;
+    const ForceBox F = force_box(c, fp, rec, rec64);
+    launch_force_prep(F, s);
     if (P.precision == TREEPM_FP32) {
-        if ((rc = ensure_table(c, s))) return rc;
-        launch_force_f32(force_box(c, fp, rec, rec64), c->n_groups, c->n_cu, s);
+        launch_force_f32(F, c->n_groups, c->n_cu, s);
     } else
         launch_force_f64(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
                          c->entries.as<uint32_t>(),
@@ -1382,11 +1439,10 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
         launch_quad(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
                     c->entries.as<uint32_t>(), c->psrc.as<double4>(), c->idx.as<uint32_t>(),
                     c->n_q.as<double>(), fp, rec, P.precision == TREEPM_FP64, rec64, s);
-    launch_force_out(rec, out_prec, (int64_t)c->n, dst[0], dst[1], dst[2], kick_dt, s);
+    launch_force_out(rec, out_prec, (int64_t)c->n, dst[0], dst[1], dst[2], kick_dt, c->n_groups,
+                     fp.pairs, F.pair_sum, s);
     HIPCHK(c, hipGetLastError());
     record(c, 5, s);
-    launch_pair_stats(c->n_groups, c->kept.as<unsigned long long>(),
-                          c->kept_sum.as<unsigned long long>(), s);
     c->last_force_prec = P.precision;
     c->ev_valid[2] = c->timing;
     if (mem_kind == TREEPM_HOST) {
@@ -1444,6 +1500,10 @@ struct BatchScope {
     }
 };
 
+// The leader's descriptor buffer: four runs of walk descriptors, the force descriptors, the
+// walk's counters.
+constexpr size_t kBatchForceAt = 4 * (size_t)kMaxBatch * sizeof(WalkBox);
+
 // The box descriptors of one shared launch, copied to the leader's device buffer at `at`
 // (bytes); the host copy stays alive until the batch has synchronised.
 template <typename T>
@@ -1453,26 +1513,6 @@ int upload(treepm_ctx *lead, hipStream_t s, const std::vector<T> &v, size_t at, 
     if (!v.empty())
         HIPCHK(lead, hipMemcpyAsync(*dev, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice, s));
     return TREEPM_OK;
-}
-
-WalkBox walk_box(treepm_ctx *c, const BoxWalk &bw, uint32_t g0)
-{
-    WalkBox w{};
-    w.wn = c->n_walk.as<WalkNode>();
-    w.gr = groups_view(c);
-    w.wp = bw.wp;
-    w.off = c->off.as<uint64_t>();
-    w.len = c->glen.as<uint32_t>();
-    w.entries = c->entries.as<uint32_t>();
-    w.gcells = c->gcells.as<uint32_t>();
-    w.pool_next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() + kXcds * kQueueStride);
-    w.pool_cap = bw.pool;
-    w.chunk = bw.chunk;
-    w.reserve = bw.reserve_len;
-    w.overflow = c->overflow.as<unsigned>();
-    w.g0 = g0;
-    w.n_groups = bw.G;
-    return w;
 }
 
 // The walk of boxes cs[0 .. nb) with shared launches: the boxes whose last walk sizes a pool
@@ -1489,10 +1529,17 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
         Bind bind(cs[b], s);
         if ((rc = prepare_walk(cs[b], s, bw[b]))) return rc;
     }
-    std::vector<WalkBox> two, pool;
+    std::vector<WalkBox> two, pool, all, small;
     std::vector<int> two_ix;
+    std::vector<WalkResults> wr(nb);
     uint32_t two_total = 0, pool_total = 0, pool_waves_sum = 0;
     for (int b = 0; b < nb; ++b) {
+        all.push_back(walk_box(cs[b], bw[b], 0));
+        if (results_by_one(cs[b])) {
+            WalkBox w = all.back();
+            w.mailbox = cs[b]->mbox_d;
+            small.push_back(w);
+        }
         if (!bw[b].G) continue;
         if (bw[b].pooled) {
             pool.push_back(walk_box(cs[b], bw[b], pool_total));
@@ -1506,33 +1553,50 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
     }
     {
         Bind bind(lead, s);
-        const size_t bytes = (2 * (size_t)kMaxBatch) * sizeof(WalkBox) +
-                             (size_t)kMaxBatch * sizeof(ForceBox) + kWalkCounterWords * 4;
+        const size_t bytes = kBatchForceAt + (size_t)kMaxBatch * sizeof(ForceBox) +
+                             kWalkCounterWords * 4;
         hipError_t e = reserve(lead->bdesc, bytes);
         if (e != hipSuccess) return hip_fail(lead, e, "batch descriptors");
     }
-    const size_t at_two = 0, at_pool = (size_t)kMaxBatch * sizeof(WalkBox);
-    const size_t at_ctr = 2 * (size_t)kMaxBatch * sizeof(WalkBox) + (size_t)kMaxBatch * sizeof(ForceBox);
+    // descriptor runs: all boxes, two-pass boxes, pooled ones, those of few groups
+    constexpr size_t kRun = (size_t)kMaxBatch * sizeof(WalkBox);
+    const size_t at_ctr = kBatchForceAt + (size_t)kMaxBatch * sizeof(ForceBox);
     uint32_t *counters = reinterpret_cast<uint32_t *>(static_cast<char *>(lead->bdesc.p) + at_ctr);
     WalkBox *dev = nullptr;
+    if ((rc = upload(lead, s, all, 0, &dev))) return rc;
+    launch_walk_init_multi(dev, nb, s);
     if (!two.empty()) {
-        for (const WalkBox &w : two) fill_u64(w.off, (size_t)w.n_groups + 1, 0ull, s);
-        if ((rc = upload(lead, s, two, at_two, &dev))) return rc;
+        if ((rc = upload(lead, s, two, kRun, &dev))) return rc;
         launch_walk_count_multi(dev, (int)two.size(), two_total, s);
+        bool few = true;
+        for (const WalkBox &w : two) few = few && w.n_groups < kOneBlockGroups;
+        if (few)
+            launch_walk_scan_multi(dev, (int)two.size(), s);
+        else
+            for (size_t k = 0; k < two.size(); ++k) {
+                uint64_t *tot = cs[two_ix[k]]->scan64.as<uint64_t>();
+                scan_u64(two[k].off, (size_t)two[k].n_groups + 1, tot, tot + 1, s);
+            }
+        // boxes walked before write into the room that walk left; the others wait for their
+        // lengths (all together)
         std::vector<uint64_t> total(two.size());
         std::vector<unsigned> ov(two.size());
-        std::vector<uint32_t> seq(two.size());
+        std::vector<uint32_t> seq(two.size(), 0);
+        bool fresh = false;
         for (size_t k = 0; k < two.size(); ++k) {
             treepm_ctx *c = cs[two_ix[k]];
-            uint64_t *tot = c->scan64.as<uint64_t>();
-            scan_u64(two[k].off, (size_t)two[k].n_groups + 1, tot, tot + 1, s);
+            if (c->walk_hint && c->entries.p) continue;
+            fresh = true;
+            const uint64_t *tot = two[k].off + two[k].n_groups;
             if ((rc = fetch_post(c, s, &seq[k], {&total[k], tot, sizeof total[k]},
                                  {&ov[k], two[k].overflow, sizeof ov[k]})))
                 return rc;
         }
         for (size_t k = 0; k < two.size(); ++k) {
             treepm_ctx *c = cs[two_ix[k]];
-            if ((rc = fetch_wait(c, s, seq[k], {&total[k], c->scan64.p, sizeof total[k]},
+            if (c->walk_hint && c->entries.p) continue;
+            if ((rc = fetch_wait(c, s, seq[k],
+                                 {&total[k], two[k].off + two[k].n_groups, sizeof total[k]},
                                  {&ov[k], two[k].overflow, sizeof ov[k]})))
                 return rc;
             if (ov[k])
@@ -1542,19 +1606,30 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
             hipError_t e = reserve(c->entries, std::max<size_t>(total[k], 1) * 4);
             if (e != hipSuccess) return hip_fail(c, e, "interaction lists");
             two[k].entries = c->entries.as<uint32_t>();
+            two[k].entries_cap = c->entries.bytes / 4;
         }
-        if ((rc = upload(lead, s, two, at_two, &dev))) return rc;
+        if (fresh && (rc = upload(lead, s, two, kRun, &dev))) return rc;
         launch_walk_emit_multi(dev, (int)two.size(), two_total, s);
     }
     if (!pool.empty()) {
         for (const WalkBox &w : pool) fill_u64(reinterpret_cast<uint64_t *>(w.pool_next), 1, 0ull, s);
-        if ((rc = upload(lead, s, pool, at_pool, &dev))) return rc;
+        if ((rc = upload(lead, s, pool, 2 * kRun, &dev))) return rc;
         launch_walk_pool_multi(dev, (int)pool.size(), pool_total,
                                std::max(1u, std::min(8192u, pool_waves_sum)), counters, s);
     }
-    std::vector<WalkResults> wr(nb);
+    if (!small.empty()) {
+        size_t k = 0;
+        for (int b = 0; b < nb; ++b)
+            if (results_by_one(cs[b])) {
+                wr[b].seq = small[k].seq = next_seq(cs[b]);
+                small[k].entries = cs[b]->entries.as<uint32_t>();
+                ++k;
+            }
+        if ((rc = upload(lead, s, small, 3 * kRun, &dev))) return rc;
+        launch_walk_results_multi(dev, (int)small.size(), s);
+    }
     for (int b = 0; b < nb; ++b)
-        if ((rc = post_walk_results(cs[b], s, wr[b]))) return rc;
+        if (!results_by_one(cs[b]) && (rc = post_walk_results(cs[b], s, bw[b], wr[b]))) return rc;
     for (int b = 0; b < nb; ++b)
         if ((rc = wait_walk_results(cs[b], s, wr[b]))) return rc;
     for (int b = 0; b < nb; ++b) {
@@ -1593,8 +1668,7 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         const ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
                              c->kept.as<unsigned long long>()};
         fb[b] = force_box(c, fp, c->rec.p, 0);
-        launch_force_prep(fb[b].cls, fp.pairs, c->n_groups,
-                          c->kept_sum.as<unsigned long long>(), s);
+        for (int a = 0; a < 3; ++a) fb[b].out[a] = dst[b][a];
     }
     // the boxes by table: each launch's workgroups then load one table
     std::vector<int> order(nb);
@@ -1604,8 +1678,8 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
     std::vector<ForceBox> sorted(nb);
     for (int k = 0; k < nb; ++k) sorted[k] = fb[order[k]];
     ForceBox *dev = nullptr;
-    const size_t at_force = 2 * (size_t)kMaxBatch * sizeof(WalkBox);
-    if ((rc = upload(lead, s, sorted, at_force, &dev))) return rc;
+    if ((rc = upload(lead, s, sorted, kBatchForceAt, &dev))) return rc;
+    launch_force_prep_multi(dev, nb, s);
     for (int k = 0; k < nb;) {
         int k1 = k;
         uint32_t groups = 0;
@@ -1614,19 +1688,18 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         launch_force_f32_multi(dev + k, k1 - k, groups, lead->n_cu, s);
         k = k1;
     }
+    int64_t most = 0;
     for (int b = 0; b < nb; ++b) {
         treepm_ctx *c = cs[b];
         const ForceBox &F = fb[b];
         if (c->prm.quadrupole)
             launch_quad(F.nd, F.gr, c->n_groups, F.off, F.len, F.entries, F.ps, F.pidx,
                         c->n_q.as<double>(), F.fp, F.rec, 0, 0, s);
-        launch_force_out(F.rec, TREEPM_FP32, (int64_t)c->n, dst[b][0], dst[b][1], dst[b][2],
-                         0.0, s);
-        launch_pair_stats(c->n_groups, c->kept.as<unsigned long long>(),
-                          c->kept_sum.as<unsigned long long>(), s);
+        most = std::max(most, c->n);
         c->last_force_prec = TREEPM_FP32;
         c->ev_valid[1] = c->ev_valid[2] = false;
     }
+    launch_force_out_multi(dev, nb, most, s);
     HIPCHK(lead, hipGetLastError());
     if (mem_kind == TREEPM_HOST)
         for (int b = 0; b < nb; ++b) {

@@ -87,3 +87,46 @@ def test_build_sizes(tp, orc, n, clump, side):
             assert tp.treepm_walk(ctx).interactions == T.interactions()
     finally:
         tp.treepm_destroy(ctx)
+
+
+def test_lists_in_the_room_an_earlier_walk_left(tp, orc):
+    """Two-pass walks of a used context write the lists into the room that is there without
+    waiting for their lengths: a box with more entries than fit, and then boxes that do fit, must
+    leave the oracle's lists, alone and in a batch."""
+    r_cut, theta, n_leaf, n_crit = 0.06, 0.5, 10, 64
+    eps = r_cut / 60
+    boxes = [boxgen.nfw_box(3000, 3, 21), boxgen.nfw_box(60000, 100, 2), boxgen.nfw_box(3000, 3, 22),
+             boxgen.nfw_box(90000, 9, 23)]
+    trees = [orc.Tree(*b, 1.0, r_cut, eps, theta, n_leaf, n_crit) for b in boxes]
+    p = tp.treepm_params(1.0, r_cut / 3.0, r_cut, eps, theta, n_leaf, n_crit, tp.TREEPM_FP32)
+
+    def check(ctx, k, what):
+        print(f"[gpu-case] room: box {k} {what}", flush=True)
+        off, isc, val = tp.treepm_export_lists(ctx)
+        oo, oc, ov = trees[k].lists()
+        np.testing.assert_array_equal(np.diff(off), np.diff(oo))
+        g = np.repeat(np.arange(oo.size - 1), np.diff(oo))
+        a, b = np.lexsort((val, isc, g)), np.lexsort((ov, oc, g))
+        np.testing.assert_array_equal(isc[a], oc[b])
+        np.testing.assert_array_equal(val[a], ov[b])
+
+    ctxs = [tp.treepm_create(p, 0) for _ in range(3)]
+    try:
+        for k in (0, 1, 2, 3):
+            tp.treepm_build(ctxs[0], *[torch.from_numpy(a).cuda() for a in boxes[k]])
+            assert tp.treepm_walk(ctxs[0]).interactions == trees[k].interactions()
+            check(ctxs[0], k, "alone")
+        # a batch of a used context with too little room, a fresh one, and one that fits
+        tp.treepm_build(ctxs[1], *[torch.from_numpy(a).cuda() for a in boxes[0]])
+        tp.treepm_walk(ctxs[1])
+        use = (3, 1, 2)
+        for c, k in zip(ctxs, use):
+            tp.treepm_build(c, *[torch.from_numpy(a).cuda() for a in boxes[k]])
+        outs = [[torch.zeros(boxes[k][0].size, dtype=torch.float32, device="cuda")
+                 for _ in range(3)] for k in use]
+        tp.treepm_force_short_batch(ctxs, outs)
+        for c, k in zip(ctxs, use):
+            check(c, k, "batch")
+    finally:
+        for c in ctxs:
+            tp.treepm_destroy(c)
