@@ -29,6 +29,8 @@ SOURCES = {
     "k_build.hip": ["-ffp-contract=off"],
     "k_walk.hip": ["-ffp-contract=off"],
     "k_force.hip": [],
+    "k_force64.hip": [],
+    "force_table64.cpp": [],
     "k_pm.hip": [],
     "k_quad.hip": [],
     "k_step.hip": ["-ffp-contract=off"],

@@ -257,6 +257,17 @@ struct ForceTable {
 // pointer; false if eps / r_cut is not in [2^-13, 8).
 bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTable &ft);
 
+// The FP64 kernel's table: pieces of p = G^(1/5) of degree kTab64Deg in t, 64 per octave over
+// kTab64Oct octaves of u = c + (1 - c) s, c = 2^-kTab64Oct (see force_table64.cpp); the entry of
+// u = 1 is zero.  The coefficients of powers 0 .. kTab64F64 - 1 are doubles, the others floats,
+// each power an array of kTab64Entries.
+constexpr int kTab64Exp = 18;
+constexpr int kTab64Deg = 6, kTab64Oct = 24, kTab64F64 = 4;
+constexpr uint32_t kTab64Entries = (uint32_t)kTab64Oct * 64u + 1u;
+// False if (eps / r_cut)^2 is below 2^(1 - kTab64Oct) (the first pieces would not resolve it) or
+// above 64: the kernel then evaluates eq. (2) pair by pair.
+bool build_force_table64(double eps_over_rcut, std::vector<double> &hi, std::vector<float> &lo);
+
 // Layout of the queue buffer (u32 words): the kXcds + 1 part starts and the kXcds ends of the
 // parts' runs of split groups (absolute word positions in the buffer), the queue counters of
 // the split and of the other groups, the (part, cost bucket) cursors, then the group ids, each
@@ -289,6 +300,8 @@ struct ForceBox {
     ForceTable ft;
     void *rec;
     int rec64; // rec holds double4 records
+    const double *tab64_hi; // FP64 kernel: its table, or null (pair by pair)
+    const float *tab64_lo;
     uint32_t n_groups;
     unsigned long long *pair_sum; // pairs evaluated, over all groups
     int64_t n;
@@ -317,9 +330,8 @@ void launch_force_out_multi(const ForceBox *boxes, int nb, int64_t most, hipStre
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,
                          const double *mj, const double *xg, double eta, ForceTable ft,
                          double *out, hipStream_t s);
-void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
-                      const uint32_t *len, const uint32_t *entries, const double4 *ps, const uint32_t *pidx,
-                      ForceParams fp, void *rec, int rec64, hipStream_t s);
+// The FP64 force (k_force64.hip), over the same queues.
+void launch_force_f64(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
 
 // Particle-mesh long-range force (k_pm.hip), mesh N^3 with N a power of two in [16, 1024].
 // Lines per FFT workgroup for mesh size N.

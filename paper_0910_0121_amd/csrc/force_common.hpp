@@ -1,0 +1,434 @@
+// Parts shared by the FP32 and FP64 force kernels: the persistent workgroups and their queues,
+// the split of a group into chunks of particles, and the reduction and output of their sums.
+// A kernel is a policy P: kWaves (waves per workgroup), kTilesAt and kTileBytes (the waves' LDS
+// tiles), Frame (a group's origin and units, with `scale`, the factor of the sums), load_table,
+// group (reads a group, makes its frame and calls finish_group) and chunk_sums<K> (a wave's sums
+// for a chunk over a range of the group's list; returns the entries that survived the cull).
+#pragma once
+
+#include "common.hpp"
+
+namespace tpm {
+namespace {
+
+// The force kernels leave one record per particle, in the caller's order: float4 (ax, ay, az,
+// 0) for float results, double4 for double results and for the kick.  The caller's order is
+// arbitrary, so each store lands in its own 32-byte HBM sector: one 16- or 32-byte record costs
+// one sector where three 4- or 8-byte component stores cost three.  k_force_out then walks the
+// records in order and splits them into the caller's three arrays (kOutF32, kOutF64) or adds dt
+// times them to double velocities (kOutKick: the kick of Section 2.2 step 5 taken with the
+// short-range force as soon as it is known), each product and sum rounded on its own.
+enum { kOutF32 = 0, kOutF64 = 1, kOutKick = 2 };
+
+template <int REC64>
+__device__ __forceinline__ void store_rec(void *rec, uint32_t i, double vx, double vy, double vz)
+{
+    if (REC64)
+        ((double4 *)rec)[i] = make_double4(vx, vy, vz, 0.0);
+    else
+        ((float4 *)rec)[i] = make_float4((float)vx, (float)vy, (float)vz, 0.0f);
+}
+
+// The LDS writes of this wave are complete before any of its lanes reads LDS again (the
+// waves of a workgroup work on different lists, so a workgroup barrier is not wanted).
+__device__ __forceinline__ void wave_lds_sync()
+{
+    __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0); vector memory counters untouched
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Wave-uniform values that the compiler cannot know to be uniform, into scalar registers.
+__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uni(double v)
+{
+    return __hiloint2double((int)uni((uint32_t)__double2hiint(v)),
+                            (int)uni((uint32_t)__double2loint(v)));
+}
+__device__ __forceinline__ float uni(float v) { return __uint_as_float(uni(__float_as_uint(v))); }
+
+// Keeps a wave-uniform value in a vector register.
+__device__ __forceinline__ float in_vgpr(float v)
+{
+    asm("" : "+v"(v));
+    return v;
+}
+
+// The list entries of the tile starting at jb (jb < je), one per lane and round.  Slots past
+// the range's end read its last entry and are dropped when the tile is packed.  The caller issues
+// these reads one tile ahead, so they are in flight while the previous tile is evaluated.
+template <int ROUNDS>
+__device__ __forceinline__ void fetch_entries(const uint32_t *__restrict__ list, uint32_t jb,
+                                              uint32_t je, uint32_t *ent)
+{
+    const uint32_t lane = __lane_id();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const uint32_t j = jb + (uint32_t)(r * 64) + lane;
+        ent[r] = list[j < je ? j : je - 1];
+    }
+}
+
+// The bounding box of a chunk of the group's particles in x' units, for the cull.
+struct ChunkBox {
+    float c0, c1, c2; // centre
+    float h0, h1, h2; // minus half the half size
+    float thr;        // a quarter of the squared cull distance, with margin
+};
+
+// The group's particles run in chunks of S lanes x K particles per lane, the wave's 64 / S
+// streams taking every J-th source.  A chunk is the largest of 128, 64, 32 and 16 (K = 4) that
+// wastes at most a sixth of its slots; up to 8 particles run as S = 4, K = 2.  Loading a tile
+// costs as much as two or three particles' pairs with it, so two chunks with few idle slots
+// beat one with many, and one kernel within 128 VGPRs (four waves per SIMD) serves every group
+// size.  Force call of the 256^3 clustered box with chunks of up to 32, 64, 128 and 256: 11.1,
+// 10.5, 10.4 and 10.6 ms; with five and six waves per SIMD (and the spills that takes) 12.8
+// and 12.4 ms.
+__host__ __device__ __forceinline__ void chunk_layout(uint32_t r, int &S, int &K)
+{
+    K = 4;
+    S = r >= 107 ? 32 : r >= 54 ? 16 : r >= 27 ? 8 : 4;
+    if (r <= 8) K = 2;
+}
+
+// The least (or, on negated values, the greatest) of v over each run of S lanes.
+__device__ __forceinline__ float run_min(float v, int S)
+{
+#define TPM_MIN_DPP(ctrl)                                                                      \
+    v = fminf(v, __uint_as_float(__builtin_amdgcn_update_dpp(                                  \
+                     0, __float_as_uint(v), ctrl, 0xf, 0xf, false)))
+    TPM_MIN_DPP(0xb1);               // quad_perm 1, 0, 3, 2
+    TPM_MIN_DPP(0x4e);               // quad_perm 2, 3, 0, 1
+    if (S >= 8) TPM_MIN_DPP(0x141);  // row_half_mirror: the other four of eight
+    if (S >= 16) TPM_MIN_DPP(0x140); // row_mirror: the other eight of sixteen
+#undef TPM_MIN_DPP
+    if (S >= 32) v = fminf(v, __shfl_xor(v, 16, 64));
+    if (S >= 64) v = fminf(v, __shfl_xor(v, 32, 64));
+    return v;
+}
+
+// The box of the chunk's particles, K per lane and repeated over the J streams.
+template <int K>
+__device__ __forceinline__ ChunkBox chunk_box(const float *xi, const float *yi, const float *zi,
+                                              int S)
+{
+    ChunkBox C;
+    float lo[3] = {xi[0], yi[0], zi[0]}, hi[3] = {-xi[0], -yi[0], -zi[0]};
+#pragma unroll
+    for (int k = 1; k < K; ++k) {
+        lo[0] = fminf(lo[0], xi[k]);
+        lo[1] = fminf(lo[1], yi[k]);
+        lo[2] = fminf(lo[2], zi[k]);
+        hi[0] = fminf(hi[0], -xi[k]);
+        hi[1] = fminf(hi[1], -yi[k]);
+        hi[2] = fminf(hi[2], -zi[k]);
+    }
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        lo[a] = uni(run_min(lo[a], S));
+        hi[a] = -uni(run_min(hi[a], S));
+    }
+    C.c0 = 0.5f * (lo[0] + hi[0]);
+    C.c1 = 0.5f * (lo[1] + hi[1]);
+    C.c2 = 0.5f * (lo[2] + hi[2]);
+    C.h0 = -0.25f * (hi[0] - lo[0]);
+    C.h1 = -0.25f * (hi[1] - lo[1]);
+    C.h2 = -0.25f * (hi[2] - lo[2]);
+    // The coordinates near the threshold are at most 1 + 2 max(h) + |c| in size, each rounded a
+    // few times to 2^-24 of that; the cull distance is at most 1.
+    const float big = 1.0f + 4.0f * fmaxf(fmaxf(-C.h0, -C.h1), -C.h2) +
+                      fmaxf(fmaxf(fabsf(C.c0), fabsf(C.c1)), fabsf(C.c2));
+    C.thr = uni(0.25f * (1.0f + 0x1p-12f + 0x1p-20f * big));
+    return C;
+}
+
+// The J streams' sums on every lane, in a fixed tree.
+template <int K>
+__device__ __forceinline__ void add_streams(double *ax, double *ay, double *az, int S)
+{
+    for (int d = S; d < 64; d <<= 1) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            ax[k] += __shfl_xor(ax[k], d, 64);
+            ay[k] += __shfl_xor(ay[k], d, 64);
+            az[k] += __shfl_xor(az[k], d, 64);
+        }
+    }
+}
+
+// One chunk by one wave (whole list), or by the workgroup's waves, each on its own
+// part [j0, j1) of the list: then the waves' sums meet in LDS (the tiles, two k at a time: 128
+// particles x 3 doubles fill one tile) and are added in wave order.
+template <class P, int K>
+__device__ __forceinline__ uint32_t run_chunk(char *tiles, int wave, bool split, int S,
+                                              uint32_t n_i, uint32_t f, const uint32_t *list,
+                                              uint32_t j0, uint32_t j1, const ForceBox &B,
+                                              const typename P::Frame &F)
+{
+    double ax[K], ay[K], az[K];
+    const uint32_t kept = P::template chunk_sums<K>(tiles + wave * P::kTileBytes, S, n_i, f, list,
+                                                    j0, j1, B, F, ax, ay, az);
+    const double scale = F.scale;
+    const uint32_t *__restrict__ const pidx = B.pidx;
+    void *const rec = B.rec;
+    const int rec64 = B.rec64;
+    const int lane = __lane_id();
+    if (!split) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t i = (uint32_t)(lane + S * k);
+            if (lane < S && i < n_i) {
+                if (rec64)
+                    store_rec<1>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
+                else
+                    store_rec<0>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
+            }
+        }
+        return kept;
+    }
+    double *const red = reinterpret_cast<double *>(tiles);
+    constexpr int kWaveWords = P::kTileBytes / 8;
+    static_assert(128 * 24 <= P::kTileBytes, "128 particles' sums fit a tile");
+#pragma unroll
+    for (int kb = 0; kb < K; kb += 2) {
+#pragma unroll
+        for (int k = kb; k < kb + 2 && k < K; ++k)
+            if (lane < S) {
+                double *const d = red + wave * kWaveWords + ((k - kb) * 64 + lane) * 3;
+                d[0] = ax[k];
+                d[1] = ay[k];
+                d[2] = az[k];
+            }
+        __syncthreads();
+        const int t = threadIdx.x;
+        const int k = kb + (t >> 6);
+        const uint32_t i = (uint32_t)(lane + S * k);
+        if (t < 128 && k < K && lane < S && i < n_i) {
+            double vx = 0.0, vy = 0.0, vz = 0.0;
+            for (int w = 0; w < P::kWaves; ++w) {
+                const double *d = red + w * kWaveWords + t * 3;
+                vx += d[0];
+                vy += d[1];
+                vz += d[2];
+            }
+            if (rec64)
+                store_rec<1>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+            else
+                store_rec<0>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+        }
+        __syncthreads();
+    }
+    return kept;
+}
+
+// All chunks of a group over the list range [j0, j1); returns the pairs with the entries that
+// survived the cull.
+template <class P>
+__device__ __forceinline__ uint64_t run_group(char *tiles, int wave, bool split,
+                                              const ForceBox &B, uint32_t n_g, uint32_t f,
+                                              const uint32_t *list, uint32_t j0, uint32_t j1,
+                                              const typename P::Frame &F)
+{
+    uint64_t pairs = 0;
+    for (uint32_t ib = 0; ib < n_g;) {
+        int S, K;
+        chunk_layout(n_g - ib, S, K);
+        const uint32_t n_i = n_g - ib < (uint32_t)(S * K) ? n_g - ib : (uint32_t)(S * K);
+        uint32_t kept;
+        if (K == 4)
+            kept = run_chunk<P, 4>(tiles, wave, split, S, n_i, f + ib, list, j0, j1, B, F);
+        else
+            kept = run_chunk<P, 2>(tiles, wave, split, S, n_i, f + ib, list, j0, j1, B, F);
+        ib += n_i;
+        pairs += (uint64_t)kept * n_i;
+    }
+    return pairs;
+}
+
+// What the kernels read about a group, all of it before any is used: one memory latency.
+struct GroupRead {
+    double lo[3], hi[3], xg[3];
+    uint32_t count, first, len;
+    uint64_t off;
+    __device__ __forceinline__ GroupRead(const ForceBox &B, uint32_t g)
+    {
+        const GroupArrays &gr = B.gr;
+        lo[0] = gr.lox[g]; lo[1] = gr.loy[g]; lo[2] = gr.loz[g];
+        hi[0] = gr.hix[g]; hi[1] = gr.hiy[g]; hi[2] = gr.hiz[g];
+        xg[0] = gr.xgx[g]; xg[1] = gr.xgy[g]; xg[2] = gr.xgz[g];
+        count = gr.count[g];
+        first = gr.first[g];
+        len = B.len[g];
+        off = B.off[g];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // Whether the bounding box, grown by r_cut (and clear of rounding), leaves [0, L) anywhere:
+    // otherwise a source within r_cut of the box is its own nearest image, and a source whose
+    // nearest image lies across the boundary is at least r_cut from the box without the wrap as
+    // with it, so no coordinate needs wrapping.
+    __device__ __forceinline__ bool wraps(const ForceParams &fp) const
+    {
+        const double rc = fp.rc * (1.0 + 0x1p-10);
+        return __ballot(!((lo[0] - rc >= 0.0) & (hi[0] + rc < fp.L) & (lo[1] - rc >= 0.0) &
+                          (hi[1] + rc < fp.L) & (lo[2] - rc >= 0.0) & (hi[2] + rc < fp.L))) != 0;
+    }
+};
+
+// The group once its frame is known: by one wave, or, split, by the workgroup.
+template <class P>
+__device__ __forceinline__ void finish_group(char *tiles, int wave, bool split, const ForceBox &B,
+                                             uint32_t g, const GroupRead &R,
+                                             const typename P::Frame &F)
+{
+    const uint32_t Lg = uni(R.len);
+    uint32_t j0 = 0, j1 = Lg;
+    if (split) { // whole rounds of 64 entries per wave
+        const uint32_t per = ((Lg + 64 * P::kWaves - 1) / (64 * P::kWaves)) * 64;
+        j0 = per * (uint32_t)wave < Lg ? per * (uint32_t)wave : Lg;
+        j1 = j0 + per < Lg ? j0 + per : Lg;
+    }
+    const uint32_t *list =
+        B.entries + (((uint64_t)uni((uint32_t)(R.off >> 32)) << 32) | uni((uint32_t)R.off));
+    const uint64_t pairs =
+        run_group<P>(tiles, wave, split, B, uni(R.count), uni(R.first), list, j0, j1, F);
+    if (__lane_id() == 0) {
+        if (split)
+            atomicAdd(&B.fp.pairs[g], (unsigned long long)pairs); // zeroed by the prep launch
+        else
+            B.fp.pairs[g] = pairs;
+    }
+}
+
+// The first part at or after `from` (cyclically) whose counter has not reached its size, or
+// kXcds.  Lane p < kXcds holds part p's size.  One read of all counters, so a wave that finds
+// everything taken leaves after one memory latency, and no atomic is spent on empty queues.
+__device__ __forceinline__ uint32_t next_part(uint32_t *ctr, uint32_t size, uint32_t from)
+{
+    const uint32_t lane = __lane_id();
+    uint32_t v = 0;
+    if (lane < kXcds)
+        v = __hip_atomic_load(&ctr[lane * kQueueStride], __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t m = (uint32_t)__ballot(lane < kXcds && v < size);
+    if (!m) return kXcds;
+    const uint32_t rot = ((m >> from) | (m << (kXcds - from))) & ((1u << kXcds) - 1u);
+    return (from + (uint32_t)__builtin_ctz(rot)) % kXcds;
+}
+
+// Item q of part `part` over the boxes (their runs laid end to end): lane b < nb holds box b's
+// run end in `ends` (inclusive prefix).
+struct Item {
+    uint32_t box, k;
+};
+__device__ __forceinline__ Item find_item(uint32_t ends, int nb, uint32_t q)
+{
+    const uint32_t lane = __lane_id();
+    const uint32_t b = (uint32_t)__popcll(__ballot((int)lane < nb && ends <= q));
+    const uint32_t before = b ? (uint32_t)__builtin_amdgcn_readlane((int)ends, (int)b - 1) : 0u;
+    return {b, q - before};
+}
+
+// Box b's run of part p in the queue of split (heavy = 1) or single-wave groups.
+__device__ __forceinline__ uint32_t run_start(const uint32_t *cls, uint32_t p, int heavy)
+{
+    return cls[heavy ? kClsStarts + p : kClsHeavyEnd + p];
+}
+__device__ __forceinline__ uint32_t run_size(const uint32_t *cls, uint32_t p, int heavy)
+{
+    return cls[heavy ? kClsHeavyEnd + p : kClsStarts + p + 1] - run_start(cls, p, heavy);
+}
+
+// Per lane p < kXcds the total size of part p over the boxes.
+__device__ __forceinline__ uint32_t part_sizes(const ForceBox *bx, int nb, int heavy)
+{
+    const uint32_t lane = __lane_id();
+    uint32_t n = 0;
+    if (lane < kXcds)
+        for (int b = 0; b < nb; ++b) n += run_size(bx[b].cls, lane, heavy);
+    return n;
+}
+// Per lane the inclusive prefix over the boxes of their runs of `part`.
+__device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_t part, int heavy)
+{
+    const int lane = __lane_id();
+    uint32_t v = lane < nb ? run_size(bx[lane].cls, part, heavy) : 0u;
+#pragma unroll
+    for (int d = 1; d < kMaxBatch; d <<= 1) {
+        const uint32_t u = __shfl_up(v, d, 64);
+        if (lane >= d) v += u;
+    }
+    return v;
+}
+
+// Persistent: each workgroup copies the table into LDS once, takes split groups as a whole
+// until none are left, and then its waves take single groups, each from the queues of
+// kXcds contiguous key ranges (its own XCD's first: neighbouring groups share sources through
+// one L2; then what is left of the others).  Every box of a launch has the same table.
+//
+// A group with at least 2^t pairs is split over the workgroup's waves, 2^t being about a
+// 16384th of the box's pairs (at least 2^12): one wave alone would hold up the end of the
+// launch.  On the 700,001-particle clustered box the longest single-wave group took 1.3 ms of
+// a 1.5 ms force call whose work fills the device for 0.6 ms.
+template <class P, bool MULTI>
+__device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
+{
+    extern __shared__ float4 smem[];
+    const int nb = MULTI ? n_boxes : 1;
+    char *const lds = reinterpret_cast<char *>(smem);
+    P::load_table(lds, bx[0]);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // known to be uniform
+    const uint32_t lane = __lane_id();
+    const uint32_t xcd = blockIdx.x % kXcds;
+    uint32_t *const hq = bx[0].cls + kClsQueue, *const lq = hq + kXcds * kQueueStride;
+    __syncthreads();
+    char *const tiles = lds + P::kTilesAt;
+    uint32_t *const word = reinterpret_cast<uint32_t *>(tiles); // free between groups
+    uint32_t size = part_sizes(bx, nb, 1), part = xcd, ends = 0, have = kXcds, next = 0;
+    bool split = __ballot(size != 0) != 0;
+    if (!split) size = part_sizes(bx, nb, 0);
+    for (;;) {
+        uint32_t *const ctr = split ? hq : lq;
+        uint32_t q = next;
+        if (!split || wave == 0)
+            for (;;) {
+                // a single wave asked for its next item before it began the last one
+                if (split || part != have) {
+                    part = uni(next_part(ctr, size, part));
+                    if (part == kXcds) break;
+                    if (lane == 0) q = atomicAdd(&ctr[part * kQueueStride], 1u);
+                }
+                q = uni(q);
+                if (q < (uint32_t)__builtin_amdgcn_readlane((int)size, (int)part)) break;
+                have = kXcds; // found empty: on to the next part that is not
+            }
+        if (split) {
+            if (threadIdx.x == 0) {
+                word[0] = part;
+                word[1] = q;
+            }
+            __syncthreads();
+            part = word[0];
+            q = word[1];
+            __syncthreads();
+        }
+        part = uni(part);
+        q = uni(q);
+        if (part == kXcds) {
+            if (!split) break;
+            split = false; // on to the single-wave groups
+            size = part_sizes(bx, nb, 0);
+            part = xcd;
+            have = kXcds;
+            continue;
+        }
+        if (MULTI && part != have) ends = run_ends(bx, nb, part, split);
+        have = part;
+        if (!split && lane == 0) next = atomicAdd(&ctr[part * kQueueStride], 1u);
+        Item it{0, q};
+        if (MULTI) it = find_item(ends, nb, q);
+        const ForceBox &B = MULTI ? bx[uni(it.box)] : bx[0];
+        P::group(tiles, wave, split, B, uni(B.cls[run_start(B.cls, part, split) + it.k]));
+    }
+}
+
+} // namespace
+} // namespace tpm

@@ -17,15 +17,9 @@
 // queues, the heaviest groups first.  Each particle's result
 // leaves the kernels as one record in the caller's order, which a last pass splits into the
 // output arrays or applies as a kick.
-//
-// FP64 path: the same relative coordinates in FP64 (nearest image once per entry, or per pair
-// when the group's cube plus r_cut reaches half the box), (r^2 + eps^2)^(-1/2) and r^(-1)
-// from the hardware estimate refined by two Newton steps, and eq. (2) evaluated directly in a
-// form with no cancellation: for R < 1,
-//   g = 1 + R^3 (-8/5 + R^2 (8/5 + R (-1/2 + R (-12/35 + 3R/20)))),
-// and for R >= 1, g = max(2 - R, 0)^5 (7R^3 + 22R^2 + 10R + 4) / 140 (zero from R = 2 on).
-// Both are eq. (2) rearranged.
-#include "common.hpp"
+// The FP64 kernel is in k_force64.hip; the queues and the reduction, which they share, in
+// force_common.hpp.
+#include "force_common.hpp"
 
 #include <cmath>
 #include <utility>
@@ -34,63 +28,6 @@
 namespace tpm {
 namespace {
 
-
-// First branch of eq. (2) alone, for separations known to be below eta (R < 1).
-__device__ __forceinline__ double g_in_f64(double R)
-{
-    double R2 = R * R;
-    double p = fma(0.15, R, -12.0 / 35.0);
-    p = fma(p, R, -0.5);
-    p = fma(p, R, 1.6);
-    p = fma(p, R2, -1.6);
-    return fma(p, R2 * R, 1.0);
-}
-
-__device__ __forceinline__ double g_p3m_f64(double R)
-{
-    double g1 = g_in_f64(R);
-    double u = fmax(2.0 - R, 0.0);
-    double u2 = u * u;
-    double u5 = u2 * u2 * u;
-    double c = fma(fma(fma(0.05, R, 22.0 / 140.0), R, 10.0 / 140.0), R, 4.0 / 140.0);
-    return R < 1.0 ? g1 : u5 * c;
-}
-
-// Second branch of eq. (2) alone, for separations known to be at least eta (R >= 1).
-__device__ __forceinline__ double g_far_f64(double R)
-{
-    double u = fmax(2.0 - R, 0.0);
-    double u2 = u * u;
-    double u5 = u2 * u2 * u;
-    double c = fma(fma(fma(0.05, R, 22.0 / 140.0), R, 10.0 / 140.0), R, 4.0 / 140.0);
-    return u5 * c;
-}
-
-__device__ __forceinline__ double wrapd(double v, double L)
-{
-    double h = 0.5 * L;
-    if (v >= h) return v - L;
-    if (v < -h) return v + L;
-    return v;
-}
-
-// The force kernels leave one record per particle, in the caller's order: float4 (ax, ay, az,
-// 0) for float results, double4 for double results and for the kick.  The caller's order is
-// arbitrary, so each store lands in its own 32-byte HBM sector: one 16- or 32-byte record costs
-// one sector where three 4- or 8-byte component stores cost three.  k_force_out then walks the
-// records in order and splits them into the caller's three arrays (kOutF32, kOutF64) or adds dt
-// times them to double velocities (kOutKick: the kick of Section 2.2 step 5 taken with the
-// short-range force as soon as it is known), each product and sum rounded on its own.
-enum { kOutF32 = 0, kOutF64 = 1, kOutKick = 2 };
-
-template <int REC64>
-__device__ __forceinline__ void store_rec(void *rec, uint32_t i, double vx, double vy, double vz)
-{
-    if (REC64)
-        ((double4 *)rec)[i] = make_double4(vx, vy, vz, 0.0);
-    else
-        ((float4 *)rec)[i] = make_float4((float)vx, (float)vy, (float)vz, 0.0f);
-}
 
 // FP32 path.  Lengths are in units of r_cut / lam, lam = sqrt(1 - c), and the pair law is
 //   a_i = 1/(r_cut^2 lam) sum_j m_j d'_ij G(s),  G(s) = g(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2),
@@ -136,62 +73,16 @@ static_assert(kTabPlane >= (uint32_t)(-kTabMinExp) * 256u + 4u && kTabPlane % 25
               "planes do not overlap");
 
 // What a wave needs of its group.  Coordinates are x' = x inv - xg', one fused operation.
-struct GroupFrame {
+struct FrameF32 {
     bool wrap;            // coordinates need the nearest image
     double xg0, xg1, xg2; // wrap: x_g; else x_g inv
     double L, inv_L, inv; // inv = lam / r_cut
+    double scale;
+    float c;
 };
 
-// The bounding box of a chunk of the group's particles in x' units, for the cull.
-struct ChunkBox {
-    float c0, c1, c2; // centre
-    float h0, h1, h2; // minus half the half size
-    float thr;        // a quarter of the squared cull distance, with margin
-};
-
-// The LDS writes of this wave are complete before any of its lanes reads LDS again (the
-// waves of a workgroup work on different lists, so a workgroup barrier is not wanted).
-__device__ __forceinline__ void wave_lds_sync()
-{
-    __builtin_amdgcn_s_waitcnt(0xc07f); // lgkmcnt(0); vector memory counters untouched
-    __builtin_amdgcn_wave_barrier();
-}
-
-// Wave-uniform values that the compiler cannot know to be uniform, into scalar registers.
-__device__ __forceinline__ uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ double uni(double v)
-{
-    return __hiloint2double((int)uni((uint32_t)__double2hiint(v)),
-                            (int)uni((uint32_t)__double2loint(v)));
-}
-__device__ __forceinline__ float uni(float v) { return __uint_as_float(uni(__float_as_uint(v))); }
-
-// Keeps a wave-uniform value in a vector register.
-__device__ __forceinline__ float in_vgpr(float v)
-{
-    asm("" : "+v"(v));
-    return v;
-}
-
-// The list entries of the tile starting at jb (jb < je), one per lane and round.  Slots past
-// the range's end read its last entry and are dropped by load_tile_f32.  The caller issues
-// these reads one tile ahead, so they are in flight while the previous tile is evaluated.
-__device__ __forceinline__ void fetch_entries(const uint32_t *__restrict__ list, uint32_t jb,
-                                              uint32_t je, uint32_t *ent)
-{
-    const uint32_t lane = __lane_id();
-#pragma unroll
-    for (int r = 0; r < kTileRounds; ++r) {
-        const uint32_t j = jb + (uint32_t)(r * 64) + lane;
-        ent[r] = list[j < je ? j : je - 1];
-    }
-}
-
-// A position relative to x_g in x' units.  wrap = false for a group whose bounding box, grown
-// by r_cut, lies inside [0, L) on every axis: then a source within r_cut of the box is its own
-// nearest image, and a source whose nearest image lies across the boundary is at least r_cut
-// from the box without the wrap as with it, so no coordinate needs wrapping.
-__device__ __forceinline__ float4 rel_f32(const double4 r, const GroupFrame &F)
+// A position relative to x_g in x' units (wrap: see GroupRead::wraps).
+__device__ __forceinline__ float4 rel_f32(const double4 r, const FrameF32 &F)
 {
     if (F.wrap) {
         double dx = r.x - F.xg0, dy = r.y - F.xg1, dz = r.z - F.xg2;
@@ -208,7 +99,7 @@ __device__ __forceinline__ float4 rel_f32(const double4 r, const GroupFrame &F)
 // Culls and packs one tile; returns the number of survivors (the same on every lane).
 __device__ __forceinline__ int load_tile_f32(float4 *tile, const uint32_t *ent, uint32_t jb,
                                              uint32_t je, int J, NodeArrays nd,
-                                             const GroupFrame &F, const ChunkBox &C)
+                                             const FrameF32 &F, const ChunkBox &C)
 {
     constexpr int kR = kTileRounds;
     const int lane = __lane_id();
@@ -325,46 +216,18 @@ __device__ __forceinline__ void tile_pass(const float4 *ts, int steps, int J, co
 static_assert((kForceWaves * kTileF32 + 64) * 16 <= ((127 + kTabMinExp) << 8),
               "a read ahead of the last tile's last row stays below the table");
 
-// The group's particles run in chunks of S lanes x K particles per lane, the wave's 64 / S
-// streams taking every J-th source.  A chunk is the largest of 128, 64, 32 and 16 (K = 4) that
-// wastes at most a sixth of its slots; up to 8 particles run as S = 4, K = 2.  Loading a tile
-// costs as much as two or three particles' pairs with it, so two chunks with few idle slots
-// beat one with many, and one kernel within 128 VGPRs (four waves per SIMD) serves every group
-// size.  Force call of the 256^3 clustered box with chunks of up to 32, 64, 128 and 256: 11.1,
-// 10.5, 10.4 and 10.6 ms; with five and six waves per SIMD (and the spills that takes) 12.8
-// and 12.4 ms.
-__host__ __device__ __forceinline__ void chunk_layout(uint32_t r, int &S, int &K)
-{
-    K = 4;
-    S = r >= 107 ? 32 : r >= 54 ? 16 : r >= 27 ? 8 : 4;
-    if (r <= 8) K = 2;
-}
-
-// The least (or, on negated values, the greatest) of v over each run of S lanes.
-__device__ __forceinline__ float run_min(float v, int S)
-{
-#define TPM_MIN_DPP(ctrl)                                                                      \
-    v = fminf(v, __uint_as_float(__builtin_amdgcn_update_dpp(                                  \
-                     0, __float_as_uint(v), ctrl, 0xf, 0xf, false)))
-    TPM_MIN_DPP(0xb1);               // quad_perm 1, 0, 3, 2
-    TPM_MIN_DPP(0x4e);               // quad_perm 2, 3, 0, 1
-    if (S >= 8) TPM_MIN_DPP(0x141);  // row_half_mirror: the other four of eight
-    if (S >= 16) TPM_MIN_DPP(0x140); // row_mirror: the other eight of sixteen
-#undef TPM_MIN_DPP
-    if (S >= 32) v = fminf(v, __shfl_xor(v, 16, 64));
-    if (S >= 64) v = fminf(v, __shfl_xor(v, 32, 64));
-    return v;
-}
-
-// The force of the list range [j0, j1) on the chunk's particles f + ib ..: per lane K sums
-// over its stream's sources, the per-tile FP32 sums added up in FP64.
+// The force of the list range [j0, j1) on the chunk's particles f ..: per lane K sums over its
+// stream's sources, the per-tile FP32 sums added up in FP64.
 template <int K>
-__device__ __forceinline__ void chunk_sums(float4 *tile, float c, const NodeArrays &nd, int S,
-                                           uint32_t n_i, uint32_t f, const uint32_t *list,
-                                           uint32_t j0, uint32_t j1,
-                                           const double4 *__restrict__ ps, const GroupFrame &F,
-                                           double *ax, double *ay, double *az, uint32_t &kept)
+__device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t n_i, uint32_t f,
+                                                   const uint32_t *list, uint32_t j0, uint32_t j1,
+                                                   const ForceBox &B, const FrameF32 &F,
+                                                   double *ax, double *ay, double *az)
 {
+    const NodeArrays &nd = B.nd;
+    const double4 *__restrict__ const ps = B.ps;
+    const float c = in_vgpr(F.c);
+    uint32_t kept = 0;
     const int lane = __lane_id();
     const int J = 64 / S, lgJ = 31 - __builtin_clz(J);
     const int slot = lane & (S - 1), stream = lane / S;
@@ -378,42 +241,14 @@ __device__ __forceinline__ void chunk_sums(float4 *tile, float c, const NodeArra
         zi[k] = v.z;
         ax[k] = ay[k] = az[k] = 0.0;
     }
-    ChunkBox C;
-    {
-        float lo[3] = {xi[0], yi[0], zi[0]}, hi[3] = {-xi[0], -yi[0], -zi[0]};
-#pragma unroll
-        for (int k = 1; k < K; ++k) {
-            lo[0] = fminf(lo[0], xi[k]);
-            lo[1] = fminf(lo[1], yi[k]);
-            lo[2] = fminf(lo[2], zi[k]);
-            hi[0] = fminf(hi[0], -xi[k]);
-            hi[1] = fminf(hi[1], -yi[k]);
-            hi[2] = fminf(hi[2], -zi[k]);
-        }
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            lo[a] = uni(run_min(lo[a], S));
-            hi[a] = -uni(run_min(hi[a], S));
-        }
-        C.c0 = 0.5f * (lo[0] + hi[0]);
-        C.c1 = 0.5f * (lo[1] + hi[1]);
-        C.c2 = 0.5f * (lo[2] + hi[2]);
-        C.h0 = -0.25f * (hi[0] - lo[0]);
-        C.h1 = -0.25f * (hi[1] - lo[1]);
-        C.h2 = -0.25f * (hi[2] - lo[2]);
-        // The coordinates near the threshold are at most 1 + 2 max(h) + |c| in size, each
-        // rounded a few times to 2^-24 of that; the cull distance is lam <= 1.
-        const float big = 1.0f + 4.0f * fmaxf(fmaxf(-C.h0, -C.h1), -C.h2) +
-                          fmaxf(fmaxf(fabsf(C.c0), fabsf(C.c1)), fabsf(C.c2));
-        C.thr = uni(0.25f * (1.0f + 0x1p-12f + 0x1p-20f * big));
-    }
+    const ChunkBox C = chunk_box<K>(xi, yi, zi, S);
     uint32_t ent[kTileRounds];
-    if (j0 < j1) fetch_entries(list, j0, j1, ent);
+    if (j0 < j1) fetch_entries<kTileRounds>(list, j0, j1, ent);
     for (uint32_t jb = j0; jb < j1; jb += kTileF32) {
         const int nt = load_tile_f32(tile, ent, jb, j1, J, nd, F, C);
         kept += (uint32_t)nt;
         wave_lds_sync();
-        if (jb + kTileF32 < j1) fetch_entries(list, jb + kTileF32, j1, ent);
+        if (jb + kTileF32 < j1) fetch_entries<kTileRounds>(list, jb + kTileF32, j1, ent);
         const int steps = (nt + J - 1) >> lgJ; // the same on every lane
         float tx[K], ty[K], tz[K];
 #pragma unroll
@@ -427,302 +262,70 @@ __device__ __forceinline__ void chunk_sums(float4 *tile, float c, const NodeArra
             az[k] += (double)tz[k];
         }
     }
-    // the J streams' sums, in a fixed tree
-    for (int d = S; d < 64; d <<= 1) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            ax[k] += __shfl_xor(ax[k], d, 64);
-            ay[k] += __shfl_xor(ay[k], d, 64);
-            az[k] += __shfl_xor(az[k], d, 64);
-        }
-    }
+    add_streams<K>(ax, ay, az, S);
+    return kept;
 }
 
-// One chunk by one wave (whole list), or by the workgroup's kForceWaves waves, each on its own
-// part [j0, j1) of the list: then the waves' sums meet in LDS (the tiles, two k at a time: 128
-// particles x 3 doubles fill one tile) and are added in wave order.
-template <int K>
-__device__ __forceinline__ void run_chunk(float4 *tiles, int wave, bool split, float c,
-                                          const NodeArrays &nd, int S, uint32_t n_i, uint32_t f,
-                                          const uint32_t *list, uint32_t j0, uint32_t j1,
-                                          const double4 *__restrict__ ps,
-                                          const uint32_t *__restrict__ pidx, const GroupFrame &F,
-                                          double scale, void *rec, int rec64, uint32_t &kept)
-{
-    double ax[K], ay[K], az[K];
-    chunk_sums<K>(tiles + wave * kTileF32, c, nd, S, n_i, f, list, j0, j1, ps, F, ax, ay,
-                        az, kept);
-    const int lane = __lane_id();
-    if (!split) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const uint32_t i = (uint32_t)(lane + S * k);
-            if (lane < S && i < n_i) {
-                if (rec64)
-                    store_rec<1>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
-                else
-                    store_rec<0>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
-            }
-        }
-        return;
-    }
-    double *const red = reinterpret_cast<double *>(tiles);
-    constexpr int kWaveWords = kTileF32 * 2; // doubles per wave's tile
-#pragma unroll
-    for (int kb = 0; kb < K; kb += 2) {
-#pragma unroll
-        for (int k = kb; k < kb + 2 && k < K; ++k)
-            if (lane < S) {
-                double *const d = red + wave * kWaveWords + ((k - kb) * 64 + lane) * 3;
-                d[0] = ax[k];
-                d[1] = ay[k];
-                d[2] = az[k];
-            }
-        __syncthreads();
-        const int t = threadIdx.x;
-        const int k = kb + (t >> 6);
-        const uint32_t i = (uint32_t)(lane + S * k);
-        if (t < 128 && k < K && lane < S && i < n_i) {
-            double vx = 0.0, vy = 0.0, vz = 0.0;
-            for (int w = 0; w < kForceWaves; ++w) {
-                const double *d = red + w * kWaveWords + t * 3;
-                vx += d[0];
-                vy += d[1];
-                vz += d[2];
-            }
-            if (rec64)
-                store_rec<1>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
-            else
-                store_rec<0>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
-        }
-        __syncthreads();
-    }
-}
-static_assert(128 * 24 <= kTileF32 * 16, "128 particles' sums fit a tile");
-
-__device__ __forceinline__ uint64_t run_group(float4 *tiles, int wave, bool split, float c,
-                                              const ForceBox &B, uint32_t n_g, uint32_t f,
-                                              const uint32_t *list, uint32_t j0, uint32_t j1,
-                                              const GroupFrame &F, double scale)
-{
-    uint64_t pairs = 0;
-    for (uint32_t ib = 0; ib < n_g;) {
-        int S, K;
-        chunk_layout(n_g - ib, S, K);
-        const uint32_t n_i = n_g - ib < (uint32_t)(S * K) ? n_g - ib : (uint32_t)(S * K);
-        uint32_t kept = 0;
-#define TPM_CHUNK(KK)                                                                          \
-    run_chunk<KK>(tiles, wave, split, c, B.nd, S, n_i, f + ib, list, j0, j1, B.ps,       \
-                        B.pidx, F, scale, B.rec, B.rec64, kept)
-        if (K == 4)
-            TPM_CHUNK(4);
-        else
-            TPM_CHUNK(2);
-#undef TPM_CHUNK
-        ib += n_i;
-        pairs += (uint64_t)kept * n_i;
-    }
-    return pairs; // pairs with the entries of [j0, j1) that survived the cull
-}
-
-// Group g of box B by one wave, or, split, by the workgroup.
-__device__ __forceinline__ void force_group_f32(float4 *tiles, int wave, bool split,
-                                                const ForceBox &B, uint32_t g)
-{
-    const GroupArrays &gr = B.gr;
-    const ForceParams &fp = B.fp;
-    // everything about the group is read before any of it is used: one memory latency
-    const double lo0 = gr.lox[g], lo1 = gr.loy[g], lo2 = gr.loz[g];
-    const double hi0 = gr.hix[g], hi1 = gr.hiy[g], hi2 = gr.hiz[g];
-    const double x0 = gr.xgx[g], x1 = gr.xgy[g], x2 = gr.xgz[g];
-    const uint32_t count = gr.count[g], first = gr.first[g], len = B.len[g];
-    const uint64_t off = B.off[g];
-    __builtin_amdgcn_sched_barrier(0);
-    const double lam = sqrt(1.0 - (double)B.ft.c);
-    const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
-    const double scale = uni(inv_len * inv_len / lam);
-    const double rc = fp.rc * (1.0 + 0x1p-10); // clear of rounding at the boundary
-    GroupFrame F;
-    F.wrap = __ballot(!((lo0 - rc >= 0.0) & (hi0 + rc < fp.L) & (lo1 - rc >= 0.0) &
-                        (hi1 + rc < fp.L) & (lo2 - rc >= 0.0) & (hi2 + rc < fp.L))) != 0;
-    F.L = fp.L;
-    F.inv_L = uni(1.0 / fp.L);
-    F.inv = uni(inv_len * lam);
-    F.xg0 = uni(F.wrap ? x0 : x0 * F.inv);
-    F.xg1 = uni(F.wrap ? x1 : x1 * F.inv);
-    F.xg2 = uni(F.wrap ? x2 : x2 * F.inv);
-    const float c = in_vgpr(B.ft.c);
-    const uint32_t Lg = uni(len);
-    uint32_t j0 = 0, j1 = Lg;
-    if (split) { // whole rounds of 64 entries per wave
-        const uint32_t per = ((Lg + 64 * kForceWaves - 1) / (64 * kForceWaves)) * 64;
-        j0 = per * (uint32_t)wave < Lg ? per * (uint32_t)wave : Lg;
-        j1 = j0 + per < Lg ? j0 + per : Lg;
-    }
-    const uint32_t *list =
-        B.entries + (((uint64_t)uni((uint32_t)(off >> 32)) << 32) | uni((uint32_t)off));
-    const uint64_t pairs =
-        run_group(tiles, wave, split, c, B, uni(count), uni(first), list, j0, j1, F, scale);
-    if (__lane_id() == 0) {
-        if (split)
-            atomicAdd(&fp.pairs[g], (unsigned long long)pairs); // zeroed by the prep launch
-        else
-            fp.pairs[g] = pairs;
-    }
-}
-
-// The first part at or after `from` (cyclically) whose counter has not reached its size, or
-// kXcds.  Lane p < kXcds holds part p's size.  One read of all counters, so a wave that finds
-// everything taken leaves after one memory latency, and no atomic is spent on empty queues.
-__device__ __forceinline__ uint32_t next_part(uint32_t *ctr, uint32_t size, uint32_t from)
-{
-    const uint32_t lane = __lane_id();
-    uint32_t v = 0;
-    if (lane < kXcds)
-        v = __hip_atomic_load(&ctr[lane * kQueueStride], __ATOMIC_RELAXED,
-                              __HIP_MEMORY_SCOPE_AGENT);
-    const uint32_t m = (uint32_t)__ballot(lane < kXcds && v < size);
-    if (!m) return kXcds;
-    const uint32_t rot = ((m >> from) | (m << (kXcds - from))) & ((1u << kXcds) - 1u);
-    return (from + (uint32_t)__builtin_ctz(rot)) % kXcds;
-}
-
-// Item q of part `part` over the boxes (their runs laid end to end): lane b < nb holds box b's
-// run end in `ends` (inclusive prefix).
-struct Item {
-    uint32_t box, k;
-};
-__device__ __forceinline__ Item find_item(uint32_t ends, int nb, uint32_t q)
-{
-    const uint32_t lane = __lane_id();
-    const uint32_t b = (uint32_t)__popcll(__ballot((int)lane < nb && ends <= q));
-    const uint32_t before = b ? (uint32_t)__builtin_amdgcn_readlane((int)ends, (int)b - 1) : 0u;
-    return {b, q - before};
-}
-
-// Box b's run of part p in the queue of split (heavy = 1) or single-wave groups.
-__device__ __forceinline__ uint32_t run_start(const uint32_t *cls, uint32_t p, int heavy)
-{
-    return cls[heavy ? kClsStarts + p : kClsHeavyEnd + p];
-}
-__device__ __forceinline__ uint32_t run_size(const uint32_t *cls, uint32_t p, int heavy)
-{
-    return cls[heavy ? kClsHeavyEnd + p : kClsStarts + p + 1] - run_start(cls, p, heavy);
-}
-
-// Per lane p < kXcds the total size of part p over the boxes.
-__device__ __forceinline__ uint32_t part_sizes(const ForceBox *bx, int nb, int heavy)
-{
-    const uint32_t lane = __lane_id();
-    uint32_t n = 0;
-    if (lane < kXcds)
-        for (int b = 0; b < nb; ++b) n += run_size(bx[b].cls, lane, heavy);
-    return n;
-}
-// Per lane the inclusive prefix over the boxes of their runs of `part`.
-__device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_t part, int heavy)
-{
-    const int lane = __lane_id();
-    uint32_t v = lane < nb ? run_size(bx[lane].cls, part, heavy) : 0u;
-#pragma unroll
-    for (int d = 1; d < kMaxBatch; d <<= 1) {
-        const uint32_t u = __shfl_up(v, d, 64);
-        if (lane >= d) v += u;
-    }
-    return v;
-}
-
-// Persistent: each workgroup copies the table into LDS once, takes split groups as a whole
-// until none are left, and then its waves take single groups, each from the queues of
-// kXcds contiguous key ranges (its own XCD's first: neighbouring groups share sources through
-// one L2; then what is left of the others).  Every box of a launch has the same table.
-//
-// A group with at least 2^t pairs is split over the workgroup's waves, 2^t being about a
-// 16384th of the box's pairs (at least 2^12): one wave alone would hold up the end of the
-// launch.  On the 700,001-particle clustered box the longest single-wave group took 1.3 ms of
-// a 1.5 ms force call whose work fills the device for 0.6 ms.
-//
 // What bounds it (256^3 clustered box, n_crit 256): the LDS pipe is busy 93 % of the time and
 // the vector units 80 %; without the table reads the call takes 8.7 ms, with conflict-free ones
 // 10.2, as it is 10.4 (12.4 with a kernel per blocking factor, a table of 16-byte entries and
 // queue counters side by side: 311,000 groups taken through counters in one cache line alone
 // cost about 12 ms, at 40 ns each).  700,001 particles: the whole step 3.41 -> 1.53 ms.
-template <bool MULTI>
-__device__ __forceinline__ void force_f32_body(const ForceBox *bx, int n_boxes)
-{
-    extern __shared__ float4 smem[];
-    const int nb = MULTI ? n_boxes : 1;
+struct PolicyF32 {
+    static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
+    using Frame = FrameF32;
+
+    static __device__ __forceinline__ void load_table(char *lds, const ForceBox &B)
     {
-        const ForceTable ft = bx[0].ft;
-        float *const lds = reinterpret_cast<float *>(smem);
+        const ForceTable ft = B.ft;
+        float *const t = reinterpret_cast<float *>(lds);
         for (uint32_t i = threadIdx.x; i < ft.entries; i += blockDim.x)
 #pragma unroll
             for (uint32_t q = 0; q < 3; ++q)
-                lds[(ft.base + q * kTabPlane) / 4 + i] = ft.coef[q * ft.entries + i];
+                t[(ft.base + q * kTabPlane) / 4 + i] = ft.coef[q * ft.entries + i];
     }
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // known to be uniform
-    const uint32_t lane = __lane_id();
-    const uint32_t xcd = blockIdx.x % kXcds;
-    uint32_t *const hq = bx[0].cls + kClsQueue, *const lq = hq + kXcds * kQueueStride;
-    __syncthreads();
-    uint32_t *const word = reinterpret_cast<uint32_t *>(smem); // a tile is free between groups
-    uint32_t size = part_sizes(bx, nb, 1), part = xcd, ends = 0, have = kXcds, next = 0;
-    bool split = __ballot(size != 0) != 0;
-    if (!split) size = part_sizes(bx, nb, 0);
-    for (;;) {
-        uint32_t *const ctr = split ? hq : lq;
-        uint32_t q = next;
-        if (!split || wave == 0)
-            for (;;) {
-                // a single wave asked for its next item before it began the last one
-                if (split || part != have) {
-                    part = uni(next_part(ctr, size, part));
-                    if (part == kXcds) break;
-                    if (lane == 0) q = atomicAdd(&ctr[part * kQueueStride], 1u);
-                }
-                q = uni(q);
-                if (q < (uint32_t)__builtin_amdgcn_readlane((int)size, (int)part)) break;
-                have = kXcds; // found empty: on to the next part that is not
-            }
-        if (split) {
-            if (threadIdx.x == 0) {
-                word[0] = part;
-                word[1] = q;
-            }
-            __syncthreads();
-            part = word[0];
-            q = word[1];
-            __syncthreads();
-        }
-        part = uni(part);
-        q = uni(q);
-        if (part == kXcds) {
-            if (!split) break;
-            split = false; // on to the single-wave groups
-            size = part_sizes(bx, nb, 0);
-            part = xcd;
-            have = kXcds;
-            continue;
-        }
-        if (MULTI && part != have) ends = run_ends(bx, nb, part, split);
-        have = part;
-        if (!split && lane == 0) next = atomicAdd(&ctr[part * kQueueStride], 1u);
-        Item it{0, q};
-        if (MULTI) it = find_item(ends, nb, q);
-        const ForceBox &B = MULTI ? bx[uni(it.box)] : bx[0];
-        force_group_f32(smem, wave, split, B, uni(B.cls[run_start(B.cls, part, split) + it.k]));
+
+    template <int K>
+    static __device__ __forceinline__ uint32_t chunk_sums(char *tile, int S, uint32_t n_i,
+                                                          uint32_t f, const uint32_t *list,
+                                                          uint32_t j0, uint32_t j1,
+                                                          const ForceBox &B, const Frame &F,
+                                                          double *ax, double *ay, double *az)
+    {
+        return chunk_sums_f32<K>(reinterpret_cast<float4 *>(tile), S, n_i, f, list, j0, j1, B, F,
+                                 ax, ay, az);
     }
-}
+
+    static __device__ __forceinline__ void group(char *tiles, int wave, bool split,
+                                                 const ForceBox &B, uint32_t g)
+    {
+        const GroupRead R(B, g);
+        const ForceParams &fp = B.fp;
+        const double lam = sqrt(1.0 - (double)B.ft.c);
+        const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
+        Frame F;
+        F.scale = uni(inv_len * inv_len / lam);
+        F.wrap = R.wraps(fp);
+        F.L = fp.L;
+        F.inv_L = uni(1.0 / fp.L);
+        F.inv = uni(inv_len * lam);
+        F.xg0 = uni(F.wrap ? R.xg[0] : R.xg[0] * F.inv);
+        F.xg1 = uni(F.wrap ? R.xg[1] : R.xg[1] * F.inv);
+        F.xg2 = uni(F.wrap ? R.xg[2] : R.xg[2] * F.inv);
+        F.c = B.ft.c;
+        finish_group<PolicyF32>(tiles, wave, split, B, g, R, F);
+    }
+};
 
 __global__ __launch_bounds__(64 * kForceWaves, 4) void k_force_f32(ForceBox box)
 {
-    force_f32_body<false>(&box, 1);
+    force_body<PolicyF32, false>(&box, 1);
 }
 
 __global__ __launch_bounds__(64 * kForceWaves, 4) void k_force_f32_multi(
     const ForceBox *__restrict__ bx, int nb)
 {
-    force_f32_body<true>(bx, nb);
+    force_body<PolicyF32, true>(bx, nb);
 }
 
 // Adds the groups' pairs into *sum: blocks b of nb.
@@ -775,7 +378,7 @@ __global__ __launch_bounds__(256) void k_pairwise_f32(int64_t n_i, const double 
 
 // Queues of the FP32 force.  Group g belongs to XCD part p = floor(8 g / G) (contiguous key
 // ranges) and to a cost bucket: the octave of its pairs n_g L_g if it has at least 2^kHeavyCost
-// of them or is split (at least 2^t, see k_force_f32), one bucket for all others.  The bins (p,
+// of them or is split (at least 2^t, see force_body), one bucket for all others.  The bins (p,
 // bucket) are laid out with the costliest first, so each part lists its split groups, its heavy
 // ones longest first and then the rest in about key order (consecutive groups share sources
 // through the XCD's L2).  Three passes: count the bins, scan them into cursors and part
@@ -883,140 +486,6 @@ __global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t 
 #pragma unroll
     for (int r = 0; r < kClassifyItems; ++r)
         if (bin[r] != ~0u) cls[s_cnt[bin[r]] + loc[r]] = base + (uint32_t)r * 256u + threadIdx.x;
-}
-
-// 1/sqrt(x) in FP64 for x > 0: the hardware estimate refined by two Newton steps
-// y <- y + y (1/2 - (x/2) y^2), each of which squares the relative error (to within rounding).
-__device__ __forceinline__ double rsqrt_f64(double x)
-{
-    double y = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    y = fma(y, fma(-h, y * y, 0.5), y);
-    y = fma(y, fma(-h, y * y, 0.5), y);
-    return y;
-}
-
-// FP64 path, one wave per group, 64 i-particles per pass.  Each tile of 64 list entries is
-// culled against the group's box as in the FP32 path (a source at least r_cut from the box
-// adds exactly zero) and the survivors are stored relative to x_g (nearest image, once per
-// entry) in three runs: "inner" sources, whose farthest point of the box is within eta (every
-// pair has R < 1: eq. (2)'s first branch only), from the front of the tile; "far" ones, at
-// least eta from the box (every pair has R >= 1: the second branch only), from the back; the
-// others ("near", both branches and a select) in between.  The FP64 pair evaluates both
-// branches of g for a near source, so the inner run saves the second branch and the select.
-// When the group's cube and cutoff fit in half the box (half side + r_cut < L/2) the
-// difference of two relative positions is the nearest-image separation and the pairs need no
-// wrap; otherwise the pair wraps it.  (r^2 + eps^2)^(-1/2) and r^(-1) come from
-// rsqrt_f64 (r = r^2 r^(-1)); a pair at zero separation adds nothing.
-constexpr int kTileF64 = 64;
-
-enum F64Kind { kF64Near = 0, kF64Far = 1, kF64Inner = 2 };
-
-template <int REC64>
-__global__ __launch_bounds__(64) void k_force_f64(
-    NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *__restrict__ off,
-    const uint32_t *__restrict__ len, const uint32_t *__restrict__ entries,
-    const double4 *__restrict__ ps, const uint32_t *__restrict__ pidx, ForceParams fp,
-    void *rec)
-{
-    __shared__ double4 tile[kTileF64];
-    const uint32_t g = xcd_block(blockIdx.x, gridDim.x);
-    const int lane = threadIdx.x;
-    if (g >= n_groups) return;
-    const uint32_t n_g = gr.count[g], f = gr.first[g];
-    const uint64_t b = off[g];
-    const uint64_t Lg = len[g];
-    const double L = fp.L, eps2 = fp.eps2, inv_eta = fp.inv_eta, eta2 = fp.eta * fp.eta;
-    const double xg0 = gr.xgx[g], xg1 = gr.xgy[g], xg2 = gr.xgz[g];
-    const double cg0 = gr.cgx[g], cg1 = gr.cgy[g], cg2 = gr.cgz[g];
-    const double hg0 = gr.hgx[g], hg1 = gr.hgy[g], hg2 = gr.hgz[g];
-    const double half_side = 0.5 * ldexp(L, -(int)nd.level[gr.node[g]]);
-    const bool pair_wrap = !(half_side + sqrt(fp.rc2) < 0.5 * L);
-    const uint64_t lt = lane ? (~0ull >> (64 - lane)) : 0ull;
-    uint32_t kept_total = 0;
-    for (uint32_t ib = 0; ib < n_g; ib += 64) {
-        const uint32_t i = ib + lane;
-        const bool act = i < n_g;
-        kept_total = 0;
-        double xi = 0.0, yi = 0.0, zi = 0.0;
-        if (act) {
-            const double4 r = ps[f + i];
-            xi = wrapd(r.x - xg0, L);
-            yi = wrapd(r.y - xg1, L);
-            zi = wrapd(r.z - xg2, L);
-        }
-        double ax_ = 0.0, ay_ = 0.0, az_ = 0.0;
-        for (uint64_t jb = 0; jb < Lg; jb += kTileF64) {
-            const uint64_t j = jb + lane;
-            bool keep = false, far = false, inner = false;
-            double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
-            if (j < Lg) {
-                const uint32_t e = entries[b + j];
-                const double4 r = (e & kCellTag) ? nd.nsrc[e & ~kCellTag] : nd.psrc[e];
-                const double a0 = fabs(wrapd(r.x - cg0, L));
-                const double a1 = fabs(wrapd(r.y - cg1, L));
-                const double a2 = fabs(wrapd(r.z - cg2, L));
-                double w0 = a0 - hg0, w1 = a1 - hg1, w2 = a2 - hg2;
-                w0 = w0 > 0.0 ? w0 : 0.0;
-                w1 = w1 > 0.0 ? w1 : 0.0;
-                w2 = w2 > 0.0 ? w2 : 0.0;
-                const double gap2 = w0 * w0 + w1 * w1 + w2 * w2;
-                const double e0 = a0 + hg0, e1 = a1 + hg1, e2 = a2 + hg2;
-                keep = gap2 < fp.rc2;
-                far = gap2 >= eta2;
-                inner = e0 * e0 + e1 * e1 + e2 * e2 < eta2;
-                v = make_double4(wrapd(r.x - xg0, L), wrapd(r.y - xg1, L), wrapd(r.z - xg2, L),
-                                 r.w);
-            }
-            const uint64_t mi = __ballot(keep && inner), mn = __ballot(keep && !far && !inner),
-                           mf = __ballot(keep && far);
-            const int ni = __popcll(mi), nn = __popcll(mn), nf = __popcll(mf);
-            kept_total += (uint32_t)(ni + nn + nf);
-            if (keep) {
-                if (far)
-                    tile[kTileF64 - 1 - __popcll(mf & lt)] = v;
-                else if (inner)
-                    tile[__popcll(mi & lt)] = v;
-                else
-                    tile[ni + __popcll(mn & lt)] = v;
-            }
-            __syncthreads();
-#define TPM_F64_PAIRS(KIND, WRAP, T0, T1)                                                       \
-    for (int t = (T0); t < (T1); ++t) {                                                        \
-        const double4 s = tile[t];                                                             \
-        double dx = s.x - xi, dy = s.y - yi, dz = s.z - zi;                                    \
-        if (WRAP) {                                                                            \
-            dx = wrapd(dx, L);                                                                 \
-            dy = wrapd(dy, L);                                                                 \
-            dz = wrapd(dz, L);                                                                 \
-        }                                                                                      \
-        const double r2 = dx * dx + dy * dy + dz * dz;                                         \
-        const double is = rsqrt_f64(r2 + eps2);                                                \
-        const double R = r2 * rsqrt_f64(r2) * inv_eta;                                         \
-        const double g = KIND == kF64Far     ? g_far_f64(R)                                   \
-                         : KIND == kF64Inner ? g_in_f64(R)                                    \
-                                             : g_p3m_f64(R);                                  \
-        double fm = s.w * g * (is * is * is);                                                  \
-        fm = r2 > 0.0 ? fm : 0.0;                                                              \
-        ax_ += fm * dx;                                                                        \
-        ay_ += fm * dy;                                                                        \
-        az_ += fm * dz;                                                                        \
-    }
-            if (pair_wrap) {
-                TPM_F64_PAIRS(kF64Inner, true, 0, ni)
-                TPM_F64_PAIRS(kF64Near, true, ni, ni + nn)
-                TPM_F64_PAIRS(kF64Far, true, kTileF64 - nf, kTileF64)
-            } else {
-                TPM_F64_PAIRS(kF64Inner, false, 0, ni)
-                TPM_F64_PAIRS(kF64Near, false, ni, ni + nn)
-                TPM_F64_PAIRS(kF64Far, false, kTileF64 - nf, kTileF64)
-            }
-#undef TPM_F64_PAIRS
-            __syncthreads();
-        }
-        if (act) store_rec<REC64>(rec, pidx[f + i], ax_, ay_, az_);
-    }
-    if (lane == 0) fp.pairs[g] = (unsigned long long)kept_total * n_g;
 }
 
 // The records in the caller's order, split into three arrays or applied as a kick (modes as
@@ -1216,19 +685,6 @@ void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const doubl
     k_pairwise_f32<<<(unsigned)(b < 65536 ? (b > 0 ? b : 1) : 65536), 256, 0, s>>>(
         n_i, xi, n_j, xj, mj, xg[0], xg[1], xg[2], inv_len * lam, ft, inv_len * inv_len / lam,
         out);
-}
-
-void launch_force_f64(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
-                      const uint32_t *len, const uint32_t *entries, const double4 *ps, const uint32_t *pidx,
-                      ForceParams fp, void *rec, int rec64, hipStream_t s)
-{
-    if (!n_groups) return;
-    if (rec64)
-        k_force_f64<1><<<n_groups, 64, 0, s>>>(nd, gr, n_groups, off, len, entries, ps, pidx,
-                                              fp, rec);
-    else
-        k_force_f64<0><<<n_groups, 64, 0, s>>>(nd, gr, n_groups, off, len, entries, ps, pidx,
-                                              fp, rec);
 }
 
 static uint32_t stat_blocks(uint32_t n_groups)

@@ -99,6 +99,11 @@ struct treepm_ctx {
     Buf tab;
     double tab_key = 0.0;
     ForceTable ftab{};
+    // FP64 pair-law table (doubles, then floats) and the eps / r_cut it was tried for (-1: none);
+    // tab64_ok: that ratio has one.
+    Buf tab64;
+    double tab64_key = -1.0;
+    bool tab64_ok = false;
     int n_cu = 256; // compute units of the device (persistent force grids)
     // particle mesh: fixed-point masses (later the potential), the complex work mesh, the
     // force mesh, the Green's table, twiddles, max mass
@@ -1060,7 +1065,7 @@ size_t treepm_internal_ctx_bytes(const treepm_ctx *c)
                         &c->g_hi[0], &c->g_hi[1], &c->g_hi[2], &c->g_misc, &c->off, &c->glen, &c->wctr, &c->scan64,
                         &c->entries, &c->wstats, &c->overflow, &c->gcells, &c->cls,
                         &c->kept, &c->kept_sum, &c->out[0], &c->out[1], &c->out[2], &c->bnd, &c->runs,
-                        &c->tab};
+                        &c->tab, &c->tab64};
     size_t t = 0;
     for (const Buf *b : all) t += b->bytes;
     return t;
@@ -1197,7 +1202,7 @@ TREEPM_API int treepm_destroy(treepm_ctx *c)
                   &c->wstats, &c->overflow, &c->rec, &c->kept, &c->kept_sum, &c->gcells, &c->cls, &c->out[0],
                   &c->out[1], &c->out[2], &c->bnd, &c->runs, &c->pm_mass, &c->pm_grid,
                   &c->pm_f, &c->pm_green, &c->pm_tw, &c->pm_mx, &c->pm_stage, &c->pm_cells, &c->pm_slots,
-                  &c->n_q, &c->step_min, &c->tab, &c->bdesc};
+                  &c->n_q, &c->step_min, &c->tab, &c->tab64, &c->bdesc};
     {
         // the work is done: the buffers are kept for reuse at once, not behind a stream
         CallScope scope(c, c->own ? c->own : c->last);
@@ -1353,8 +1358,29 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
     return TREEPM_OK;
 }
 
+// The same for the FP64 kernel; a softening too small for a table is no error.
+int ensure_table64(treepm_ctx *c, hipStream_t s)
+{
+    const double key = c->prm.eps / c->prm.r_cut;
+    if (c->tab64_key == key) return TREEPM_OK;
+    std::vector<double> hi;
+    std::vector<float> lo;
+    c->tab64_ok = false;
+    if (build_force_table64(key, hi, lo)) {
+        hipError_t e = reserve(c->tab64, hi.size() * 8 + lo.size() * 4);
+        if (e != hipSuccess) return hip_fail(c, e, "pair-law table");
+        HIPCHK(c, hipMemcpyAsync(c->tab64.p, hi.data(), hi.size() * 8, hipMemcpyHostToDevice, s));
+        HIPCHK(c, hipMemcpyAsync(c->tab64.as<double>() + hi.size(), lo.data(), lo.size() * 4,
+                                 hipMemcpyHostToDevice, s));
+        HIPCHK(c, hipStreamSynchronize(s)); // host temporaries
+        c->tab64_ok = true;
+    }
+    c->tab64_key = key;
+    return TREEPM_OK;
+}
+
 // The context as the force launches read it (pairs and pair sums are reserved; for the FP32
-// kernel, ensure_table has run).
+// kernel, ensure_table has run; for the FP64 one, ensure_table64).
 ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
 {
     ForceBox F{};
@@ -1370,6 +1396,11 @@ ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
     F.ft = c->ftab;
     F.rec = rec;
     F.rec64 = rec64;
+    if (c->prm.precision == TREEPM_FP64 && c->tab64_ok) {
+        F.tab64_hi = c->tab64.as<double>();
+        F.tab64_lo = reinterpret_cast<const float *>(F.tab64_hi +
+                                                     (size_t)kTab64F64 * kTab64Entries);
+    }
     F.n_groups = c->n_groups;
     F.pair_sum = c->kept_sum.as<unsigned long long>();
     F.n = c->n;
@@ -1426,15 +1457,14 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
                    c->kept.as<unsigned long long>()};
     const int rec64 = out_prec != TREEPM_FP32;
     void *rec = c->rec.p; // n x 32 bytes since the build
-    if (P.precision == TREEPM_FP32 && (rc = ensure_table(c, s))) return rc;
+    rc = P.precision == TREEPM_FP32 ? ensure_table(c, s) : ensure_table64(c, s);
+    if (rc) return rc;
     const ForceBox F = force_box(c, fp, rec, rec64);
     launch_force_prep(F, s);
     if (P.precision == TREEPM_FP32) {
         launch_force_f32(F, c->n_groups, c->n_cu, s);
     } else
-        launch_force_f64(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
-                         c->entries.as<uint32_t>(),
-                         c->psrc.as<double4>(), c->idx.as<uint32_t>(), fp, rec, rec64, s);
+        launch_force_f64(F, c->n_groups, c->n_cu, s);
     if (P.quadrupole)
         launch_quad(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
                     c->entries.as<uint32_t>(), c->psrc.as<double4>(), c->idx.as<uint32_t>(),
