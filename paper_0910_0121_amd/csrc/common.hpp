@@ -138,6 +138,8 @@ constexpr int kTreeWin = 256;
 struct TreeOffsets {
     uint32_t off[kMaxLevel + 3]; // first node of each level; past the last, the node count
 };
+// Levels of at most this many nodes next to each other share a launch of the moments.
+constexpr uint32_t kFewNodes = 2048;
 // Moments of all nodes, deepest level first (levels 0 .. max_level at to.off): mass, position
 // sums S (comx/comy/comz; the centre of mass S / M goes to nsrc and the walk records wn).
 // derive = 1 for a tree from launch_tree_emit: nchild and internal counts are set here, the
@@ -268,14 +270,35 @@ constexpr uint32_t kTab64Entries = (uint32_t)kTab64Oct * 64u + 1u;
 // above 64: the kernel then evaluates eq. (2) pair by pair.
 bool build_force_table64(double eps_over_rcut, std::vector<double> &hi, std::vector<float> &lo);
 
+// The FP32 quadrupole kernel's table: U = 2 dG/du as cubic pieces in t, 2^kQuadSegBits per octave
+// of the same u from the same c, the entry of u = 1 zero; its derivative V = dU/du by the same
+// coefficients: per piece U's constant, V's constant, linear and quadratic term, each an array of
+// `entries` floats.  U and V carry a factor 2^scale_exp, which the moments make up for.
+constexpr int kQuadSegBits = 7;
+constexpr int kQuadShift = 23 - kQuadSegBits;
+constexpr int kQuadAddrShift = kQuadShift - 2;
+struct QuadTable {
+    const float *coef;
+    uint32_t entries;
+    uint32_t base; // byte address of the first entry: bits(c) >> kQuadAddrShift
+    int scale_exp;
+};
+// For the c (a power of two) of the FP32 table of this eps / r_cut.
+void build_quad_table(double eps_over_rcut, double c, std::vector<float> &coef, QuadTable &qt);
+
 // Layout of the queue buffer (u32 words): the kXcds + 1 part starts and the kXcds ends of the
 // parts' runs of split groups (absolute word positions in the buffer), the queue counters of
 // the split and of the other groups, the (part, cost bucket) cursors, then the group ids, each
 // part's longest first.
 constexpr uint32_t kClsStarts = 0;
 constexpr uint32_t kClsHeavyEnd = kClsStarts + kXcds + 1;
-constexpr uint32_t kClsQueue = kClsHeavyEnd + kXcds;
-constexpr uint32_t kClsBins = kClsQueue + 2 * kXcds * kQueueStride;
+// the same for the kernels with workgroups of 16 waves, which split groups of at least 2^(t +
+// kCoarser16) pairs instead of 2^t
+constexpr uint32_t kCoarser16 = 2;
+constexpr uint32_t kClsEnd16 = kClsHeavyEnd + kXcds;
+constexpr uint32_t kClsQueue = kClsEnd16 + kXcds;
+constexpr uint32_t kClsQuadQueue = kClsQueue + 2 * kXcds * kQueueStride; // k_quad_f32's
+constexpr uint32_t kClsBins = kClsQuadQueue + 2 * kXcds * kQueueStride;
 constexpr uint32_t kClsLists = kClsBins + kXcds * 64;
 // Parts and longest-first order of the groups (len: list lengths; pairs: the box's
 // interactions, device), into cls (kClsLists + n_groups words).
@@ -300,6 +323,8 @@ struct ForceBox {
     ForceTable ft;
     void *rec;
     int rec64; // rec holds double4 records
+    QuadTable qt;         // with quadrupole terms, FP32: its table
+    const double *moments; // and the cells' second moments, six per node
     const double *tab64_hi; // FP64 kernel: its table, or null (pair by pair)
     const float *tab64_lo;
     uint32_t n_groups;
@@ -307,7 +332,7 @@ struct ForceBox {
     int64_t n;
     void *out[3]; // launch_force_out_multi: the float outputs
 };
-// Empties a box's force queues and zeroes its pairs (which split groups add to) and *pair_sum
+// Empties a box's force and quadrupole queues and zeroes its pairs (which split groups add to) and *pair_sum
 // (which the output pass adds to).
 void launch_force_prep(const ForceBox &box, hipStream_t s);
 void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s); // device array
@@ -367,14 +392,11 @@ void launch_pm_split(const float4 *stage, int64_t n, void *ax, void *ay, void *a
 
 // Quadrupole terms of the cell entries (k_quad.hip).  Q: 6 doubles per node (xx, yy, zz,
 // xy, xz, yz about the centre of mass), filled level by level from the deepest.
-void launch_second_moments(NodeArrays nd, const double4 *ps, uint32_t lo, uint32_t hi,
+void launch_second_moments(NodeArrays nd, const double4 *ps, const TreeOffsets &to, int max_level,
                            double *Q, hipStream_t s);
-// Adds the cells' second-order terms to the force records (caller's order, float4 or, with
-// rec64, double4), computed in FP64 (fp64_math) or FP32.
-void launch_quad(NodeArrays nd, GroupArrays gr, uint32_t n_groups, const uint64_t *off,
-                 const uint32_t *len, const uint32_t *entries, const double4 *ps,
-                 const uint32_t *pidx, const double *Q, ForceParams fp, void *rec,
-                 int fp64_math, int rec64, hipStream_t s);
+// Adds the cells' second-order terms to the box's force records, computed in FP64 or FP32 (then
+// box.qt is its table; a persistent launch over queues of its own, emptied by launch_force_prep).
+void launch_quad(const ForceBox &box, uint32_t n_groups, int fp64, int n_cu, hipStream_t s);
 
 // Time stepping (k_step.hip).  Accelerations are float (acc_fp64 = 0) or double arrays.
 // out receives the bit pattern of min_i(sqrt(eps / |a_i|), eps / |v_i|) (+inf if none binds).

@@ -1,7 +1,9 @@
 // Parts shared by the FP32 and FP64 force kernels: the persistent workgroups and their queues,
 // the split of a group into chunks of particles, and the reduction and output of their sums.
 // A kernel is a policy P: kWaves (waves per workgroup), kTilesAt and kTileBytes (the waves' LDS
-// tiles), Frame (a group's origin and units, with `scale`, the factor of the sums), load_table,
+// tiles), kQueueAt (its queue counters), kSplitEnd
+// (the ends of its runs of split groups), kAdd (sums are added to the records and no pairs are
+// counted), Frame (a group's origin and units, with `scale`, the factor of the sums), load_table,
 // group (reads a group, makes its frame and calls finish_group) and chunk_sums<K> (a wave's sums
 // for a chunk over a range of the group's list; returns the entries that survived the cull).
 #pragma once
@@ -20,9 +22,21 @@ namespace {
 // short-range force as soon as it is known), each product and sum rounded on its own.
 enum { kOutF32 = 0, kOutF64 = 1, kOutKick = 2 };
 
-template <int REC64>
+template <int REC64, bool ADD>
 __device__ __forceinline__ void store_rec(void *rec, uint32_t i, double vx, double vy, double vz)
 {
+    if (ADD) { // each record belongs to one particle of one chunk
+        if (REC64) {
+            double4 *const r = (double4 *)rec + i;
+            const double4 o = *r;
+            *r = make_double4(o.x + vx, o.y + vy, o.z + vz, 0.0);
+        } else {
+            float4 *const r = (float4 *)rec + i;
+            const float4 o = *r;
+            *r = make_float4(o.x + (float)vx, o.y + (float)vy, o.z + (float)vz, 0.0f);
+        }
+        return;
+    }
     if (REC64)
         ((double4 *)rec)[i] = make_double4(vx, vy, vz, 0.0);
     else
@@ -178,9 +192,11 @@ __device__ __forceinline__ uint32_t run_chunk(char *tiles, int wave, bool split,
             const uint32_t i = (uint32_t)(lane + S * k);
             if (lane < S && i < n_i) {
                 if (rec64)
-                    store_rec<1>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
+                    store_rec<1, P::kAdd>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale,
+                                          az[k] * scale);
                 else
-                    store_rec<0>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale, az[k] * scale);
+                    store_rec<0, P::kAdd>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale,
+                                          az[k] * scale);
             }
         }
         return kept;
@@ -211,9 +227,9 @@ __device__ __forceinline__ uint32_t run_chunk(char *tiles, int wave, bool split,
                 vz += d[2];
             }
             if (rec64)
-                store_rec<1>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+                store_rec<1, P::kAdd>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
             else
-                store_rec<0>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+                store_rec<0, P::kAdd>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
         }
         __syncthreads();
     }
@@ -273,6 +289,58 @@ struct GroupRead {
     }
 };
 
+// What a wave of the FP32 kernels needs of its group.  Coordinates are x' = x inv - xg', one fused operation.
+struct FrameF32 {
+    bool wrap;            // coordinates need the nearest image
+    double xg0, xg1, xg2; // wrap: x_g; else x_g inv
+    double L, inv_L, inv; // inv = lam / r_cut
+    double scale;
+    float c;
+};
+
+// A position relative to x_g in x' units (wrap: see GroupRead::wraps).
+__device__ __forceinline__ float4 rel_f32(const double4 r, const FrameF32 &F)
+{
+    if (F.wrap) {
+        double dx = r.x - F.xg0, dy = r.y - F.xg1, dz = r.z - F.xg2;
+        dx = fma(-F.L, rint(dx * F.inv_L), dx);
+        dy = fma(-F.L, rint(dy * F.inv_L), dy);
+        dz = fma(-F.L, rint(dz * F.inv_L), dz);
+        return make_float4((float)(dx * F.inv), (float)(dy * F.inv), (float)(dz * F.inv),
+                           (float)r.w);
+    }
+    return make_float4((float)fma(r.x, F.inv, -F.xg0), (float)fma(r.y, F.inv, -F.xg1),
+                       (float)fma(r.z, F.inv, -F.xg2), (float)r.w);
+}
+
+__device__ __forceinline__ FrameF32 frame_f32(const ForceBox &B, const GroupRead &R)
+{
+    const ForceParams &fp = B.fp;
+    const double lam = sqrt(1.0 - (double)B.ft.c);
+    const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
+    FrameF32 F;
+    F.scale = uni(inv_len * inv_len / lam);
+    F.wrap = R.wraps(fp);
+    F.L = fp.L;
+    F.inv_L = uni(1.0 / fp.L);
+    F.inv = uni(inv_len * lam);
+    F.xg0 = uni(F.wrap ? R.xg[0] : R.xg[0] * F.inv);
+    F.xg1 = uni(F.wrap ? R.xg[1] : R.xg[1] * F.inv);
+    F.xg2 = uni(F.wrap ? R.xg[2] : R.xg[2] * F.inv);
+    F.c = B.ft.c;
+    return F;
+}
+
+// One pair in x' units: a source s against a particle, and u = min(|d'|^2 + c, 1).
+__device__ __forceinline__ float pair_u(const float4 s, float xi, float yi, float zi, float c,
+                                        float &dx, float &dy, float &dz)
+{
+    dx = s.x - xi;
+    dy = s.y - yi;
+    dz = s.z - zi;
+    // u = min(|d|^2 + c, 1): the clamp is an output modifier of the last fma
+    return __builtin_amdgcn_fmed3f(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, c))), 0.0f, 1.0f);
+}
 // The group once its frame is known: by one wave, or, split, by the workgroup.
 template <class P>
 __device__ __forceinline__ void finish_group(char *tiles, int wave, bool split, const ForceBox &B,
@@ -290,7 +358,7 @@ __device__ __forceinline__ void finish_group(char *tiles, int wave, bool split, 
         B.entries + (((uint64_t)uni((uint32_t)(R.off >> 32)) << 32) | uni((uint32_t)R.off));
     const uint64_t pairs =
         run_group<P>(tiles, wave, split, B, uni(R.count), uni(R.first), list, j0, j1, F);
-    if (__lane_id() == 0) {
+    if (!P::kAdd && __lane_id() == 0) {
         if (split)
             atomicAdd(&B.fp.pairs[g], (unsigned long long)pairs); // zeroed by the prep launch
         else
@@ -328,29 +396,33 @@ __device__ __forceinline__ Item find_item(uint32_t ends, int nb, uint32_t q)
 }
 
 // Box b's run of part p in the queue of split (heavy = 1) or single-wave groups.
+template <class P>
 __device__ __forceinline__ uint32_t run_start(const uint32_t *cls, uint32_t p, int heavy)
 {
-    return cls[heavy ? kClsStarts + p : kClsHeavyEnd + p];
+    return cls[heavy ? kClsStarts + p : P::kSplitEnd + p];
 }
+template <class P>
 __device__ __forceinline__ uint32_t run_size(const uint32_t *cls, uint32_t p, int heavy)
 {
-    return cls[heavy ? kClsHeavyEnd + p : kClsStarts + p + 1] - run_start(cls, p, heavy);
+    return cls[heavy ? P::kSplitEnd + p : kClsStarts + p + 1] - run_start<P>(cls, p, heavy);
 }
 
 // Per lane p < kXcds the total size of part p over the boxes.
+template <class P>
 __device__ __forceinline__ uint32_t part_sizes(const ForceBox *bx, int nb, int heavy)
 {
     const uint32_t lane = __lane_id();
     uint32_t n = 0;
     if (lane < kXcds)
-        for (int b = 0; b < nb; ++b) n += run_size(bx[b].cls, lane, heavy);
+        for (int b = 0; b < nb; ++b) n += run_size<P>(bx[b].cls, lane, heavy);
     return n;
 }
 // Per lane the inclusive prefix over the boxes of their runs of `part`.
+template <class P>
 __device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_t part, int heavy)
 {
     const int lane = __lane_id();
-    uint32_t v = lane < nb ? run_size(bx[lane].cls, part, heavy) : 0u;
+    uint32_t v = lane < nb ? run_size<P>(bx[lane].cls, part, heavy) : 0u;
 #pragma unroll
     for (int d = 1; d < kMaxBatch; d <<= 1) {
         const uint32_t u = __shfl_up(v, d, 64);
@@ -367,7 +439,10 @@ __device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_
 // A group with at least 2^t pairs is split over the workgroup's waves, 2^t being about a
 // 16384th of the box's pairs (at least 2^12): one wave alone would hold up the end of the
 // launch.  On the 700,001-particle clustered box the longest single-wave group took 1.3 ms of
-// a 1.5 ms force call whose work fills the device for 0.6 ms.
+// a 1.5 ms force call whose work fills the device for 0.6 ms.  Workgroups of 16 waves leave each
+// wave half as much of a group and split from 2^(t+2) on: quadrupole terms of a million particles
+// from 2^t, 2^(t+1), 2^(t+2) and 2^(t+3) on: 0.98, 0.94, 0.67 and 0.80 ms; FP64 force of the
+// 128^3 clustered box from 2^t and 2^(t+2) on: 3.72 and 3.39 ms.
 template <class P, bool MULTI>
 __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
 {
@@ -378,13 +453,13 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // known to be uniform
     const uint32_t lane = __lane_id();
     const uint32_t xcd = blockIdx.x % kXcds;
-    uint32_t *const hq = bx[0].cls + kClsQueue, *const lq = hq + kXcds * kQueueStride;
+    uint32_t *const hq = bx[0].cls + P::kQueueAt, *const lq = hq + kXcds * kQueueStride;
     __syncthreads();
     char *const tiles = lds + P::kTilesAt;
     uint32_t *const word = reinterpret_cast<uint32_t *>(tiles); // free between groups
-    uint32_t size = part_sizes(bx, nb, 1), part = xcd, ends = 0, have = kXcds, next = 0;
+    uint32_t size = part_sizes<P>(bx, nb, 1), part = xcd, ends = 0, have = kXcds, next = 0;
     bool split = __ballot(size != 0) != 0;
-    if (!split) size = part_sizes(bx, nb, 0);
+    if (!split) size = part_sizes<P>(bx, nb, 0);
     for (;;) {
         uint32_t *const ctr = split ? hq : lq;
         uint32_t q = next;
@@ -415,18 +490,18 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
         if (part == kXcds) {
             if (!split) break;
             split = false; // on to the single-wave groups
-            size = part_sizes(bx, nb, 0);
+            size = part_sizes<P>(bx, nb, 0);
             part = xcd;
             have = kXcds;
             continue;
         }
-        if (MULTI && part != have) ends = run_ends(bx, nb, part, split);
+        if (MULTI && part != have) ends = run_ends<P>(bx, nb, part, split);
         have = part;
         if (!split && lane == 0) next = atomicAdd(&ctr[part * kQueueStride], 1u);
         Item it{0, q};
         if (MULTI) it = find_item(ends, nb, q);
         const ForceBox &B = MULTI ? bx[uni(it.box)] : bx[0];
-        P::group(tiles, wave, split, B, uni(B.cls[run_start(B.cls, part, split) + it.k]));
+        P::group(tiles, wave, split, B, uni(B.cls[run_start<P>(B.cls, part, split) + it.k]));
     }
 }
 

@@ -1128,9 +1128,6 @@ void launch_emit(NodeArrays nd, const uint32_t *bnd, uint32_t lo, uint32_t hi, i
     k_emit<<<grid_for(hi - lo, 256), 256, 0, s>>>(nd, bnd, lo, hi, level, base, cnt, L);
 }
 
-// Levels of at most this many nodes next to each other share a launch.
-constexpr uint32_t kFewNodes = 2048;
-
 void launch_moments(NodeArrays nd, const double4 *ps, const TreeOffsets &to, int max_level,
                     int derive, WalkNode *wn, hipStream_t s)
 {

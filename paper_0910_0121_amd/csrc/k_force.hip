@@ -72,30 +72,6 @@ static_assert(kForceWaves * kTileF32 * 16 <= ((127 + kTabMinExp) << 8), "tiles e
 static_assert(kTabPlane >= (uint32_t)(-kTabMinExp) * 256u + 4u && kTabPlane % 256 == 0,
               "planes do not overlap");
 
-// What a wave needs of its group.  Coordinates are x' = x inv - xg', one fused operation.
-struct FrameF32 {
-    bool wrap;            // coordinates need the nearest image
-    double xg0, xg1, xg2; // wrap: x_g; else x_g inv
-    double L, inv_L, inv; // inv = lam / r_cut
-    double scale;
-    float c;
-};
-
-// A position relative to x_g in x' units (wrap: see GroupRead::wraps).
-__device__ __forceinline__ float4 rel_f32(const double4 r, const FrameF32 &F)
-{
-    if (F.wrap) {
-        double dx = r.x - F.xg0, dy = r.y - F.xg1, dz = r.z - F.xg2;
-        dx = fma(-F.L, rint(dx * F.inv_L), dx);
-        dy = fma(-F.L, rint(dy * F.inv_L), dy);
-        dz = fma(-F.L, rint(dz * F.inv_L), dz);
-        return make_float4((float)(dx * F.inv), (float)(dy * F.inv), (float)(dz * F.inv),
-                           (float)r.w);
-    }
-    return make_float4((float)fma(r.x, F.inv, -F.xg0), (float)fma(r.y, F.inv, -F.xg1),
-                       (float)fma(r.z, F.inv, -F.xg2), (float)r.w);
-}
-
 // Culls and packs one tile; returns the number of survivors (the same on every lane).
 __device__ __forceinline__ int load_tile_f32(float4 *tile, const uint32_t *ent, uint32_t jb,
                                              uint32_t je, int J, NodeArrays nd,
@@ -140,16 +116,7 @@ __device__ __forceinline__ int load_tile_f32(float4 *tile, const uint32_t *ent, 
 }
 static_assert(kTileF32 % 16 == 0, "J divides a tile");
 
-// One pair: s = (x_j', m_j), lane particle (xi, yi, zi).  u and t as in the header above.
-__device__ __forceinline__ float pair_u(const float4 s, float xi, float yi, float zi, float c,
-                                        float &dx, float &dy, float &dz)
-{
-    dx = s.x - xi;
-    dy = s.y - yi;
-    dz = s.z - zi;
-    // u = min(|d|^2 + c, 1): the clamp is an output modifier of the last fma
-    return __builtin_amdgcn_fmed3f(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, c))), 0.0f, 1.0f);
-}
+// One pair (see pair_u): the force from its piece's coefficients.
 __device__ __forceinline__ float pair_f(float c0, float c1, float c2, float t, float m)
 {
     const float p = fmaf(fmaf(c2, t, c1), t, c0);
@@ -273,6 +240,8 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
 // cost about 12 ms, at 40 ns each).  700,001 particles: the whole step 3.41 -> 1.53 ms.
 struct PolicyF32 {
     static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
+    static constexpr uint32_t kQueueAt = kClsQueue, kSplitEnd = kClsHeavyEnd;
+    static constexpr bool kAdd = false;
     using Frame = FrameF32;
 
     static __device__ __forceinline__ void load_table(char *lds, const ForceBox &B)
@@ -300,20 +269,7 @@ struct PolicyF32 {
                                                  const ForceBox &B, uint32_t g)
     {
         const GroupRead R(B, g);
-        const ForceParams &fp = B.fp;
-        const double lam = sqrt(1.0 - (double)B.ft.c);
-        const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
-        Frame F;
-        F.scale = uni(inv_len * inv_len / lam);
-        F.wrap = R.wraps(fp);
-        F.L = fp.L;
-        F.inv_L = uni(1.0 / fp.L);
-        F.inv = uni(inv_len * lam);
-        F.xg0 = uni(F.wrap ? R.xg[0] : R.xg[0] * F.inv);
-        F.xg1 = uni(F.wrap ? R.xg[1] : R.xg[1] * F.inv);
-        F.xg2 = uni(F.wrap ? R.xg[2] : R.xg[2] * F.inv);
-        F.c = B.ft.c;
-        finish_group<PolicyF32>(tiles, wave, split, B, g, R, F);
+        finish_group<PolicyF32>(tiles, wave, split, B, g, R, frame_f32(B, R));
     }
 };
 
@@ -449,6 +405,7 @@ __device__ __forceinline__ void scan_bins(uint32_t *bins, uint32_t *cls, uint32_
         // bucket lane holds lg = 63 - lane: split for lg >= t
         if (lane == 0) cls[kClsStarts + p] = pos;
         if (lane == 63 - (int)t) cls[kClsHeavyEnd + p] = pos + v;
+        if (lane == 63 - (int)(t + kCoarser16)) cls[kClsEnd16 + p] = pos + v;
         pos += (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
     }
     if (lane == 0) cls[kClsStarts + kXcds] = pos;
@@ -611,7 +568,7 @@ __global__ __launch_bounds__(1024) void k_walk_results_multi(const WalkBox *__re
 __device__ __forceinline__ void force_prep(const ForceBox &B, uint32_t b, uint32_t nb)
 {
     const uint32_t i = b * 256u + threadIdx.x;
-    if (i < 2 * kXcds) B.cls[kClsQueue + i * kQueueStride] = 0;
+    if (i < 4 * kXcds) B.cls[kClsQueue + i * kQueueStride] = 0;
     if (i == 0) *B.pair_sum = 0;
     for (uint32_t k = i; k < B.n_groups; k += nb * 256u) B.fp.pairs[k] = 0;
 }

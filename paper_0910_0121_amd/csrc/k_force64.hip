@@ -16,7 +16,7 @@
 // 16-byte read costs two to three times as much per byte once the lanes spread over pieces),
 // and the three highest, whose share of p is at most 7e-9, are floats and are summed in FP32: 26
 // cycles of LDS time a pair against 32, and two conversions less.  Measured on the 128^3 clustered
-// box (2.1 million particles): 3.7 ms, LDS busy 70 % of it and the vector units about 75 %; pair by
+// box (2.1 million particles): 3.4 ms, LDS and vector units both busy three quarters of it; pair by
 // pair, with one group a wave, it was 8.2 ms.
 #include "force_common.hpp"
 
@@ -220,6 +220,8 @@ template <bool TABLE>
 struct Policy64 {
     static constexpr int kWaves = 16, kTilesAt = TABLE ? (int)kTable64 : 0,
                          kTileBytes = kTile64 * 32;
+    static constexpr uint32_t kQueueAt = kClsQueue, kSplitEnd = kClsEnd16;
+    static constexpr bool kAdd = false;
     static constexpr uint32_t kLds = kTilesAt + kWaves * kTileBytes;
     using Frame = Frame64;
 

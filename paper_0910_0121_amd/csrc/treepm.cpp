@@ -99,6 +99,7 @@ struct treepm_ctx {
     Buf tab;
     double tab_key = 0.0;
     ForceTable ftab{};
+    QuadTable qtab{}; // behind it, for boxes with quadrupole terms (no entries: none)
     // FP64 pair-law table (doubles, then floats) and the eps / r_cut it was tried for (-1: none);
     // tab64_ok: that ratio has one.
     Buf tab64;
@@ -787,8 +788,7 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     if (P.quadrupole) {
         hipError_t e = reserve(c->n_q, (size_t)c->n_nodes * 6 * sizeof(double));
         if (e != hipSuccess) return hip_fail(c, e, "second moments");
-        for (int l = c->max_level; l >= 0; --l)
-            launch_second_moments(nd, ps, c->lvl[l], c->lvl[l + 1], c->n_q.as<double>(), s);
+        launch_second_moments(nd, ps, levels, c->max_level, c->n_q.as<double>(), s);
     }
     // groups in key order
     int n_crit = P.n_crit > 0 ? P.n_crit : kDefaultNCrit;
@@ -1337,16 +1337,24 @@ double table_key(const treepm_params &P)
     return std::ldexp(std::nearbyint(std::ldexp(f, 36)), e - 36);
 }
 
-// The FP32 pair-law table of the context's eps / r_cut, built on the host and copied to the
+// The FP32 pair-law table of the context's eps / r_cut (and the quadrupole's behind it), built on the host and copied to the
 // device once per parameter set.
 int ensure_table(treepm_ctx *c, hipStream_t s)
 {
     const double key = table_key(c->prm);
-    if (c->tab.p && c->tab_key == key) return TREEPM_OK;
+    if (c->tab.p && c->tab_key == key && (!c->prm.quadrupole || c->qtab.entries))
+        return TREEPM_OK;
     std::vector<float> coef;
     ForceTable ft{};
     if (!build_force_table(key, coef, ft))
         return fail(c, TREEPM_ERR_ARG, "eps / r_cut = %g is outside the FP32 table's range", key);
+    QuadTable qt{};
+    const size_t pair_words = coef.size();
+    if (c->prm.quadrupole) {
+        std::vector<float> quad;
+        build_quad_table(key, (double)ft.c, quad, qt);
+        coef.insert(coef.end(), quad.begin(), quad.end());
+    }
     hipError_t e = reserve(c->tab, coef.size() * sizeof(float));
     if (e != hipSuccess) return hip_fail(c, e, "pair-law table");
     HIPCHK(c, hipMemcpyAsync(c->tab.p, coef.data(), coef.size() * sizeof(float),
@@ -1354,6 +1362,8 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
     HIPCHK(c, hipStreamSynchronize(s)); // coef is a host temporary
     c->ftab = ft;
     c->ftab.coef = c->tab.as<float>();
+    c->qtab = qt;
+    c->qtab.coef = c->ftab.coef + pair_words;
     c->tab_key = key;
     return TREEPM_OK;
 }
@@ -1394,6 +1404,8 @@ ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
     F.pidx = c->idx.as<uint32_t>();
     F.fp = fp;
     F.ft = c->ftab;
+    F.qt = c->qtab;
+    F.moments = c->n_q.as<double>();
     F.rec = rec;
     F.rec64 = rec64;
     if (c->prm.precision == TREEPM_FP64 && c->tab64_ok) {
@@ -1466,9 +1478,7 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     } else
         launch_force_f64(F, c->n_groups, c->n_cu, s);
     if (P.quadrupole)
-        launch_quad(nd, gr, c->n_groups, c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
-                    c->entries.as<uint32_t>(), c->psrc.as<double4>(), c->idx.as<uint32_t>(),
-                    c->n_q.as<double>(), fp, rec, P.precision == TREEPM_FP64, rec64, s);
+        launch_quad(F, c->n_groups, P.precision == TREEPM_FP64, c->n_cu, s);
     launch_force_out(rec, out_prec, (int64_t)c->n, dst[0], dst[1], dst[2], kick_dt, c->n_groups,
                      fp.pairs, F.pair_sum, s);
     HIPCHK(c, hipGetLastError());
@@ -1723,8 +1733,7 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         treepm_ctx *c = cs[b];
         const ForceBox &F = fb[b];
         if (c->prm.quadrupole)
-            launch_quad(F.nd, F.gr, c->n_groups, F.off, F.len, F.entries, F.ps, F.pidx,
-                        c->n_q.as<double>(), F.fp, F.rec, 0, 0, s);
+            launch_quad(F, c->n_groups, 0, c->n_cu, s);
         most = std::max(most, c->n);
         c->last_force_prec = TREEPM_FP32;
         c->ev_valid[1] = c->ev_valid[2] = false;
