@@ -359,8 +359,6 @@ void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const doubl
 void launch_force_f64(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
 
 // Particle-mesh long-range force (k_pm.hip), mesh N^3 with N a power of two in [16, 1024].
-// Lines per FFT workgroup for mesh size N.
-int pm_bundle_lines(int N);
 // Octant table of the Green's function ((N/2+1)^3 floats) and N/2 twiddles.
 void launch_pm_green(int N, double L, double eta, float *green, float2 *tw, hipStream_t s);
 // Fills the fixed-point mass mesh (N^3 words, every word written) from the key-ordered records
@@ -374,16 +372,16 @@ void launch_pm_assign(const double4 *ps, const uint64_t *key, int64_t n, int N, 
                       const unsigned long long *mx, uint32_t *cell_start, uint32_t *item_start,
                       uint32_t *scan_tmp, unsigned long long *slots, unsigned long long *mass,
                       hipStream_t s);
-// Potential phi (N^3 floats) from the mass mesh, through the complex work mesh grid.
+// Potential phi (N^3 floats; may lie where the masses do) from the mass mesh, through the complex
+// work mesh grid (the half spectrum, pm_grid_points values).
+size_t pm_grid_points(int N);
 void launch_pm_potential(const unsigned long long *mass, const unsigned long long *mx,
                          int64_t n, int N, float2 *grid, float *phi, const float *green,
                          const float2 *tw, hipStream_t s);
-// Mesh force (N^3 float4: Fx, Fy, Fz, 0) from phi.
-void launch_pm_force(const float *phi, int N, double L, float4 *f, hipStream_t s);
 // Interpolated force of key-ordered particle k (ps[k]) into stage[idx[k]] = (ax, ay, az, 0),
 // i.e. in the caller's order (idx is the sort permutation).  cell_start and item_start as
 // launch_pm_assign left them for the same particles.
-void launch_pm_interp(const double4 *ps, int64_t n, int N, double L, const float4 *f,
+void launch_pm_interp(const double4 *ps, int64_t n, int N, double L, const float *phi,
                       const uint32_t *idx, float4 *stage, const uint32_t *cell_start,
                       const uint32_t *item_start, hipStream_t s);
 // ax[o] = stage[o].x etc. (float or double; accumulate adds).

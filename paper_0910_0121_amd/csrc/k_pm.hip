@@ -10,25 +10,20 @@
 //    workgroup per cell adds, for each of its points, the slot words that cover it.  Masses
 //    are 64-bit fixed point and every sum is a fixed set of integer adds, so the mesh is the
 //    same on every run; there are no global atomics;
-//  * FFT: complex, radix 2, one workgroup per bundle of B lines of one axis held in LDS
-//    (B N = 4096 values, B <= 16).  Bundles along x and y are B neighbouring lines in z, so a
-//    load of one element row is B contiguous values; bundles along z are B contiguous rows.
-//    The passes are: x forward (reading the fixed-point masses), y forward, z forward +
-//    Green's function + z inverse in one kernel (a DIF forward leaves bit-reversed order, which
-//    is what the DIT inverse reads), y inverse, x inverse (writing the real potential);
-//  * mesh force: fourth-order central differences of the potential, one float4 per point;
-//  * interpolation: over the assignment's chunks, the cell's 11^3 box of force words read
-//    into LDS once, each particle's 27 words from there; the 16-byte result goes to the
-//    particle's slot in the caller's order through the sort permutation (a scattered write);
-//    k_pm_split then writes the three output arrays contiguously.
+//  * FFT: five passes over bundles of lines (4096 values at most) of the half spectrum kx <= N/2
+//    of the real mesh: x forward (reading the fixed-point masses, two real lines as one complex
+//    line), y forward, z forward + Green's function + z inverse in one kernel, y inverse,
+//    x inverse (writing the real potential).  Bundles along x and y are neighbouring lines in z,
+//    so a load of one element row is contiguous; bundles along z are contiguous rows;
+//  * mesh force and interpolation: over the assignment's chunks, the potential around the cell
+//    is read into LDS, the fourth-order central differences on the cell's 11^3 box formed there,
+//    and each particle's 27 points read from those; the 16-byte result goes to the particle's
+//    slot in the caller's order through the sort permutation (a scattered write); k_pm_split
+//    then writes the three output arrays contiguously.
 #include "common.hpp"
 
 namespace tpm {
 namespace {
-
-constexpr int kFftThreads = 256;
-constexpr int kFftElems = 4096;
-constexpr int kMaxTwiddles = 512; // N <= 1024
 
 __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
@@ -140,19 +135,22 @@ __global__ __launch_bounds__(256) void k_pm_cell_items(const uint32_t *__restric
     items[m] = (c + kCellChunk - 1) / kCellChunk;
 }
 
-// The cell whose chunks include chunk `item`: the last m with item_start[m] <= item.
+// The cell whose chunks include chunk `item`: the last m with item_start[m] <= item.  Every lane
+// of the wave probes one place of the range, so 32768 cells take three memory latencies and not
+// fifteen.
 __device__ __forceinline__ uint32_t item_cell(const uint32_t *__restrict__ item_start,
                                               uint32_t ncells, uint32_t item)
 {
-    uint32_t lo = 0, hi = ncells;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (item_start[mid] <= item)
-            lo = mid;
-        else
-            hi = mid;
+    const uint32_t lane = __lane_id();
+    uint32_t lo = 0, len = ncells;
+    while (len > 1) {
+        const uint32_t step = (len + 63) / 64, at = lane * step;
+        const bool before = at < len && item_start[lo + at] <= item;
+        const uint32_t k = (uint32_t)__popcll(__ballot(before)) - 1u; // lane 0 always is
+        lo += k * step;
+        len = min(step, len - k * step);
     }
-    return lo;
+    return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // One workgroup per chunk (grid: an upper bound on the chunks; the rest leave).
@@ -224,7 +222,9 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_assign(
 // One workgroup per cell, one thread per mesh point of the cell: the sum of the slot words of
 // every chunk of every cell whose box covers the point (its own cell, and the neighbour on
 // the low side for the cell's first two planes, on the high side for its last plane, per
-// axis).  The 27 neighbours' chunk ranges are read into LDS once.
+// axis): at most two cells per axis, whose first chunks are read together.  The 27 neighbours'
+// chunk ranges are read into LDS once.  256^3 mesh, 16.8 million clustered particles: 0.29 ms
+// with a loop over the 27 cells and one read in flight a thread, 0.16 as it is.
 __global__ __launch_bounds__(kCellPts * kCellPts * kCellPts) void k_pm_gather(
     int N, const uint32_t *__restrict__ item_start, const unsigned long long *__restrict__ slots,
     unsigned long long *__restrict__ mass)
@@ -244,221 +244,336 @@ __global__ __launch_bounds__(kCellPts * kCellPts * kCellPts) void k_pm_gather(
     }
     __syncthreads();
     const int x0 = t >> 6, y0 = (t >> 3) & 7, z0 = t & 7; // point within the cell
-    unsigned long long sum = 0ull;
-    for (int dx = -1; dx <= 1; ++dx) {
-        const int lx = x0 - 8 * dx + 1; // the point in the box of neighbour dx
-        if (lx < 0 || lx >= kBox) continue;
-        for (int dy = -1; dy <= 1; ++dy) {
-            const int ly = y0 - 8 * dy + 1;
-            if (ly < 0 || ly >= kBox) continue;
-            for (int dz = -1; dz <= 1; ++dz) {
-                const int lz = z0 - 8 * dz + 1;
-                if (lz < 0 || lz >= kBox) continue;
-                const int k = ((dx + 1) * 3 + (dy + 1)) * 3 + (dz + 1);
-                const int w = (lx * kBox + ly) * kBox + lz;
-                for (uint32_t it = rng[k][0]; it < rng[k][1]; ++it)
-                    sum += slots[(size_t)it * kBoxWords + w];
-            }
-        }
+    auto other = [](int p) { return p < 2 ? -1 : p == kCellPts - 1 ? 1 : 0; };
+    const int ox = other(x0), oy = other(y0), oz = other(z0); // 0: only its own cell covers it
+    unsigned long long v[8];
+    uint32_t next[8], end[8], word[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) { // own or other cell per axis
+        const int dx = j & 4 ? ox : 0, dy = j & 2 ? oy : 0, dz = j & 1 ? oz : 0;
+        const bool cover = (!(j & 4) || ox) && (!(j & 2) || oy) && (!(j & 1) || oz);
+        const int k = ((dx + 1) * 3 + (dy + 1)) * 3 + (dz + 1);
+        next[j] = rng[k][0];
+        end[j] = cover ? rng[k][1] : 0u;
+        word[j] = (uint32_t)(((x0 - 8 * dx + 1) * kBox + (y0 - 8 * dy + 1)) * kBox +
+                             (z0 - 8 * dz + 1));
+        const bool some = next[j] < end[j];
+        v[j] = slots[some ? (size_t)next[j] * kBoxWords + word[j] : 0];
+        if (!some) v[j] = 0ull;
     }
+    unsigned long long sum = 0ull;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) sum += v[j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) // cells of more than one chunk
+        for (uint32_t it = next[j] + 1; it < end[j]; ++it)
+            sum += slots[(size_t)it * kBoxWords + word[j]];
     mass[((size_t)(8 * cx + x0) * N + (size_t)(8 * cy + y0)) * N + (size_t)(8 * cz + z0)] = sum;
 }
 
 // ---------------------------------------------------------------- FFT on bundles of lines
+//
+// A line of N = 2^LOGN points is transformed by N / 16 threads with 16 points each in registers, in
+// one to three steps of radix 16, 8 or 4 (Stockham's ordering: natural in, natural out); between
+// steps the points change places through LDS once.  Step s with radix R after steps of product
+// NS: butterfly j takes points j + r N / R, times exp(-2 pi i r (j mod NS) / (NS R)), to points
+// (j / NS) NS R + (j mod NS) + r NS.
+// N = 256, five passes from the masses to the potential: 0.14 ms for 0.75 GB read and written;
+// with radix-2 stages through LDS on the full complex mesh 0.59 ms.
 
-struct Bundle {
-    int N, logN, B, p, q0;
+template <int LOGN>
+struct Radix; // the steps' radices, 0 where there is none
+template <> struct Radix<4> { static constexpr int a = 16, b = 0, c = 0; };
+template <> struct Radix<5> { static constexpr int a = 8, b = 4, c = 0; };
+template <> struct Radix<6> { static constexpr int a = 8, b = 8, c = 0; };
+template <> struct Radix<7> { static constexpr int a = 16, b = 8, c = 0; };
+template <> struct Radix<8> { static constexpr int a = 16, b = 16, c = 0; };
+template <> struct Radix<9> { static constexpr int a = 8, b = 8, c = 8; };
+template <> struct Radix<10> { static constexpr int a = 16, b = 8, c = 8; };
+
+// Lines per workgroup; threads per line; LDS points, with a row left free after every 16 (points
+// 16 apart would fall on the same banks).
+template <int LOGN>
+struct Lines {
+    static constexpr int N = 1 << LOGN, B = N >= 256 ? 4096 / N : 16, T = N / 16;
+    static constexpr int P = B < N / 2 ? B : N / 2; // pairs of real lines per workgroup
+    static constexpr int kRows = N + N / 16;
 };
 
-__device__ __forceinline__ Bundle bundle(int N, int logN, int B)
+// Times exp(-+ i pi / 2).
+template <bool INV>
+__device__ __forceinline__ float2 quarter(float2 v)
 {
-    Bundle u;
-    u.N = N;
-    u.logN = logN;
-    u.B = B;
-    const int per_row = N / B;
-    u.p = blockIdx.x / per_row;
-    u.q0 = (blockIdx.x % per_row) * B;
-    return u;
+    return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
 }
 
-// Global address of element e of line l of the bundle, for the transform along AXIS.
-template <int AXIS>
-__device__ __forceinline__ size_t elem_addr(const Bundle &u, int l, int e)
+template <bool INV>
+__device__ __forceinline__ void dft4(float2 &a, float2 &b, float2 &c, float2 &d)
 {
-    const size_t N = u.N, NN = N * N;
-    if (AXIS == 0) return (size_t)e * NN + (size_t)u.p * N + u.q0 + l;
-    if (AXIS == 1) return (size_t)u.p * NN + (size_t)e * N + u.q0 + l;
-    return (size_t)u.p * NN + (size_t)(u.q0 + l) * N + e;
+    const float2 s = cadd(a, c), m = csub(a, c), t = cadd(b, d), u = quarter<INV>(csub(b, d));
+    a = cadd(s, t);
+    b = cadd(m, u);
+    c = csub(s, t);
+    d = csub(m, u);
 }
 
-// LDS slot of element e of line l: element-major along x and y (so a row of B lines is
-// contiguous), line-major along z.
-template <int AXIS>
-__device__ __forceinline__ int slot(const Bundle &u, int l, int e)
+// Discrete Fourier transform of R points in registers, natural order in and out.
+template <int R, bool INV>
+__device__ __forceinline__ void dft(float2 *v)
 {
-    return AXIS == 2 ? l * u.N + e : e * u.B + l;
-}
-
-// The j-th of the loaded values, in the order that makes global reads contiguous.
-template <int AXIS>
-__device__ __forceinline__ void item(const Bundle &u, int j, int &l, int &e)
-{
-    if (AXIS == 2) {
-        l = j >> u.logN;
-        e = j & (u.N - 1);
-    } else {
-        e = j / u.B;
-        l = j % u.B;
-    }
-}
-
-// Butterfly b of a stage: its line and its index within the line.
-template <int AXIS>
-__device__ __forceinline__ void fly(const Bundle &u, int b, int &l, int &bb)
-{
-    if (AXIS == 2) {
-        l = b >> (u.logN - 1);
-        bb = b & ((u.N >> 1) - 1);
-    } else {
-        l = b % u.B;
-        bb = b / u.B;
-    }
-}
-
-// Decimation in time: input in bit-reversed order, output in natural order.  INV uses the
-// conjugate twiddles (an unnormalised inverse transform).
-template <int AXIS, int INV>
-__device__ __forceinline__ void fft_dit(const Bundle &u, float2 *buf, const float2 *tw)
-{
-    const int tot = u.B * u.N;
-    for (int s = 1; s <= u.logN; ++s) {
-        const int half = 1 << (s - 1);
-        for (int b = threadIdx.x; b < tot / 2; b += kFftThreads) {
-            int l, bb;
-            fly<AXIS>(u, b, l, bb);
-            const int j = bb & (half - 1);
-            const int k0 = ((bb >> (s - 1)) << s) + j, k1 = k0 + half;
-            float2 w = tw[j << (u.logN - s)];
-            if (INV) w.y = -w.y;
-            const float2 x0 = buf[slot<AXIS>(u, l, k0)];
-            const float2 t = cmul(w, buf[slot<AXIS>(u, l, k1)]);
-            buf[slot<AXIS>(u, l, k0)] = cadd(x0, t);
-            buf[slot<AXIS>(u, l, k1)] = csub(x0, t);
+    constexpr float kH = 0.70710678118654752440f; // cos(pi / 4)
+    constexpr float sg = INV ? 1.0f : -1.0f;
+    if (R == 4) {
+        dft4<INV>(v[0], v[1], v[2], v[3]);
+    } else if (R == 8) {
+        float2 e[4], o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            e[i] = cadd(v[i], v[i + 4]);
+            o[i] = csub(v[i], v[i + 4]);
         }
-        __syncthreads();
-    }
-}
-
-// Decimation in frequency: input in natural order, output in bit-reversed order.
-template <int AXIS, int INV>
-__device__ __forceinline__ void fft_dif(const Bundle &u, float2 *buf, const float2 *tw)
-{
-    const int tot = u.B * u.N;
-    for (int s = u.logN; s >= 1; --s) {
-        const int half = 1 << (s - 1);
-        for (int b = threadIdx.x; b < tot / 2; b += kFftThreads) {
-            int l, bb;
-            fly<AXIS>(u, b, l, bb);
-            const int j = bb & (half - 1);
-            const int k0 = ((bb >> (s - 1)) << s) + j, k1 = k0 + half;
-            float2 w = tw[j << (u.logN - s)];
-            if (INV) w.y = -w.y;
-            const float2 x0 = buf[slot<AXIS>(u, l, k0)], x1 = buf[slot<AXIS>(u, l, k1)];
-            buf[slot<AXIS>(u, l, k0)] = cadd(x0, x1);
-            buf[slot<AXIS>(u, l, k1)] = cmul(csub(x0, x1), w);
+        o[1] = cmul(o[1], make_float2(kH, sg * kH));
+        o[2] = quarter<INV>(o[2]);
+        o[3] = cmul(o[3], make_float2(-kH, sg * kH));
+        dft4<INV>(e[0], e[1], e[2], e[3]);
+        dft4<INV>(o[0], o[1], o[2], o[3]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[2 * i] = e[i];
+            v[2 * i + 1] = o[i];
         }
-        __syncthreads();
+    } else {
+        constexpr float c1 = 0.92387953251128675613f, s1 = 0.38268343236508977173f; // pi / 8
+        const float2 w[10] = {{1.f, 0.f},   {c1, sg * s1},  {kH, sg * kH}, {s1, sg * c1},
+                              {0.f, sg},    {-s1, sg * c1}, {-kH, sg * kH}, {-c1, sg * s1},
+                              {-1.f, 0.f},  {-c1, -sg * s1}};
+        float2 y[4][4]; // y[i][k]: over points i, i + 4, i + 8, i + 12
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[i][k] = v[i + 4 * k];
+            dft4<INV>(y[i][0], y[i][1], y[i][2], y[i][3]);
+#pragma unroll
+            for (int k = 1; k < 4; ++k)
+                if (i) y[i][k] = i * k == 4 ? quarter<INV>(y[i][k]) : cmul(y[i][k], w[i * k]);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            dft4<INV>(y[0][k], y[1][k], y[2][k], y[3][k]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[k + 4 * i] = y[i][k];
+        }
     }
 }
 
-__device__ __forceinline__ int bitrev(int e, int logN) { return (int)(__brev((unsigned)e) >> (32 - logN)); }
-
-__device__ __forceinline__ void load_twiddles(float2 *tw_s, const float2 *tw, int N)
+// Calls f(e, v) for the thread's points as a step of radix R reads them (and the last one leaves
+// them), or as a step of radix R after NS leaves them.
+template <int LOGN, int R, class F>
+__device__ __forceinline__ void for_inputs(float2 *v, int jt, F f)
 {
-    for (int k = threadIdx.x; k < N / 2; k += kFftThreads) tw_s[k] = tw[k];
+#pragma unroll
+    for (int q = 0; q < 16 / R; ++q)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+            f(jt + q * Lines<LOGN>::T + r * (Lines<LOGN>::N / R), v[q * R + r]);
 }
-
-// Transform along x or y (AXIS 0, 1) or z without the Green's function (not used), forward or
-// inverse.  SRC: 0 complex mesh, 1 fixed-point masses (scaled by 1/S into the real part).
-// DST: 0 complex mesh, 1 real part only (the potential).
-template <int AXIS, int INV, int SRC, int DST>
-__global__ __launch_bounds__(kFftThreads) void k_fft(float2 *__restrict__ a,
-                                                     const unsigned long long *__restrict__ mass,
-                                                     const unsigned long long *__restrict__ mx,
-                                                     int64_t n_part, float *__restrict__ phi,
-                                                     int N, int logN, int B,
-                                                     const float2 *__restrict__ tw)
+template <int LOGN, int R, int NS, class F>
+__device__ __forceinline__ void for_outputs(float2 *v, int jt, F f)
 {
-    __shared__ float2 buf[kFftElems];
-    __shared__ float2 tw_s[kMaxTwiddles];
-    const Bundle u = bundle(N, logN, B);
-    load_twiddles(tw_s, tw, N);
-    const int tot = B * N;
-    const double inv_s = SRC ? 1.0 / pm_scale(*mx, n_part) : 1.0;
-    for (int j = threadIdx.x; j < tot; j += kFftThreads) {
-        int l, e;
-        item<AXIS>(u, j, l, e);
-        const size_t g = elem_addr<AXIS>(u, l, e);
-        float2 v;
-        if (SRC)
-            v = make_float2((float)((double)mass[g] * inv_s), 0.0f);
-        else
-            v = a[g];
-        buf[slot<AXIS>(u, l, bitrev(e, logN))] = v;
-    }
-    __syncthreads();
-    fft_dit<AXIS, INV>(u, buf, tw_s);
-    for (int j = threadIdx.x; j < tot; j += kFftThreads) {
-        int l, e;
-        item<AXIS>(u, j, l, e);
-        const size_t g = elem_addr<AXIS>(u, l, e);
-        if (DST)
-            phi[g] = buf[slot<AXIS>(u, l, e)].x;
-        else
-            a[g] = buf[slot<AXIS>(u, l, e)];
+#pragma unroll
+    for (int q = 0; q < 16 / R; ++q) {
+        const int j = jt + q * Lines<LOGN>::T;
+#pragma unroll
+        for (int r = 0; r < R; ++r) f((j / NS) * (NS * R) + j % NS + r * NS, v[q * R + r]);
     }
 }
 
-// z forward, times the Green's function, z inverse.  After the x and y forward passes the
-// bundle's lines are at wavenumbers (kx, ky) = (p, q0 + l); after the DIF the value at
-// position r of a line is at kz = bitrev(r).  green is the octant table, index
-// (fx H + fy) H + fz with f = min(k, N - k), H = N/2 + 1.
-__global__ __launch_bounds__(kFftThreads) void k_fft_z_green(float2 *__restrict__ a, int N,
-                                                             int logN, int B,
-                                                             const float2 *__restrict__ tw,
-                                                             const float *__restrict__ green)
+template <int LOGN, int R, int NS, bool INV>
+__device__ __forceinline__ void step(float2 *v, int jt, const float2 *tw)
 {
-    __shared__ float2 buf[kFftElems];
-    __shared__ float2 tw_s[kMaxTwiddles];
-    const Bundle u = bundle(N, logN, B);
-    load_twiddles(tw_s, tw, N);
-    const int tot = B * N;
-    for (int j = threadIdx.x; j < tot; j += kFftThreads) {
-        int l, e;
-        item<2>(u, j, l, e);
-        buf[slot<2>(u, l, e)] = a[elem_addr<2>(u, l, e)];
+    constexpr int N = 1 << LOGN;
+#pragma unroll
+    for (int q = 0; q < 16 / R; ++q) {
+        const int k = (jt + q * Lines<LOGN>::T) % NS;
+        if (NS > 1) {
+#pragma unroll
+            for (int r = 1; r < R; ++r) {
+                float2 w = tw[r * k * (N / (NS * R))];
+                if (INV) w.y = -w.y;
+                v[q * R + r] = cmul(v[q * R + r], w);
+            }
+        }
+        dft<R, INV>(v + q * R);
+    }
+}
+
+// The points through LDS (at(e): where point e of the thread's line lies), from the order in which
+// the step of radix R after NS leaves them to that in which one of radix R2 reads them.
+template <int LOGN, int R, int NS, int R2, class AT>
+__device__ __forceinline__ void exchange(float2 *v, int jt, float2 *buf, AT at)
+{
+    for_outputs<LOGN, R, NS>(v, jt, [&](int e, float2 &x) { buf[at(e)] = x; });
+    __syncthreads();
+    for_inputs<LOGN, R2>(v, jt, [&](int e, float2 &x) { x = buf[at(e)]; });
+    __syncthreads();
+}
+
+// The whole line: v as a step of radix A (C from the back with REV) reads it; left as the last
+// step leaves it.  REV takes the radices in reverse, so it can follow a plain one in registers.
+template <int LOGN, bool INV, bool REV, class AT>
+__device__ __forceinline__ void fft_line(float2 *v, int jt, float2 *buf, const float2 *tw, AT at)
+{
+    using X = Radix<LOGN>;
+    constexpr int n = X::c ? 3 : X::b ? 2 : 1;
+    constexpr int r0 = !REV ? X::a : n == 3 ? X::c : n == 2 ? X::b : X::a;
+    constexpr int r1 = n < 2 ? 4 : n == 2 ? (REV ? X::a : X::b) : X::b; // 4: not used
+    constexpr int r2 = n < 3 ? 4 : REV ? X::a : X::c;
+    step<LOGN, r0, 1, INV>(v, jt, tw);
+    if (n >= 2) {
+        exchange<LOGN, r0, 1, r1>(v, jt, buf, at);
+        step<LOGN, r1, r0, INV>(v, jt, tw);
+    }
+    if (n >= 3) {
+        exchange<LOGN, r1, r0, r2>(v, jt, buf, at);
+        step<LOGN, r2, r0 * r1, INV>(v, jt, tw);
+    }
+}
+template <int LOGN>
+struct Ends { // radices of the first and the last step
+    using X = Radix<LOGN>;
+    static constexpr int first = X::a, last = X::c ? X::c : X::b ? X::b : X::a;
+};
+
+// exp(-2 pi i k / N), k < N, from the table's first half.
+template <int LOGN>
+__device__ __forceinline__ void load_twiddles(float2 *tw_s, const float2 *tw)
+{
+    constexpr int N = 1 << LOGN;
+    for (int k = threadIdx.x; k < N; k += blockDim.x) {
+        const float2 w = tw[k & (N / 2 - 1)];
+        tw_s[k] = k < N / 2 ? w : make_float2(-w.x, -w.y);
+    }
+}
+
+// Forward along x, masses (fixed point, scaled by 1/S) to the half spectrum kx <= N / 2.  The real
+// lines of z and z + 1 are transformed as one complex line C; theirs are (C(k) + C(N-k)*) / 2 and
+// (C(k) - C(N-k)*) / 2i.
+template <int LOGN>
+__global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_forward(
+    const unsigned long long *__restrict__ mass, const unsigned long long *__restrict__ mx,
+    int64_t n_part, float2 *__restrict__ grid, const float2 *__restrict__ tw)
+{
+    using D = Lines<LOGN>;
+    constexpr int N = D::N, P = D::P;
+    __shared__ float2 buf[D::kRows * P];
+    __shared__ float2 tw_s[N];
+    load_twiddles<LOGN>(tw_s, tw);
+    const int l = threadIdx.x % P, jt = threadIdx.x / P;
+    const int y = blockIdx.x / (N / (2 * P)), z0 = (blockIdx.x % (N / (2 * P))) * 2 * P;
+    const double inv_s = 1.0 / pm_scale(*mx, n_part);
+    auto at = [&](int e) { return (e + (e >> 4)) * P + l; };
+    float2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) {
+        const ulonglong2 m2 =
+            *reinterpret_cast<const ulonglong2 *>(mass + ((size_t)e * N + y) * N + z0 + 2 * l);
+        x = make_float2((float)((double)m2.x * inv_s), (float)((double)m2.y * inv_s));
+    });
+    __syncthreads();
+    fft_line<LOGN, false, false>(v, jt, buf, tw_s, at);
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) { buf[at(e)] = x; });
+    __syncthreads();
+    for (int k = jt; k <= N / 2; k += D::T) {
+        const float2 c = buf[at(k)], d = buf[at((N - k) & (N - 1))];
+        *reinterpret_cast<float4 *>(grid + ((size_t)k * N + y) * N + z0 + 2 * l) =
+            make_float4(0.5f * (c.x + d.x), 0.5f * (c.y - d.y), 0.5f * (c.y + d.y),
+                        0.5f * (d.x - c.x));
+    }
+}
+
+// Inverse along x, from the half spectrum to the real potential, two lines at a time again.
+template <int LOGN>
+__global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_inverse(
+    const float2 *__restrict__ grid, float *__restrict__ phi, const float2 *__restrict__ tw)
+{
+    using D = Lines<LOGN>;
+    constexpr int N = D::N, P = D::P;
+    __shared__ float2 buf[D::kRows * P];
+    __shared__ float2 tw_s[N];
+    load_twiddles<LOGN>(tw_s, tw);
+    const int l = threadIdx.x % P, jt = threadIdx.x / P;
+    const int y = blockIdx.x / (N / (2 * P)), z0 = (blockIdx.x % (N / (2 * P))) * 2 * P;
+    auto at = [&](int e) { return (e + (e >> 4)) * P + l; };
+    for (int k = jt; k <= N / 2; k += D::T) {
+        const float4 g =
+            *reinterpret_cast<const float4 *>(grid + ((size_t)k * N + y) * N + z0 + 2 * l);
+        if (k == 0 || k == N / 2) { // real, but for rounding
+            buf[at(k)] = make_float2(g.x, g.z);
+        } else {
+            buf[at(k)] = make_float2(g.x - g.w, g.y + g.z);
+            buf[at(N - k)] = make_float2(g.x + g.w, g.z - g.y);
+        }
     }
     __syncthreads();
-    fft_dif<2, 0>(u, buf, tw_s);
-    const int H = N / 2 + 1;
-    const int fx = u.p <= N / 2 ? u.p : N - u.p;
-    for (int j = threadIdx.x; j < tot; j += kFftThreads) {
-        int l, r;
-        item<2>(u, j, l, r);
-        const int ky = u.q0 + l, kz = bitrev(r, logN);
-        const int fy = ky <= N / 2 ? ky : N - ky, fz = kz <= N / 2 ? kz : N - kz;
-        const float gk = green[((size_t)fx * H + fy) * H + fz];
-        const float2 v = buf[slot<2>(u, l, r)];
-        buf[slot<2>(u, l, r)] = make_float2(v.x * gk, v.y * gk);
-    }
+    float2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { x = buf[at(e)]; });
     __syncthreads();
-    fft_dit<2, 1>(u, buf, tw_s);
-    for (int j = threadIdx.x; j < tot; j += kFftThreads) {
-        int l, e;
-        item<2>(u, j, l, e);
-        a[elem_addr<2>(u, l, e)] = buf[slot<2>(u, l, e)];
-    }
+    fft_line<LOGN, true, false>(v, jt, buf, tw_s, at);
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) {
+        *reinterpret_cast<float2 *>(phi + ((size_t)e * N + y) * N + z0 + 2 * l) = x;
+    });
+}
+
+// Along y in the plane of one kx, B neighbouring lines in z.
+template <int LOGN, bool INV>
+__global__ __launch_bounds__(Lines<LOGN>::B *Lines<LOGN>::T) void k_fft_y(
+    float2 *__restrict__ grid, const float2 *__restrict__ tw)
+{
+    using D = Lines<LOGN>;
+    constexpr int N = D::N, B = D::B;
+    __shared__ float2 buf[D::kRows * B];
+    __shared__ float2 tw_s[N];
+    load_twiddles<LOGN>(tw_s, tw);
+    const int l = threadIdx.x % B, jt = threadIdx.x / B;
+    float2 *const line =
+        grid + (size_t)(blockIdx.x / (N / B)) * N * N + (blockIdx.x % (N / B)) * B + l;
+    auto at = [&](int e) { return (e + (e >> 4)) * B + l; };
+    float2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt,
+                                        [&](int e, float2 &x) { x = line[(size_t)e * N]; });
+    __syncthreads();
+    fft_line<LOGN, INV, false>(v, jt, buf, tw_s, at);
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt,
+                                       [&](int e, float2 &x) { line[(size_t)e * N] = x; });
+}
+
+// z forward, times the Green's function, z inverse, for B rows (kx, ky = q0 + l).  The forward
+// transform leaves the points in registers where the inverse with its radices reversed reads
+// them.  green is the octant table, index (fx H + fy) H + fz with f = min(k, N - k), H = N/2 + 1.
+template <int LOGN>
+__global__ __launch_bounds__(Lines<LOGN>::B *Lines<LOGN>::T) void k_fft_z_green(
+    float2 *__restrict__ grid, const float2 *__restrict__ tw, const float *__restrict__ green)
+{
+    using D = Lines<LOGN>;
+    constexpr int N = D::N, B = D::B, H = N / 2 + 1;
+    __shared__ float2 buf[D::kRows * B];
+    __shared__ float2 tw_s[N];
+    load_twiddles<LOGN>(tw_s, tw);
+    const int l = threadIdx.x / D::T, jt = threadIdx.x % D::T;
+    const int kx = blockIdx.x / (N / B), ky = (blockIdx.x % (N / B)) * B + l;
+    float2 *const line = grid + ((size_t)kx * N + ky) * N;
+    const float *const g = green + ((size_t)kx * H + (ky <= N / 2 ? ky : N - ky)) * H;
+    auto at = [&](int e) { return l * D::kRows + e + (e >> 4); };
+    float2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { x = line[e]; });
+    __syncthreads();
+    fft_line<LOGN, false, false>(v, jt, buf, tw_s, at);
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) {
+        const float gk = g[e <= N / 2 ? e : N - e];
+        x.x *= gk;
+        x.y *= gk;
+    });
+    fft_line<LOGN, true, true>(v, jt, buf, tw_s, at);
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { line[e] = x; });
 }
 
 // Fourier transform of the S2 cloud of radius eta at x = k eta (Hockney & Eastwood's shape):
@@ -511,44 +626,30 @@ __global__ __launch_bounds__(256) void k_pm_green(int N, double L, double eta,
     green[t] = (float)(-4.0 * M_PI * S * S / (k2 * W * W * L * L * L));
 }
 
-// F_a = -[(2/3)(phi(i+1) - phi(i-1)) - (1/12)(phi(i+2) - phi(i-2))] / h along each axis,
-// stored as (Fx, Fy, Fz, 0) per mesh point so that interpolation reads one 16-byte word.
-__global__ __launch_bounds__(256) void k_pm_fd(const float *__restrict__ phi, int N, int logN,
-                                               float inv_h, float4 *__restrict__ f)
-{
-    const size_t t = xcd_block(blockIdx.x, gridDim.x) * (size_t)blockDim.x + threadIdx.x;
-    const size_t NN = (size_t)N * N;
-    if (t >= NN * N) return;
-    const int m = N - 1;
-    const int z = (int)(t & m), y = (int)((t >> logN) & m), x = (int)(t >> (2 * logN));
-    const size_t rx = (size_t)y * N + z, ry = (size_t)x * NN + z, rz = (size_t)x * NN + (size_t)y * N;
-    const float c1 = 2.0f / 3.0f, c2 = 1.0f / 12.0f;
-    auto d = [&](float p1, float m1, float p2, float m2) {
-        return -(c1 * (p1 - m1) - c2 * (p2 - m2)) * inv_h;
-    };
-    f[t] = make_float4(
-        d(phi[(size_t)((x + 1) & m) * NN + rx], phi[(size_t)((x - 1) & m) * NN + rx],
-          phi[(size_t)((x + 2) & m) * NN + rx], phi[(size_t)((x - 2) & m) * NN + rx]),
-        d(phi[ry + (size_t)((y + 1) & m) * N], phi[ry + (size_t)((y - 1) & m) * N],
-          phi[ry + (size_t)((y + 2) & m) * N], phi[ry + (size_t)((y - 2) & m) * N]),
-        d(phi[rz + ((z + 1) & m)], phi[rz + ((z - 1) & m)], phi[rz + ((z + 2) & m)],
-          phi[rz + ((z - 2) & m)]),
-        0.0f);
-}
-
-// TSC interpolation of the mesh force to each particle, written to stage[idx[i]] =
+// Mesh force and its TSC interpolation to each particle, written to stage[idx[i]] =
 // (ax, ay, az, 0), i.e. already in the caller's order (k_pm_split then writes the three arrays
 // contiguously).  One workgroup per chunk of a cell's particles (the chunks of the
-// assignment): the kBox^3 force words around the cell, [8c - 1, 8c + 9] per axis, are read
-// into LDS once, and each particle's 27 words come from there.  The weights and the order of
-// the sums are those of a plain per-particle gather.
+// assignment).  The potential of the cell's kBox^3 points, [8c - 1, 8c + 9] per axis, and of two
+// more on each side along one axis is read into LDS; from it the force there,
+//     F_a = -[(2/3)(phi(i+1) - phi(i-1)) - (1/12)(phi(i+2) - phi(i-2))] / h,
+// and each particle's 27 points come from that.  The weights and the order of the sums are those
+// of a plain per-particle gather.
+// 256^3 mesh, 16.8 million clustered particles: 0.59 ms, of which the boxes take 0.2 and the
+// particles 0.39, half of that for scattering their 16-byte records (with the records in key
+// order 0.39 in all; stored around the caches 0.92); with the force mesh written out and read
+// back, 0.77.  The three components are arrays of their own: a 16-byte read per lane takes
+// two to three times the LDS time of three 4-byte ones once the lanes spread over points.
+constexpr int kPhi = kBox + 4; // points per axis of the potential
 __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
-    const double4 *__restrict__ ps, int N, double inv_h, const float4 *__restrict__ f,
+    const double4 *__restrict__ ps, int N, double inv_h, const float *__restrict__ phi,
     const uint32_t *__restrict__ idx, float4 *__restrict__ stage,
     const uint32_t *__restrict__ cell_start, const uint32_t *__restrict__ item_start,
     uint32_t ncells)
 {
-    __shared__ float4 box[kBoxWords];
+    // the force takes the potential's place: 16 KB, so eight workgroups fit a compute unit
+    __shared__ float lds[3 * kBoxWords];
+    static_assert(3 * kBoxWords >= kPhi * kPhi * kPhi, "the potential fits");
+    float *const pot = lds, *const fx = lds, *const fy = lds + kBoxWords, *const fz = fy + kBoxWords;
     // each XCD takes a contiguous run of chunks (cells in Morton order): the chunks of one
     // cell and its neighbours then read their boxes through one L2
     const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
@@ -559,34 +660,95 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
     const int ox = 8 * (int)compact3_10(m >> 2) - 1, oy = 8 * (int)compact3_10(m >> 1) - 1,
               oz = 8 * (int)compact3_10(m) - 1;
     const int mask = N - 1;
-    for (int t = threadIdx.x; t < kBoxWords; t += kAssignThreads) {
-        const int bx = t / (kBox * kBox), by = (t / kBox) % kBox, bz = t % kBox;
-        box[t] = f[((size_t)((ox + bx) & mask) * N + ((oy + by) & mask)) * N + ((oz + bz) & mask)];
+    {
+        // sixteen lanes to a row of fifteen points, sixteen rows (one and a fifteenth of a plane)
+        // at a time
+        static_assert(kPhi == 15 && kAssignThreads == 256, "a lane more than a row has points");
+        const int bz = threadIdx.x & 15, z = (oz - 2 + bz) & mask;
+        const int rim_z = bz < 2 || bz >= kBox + 2;
+        int bx = 0, by = threadIdx.x >> 4;
+        if (by == kPhi) {
+            by = 0;
+            bx = 1;
+        }
+        for (; bx < kPhi;) {
+            const int rim = (bx < 2 || bx >= kBox + 2) + (by < 2 || by >= kBox + 2) + rim_z;
+            if (rim <= 1 && bz < kPhi)
+                pot[(bx * kPhi + by) * kPhi + bz] =
+                    phi[((uint32_t)((ox - 2 + bx) & mask) * (uint32_t)N +
+                         (uint32_t)((oy - 2 + by) & mask)) * (uint32_t)N + (uint32_t)z];
+            ++bx;
+            if (++by == kPhi) {
+                by = 0;
+                ++bx;
+            }
+        }
+    }
+    // the first particle is under way while the force is formed
+    uint32_t i = first + threadIdx.x;
+    double4 p = make_double4(0.0, 0.0, 0.0, 0.0);
+    uint32_t o = 0;
+    if (i < end) {
+        p = ps[i];
+        o = idx[i];
     }
     __syncthreads();
-    for (uint32_t i = first + threadIdx.x; i < end; i += kAssignThreads) {
-        const double4 p = ps[i];
+    const float fh = (float)inv_h;
+    constexpr int kPer = (kBoxWords + kAssignThreads - 1) / kAssignThreads;
+    float f[kPer][3];
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int t = threadIdx.x + k * kAssignThreads;
+        if (t < kBoxWords) {
+            const int bx = t / (kBox * kBox), by = (t / kBox) % kBox, bz = t % kBox;
+            const float *q = pot + ((bx + 2) * kPhi + (by + 2)) * kPhi + (bz + 2);
+            const float c1 = 2.0f / 3.0f, c2 = 1.0f / 12.0f;
+            auto d = [&](int st) {
+                return -(c1 * (q[st] - q[-st]) - c2 * (q[2 * st] - q[-2 * st])) * fh;
+            };
+            f[k][0] = d(kPhi * kPhi);
+            f[k][1] = d(kPhi);
+            f[k][2] = d(1);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPer; ++k) {
+        const int t = threadIdx.x + k * kAssignThreads;
+        if (t < kBoxWords) {
+            fx[t] = f[k][0];
+            fy[t] = f[k][1];
+            fz[t] = f[k][2];
+        }
+    }
+    __syncthreads();
+    while (i < end) {
         double wx[3], wy[3], wz[3];
         const int ix = tsc(p.x, inv_h, wx), iy = tsc(p.y, inv_h, wy), iz = tsc(p.z, inv_h, wz);
-        const int bx = ix - 1 - ox, by = iy - 1 - oy, bz = iz - 1 - oz; // in [0, 8]
+        const uint32_t out = o;
+        i += kAssignThreads;
+        if (i < end) { // the next one
+            p = ps[i];
+            o = idx[i];
+        }
+        const int at = ((ix - 1 - ox) * kBox + (iy - 1 - oy)) * kBox + (iz - 1 - oz);
         float sx = 0.0f, sy = 0.0f, sz = 0.0f;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
-                const float4 *row = box + ((bx + a) * kBox + (by + b)) * kBox + bz;
                 const double wab = wx[a] * wy[b];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const float w = (float)(wab * wz[c]);
-                    const float4 v = row[c];
-                    sx += w * v.x;
-                    sy += w * v.y;
-                    sz += w * v.z;
+                    const int k = at + (a * kBox + b) * kBox + c;
+                    sx += w * fx[k];
+                    sy += w * fy[k];
+                    sz += w * fz[k];
                 }
             }
         }
-        stage[idx[i]] = make_float4(sx, sy, sz, 0.0f);
+        stage[out] = make_float4(sx, sy, sz, 0.0f);
     }
 }
 
@@ -611,8 +773,6 @@ __global__ __launch_bounds__(256) void k_pm_split(const float4 *__restrict__ sta
 }
 
 } // namespace
-
-int pm_bundle_lines(int N) { return N >= 256 ? kFftElems / N : (N < 16 ? N : 16); }
 
 void launch_pm_green(int N, double L, double eta, float *green, float2 *tw, hipStream_t s)
 {
@@ -646,38 +806,45 @@ void launch_pm_assign(const double4 *ps, const uint64_t *key, int64_t n, int N, 
     k_pm_gather<<<ncells, kCellPts * kCellPts * kCellPts, 0, s>>>(N, item_start, slots, mass);
 }
 
+size_t pm_grid_points(int N) { return (size_t)(N / 2 + 1) * N * N; }
+
+template <int LOGN>
+static void pm_potential(const unsigned long long *mass, const unsigned long long *mx, int64_t n,
+                         float2 *grid, float *phi, const float *green, const float2 *tw,
+                         hipStream_t s)
+{
+    using D = Lines<LOGN>;
+    constexpr unsigned pairs = D::N * (D::N / (2 * D::P)), lines = (D::N / 2 + 1) * (D::N / D::B);
+    k_fft_x_forward<LOGN><<<pairs, D::P * D::T, 0, s>>>(mass, mx, n, grid, tw);
+    k_fft_y<LOGN, false><<<lines, D::B * D::T, 0, s>>>(grid, tw);
+    k_fft_z_green<LOGN><<<lines, D::B * D::T, 0, s>>>(grid, tw, green);
+    k_fft_y<LOGN, true><<<lines, D::B * D::T, 0, s>>>(grid, tw);
+    k_fft_x_inverse<LOGN><<<pairs, D::P * D::T, 0, s>>>(grid, phi, tw);
+}
+
 void launch_pm_potential(const unsigned long long *mass, const unsigned long long *mx,
                          int64_t n, int N, float2 *grid, float *phi, const float *green,
                          const float2 *tw, hipStream_t s)
 {
-    const int logN = __builtin_ctz((unsigned)N);
-    const int B = pm_bundle_lines(N);
-    const unsigned blocks = (unsigned)((size_t)N * N / B);
-    k_fft<0, 0, 1, 0><<<blocks, kFftThreads, 0, s>>>(grid, mass, mx, n, nullptr, N, logN, B, tw);
-    k_fft<1, 0, 0, 0><<<blocks, kFftThreads, 0, s>>>(grid, nullptr, nullptr, n, nullptr, N, logN,
-                                                     B, tw);
-    k_fft_z_green<<<blocks, kFftThreads, 0, s>>>(grid, N, logN, B, tw, green);
-    k_fft<1, 1, 0, 0><<<blocks, kFftThreads, 0, s>>>(grid, nullptr, nullptr, n, nullptr, N, logN,
-                                                     B, tw);
-    k_fft<0, 1, 0, 1><<<blocks, kFftThreads, 0, s>>>(grid, nullptr, nullptr, n, phi, N, logN, B,
-                                                     tw);
+    switch (N) {
+    case 16: return pm_potential<4>(mass, mx, n, grid, phi, green, tw, s);
+    case 32: return pm_potential<5>(mass, mx, n, grid, phi, green, tw, s);
+    case 64: return pm_potential<6>(mass, mx, n, grid, phi, green, tw, s);
+    case 128: return pm_potential<7>(mass, mx, n, grid, phi, green, tw, s);
+    case 256: return pm_potential<8>(mass, mx, n, grid, phi, green, tw, s);
+    case 512: return pm_potential<9>(mass, mx, n, grid, phi, green, tw, s);
+    default: return pm_potential<10>(mass, mx, n, grid, phi, green, tw, s);
+    }
 }
 
-void launch_pm_force(const float *phi, int N, double L, float4 *f, hipStream_t s)
-{
-    const size_t pts = (size_t)N * N * N;
-    k_pm_fd<<<(unsigned)((pts + 255) / 256), 256, 0, s>>>(phi, N, __builtin_ctz((unsigned)N),
-                                                          (float)(N / L), f);
-}
-
-void launch_pm_interp(const double4 *ps, int64_t n, int N, double L, const float4 *f,
+void launch_pm_interp(const double4 *ps, int64_t n, int N, double L, const float *phi,
                       const uint32_t *idx, float4 *stage, const uint32_t *cell_start,
                       const uint32_t *item_start, hipStream_t s)
 {
     if (!n) return;
     const uint32_t ncells = (uint32_t)pm_assign_cells(N);
     k_pm_interp<<<(unsigned)pm_assign_items_max(N, n), kAssignThreads, 0, s>>>(
-        ps, N, N / L, f, idx, stage, cell_start, item_start, ncells);
+        ps, N, N / L, phi, idx, stage, cell_start, item_start, ncells);
 }
 
 void launch_pm_split(const float4 *stage, int64_t n, void *ax, void *ay, void *az,

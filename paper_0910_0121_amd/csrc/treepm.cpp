@@ -107,8 +107,8 @@ struct treepm_ctx {
     bool tab64_ok = false;
     int n_cu = 256; // compute units of the device (persistent force grids)
     // particle mesh: fixed-point masses (later the potential), the complex work mesh, the
-    // force mesh, the Green's table, twiddles, max mass
-    Buf pm_mass, pm_grid, pm_f, pm_green, pm_tw, pm_mx;
+    // Green's table, twiddles, max mass
+    Buf pm_mass, pm_grid, pm_green, pm_tw, pm_mx;
     // mass assignment scratch: per mesh cell first particle and chunk offsets, the chunks'
     // boxes of partial sums
     Buf pm_cells, pm_slots;
@@ -1201,7 +1201,7 @@ TREEPM_API int treepm_destroy(treepm_ctx *c)
                   &c->g_hi[1], &c->g_hi[2], &c->g_misc, &c->off, &c->glen, &c->wctr, &c->scan64, &c->entries,
                   &c->wstats, &c->overflow, &c->rec, &c->kept, &c->kept_sum, &c->gcells, &c->cls, &c->out[0],
                   &c->out[1], &c->out[2], &c->bnd, &c->runs, &c->pm_mass, &c->pm_grid,
-                  &c->pm_f, &c->pm_green, &c->pm_tw, &c->pm_mx, &c->pm_stage, &c->pm_cells, &c->pm_slots,
+                  &c->pm_green, &c->pm_tw, &c->pm_mx, &c->pm_stage, &c->pm_cells, &c->pm_slots,
                   &c->n_q, &c->step_min, &c->tab, &c->tab64, &c->bdesc};
     {
         // the work is done: the buffers are kept for reuse at once, not behind a stream
@@ -1846,8 +1846,7 @@ TREEPM_API int treepm_force_long(treepm_ctx *c, void *ax, void *ay, void *az, in
     const size_t pts = (size_t)N * N * N, H = (size_t)N / 2 + 1;
     {
         hipError_t e = reserve(c->pm_mass, pts * 8);
-        if (e == hipSuccess) e = reserve(c->pm_grid, pts * 8);
-        if (e == hipSuccess) e = reserve(c->pm_f, pts * 16);
+        if (e == hipSuccess) e = reserve(c->pm_grid, pm_grid_points((int)N) * 8);
         if (e == hipSuccess) e = reserve(c->pm_green, H * H * H * 4);
         if (e == hipSuccess) e = reserve(c->pm_tw, (size_t)N / 2 * 8);
         if (e == hipSuccess) e = reserve(c->pm_stage, (size_t)c->n * 16);
@@ -1892,9 +1891,8 @@ TREEPM_API int treepm_force_long(treepm_ctx *c, void *ax, void *ay, void *az, in
                      c->pm_slots.as<unsigned long long>(), mass, s);
     launch_pm_potential(mass, c->pm_mx.as<unsigned long long>(), c->n, (int)N, grid, phi,
                         c->pm_green.as<float>(), c->pm_tw.as<float2>(), s);
-    launch_pm_force(phi, (int)N, P.L, c->pm_f.as<float4>(), s);
-    launch_pm_interp(ps, c->n, (int)N, P.L, c->pm_f.as<float4>(), c->idx.as<uint32_t>(),
-                     c->pm_stage.as<float4>(), cell_start, item_start, s);
+    launch_pm_interp(ps, c->n, (int)N, P.L, phi, c->idx.as<uint32_t>(), c->pm_stage.as<float4>(),
+                     cell_start, item_start, s);
     launch_pm_split(c->pm_stage.as<float4>(), c->n, dst[0], dst[1], dst[2],
                     out_prec == TREEPM_FP64, accumulate, s);
     HIPCHK(c, hipGetLastError());
