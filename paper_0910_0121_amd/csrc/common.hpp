@@ -175,14 +175,21 @@ struct WalkParams {
     uint32_t open;
 };
 // Group g's interaction list is entries[off[g] .. off[g] + len[g]).
+// Lists in slots: list g at entry g size; one longer than that in room of its length from
+// [spill_at, spill_end), handed out through *next, which starts at zero.  A list that fits
+// neither sets bit 4 of the overflow flags.  size 0: no slots.
+struct Slots {
+    uint64_t size, spill_at, spill_end;
+    unsigned long long *next;
+};
 // Two passes: the count pass writes each list length to counts[g]; after the caller's prefix
 // sum (counts -> off) the emit pass writes the lists, len and gcells (cell entries), and sets bit
-// 4 of *overflow if they need more than entries_cap entries.
+// 4 of *overflow if they need more than entries_cap entries.  With slots the emit pass runs alone.
 void launch_walk_count(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
                        uint64_t *counts, unsigned *overflow, hipStream_t s);
 void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
-                      const uint64_t *off, uint32_t *len, uint32_t *entries,
-                      uint64_t entries_cap, unsigned *overflow, uint32_t *gcells, hipStream_t s);
+                      uint64_t *off, uint32_t *len, uint32_t *entries, uint64_t entries_cap,
+                      const Slots &slots, unsigned *overflow, uint32_t *gcells, hipStream_t s);
 // One pass: n_waves waves write the lists into chunks of `chunk` entries taken from the
 // pool entries[0, pool_cap); a group is walked into the wave's current chunk if at least
 // `reserve` entries are left there, else (or if it did not fit) into a fresh chunk.  Sets bit 4 of *overflow if a list or the pool ran out of room
@@ -212,6 +219,7 @@ struct WalkBox {
     unsigned *overflow;
     uint32_t g0, n_groups;
     uint64_t entries_cap;          // two passes: room at entries
+    Slots slots;                   // or the room of each list, and no count pass
     unsigned long long *stats;     // see launch_walk_stats
     uint32_t *cls;                 // queue buffer of the force
     uint32_t *mailbox;             // launch_walk_results_one: where the results go, and

@@ -21,7 +21,7 @@
 //
 // A list entry is a node index with kCellTag set (the node's mass at its centre of mass) or
 // a particle's position in key order.  Group g's list is entries[off[g] .. off[g] + len[g]).
-// Two ways to lay the lists out:
+// Three ways to lay the lists out:
 //   * two passes: the count pass records each group's list length; after a prefix sum the
 //     emit pass writes the lists back to back.  The traversal order depends only on the tree,
 //     so both passes visit the same nodes in the same order.
@@ -30,8 +30,12 @@
 //     one atomic per chunk (a list that does not fit the rest of a chunk is walked again into
 //     a fresh one).  Pool and chunk sizes come from the caller (from an earlier walk); if a
 //     list or the pool runs out of room, the pass reports it and the caller falls back to
-//     two passes, so the result never depends on those sizes.
-// Both layouts also run over the groups of several boxes in one launch (k_walk_multi,
+//     two passes, so the result never depends on those sizes;
+//   * slots: a wave per group writes its list to a slot of its own, sized from an earlier walk's
+//     longest list (or, for many groups, its mean list, with room elsewhere for longer ones),
+//     with the same fallback.  It halves the walk of boxes too small for the pool: 700,001
+//     clustered particles 0.23 -> 0.12 ms.
+// All layouts also run over the groups of several boxes in one launch (k_walk_multi,
 // k_walk_pool_multi: per-box descriptors in device memory, each box's own lists and flags).
 #include "common.hpp"
 
@@ -257,33 +261,59 @@ __device__ __forceinline__ uint64_t walk_group(const WalkNode *__restrict__ wn,
     return written;
 }
 
-// Two passes, one wave per group.  Count: cnt[g] = list length.  Emit: writes the list at
-// entries + off[g], and len[g], gcells[g]; a list that ends past entries_cap sets bit 4 of
-// *overflow (the caller launches the emit pass on the room an earlier walk left, without
-// waiting for the lengths).
+// Room for a list of w entries, longer than its slot (by the whole wave): at, room; false if there
+// is none.
+__device__ __forceinline__ bool spill_room(const Slots &slots, uint64_t w, uint64_t &at,
+                                           uint64_t &room)
+{
+    if (!slots.size || slots.spill_at == slots.spill_end) return false;
+    w = (w + 15) & ~15ull;
+    unsigned long long v = 0;
+    if (threadIdx.x == 0) v = atomicAdd(slots.next, (unsigned long long)w);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
+    const uint64_t a = slots.spill_at + (((uint64_t)hi << 32) | lo);
+    if (a + w > slots.spill_end) return false;
+    at = a;
+    room = w;
+    return true;
+}
+
+// One wave per group.  Count: cnt[g] = list length.  Emit: writes the list at entries + off[g],
+// and len[g], gcells[g]; a list that ends past entries_cap sets bit 4 of *overflow (the caller
+// launches the emit pass on the room an earlier walk left, without waiting for the lengths).
+// With slots the emit pass needs no count before it (off[g] is written); a list longer than its
+// slot is walked again into room of its own.
 template <int EMIT, int OPEN>
 __global__ __launch_bounds__(64) void k_walk(const WalkNode *__restrict__ wn, GroupArrays gr,
                                              uint32_t n_groups, WalkParams wp,
                                              uint64_t *__restrict__ cnt_off,
                                              uint32_t *__restrict__ len,
                                              uint32_t *__restrict__ entries,
-                                             uint64_t entries_cap, unsigned *overflow,
-                                             uint32_t *__restrict__ gcells)
+                                             uint64_t entries_cap, Slots slots,
+                                             unsigned *overflow, uint32_t *__restrict__ gcells)
 {
     __shared__ uint32_t stk[kStackCap];
     __shared__ uint32_t s_mark[64];
     const uint32_t g = xcd_block(blockIdx.x, gridDim.x);
     if (g >= n_groups) return;
     uint64_t ncell = 0;
-    const uint64_t at = EMIT ? min(cnt_off[g], entries_cap) : 0, room = entries_cap - at;
-    const uint64_t w = walk_group<EMIT, OPEN>(wn, gr, g, wp, stk, s_mark,
+    uint64_t at = 0, room = 0;
+    if (EMIT) {
+        at = slots.size ? g * slots.size : min(cnt_off[g], entries_cap);
+        room = slots.size ? slots.size : entries_cap - at;
+    }
+    uint64_t w = walk_group<EMIT, OPEN>(wn, gr, g, wp, stk, s_mark,
                                               EMIT ? entries + at : nullptr, room, overflow,
                                               &ncell);
+    if (EMIT && w > room && spill_room(slots, w, at, room))
+        w = walk_group<1, OPEN>(wn, gr, g, wp, stk, s_mark, entries + at, room, overflow, &ncell);
     if (threadIdx.x == 0) {
         if (!EMIT) {
             cnt_off[g] = w;
         } else {
             if (w > room) atomicOr(overflow, 4u);
+            if (slots.size) cnt_off[g] = at;
             len[g] = (uint32_t)w;
             gcells[g] = (uint32_t)ncell;
         }
@@ -396,14 +426,21 @@ __global__ __launch_bounds__(64) void k_walk_multi(const WalkBox *__restrict__ b
     const WalkBox &B = bx[box_of(bx, nb, t)];
     const uint32_t g = t - B.g0;
     uint64_t ncell = 0;
-    const uint64_t at = EMIT ? min(B.off[g], B.entries_cap) : 0, room = B.entries_cap - at;
-    const uint64_t w =
+    uint64_t at = 0, room = 0;
+    if (EMIT) {
+        at = B.slots.size ? g * B.slots.size : min(B.off[g], B.entries_cap);
+        room = B.slots.size ? B.slots.size : B.entries_cap - at;
+    }
+    uint64_t w =
         walk_box_group<EMIT>(B, g, stk, s_mark, EMIT ? B.entries + at : nullptr, room, &ncell);
+    if (EMIT && w > room && spill_room(B.slots, w, at, room))
+        w = walk_box_group<1>(B, g, stk, s_mark, B.entries + at, room, &ncell);
     if (threadIdx.x == 0) {
         if (!EMIT) {
             B.off[g] = w;
         } else {
             if (w > room) atomicOr(B.overflow, 4u);
+            if (B.slots.size) B.off[g] = at;
             B.len[g] = (uint32_t)w;
             B.gcells[g] = (uint32_t)ncell;
         }
@@ -532,6 +569,7 @@ __device__ __forceinline__ void walk_init(const WalkBox &B)
     if (threadIdx.x < 4) B.stats[threadIdx.x] = 0ull;
     if (threadIdx.x == 4) *B.overflow = 0u;
     if (threadIdx.x == 5) B.off[B.n_groups] = 0ull;
+    if (threadIdx.x == 6 && B.slots.size) *B.slots.next = 0ull;
 }
 __global__ __launch_bounds__(512) void k_walk_init(WalkBox box) { walk_init(box); }
 __global__ __launch_bounds__(512) void k_walk_init_multi(const WalkBox *__restrict__ bx)
@@ -589,23 +627,23 @@ void launch_walk_count(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, Wa
     if (!n_groups) return;
     if (wp.open)
         k_walk<0, 1><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, counts, nullptr, nullptr,
-                                            0, overflow, nullptr);
+                                            0, Slots{}, overflow, nullptr);
     else
         k_walk<0, 0><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, counts, nullptr, nullptr,
-                                            0, overflow, nullptr);
+                                            0, Slots{}, overflow, nullptr);
 }
 
 void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
-                      const uint64_t *off, uint32_t *len, uint32_t *entries,
-                      uint64_t entries_cap, unsigned *overflow, uint32_t *gcells, hipStream_t s)
+                      uint64_t *off, uint32_t *len, uint32_t *entries, uint64_t entries_cap,
+                      const Slots &slots, unsigned *overflow, uint32_t *gcells, hipStream_t s)
 {
     if (!n_groups) return;
     if (wp.open)
-        k_walk<1, 1><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, const_cast<uint64_t *>(off),
-                                            len, entries, entries_cap, overflow, gcells);
+        k_walk<1, 1><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, off, len, entries,
+                                            entries_cap, slots, overflow, gcells);
     else
-        k_walk<1, 0><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, const_cast<uint64_t *>(off),
-                                            len, entries, entries_cap, overflow, gcells);
+        k_walk<1, 0><<<n_groups, 64, 0, s>>>(wn, gr, n_groups, wp, off, len, entries,
+                                            entries_cap, slots, overflow, gcells);
 }
 
 void launch_walk_pool(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,

@@ -820,11 +820,14 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
 // groups in flight keep more of their tree nodes in L2), about 16 groups each at least.
 uint32_t pool_waves(uint32_t G) { return std::max(1u, std::min(6144u, (G + 15) / 16)); }
 
-// Below this many groups the one-pass walk has fewer waves than fill the device, and the two
-// passes (a wave per group each) are faster: measured on clustered boxes with n_crit 256,
-// 0.25 against 0.41 ms at 6,800 groups, 0.87 against 0.96 at 60,000, equal at 90,000, and
-// 2.34 against 1.87 ms at 153,000.
+// Below this many groups the walk into a pool has fewer waves than fill the device: clustered
+// boxes with n_crit 256 took 0.41 ms at 6,800 groups and 0.96 at 60,000, where a count and an emit
+// pass with a wave per group took 0.25 and 0.87 (and the emit pass alone, into slots, takes half
+// of that); at 153,000 groups 1.87 against 2.34 ms for the two passes.
 constexpr uint32_t kOnePassMinGroups = 16 * 6144;
+
+// Room that slots of twice the longest list may take.
+constexpr uint64_t kSlotBytes = 1ull << 30;
 
 // One box's walk in parts, shared by treepm_walk and the shared launches of several boxes.
 struct BoxWalk {
@@ -833,6 +836,7 @@ struct BoxWalk {
     bool pooled = false; // one pass into a pool sized from the box's last walk
     uint64_t pool = 0, chunk = 0, reserve_len = 0;
     uint32_t waves = 0;
+    Slots slots{}; // lists in slots
 };
 
 // Buffers, cleared flags and statistics, the opening parameters, and the one-pass layout
@@ -866,6 +870,7 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
                        (uint32_t)c->n_nodes,
                        open ? 1u : 0u};
     bw.pooled = false;
+    bw.slots = Slots{};
     const bool one_pass = c->walk_passes == TREEPM_WALK_ONE_PASS ||
                           (c->walk_passes == TREEPM_WALK_AUTO && G >= kOnePassMinGroups);
     if (c->walk_hint && G && one_pass) {
@@ -878,6 +883,28 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
         bw.reserve_len = std::min<uint64_t>(std::max<uint64_t>(2 * mean, 64), bw.chunk / 4);
         bw.pool = c->walk_hint + c->walk_hint / 4 + (uint64_t)bw.waves * bw.chunk;
         bw.pooled = reserve(c->entries, bw.pool * 4) == hipSuccess;
+    } else if (c->walk_hint && G && c->walk_passes == TREEPM_WALK_AUTO) {
+        // Slots of twice the last walk's longest list if they fit kSlotBytes; else of four times
+        // its mean list, and for longer ones, which are walked twice, room of half of the
+        // packed lists.  Somewhat less is taken as it is: lists that grow a little from call to
+        // call do not mean an allocation each time.
+        Slots sl{};
+        const uint64_t have = c->entries.bytes / 4, longest = c->walk_hint_max;
+        uint64_t need = 0;
+        sl.size = (2 * longest + 63) / 64 * 64;
+        if (sl.size * G * 4 <= kSlotBytes) {
+            const uint64_t fit = have / G / 64 * 64;
+            if (fit >= longest + longest / 4 + 16) sl.size = std::min(sl.size, fit);
+        } else {
+            sl.size = (4 * c->walk_hint / std::max<uint32_t>(c->walk_hint_groups, 1) + 63) / 64 * 64;
+            need = c->walk_hint / 2 + 16 * longest;
+            if (have >= sl.size * G + need / 2) need = std::min(need, have - sl.size * G);
+        }
+        sl.spill_at = sl.size * G;
+        sl.spill_end = sl.spill_at + need;
+        sl.next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() +
+                                                         kXcds * kQueueStride);
+        if (reserve(c->entries, sl.spill_end * 4) == hipSuccess) bw.slots = sl;
     }
     return TREEPM_OK;
 }
@@ -901,6 +928,7 @@ WalkBox walk_box(treepm_ctx *c, const BoxWalk &bw, uint32_t g0)
     w.g0 = g0;
     w.n_groups = bw.G;
     w.entries_cap = c->entries.bytes / 4;
+    w.slots = bw.slots;
     w.stats = c->wstats.as<unsigned long long>();
     w.cls = c->cls.as<uint32_t>();
     return w;
@@ -930,7 +958,7 @@ int walk_two_pass(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, bool ahead)
         if (e != hipSuccess) return hip_fail(c, e, "interaction lists");
     }
     launch_walk_emit(wn, gr, G, bw.wp, off, c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
-                     c->entries.bytes / 4, ovf, c->gcells.as<uint32_t>(), s);
+                     c->entries.bytes / 4, Slots{}, ovf, c->gcells.as<uint32_t>(), s);
     return TREEPM_OK;
 }
 
@@ -980,7 +1008,7 @@ int wait_walk_results(treepm_ctx *c, hipStream_t s, WalkResults &wr)
     return TREEPM_OK;
 }
 
-// Until the results show complete lists: a pool that was too small (bit 4) means two
+// Until the results show complete lists: a pool or a slot that was too small (bit 4) means two
 // passes, then the statistics again.
 int settle_walk(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr)
 {
@@ -1010,6 +1038,11 @@ int do_walk(treepm_ctx *c, hipStream_t s)
         launch_walk_pool(c->n_walk.as<WalkNode>(), groups_view(c), bw.G, bw.wp, bw.waves, bw.pool,
                          bw.chunk, bw.reserve_len, c->wctr.as<uint32_t>(), c->off.as<uint64_t>(),
                          c->glen.as<uint32_t>(), c->entries.as<uint32_t>(),
+                         c->overflow.as<unsigned>(), c->gcells.as<uint32_t>(), s);
+    else if (bw.slots.size)
+        launch_walk_emit(c->n_walk.as<WalkNode>(), groups_view(c), bw.G, bw.wp,
+                         c->off.as<uint64_t>(), c->glen.as<uint32_t>(),
+                         c->entries.as<uint32_t>(), c->entries.bytes / 4, bw.slots,
                          c->overflow.as<unsigned>(), c->gcells.as<uint32_t>(), s);
     else if ((rc = walk_two_pass(c, s, bw, true)))
         return rc;
@@ -1540,9 +1573,9 @@ struct BatchScope {
     }
 };
 
-// The leader's descriptor buffer: four runs of walk descriptors, the force descriptors, the
+// The leader's descriptor buffer: five runs of walk descriptors, the force descriptors, the
 // walk's counters.
-constexpr size_t kBatchForceAt = 4 * (size_t)kMaxBatch * sizeof(WalkBox);
+constexpr size_t kBatchForceAt = 5 * (size_t)kMaxBatch * sizeof(WalkBox);
 
 // The box descriptors of one shared launch, copied to the leader's device buffer at `at`
 // (bytes); the host copy stays alive until the batch has synchronised.
@@ -1556,9 +1589,9 @@ int upload(treepm_ctx *lead, hipStream_t s, const std::vector<T> &v, size_t at, 
 }
 
 // The walk of boxes cs[0 .. nb) with shared launches: the boxes whose last walk sizes a pool
-// in one pass together, the others in two passes together (one host wait for all their
-// list lengths); then every box's statistics and classes, and one wait for all of them.  A
-// box whose pool was too small is walked again alone.  Each box ends exactly as treepm_walk
+// in one pass together, those whose last walk sizes slots likewise, the others in two passes
+// together (one host wait for all their list lengths); then every box's statistics and classes, and one wait for all of them.  A
+// box whose pool or slots were too small is walked again alone.  Each box ends exactly as treepm_walk
 // would leave it.
 int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
 {
@@ -1569,10 +1602,10 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
         Bind bind(cs[b], s);
         if ((rc = prepare_walk(cs[b], s, bw[b]))) return rc;
     }
-    std::vector<WalkBox> two, pool, all, small;
+    std::vector<WalkBox> two, slots, pool, all, small;
     std::vector<int> two_ix;
     std::vector<WalkResults> wr(nb);
-    uint32_t two_total = 0, pool_total = 0, pool_waves_sum = 0;
+    uint32_t two_total = 0, slot_total = 0, pool_total = 0, pool_waves_sum = 0;
     for (int b = 0; b < nb; ++b) {
         all.push_back(walk_box(cs[b], bw[b], 0));
         if (results_by_one(cs[b])) {
@@ -1585,6 +1618,9 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
             pool.push_back(walk_box(cs[b], bw[b], pool_total));
             pool_total += bw[b].G;
             pool_waves_sum += bw[b].waves;
+        } else if (bw[b].slots.size) {
+            slots.push_back(walk_box(cs[b], bw[b], slot_total));
+            slot_total += bw[b].G;
         } else {
             two.push_back(walk_box(cs[b], bw[b], two_total));
             two_ix.push_back(b);
@@ -1598,7 +1634,7 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
         hipError_t e = reserve(lead->bdesc, bytes);
         if (e != hipSuccess) return hip_fail(lead, e, "batch descriptors");
     }
-    // descriptor runs: all boxes, two-pass boxes, pooled ones, those of few groups
+    // descriptor runs: all boxes, two-pass boxes, pooled ones, those of few groups, those with slots
     constexpr size_t kRun = (size_t)kMaxBatch * sizeof(WalkBox);
     const size_t at_ctr = kBatchForceAt + (size_t)kMaxBatch * sizeof(ForceBox);
     uint32_t *counters = reinterpret_cast<uint32_t *>(static_cast<char *>(lead->bdesc.p) + at_ctr);
@@ -1650,6 +1686,10 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
         }
         if (fresh && (rc = upload(lead, s, two, kRun, &dev))) return rc;
         launch_walk_emit_multi(dev, (int)two.size(), two_total, s);
+    }
+    if (!slots.empty()) {
+        if ((rc = upload(lead, s, slots, 4 * kRun, &dev))) return rc;
+        launch_walk_emit_multi(dev, (int)slots.size(), slot_total, s);
     }
     if (!pool.empty()) {
         for (const WalkBox &w : pool) fill_u64(reinterpret_cast<uint64_t *>(w.pool_next), 1, 0ull, s);
