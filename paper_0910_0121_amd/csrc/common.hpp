@@ -106,7 +106,7 @@ void radix_sort(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt, uint
 // cell grows about as the square of its side: 43 particles at level 13.3 of the 256^3 box, and
 // so a few hundred at most at these limits, below kLongRun.
 int sort_run_bits(int64_t n);
-constexpr uint32_t kShortRun = 8; // the register sorting network in k_fix_runs has 8 inputs
+constexpr uint32_t kShortRun = 64; // sorted within a tile of k_fix_runs
 constexpr uint32_t kLongRun = 2048;
 bool radix_sort_high(int64_t n, int run_bits, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
                      uint32_t *idx_alt, uint32_t *hist, uint32_t *scan_tmp, uint2 *long_runs,
