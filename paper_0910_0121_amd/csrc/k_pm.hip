@@ -78,8 +78,13 @@ __device__ __forceinline__ double pm_scale(unsigned long long mmax_bits, int64_t
 constexpr int kCellPts = 8;
 constexpr int kBox = kCellPts + 3;             // 11 points per axis
 constexpr int kBoxWords = kBox * kBox * kBox;  // 1331
-constexpr int kCellChunk = 4096;               // particles per workgroup at most
 constexpr int kAssignThreads = 256;
+
+// Particles per workgroup at most.  250,007 clustered particles on a 64^3 mesh are 570 workgroups
+// of up to 4096, whose fullest decide: assignment and interpolation take 28 us each, 17 with
+// workgroups of up to 1024; 16.8 million have
+// enough with 4096, and halves of that only add slots to the gather (0.16 to 0.18 ms).
+static uint32_t cell_chunk(int64_t n) { return n < (1 << 22) ? 1024u : 4096u; }
 
 __device__ __forceinline__ uint32_t spread3_10(uint32_t v) // 10 bits -> every third bit
 {
@@ -126,13 +131,13 @@ __global__ __launch_bounds__(256) void k_pm_cells(const uint64_t *__restrict__ k
 
 // items[m] = chunks of cell m (exclusive prefix taken afterwards).
 __global__ __launch_bounds__(256) void k_pm_cell_items(const uint32_t *__restrict__ cell_start,
-                                                       uint32_t ncells,
+                                                       uint32_t ncells, uint32_t chunk,
                                                        uint32_t *__restrict__ items)
 {
     const uint32_t m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= ncells) return;
     const uint32_t c = cell_start[m + 1] - cell_start[m];
-    items[m] = (c + kCellChunk - 1) / kCellChunk;
+    items[m] = (c + chunk - 1) / chunk;
 }
 
 // The cell whose chunks include chunk `item`: the last m with item_start[m] <= item.  Every lane
@@ -157,15 +162,15 @@ __device__ __forceinline__ uint32_t item_cell(const uint32_t *__restrict__ item_
 __global__ __launch_bounds__(kAssignThreads) void k_pm_assign(
     const double4 *__restrict__ ps, int64_t n, int N, double inv_h,
     const unsigned long long *__restrict__ mx, const uint32_t *__restrict__ cell_start,
-    const uint32_t *__restrict__ item_start, uint32_t ncells,
+    const uint32_t *__restrict__ item_start, uint32_t ncells, uint32_t chunk,
     unsigned long long *__restrict__ slots)
 {
     __shared__ unsigned long long box[kBoxWords];
     const uint32_t item = blockIdx.x;
     if (item >= item_start[ncells]) return; // the same for the whole workgroup
     const uint32_t m = item_cell(item_start, ncells, item);
-    const uint32_t first = cell_start[m] + (item - item_start[m]) * (uint32_t)kCellChunk;
-    const uint32_t end = min(cell_start[m + 1], first + (uint32_t)kCellChunk);
+    const uint32_t first = cell_start[m] + (item - item_start[m]) * chunk;
+    const uint32_t end = min(cell_start[m + 1], first + chunk);
     const int ox = 8 * (int)compact3_10(m >> 2) - 1, oy = 8 * (int)compact3_10(m >> 1) - 1,
               oz = 8 * (int)compact3_10(m) - 1;
     for (int t = threadIdx.x; t < kBoxWords; t += kAssignThreads) box[t] = 0ull;
@@ -266,6 +271,7 @@ __global__ __launch_bounds__(kCellPts * kCellPts * kCellPts) void k_pm_gather(
     for (int j = 0; j < 8; ++j) sum += v[j];
 #pragma unroll
     for (int j = 0; j < 8; ++j) // cells of more than one chunk
+#pragma unroll 4
         for (uint32_t it = next[j] + 1; it < end[j]; ++it)
             sum += slots[(size_t)it * kBoxWords + word[j]];
     mass[((size_t)(8 * cx + x0) * N + (size_t)(8 * cy + y0)) * N + (size_t)(8 * cz + z0)] = sum;
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
     const double4 *__restrict__ ps, int N, double inv_h, const float *__restrict__ phi,
     const uint32_t *__restrict__ idx, float4 *__restrict__ stage,
     const uint32_t *__restrict__ cell_start, const uint32_t *__restrict__ item_start,
-    uint32_t ncells)
+    uint32_t ncells, uint32_t chunk)
 {
     // the force takes the potential's place: 16 KB, so eight workgroups fit a compute unit
     __shared__ float lds[3 * kBoxWords];
@@ -655,8 +661,8 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
     const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
     if (item >= item_start[ncells]) return; // the same for the whole workgroup
     const uint32_t m = item_cell(item_start, ncells, item);
-    const uint32_t first = cell_start[m] + (item - item_start[m]) * (uint32_t)kCellChunk;
-    const uint32_t end = min(cell_start[m + 1], first + (uint32_t)kCellChunk);
+    const uint32_t first = cell_start[m] + (item - item_start[m]) * chunk;
+    const uint32_t end = min(cell_start[m + 1], first + chunk);
     const int ox = 8 * (int)compact3_10(m >> 2) - 1, oy = 8 * (int)compact3_10(m >> 1) - 1,
               oz = 8 * (int)compact3_10(m) - 1;
     const int mask = N - 1;
@@ -784,7 +790,7 @@ void launch_pm_green(int N, double L, double eta, float *green, float2 *tw, hipS
 size_t pm_assign_cells(int N) { const size_t c = (size_t)N / kCellPts; return c * c * c; }
 size_t pm_assign_items_max(int N, int64_t n)
 {
-    return pm_assign_cells(N) + (size_t)((n + kCellChunk - 1) / kCellChunk);
+    return pm_assign_cells(N) + (size_t)((n + cell_chunk(n) - 1) / cell_chunk(n));
 }
 size_t pm_assign_slot_words() { return kBoxWords; }
 
@@ -797,12 +803,13 @@ void launch_pm_assign(const double4 *ps, const uint64_t *key, int64_t n, int N, 
     const int lc = __builtin_ctz((unsigned)(N / kCellPts)); // tree level of the cells
     const int sh = 3 * (21 - lc);
     k_pm_cells<<<(ncells + 1 + 255) / 256, 256, 0, s>>>(key, n, sh, ncells, cell_start);
-    k_pm_cell_items<<<(ncells + 255) / 256, 256, 0, s>>>(cell_start, ncells, item_start);
+    k_pm_cell_items<<<(ncells + 255) / 256, 256, 0, s>>>(cell_start, ncells, cell_chunk(n),
+                                                         item_start);
     scan_u32(item_start, ncells, item_start + ncells, scan_tmp, s); // exclusive; the total last
     const size_t items = pm_assign_items_max(N, n);
     if (n)
         k_pm_assign<<<(unsigned)items, kAssignThreads, 0, s>>>(ps, n, N, N / L, mx, cell_start,
-                                                               item_start, ncells, slots);
+                                                               item_start, ncells, cell_chunk(n), slots);
     k_pm_gather<<<ncells, kCellPts * kCellPts * kCellPts, 0, s>>>(N, item_start, slots, mass);
 }
 
@@ -844,7 +851,7 @@ void launch_pm_interp(const double4 *ps, int64_t n, int N, double L, const float
     if (!n) return;
     const uint32_t ncells = (uint32_t)pm_assign_cells(N);
     k_pm_interp<<<(unsigned)pm_assign_items_max(N, n), kAssignThreads, 0, s>>>(
-        ps, N, N / L, phi, idx, stage, cell_start, item_start, ncells);
+        ps, N, N / L, phi, idx, stage, cell_start, item_start, ncells, cell_chunk(n));
 }
 
 void launch_pm_split(const float4 *stage, int64_t n, void *ax, void *ay, void *az,
