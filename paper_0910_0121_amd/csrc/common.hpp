@@ -207,6 +207,7 @@ void launch_walk_stats(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
 // Shared launches over several boxes.  The groups of boxes 0 .. nb-1 are laid end to end as
 // one sequence of work items; box b holds items [g0, g0 + n_groups).  Each box keeps its own
 // tree, lists and flags, exactly as in a walk of that box alone.
+struct ForceItem;
 constexpr int kMaxBatch = 16;
 struct WalkBox {
     const WalkNode *wn;
@@ -221,7 +222,8 @@ struct WalkBox {
     uint64_t entries_cap;          // two passes: room at entries
     Slots slots;                   // or the room of each list, and no count pass
     unsigned long long *stats;     // see launch_walk_stats
-    uint32_t *cls;                 // queue buffer of the force
+    uint32_t *cls;                 // queue buffer of the force, and its pieces
+    ForceItem *items;
     uint32_t *mailbox;             // launch_walk_results_one: where the results go, and
     uint32_t seq;                  // the sequence number that marks them
 };
@@ -294,30 +296,60 @@ struct QuadTable {
 // For the c (a power of two) of the FP32 table of this eps / r_cut.
 void build_quad_table(double eps_over_rcut, double c, std::vector<float> &coef, QuadTable &qt);
 
-// Layout of the queue buffer (u32 words): the kXcds + 1 part starts and the kXcds ends of the
-// parts' runs of split groups (absolute word positions in the buffer), the queue counters of
-// the split and of the other groups, the (part, cost bucket) cursors, then the group ids, each
-// part's longest first.
+// Layout of the queue buffer (u32 words): the kXcds + 1 part starts of the whole groups (absolute
+// word positions in the buffer), the number of pieces, the queue counters of the force kernel and
+// of the quadrupole kernel (every wave reads the starts for each group: on the first counter's
+// line they cost the 256^3 box 5 % of its force), the (part, cost bucket) cursors, then the group ids, each part's
+// longest first.
 constexpr uint32_t kClsStarts = 0;
-constexpr uint32_t kClsHeavyEnd = kClsStarts + kXcds + 1;
-// the same for the kernels with workgroups of 16 waves, which split groups of at least 2^(t +
-// kCoarser16) pairs instead of 2^t
-constexpr uint32_t kCoarser16 = 2;
-constexpr uint32_t kClsEnd16 = kClsHeavyEnd + kXcds;
-constexpr uint32_t kClsQueue = kClsEnd16 + kXcds;
-constexpr uint32_t kClsQuadQueue = kClsQueue + 2 * kXcds * kQueueStride; // k_quad_f32's
-constexpr uint32_t kClsBins = kClsQuadQueue + 2 * kXcds * kQueueStride;
+constexpr uint32_t kClsItems = kClsStarts + kXcds + 1;
+constexpr uint32_t kClsQueue = kQueueStride;
+static_assert(kClsItems < kClsQueue, "");
+constexpr uint32_t kClsQuadQueue = kClsQueue + kXcds * kQueueStride; // k_quad_f32's
+constexpr uint32_t kClsBins = kClsQuadQueue + kXcds * kQueueStride;
 constexpr uint32_t kClsLists = kClsBins + kXcds * 64;
-// Parts and longest-first order of the groups (len: list lengths; pairs: the box's
-// interactions, device), into cls (kClsLists + n_groups words).
-// The bins have been cleared (launch_walk_init).
+// A group of more than 2^t pairs, 2^t about a 2^13th of the box's pairs, is taken in pieces: up to
+// kPieceChunk of its particles against a segment of its list.  The sums of a chunk whose list is
+// one segment go straight to the records, those of several to rows of three doubles, base +
+// seg (particles of the chunk) + i.
+struct ForceItem {
+    uint32_t g, chunk, seg_segs, base; // seg_segs: segment, and from bit 16 their number
+};
+constexpr uint32_t kPieceChunk = 128;
+constexpr uint32_t kMaxSegs = 64;
+// Entries per segment of a list of L in `segs` segments (whole rounds of 64).
+__host__ __device__ __forceinline__ uint32_t piece_entries(uint32_t L, uint32_t segs)
+{
+    return ((L + segs - 1) / segs + 63) / 64 * 64;
+}
+// An upper bound on the pieces of a box of n particles in G groups: a group in pieces has more
+// than a 2^14th of the pairs, and its chunks are pieces of at least 2^t pairs but for the last of
+// each list and one per chunk.
+__host__ __device__ __forceinline__ size_t max_force_items(uint64_t n, uint64_t G)
+{
+    const uint64_t by_pairs = (1ull << 17) + n / kPieceChunk;
+    const uint64_t by_groups = (G + n / kPieceChunk) * kMaxSegs;
+    return (size_t)(by_pairs < by_groups ? by_pairs : by_groups);
+}
+// Parts and longest-first order of the groups (len: list lengths; stats: the walk's, of which the
+// third is the box's interactions) into cls (kClsLists + n_groups words), and the pieces of long
+// ones into items (max_force_items); the rows they need and their number into stats[4] and [5].
+// The bins and those two have been cleared (launch_walk_init).
 void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
-                     const unsigned long long *pairs, uint32_t *cls, hipStream_t s);
+                     unsigned long long *stats, uint32_t *cls, ForceItem *items, hipStream_t s);
 // launch_walk_stats and launch_classify in one launch of a workgroup (boxes of at most
-// kOneBlockGroups groups), which then publishes the overflow word and the four statistics to
+// kOneBlockGroups groups), which then publishes the overflow word and the six statistics to
 // the box's mailbox.
 void launch_walk_results_one(const WalkBox &box, hipStream_t s);
 void launch_walk_results_multi(const WalkBox *boxes, int nb, hipStream_t s); // device array
+// A box's units in the force kernels, from the host so that no wave works them out (and holds them in
+// vector registers): FP32, x' = x inv, sums times scale; FP64, u = r^2 k2 + c, sums times scale
+// (1 without a table), and inv_f = 1 / r_cut and len_f = L / r_cut for the cull; 1 / L; r_cut with
+// room for rounding.
+struct ForceUnits {
+    double inv, scale, k2, inv_L, rc_wrap;
+    float inv_f, len_f;
+};
 // One box as the FP32 force kernel reads it.
 struct ForceBox {
     NodeArrays nd;
@@ -329,10 +361,14 @@ struct ForceBox {
     const uint32_t *pidx;
     ForceParams fp;
     ForceTable ft;
+    ForceUnits units;
     void *rec;
     int rec64; // rec holds double4 records
     QuadTable qt;         // with quadrupole terms, FP32: its table
     const double *moments; // and the cells' second moments, six per node
+    const ForceItem *items; // the pieces of long groups, their number, and the rows of their sums
+    uint32_t n_items;
+    double *rows;
     const double *tab64_hi; // FP64 kernel: its table, or null (pair by pair)
     const float *tab64_lo;
     uint32_t n_groups;
@@ -345,11 +381,16 @@ struct ForceBox {
 void launch_force_prep(const ForceBox &box, hipStream_t s);
 void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s); // device array
 // A persistent launch of at most two workgroups per CU over the box's queues.
-void launch_force_f32(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
+void launch_force_f32(const ForceBox &box, int n_cu, hipStream_t s);
 // The same over nb <= kMaxBatch boxes with equal tables (descriptors in device memory; the
-// queues of all boxes are taken as one, through the first box's counters; n_groups in all).
-void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_groups, int n_cu,
+// queues of all boxes are taken as one, through the first box's counters; n_work: groups and
+// pieces in all).
+void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_work, int n_cu,
                             hipStream_t s);
+// After the force and the FP32 quadrupole kernel: the rows of groups taken in pieces into their
+// records (no launch without pieces).  The FP64 quadrupole kernel follows it.
+void launch_force_merge(const ForceBox &box, hipStream_t s);
+void launch_force_merge_multi(const ForceBox *boxes, int nb, uint32_t most_items, hipStream_t s);
 // rec of the force launchers: one record per particle in the caller's order (pidx), float4
 // (ax, ay, az, 0) or, with rec64, double4.  launch_force_out then writes them out: mode 0
 // float arrays, 1 double arrays (from float4 / double4 records), 2 kick (v += dt a into double
@@ -364,7 +405,7 @@ void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const doubl
                          const double *mj, const double *xg, double eta, ForceTable ft,
                          double *out, hipStream_t s);
 // The FP64 force (k_force64.hip), over the same queues.
-void launch_force_f64(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s);
+void launch_force_f64(const ForceBox &box, int n_cu, hipStream_t s);
 
 // Particle-mesh long-range force (k_pm.hip), mesh N^3 with N a power of two in [16, 1024].
 // Octant table of the Green's function ((N/2+1)^3 floats) and N/2 twiddles.
@@ -402,7 +443,7 @@ void launch_second_moments(NodeArrays nd, const double4 *ps, const TreeOffsets &
                            double *Q, hipStream_t s);
 // Adds the cells' second-order terms to the box's force records, computed in FP64 or FP32 (then
 // box.qt is its table; a persistent launch over queues of its own, emptied by launch_force_prep).
-void launch_quad(const ForceBox &box, uint32_t n_groups, int fp64, int n_cu, hipStream_t s);
+void launch_quad(const ForceBox &box, int fp64, int n_cu, hipStream_t s);
 
 // Time stepping (k_step.hip).  Accelerations are float (acc_fp64 = 0) or double arrays.
 // out receives the bit pattern of min_i(sqrt(eps / |a_i|), eps / |v_i|) (+inf if none binds).

@@ -1,11 +1,11 @@
 // Parts shared by the FP32 and FP64 force kernels: the persistent workgroups and their queues,
 // the split of a group into chunks of particles, and the reduction and output of their sums.
 // A kernel is a policy P: kWaves (waves per workgroup), kTilesAt and kTileBytes (the waves' LDS
-// tiles), kQueueAt (its queue counters), kSplitEnd
-// (the ends of its runs of split groups), kAdd (sums are added to the records and no pairs are
+// tiles), kQueueAt (its queue counters), kAdd (sums are added to the records and no pairs are
 // counted), Frame (a group's origin and units, with `scale`, the factor of the sums), load_table,
 // group (reads a group, makes its frame and calls finish_group) and chunk_sums<K> (a wave's sums
-// for a chunk over a range of the group's list; returns the entries that survived the cull).
+// for a chunk over a range of the group's list, each lane's own stream's; returns the entries that
+// survived the cull).
 #pragma once
 
 #include "common.hpp"
@@ -60,6 +60,30 @@ __device__ __forceinline__ double uni(double v)
 }
 __device__ __forceinline__ float uni(float v) { return __uint_as_float(uni(__float_as_uint(v))); }
 
+// The lane, as a value that the compiler does not take for the same from one use to the next: what
+// is worked out from it (queue and list addresses) is not kept in vector registers across the
+// pair loops, whose 128 are all in use.
+__device__ __forceinline__ uint32_t lane_now()
+{
+    uint32_t l = __lane_id();
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
+// The chunk's particles, K per lane (slot, slot + S, ..; idle slots repeat the first), all on their
+// way before any is used.
+template <int K>
+__device__ __forceinline__ void load_chunk(const double4 *__restrict__ ps, uint32_t f,
+                                           uint32_t n_i, int slot, int S, double4 *r)
+{
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t i = (uint32_t)(slot + S * k);
+        r[k] = ps[f + (i < n_i ? i : 0)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Keeps a wave-uniform value in a vector register.
 __device__ __forceinline__ float in_vgpr(float v)
 {
@@ -74,7 +98,7 @@ template <int ROUNDS>
 __device__ __forceinline__ void fetch_entries(const uint32_t *__restrict__ list, uint32_t jb,
                                               uint32_t je, uint32_t *ent)
 {
-    const uint32_t lane = __lane_id();
+    const uint32_t lane = lane_now();
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
         const uint32_t j = jb + (uint32_t)(r * 64) + lane;
@@ -169,92 +193,70 @@ __device__ __forceinline__ void add_streams(double *ax, double *ay, double *az, 
     }
 }
 
-// One chunk by one wave (whole list), or by the workgroup's waves, each on its own
-// part [j0, j1) of the list: then the waves' sums meet in LDS (the tiles, two k at a time: 128
-// particles x 3 doubles fill one tile) and are added in wave order.
+// One chunk by one wave: its sums to the particles' records, or, for a segment of the list, to the
+// segment's rows (of three doubles, `rows`), which launch_force_merge adds up.
 template <class P, int K>
-__device__ __forceinline__ uint32_t run_chunk(char *tiles, int wave, bool split, int S,
-                                              uint32_t n_i, uint32_t f, const uint32_t *list,
-                                              uint32_t j0, uint32_t j1, const ForceBox &B,
+__device__ __forceinline__ uint32_t run_chunk(char *tile, double *rows, int S, uint32_t n_i,
+                                              uint32_t f, const uint32_t *list, uint32_t j0,
+                                              uint32_t j1, const ForceBox &B,
                                               const typename P::Frame &F)
 {
     double ax[K], ay[K], az[K];
-    const uint32_t kept = P::template chunk_sums<K>(tiles + wave * P::kTileBytes, S, n_i, f, list,
-                                                    j0, j1, B, F, ax, ay, az);
+    const uint32_t kept =
+        P::template chunk_sums<K>(tile, S, n_i, f, list, j0, j1, B, F, ax, ay, az);
     const double scale = F.scale;
     const uint32_t *__restrict__ const pidx = B.pidx;
     void *const rec = B.rec;
     const int rec64 = B.rec64;
-    const int lane = __lane_id();
-    if (!split) {
+    const int lane = (int)lane_now();
+    // the places in the caller's order are on their way while the streams are added up
+    uint32_t o[K];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const uint32_t i = (uint32_t)(lane + S * k);
-            if (lane < S && i < n_i) {
-                if (rec64)
-                    store_rec<1, P::kAdd>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale,
-                                          az[k] * scale);
-                else
-                    store_rec<0, P::kAdd>(rec, pidx[f + i], ax[k] * scale, ay[k] * scale,
-                                          az[k] * scale);
-            }
-        }
-        return kept;
-    }
-    double *const red = reinterpret_cast<double *>(tiles);
-    constexpr int kWaveWords = P::kTileBytes / 8;
-    static_assert(128 * 24 <= P::kTileBytes, "128 particles' sums fit a tile");
-#pragma unroll
-    for (int kb = 0; kb < K; kb += 2) {
-#pragma unroll
-        for (int k = kb; k < kb + 2 && k < K; ++k)
-            if (lane < S) {
-                double *const d = red + wave * kWaveWords + ((k - kb) * 64 + lane) * 3;
-                d[0] = ax[k];
-                d[1] = ay[k];
-                d[2] = az[k];
-            }
-        __syncthreads();
-        const int t = threadIdx.x;
-        const int k = kb + (t >> 6);
+    for (int k = 0; k < K; ++k) {
         const uint32_t i = (uint32_t)(lane + S * k);
-        if (t < 128 && k < K && lane < S && i < n_i) {
-            double vx = 0.0, vy = 0.0, vz = 0.0;
-            for (int w = 0; w < P::kWaves; ++w) {
-                const double *d = red + w * kWaveWords + t * 3;
-                vx += d[0];
-                vy += d[1];
-                vz += d[2];
-            }
-            if (rec64)
-                store_rec<1, P::kAdd>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+        o[k] = pidx[f + (i < n_i ? i : 0)];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    add_streams<K>(ax, ay, az, S);
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        const uint32_t i = (uint32_t)(lane + S * k);
+        if (lane < S && i < n_i) {
+            const double x = ax[k] * scale, y = ay[k] * scale, z = az[k] * scale;
+            if (rows) {
+                double *const r = rows + 3 * i;
+                r[0] = P::kAdd ? r[0] + x : x;
+                r[1] = P::kAdd ? r[1] + y : y;
+                r[2] = P::kAdd ? r[2] + z : z;
+            } else if (rec64)
+                store_rec<1, P::kAdd>(rec, o[k], x, y, z);
             else
-                store_rec<0, P::kAdd>(rec, pidx[f + i], vx * scale, vy * scale, vz * scale);
+                store_rec<0, P::kAdd>(rec, o[k], x, y, z);
         }
-        __syncthreads();
     }
     return kept;
 }
 
-// All chunks of a group over the list range [j0, j1); returns the pairs with the entries that
-// survived the cull.
+// Particles [i0, i1) of a group over the list range [j0, j1); returns the pairs with the entries
+// that survived the cull.
 template <class P>
-__device__ __forceinline__ uint64_t run_group(char *tiles, int wave, bool split,
-                                              const ForceBox &B, uint32_t n_g, uint32_t f,
+__device__ __forceinline__ uint64_t run_group(char *tile, double *rows, const ForceBox &B,
+                                              uint32_t i0, uint32_t i1, uint32_t f,
                                               const uint32_t *list, uint32_t j0, uint32_t j1,
                                               const typename P::Frame &F)
 {
     uint64_t pairs = 0;
-    for (uint32_t ib = 0; ib < n_g;) {
+    for (uint32_t ib = i0; ib < i1;) {
         int S, K;
-        chunk_layout(n_g - ib, S, K);
-        const uint32_t n_i = n_g - ib < (uint32_t)(S * K) ? n_g - ib : (uint32_t)(S * K);
+        chunk_layout(i1 - ib, S, K);
+        const uint32_t n_i = i1 - ib < (uint32_t)(S * K) ? i1 - ib : (uint32_t)(S * K);
         uint32_t kept;
         if (K == 4)
-            kept = run_chunk<P, 4>(tiles, wave, split, S, n_i, f + ib, list, j0, j1, B, F);
+            kept = run_chunk<P, 4>(tile, rows, S, n_i, f + ib, list, j0, j1, B, F);
         else
-            kept = run_chunk<P, 2>(tiles, wave, split, S, n_i, f + ib, list, j0, j1, B, F);
+            kept = run_chunk<P, 2>(tile, rows, S, n_i, f + ib, list, j0, j1, B, F);
         ib += n_i;
+        if (rows) rows += 3 * n_i;
         pairs += (uint64_t)kept * n_i;
     }
     return pairs;
@@ -281,9 +283,10 @@ struct GroupRead {
     // otherwise a source within r_cut of the box is its own nearest image, and a source whose
     // nearest image lies across the boundary is at least r_cut from the box without the wrap as
     // with it, so no coordinate needs wrapping.
-    __device__ __forceinline__ bool wraps(const ForceParams &fp) const
+    __device__ __forceinline__ bool wraps(const ForceBox &B) const
     {
-        const double rc = fp.rc * (1.0 + 0x1p-10);
+        const ForceParams &fp = B.fp;
+        const double rc = B.units.rc_wrap;
         return __ballot(!((lo[0] - rc >= 0.0) & (hi[0] + rc < fp.L) & (lo[1] - rc >= 0.0) &
                           (hi[1] + rc < fp.L) & (lo[2] - rc >= 0.0) & (hi[2] + rc < fp.L))) != 0;
     }
@@ -315,15 +318,13 @@ __device__ __forceinline__ float4 rel_f32(const double4 r, const FrameF32 &F)
 
 __device__ __forceinline__ FrameF32 frame_f32(const ForceBox &B, const GroupRead &R)
 {
-    const ForceParams &fp = B.fp;
-    const double lam = sqrt(1.0 - (double)B.ft.c);
-    const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
+    const ForceUnits &U = B.units;
     FrameF32 F;
-    F.scale = uni(inv_len * inv_len / lam);
-    F.wrap = R.wraps(fp);
-    F.L = fp.L;
-    F.inv_L = uni(1.0 / fp.L);
-    F.inv = uni(inv_len * lam);
+    F.scale = U.scale;
+    F.wrap = R.wraps(B);
+    F.L = B.fp.L;
+    F.inv_L = U.inv_L;
+    F.inv = U.inv;
     F.xg0 = uni(F.wrap ? R.xg[0] : R.xg[0] * F.inv);
     F.xg1 = uni(F.wrap ? R.xg[1] : R.xg[1] * F.inv);
     F.xg2 = uni(F.wrap ? R.xg[2] : R.xg[2] * F.inv);
@@ -341,37 +342,48 @@ __device__ __forceinline__ float pair_u(const float4 s, float xi, float yi, floa
     // u = min(|d|^2 + c, 1): the clamp is an output modifier of the last fma
     return __builtin_amdgcn_fmed3f(fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, c))), 0.0f, 1.0f);
 }
-// The group once its frame is known: by one wave, or, split, by the workgroup.
+// The piece of a group that a wave takes: all of it, or a part of its particles and of its list.
+struct Piece {
+    uint32_t g;
+    bool whole;
+    uint32_t chunk, seg, segs, base; // see ForceItem
+};
+
+// The piece once its group's frame is known.
 template <class P>
-__device__ __forceinline__ void finish_group(char *tiles, int wave, bool split, const ForceBox &B,
-                                             uint32_t g, const GroupRead &R,
-                                             const typename P::Frame &F)
+__device__ __forceinline__ void finish_group(char *tile, const ForceBox &B, const Piece &w,
+                                             const GroupRead &R, const typename P::Frame &F)
 {
-    const uint32_t Lg = uni(R.len);
-    uint32_t j0 = 0, j1 = Lg;
-    if (split) { // whole rounds of 64 entries per wave
-        const uint32_t per = ((Lg + 64 * P::kWaves - 1) / (64 * P::kWaves)) * 64;
-        j0 = per * (uint32_t)wave < Lg ? per * (uint32_t)wave : Lg;
+    const uint32_t Lg = uni(R.len), n_g = uni(R.count);
+    uint32_t i0 = 0, i1 = n_g, j0 = 0, j1 = Lg;
+    double *rows = nullptr;
+    if (!w.whole) {
+        i0 = w.chunk * kPieceChunk;
+        i1 = n_g - i0 < kPieceChunk ? n_g : i0 + kPieceChunk;
+        const uint32_t per = piece_entries(Lg, w.segs);
+        j0 = w.seg * per;
         j1 = j0 + per < Lg ? j0 + per : Lg;
+        if (w.segs > 1) rows = B.rows + 3 * ((uint64_t)w.base + (uint64_t)w.seg * (i1 - i0));
     }
     const uint32_t *list =
         B.entries + (((uint64_t)uni((uint32_t)(R.off >> 32)) << 32) | uni((uint32_t)R.off));
-    const uint64_t pairs =
-        run_group<P>(tiles, wave, split, B, uni(R.count), uni(R.first), list, j0, j1, F);
+    // (uniform already, which the compiler loses sight of: the pair loops' counters would be vectors)
+    const uint64_t pairs = run_group<P>(tile, rows, B, uni(i0), uni(i1), uni(R.first), list, uni(j0),
+                                        uni(j1), F);
     if (!P::kAdd && __lane_id() == 0) {
-        if (split)
-            atomicAdd(&B.fp.pairs[g], (unsigned long long)pairs); // zeroed by the prep launch
+        if (w.whole)
+            B.fp.pairs[w.g] = pairs;
         else
-            B.fp.pairs[g] = pairs;
+            atomicAdd(&B.fp.pairs[w.g], (unsigned long long)pairs); // zeroed by the prep launch
     }
 }
 
 // The first part at or after `from` (cyclically) whose counter has not reached its size, or
-// kXcds.  Lane p < kXcds holds part p's size.  One read of all counters, so a wave that finds
+// kXcds.  Lane p < kXcds holds part p's size, less what is dealt.  One read of all counters, so a wave that finds
 // everything taken leaves after one memory latency, and no atomic is spent on empty queues.
 __device__ __forceinline__ uint32_t next_part(uint32_t *ctr, uint32_t size, uint32_t from)
 {
-    const uint32_t lane = __lane_id();
+    const uint32_t lane = lane_now();
     uint32_t v = 0;
     if (lane < kXcds)
         v = __hip_atomic_load(&ctr[lane * kQueueStride], __ATOMIC_RELAXED,
@@ -395,34 +407,25 @@ __device__ __forceinline__ Item find_item(uint32_t ends, int nb, uint32_t q)
     return {b, q - before};
 }
 
-// Box b's run of part p in the queue of split (heavy = 1) or single-wave groups.
-template <class P>
-__device__ __forceinline__ uint32_t run_start(const uint32_t *cls, uint32_t p, int heavy)
+// Box b's run of part p in the queue of whole groups.
+__device__ __forceinline__ uint32_t run_size(const uint32_t *cls, uint32_t p)
 {
-    return cls[heavy ? kClsStarts + p : P::kSplitEnd + p];
-}
-template <class P>
-__device__ __forceinline__ uint32_t run_size(const uint32_t *cls, uint32_t p, int heavy)
-{
-    return cls[heavy ? P::kSplitEnd + p : kClsStarts + p + 1] - run_start<P>(cls, p, heavy);
+    return cls[kClsStarts + p + 1] - cls[kClsStarts + p];
 }
 
 // Per lane p < kXcds the total size of part p over the boxes.
-template <class P>
-__device__ __forceinline__ uint32_t part_sizes(const ForceBox *bx, int nb, int heavy)
+__device__ __forceinline__ uint32_t part_sizes(const ForceBox *bx, int nb)
 {
-    const uint32_t lane = __lane_id();
+    const uint32_t lane = lane_now();
     uint32_t n = 0;
     if (lane < kXcds)
-        for (int b = 0; b < nb; ++b) n += run_size<P>(bx[b].cls, lane, heavy);
+        for (int b = 0; b < nb; ++b) n += run_size(bx[b].cls, lane);
     return n;
 }
-// Per lane the inclusive prefix over the boxes of their runs of `part`.
-template <class P>
-__device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_t part, int heavy)
+// Per lane the inclusive prefix over the boxes (lane b < nb: v).
+__device__ __forceinline__ uint32_t box_ends(uint32_t v)
 {
     const int lane = __lane_id();
-    uint32_t v = lane < nb ? run_size<P>(bx[lane].cls, part, heavy) : 0u;
 #pragma unroll
     for (int d = 1; d < kMaxBatch; d <<= 1) {
         const uint32_t u = __shfl_up(v, d, 64);
@@ -431,18 +434,23 @@ __device__ __forceinline__ uint32_t run_ends(const ForceBox *bx, int nb, uint32_
     return v;
 }
 
-// Persistent: each workgroup copies the table into LDS once, takes split groups as a whole
-// until none are left, and then its waves take single groups, each from the queues of
-// kXcds contiguous key ranges (its own XCD's first: neighbouring groups share sources through
-// one L2; then what is left of the others).  Every box of a launch has the same table.
-//
-// A group with at least 2^t pairs is split over the workgroup's waves, 2^t being about a
-// 16384th of the box's pairs (at least 2^12): one wave alone would hold up the end of the
-// launch.  On the 700,001-particle clustered box the longest single-wave group took 1.3 ms of
-// a 1.5 ms force call whose work fills the device for 0.6 ms.  Workgroups of 16 waves leave each
-// wave half as much of a group and split from 2^(t+2) on: quadrupole terms of a million particles
-// from 2^t, 2^(t+1), 2^(t+2) and 2^(t+3) on: 0.98, 0.94, 0.67 and 0.80 ms; FP64 force of the
-// 128^3 clustered box from 2^t and 2^(t+2) on: 3.72 and 3.39 ms.
+// Waves of the launch on XCD p.
+template <class P>
+__device__ __forceinline__ uint32_t dealt_waves(uint32_t p)
+{
+    return (gridDim.x - p + kXcds - 1) / kXcds * P::kWaves;
+}
+
+// Persistent: each workgroup copies the table into LDS once; then its waves, each for itself, take
+// the pieces of groups that are too long for one wave and after them whole groups.
+// The pieces, all of much the same cost, are dealt: an eighth of the list, which is in key order,
+// to each XCD's waves in turn.  (From a counter per XCD they would come one per 45 ns: 6000 of
+// them, for a box of 250,007 particles, took 0.75 ms where their pairs take 0.16.)
+// The whole groups lie in kXcds contiguous key ranges (neighbouring groups share sources through
+// one L2).  The first of each are dealt to the waves of its XCD, one each; the others come
+// from a queue per range, the own XCD's first and then what is left of the others, and a wave asks
+// for its next one before it begins one.  So a small box needs no counter (all 4096 waves asking at
+// once took 40 us).  Every box of a launch has the same table.
 template <class P, bool MULTI>
 __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
 {
@@ -451,23 +459,42 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
     char *const lds = reinterpret_cast<char *>(smem);
     P::load_table(lds, bx[0]);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); // known to be uniform
-    const uint32_t lane = __lane_id();
-    const uint32_t xcd = blockIdx.x % kXcds;
-    uint32_t *const hq = bx[0].cls + P::kQueueAt, *const lq = hq + kXcds * kQueueStride;
+    const uint32_t lane = __lane_id(), xcd = blockIdx.x % kXcds;
     __syncthreads();
-    char *const tiles = lds + P::kTilesAt;
-    uint32_t *const word = reinterpret_cast<uint32_t *>(tiles); // free between groups
-    uint32_t size = part_sizes<P>(bx, nb, 1), part = xcd, ends = 0, have = kXcds, next = 0;
-    bool split = __ballot(size != 0) != 0;
-    if (!split) size = part_sizes<P>(bx, nb, 0);
-    for (;;) {
-        uint32_t *const ctr = split ? hq : lq;
-        uint32_t q = next;
-        if (!split || wave == 0)
+    char *const tile = lds + P::kTilesAt + wave * P::kTileBytes;
+    // the pieces: places at, at + step, .. below hi
+    uint32_t ends = 0, total = bx[0].cls[kClsItems];
+    if (MULTI) {
+        ends = box_ends((int)lane < nb ? bx[lane].cls[kClsItems] : 0u);
+        total = (uint32_t)__builtin_amdgcn_readlane((int)ends, nb - 1);
+    }
+    total = uni(total);
+    const bool by_xcd = gridDim.x >= kXcds; // else some XCD has no workgroup
+    const uint32_t hi = by_xcd ? (uint32_t)((uint64_t)total * (xcd + 1) / kXcds) : total;
+    const uint32_t blocks = by_xcd ? (gridDim.x - xcd + kXcds - 1) / kXcds : gridDim.x;
+    const uint32_t place = (uint32_t)wave * blocks + (by_xcd ? blockIdx.x / kXcds : blockIdx.x);
+    uint32_t at = place + (by_xcd ? (uint32_t)((uint64_t)total * xcd / kXcds) : 0u);
+    bool pieces = true;
+    uint32_t *const ctr = bx[0].cls + P::kQueueAt;
+    uint32_t size = 0, part = xcd, have = kXcds, next = 0;
+    for (;;) { // one place where a group is taken, whichever way it was found
+        Piece w{0, false, 0, 0, 1, 0};
+        Item it{0, at};
+        bool dealt = false;
+        if (pieces && at >= hi) {
+            pieces = false;
+            size = part_sizes(bx, nb);
+            dealt = by_xcd && place < (uint32_t)__builtin_amdgcn_readlane((int)size, (int)xcd);
+            // what is left of part p once its XCD's waves have one each
+            const uint32_t p = lane_now(), w_p = by_xcd ? dealt_waves<P>(p) : 0u;
+            size = p < kXcds && size > w_p ? size - w_p : 0u;
+            it.k = place;
+        }
+        if (!pieces && !dealt) {
+            uint32_t q = next;
             for (;;) {
-                // a single wave asked for its next item before it began the last one
-                if (split || part != have) {
-                    part = uni(next_part(ctr, size, part));
+                if (part != have) {
+                    part = __ballot(size != 0) ? uni(next_part(ctr, size, part)) : kXcds;
                     if (part == kXcds) break;
                     if (lane == 0) q = atomicAdd(&ctr[part * kQueueStride], 1u);
                 }
@@ -475,33 +502,26 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
                 if (q < (uint32_t)__builtin_amdgcn_readlane((int)size, (int)part)) break;
                 have = kXcds; // found empty: on to the next part that is not
             }
-        if (split) {
-            if (threadIdx.x == 0) {
-                word[0] = part;
-                word[1] = q;
-            }
-            __syncthreads();
-            part = word[0];
-            q = word[1];
-            __syncthreads();
-        }
-        part = uni(part);
-        q = uni(q);
-        if (part == kXcds) {
-            if (!split) break;
-            split = false; // on to the single-wave groups
-            size = part_sizes<P>(bx, nb, 0);
-            part = xcd;
-            have = kXcds;
-            continue;
-        }
-        if (MULTI && part != have) ends = run_ends<P>(bx, nb, part, split);
-        have = part;
-        if (!split && lane == 0) next = atomicAdd(&ctr[part * kQueueStride], 1u);
-        Item it{0, q};
-        if (MULTI) it = find_item(ends, nb, q);
+            if (part == kXcds) break;
+            if (MULTI && part != have)
+                ends = box_ends((int)lane < nb ? run_size(bx[lane].cls, part) : 0u);
+            have = part;
+            if (lane == 0) next = atomicAdd(&ctr[part * kQueueStride], 1u);
+            it.k = uni(q + (by_xcd ? dealt_waves<P>(part) : 0u));
+        } else if (MULTI && dealt)
+            ends = box_ends((int)lane < nb ? run_size(bx[lane].cls, xcd) : 0u);
+        if (MULTI) it = find_item(ends, nb, it.k);
         const ForceBox &B = MULTI ? bx[uni(it.box)] : bx[0];
-        P::group(tiles, wave, split, B, uni(B.cls[run_start<P>(B.cls, part, split) + it.k]));
+        if (pieces) {
+            const ForceItem f = B.items[it.k];
+            w = Piece{uni(f.g), false, uni(f.chunk), uni(f.seg_segs & 0xffffu),
+                      uni(f.seg_segs >> 16), uni(f.base)};
+            at += blocks * P::kWaves;
+        } else {
+            w.g = uni(B.cls[B.cls[kClsStarts + (dealt ? xcd : part)] + it.k]);
+            w.whole = true;
+        }
+        P::group(tile, B, w);
     }
 }
 

@@ -198,19 +198,20 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
     const int lane = __lane_id();
     const int J = 64 / S, lgJ = 31 - __builtin_clz(J);
     const int slot = lane & (S - 1), stream = lane / S;
+    uint32_t ent[kTileRounds];
+    if (j0 < j1) fetch_entries<kTileRounds>(list, j0, j1, ent);
+    double4 pos[K];
+    load_chunk<K>(ps, f, n_i, slot, S, pos);
     float xi[K], yi[K], zi[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        const uint32_t i = slot + S * k;
-        const float4 v = rel_f32(ps[f + (i < n_i ? i : 0)], F); // idle slots repeat the first
+        const float4 v = rel_f32(pos[k], F);
         xi[k] = v.x;
         yi[k] = v.y;
         zi[k] = v.z;
         ax[k] = ay[k] = az[k] = 0.0;
     }
     const ChunkBox C = chunk_box<K>(xi, yi, zi, S);
-    uint32_t ent[kTileRounds];
-    if (j0 < j1) fetch_entries<kTileRounds>(list, j0, j1, ent);
     for (uint32_t jb = j0; jb < j1; jb += kTileF32) {
         const int nt = load_tile_f32(tile, ent, jb, j1, J, nd, F, C);
         kept += (uint32_t)nt;
@@ -229,7 +230,6 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
             az[k] += (double)tz[k];
         }
     }
-    add_streams<K>(ax, ay, az, S);
     return kept;
 }
 
@@ -240,7 +240,7 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
 // cost about 12 ms, at 40 ns each).  700,001 particles: the whole step 3.41 -> 1.53 ms.
 struct PolicyF32 {
     static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
-    static constexpr uint32_t kQueueAt = kClsQueue, kSplitEnd = kClsHeavyEnd;
+    static constexpr uint32_t kQueueAt = kClsQueue;
     static constexpr bool kAdd = false;
     using Frame = FrameF32;
 
@@ -265,11 +265,10 @@ struct PolicyF32 {
                                  ax, ay, az);
     }
 
-    static __device__ __forceinline__ void group(char *tiles, int wave, bool split,
-                                                 const ForceBox &B, uint32_t g)
+    static __device__ __forceinline__ void group(char *tile, const ForceBox &B, const Piece &w)
     {
-        const GroupRead R(B, g);
-        finish_group<PolicyF32>(tiles, wave, split, B, g, R, frame_f32(B, R));
+        const GroupRead R(B, w.g);
+        finish_group<PolicyF32>(tile, B, w, R, frame_f32(B, R));
     }
 };
 
@@ -332,51 +331,98 @@ __global__ __launch_bounds__(256) void k_pairwise_f32(int64_t n_i, const double 
     }
 }
 
-// Queues of the FP32 force.  Group g belongs to XCD part p = floor(8 g / G) (contiguous key
-// ranges) and to a cost bucket: the octave of its pairs n_g L_g if it has at least 2^kHeavyCost
-// of them or is split (at least 2^t, see force_body), one bucket for all others.  The bins (p,
-// bucket) are laid out with the costliest first, so each part lists its split groups, its heavy
-// ones longest first and then the rest in about key order (consecutive groups share sources
-// through the XCD's L2).  Three passes: count the bins, scan them into cursors and part
-// starts, scatter.  Blocks take kClassifyItems * 256 consecutive groups and aggregate their
-// bins in LDS first.
+// Queues of the force.  Group g belongs to XCD part p = floor(8 g / G) (contiguous key ranges) and,
+// unless it is taken in pieces (more than 2^t pairs, see ForceItem), to a cost bucket: the octave
+// of its pairs n_g L_g if it has at least 2^kHeavyCost of them or an eighth of 2^t, one bucket for
+// all others.  The bins (p, bucket) are laid out with the costliest first, so each part lists its
+// heavy groups longest first and then the rest in about key order (consecutive groups share
+// sources through the XCD's L2); the pieces, all of about one cost, have a queue of their own
+// before them.  Three passes: count the bins, scan them into cursors and part starts, scatter.
+// Blocks take kClassifyItems * 256 consecutive groups and aggregate their bins in LDS first.
+//
+// Why pieces, and of 2^t: a wave alone would hold up the end of the launch, and a device of 4096
+// waves needs several items for each.  Shared by the eight waves of a workgroup instead, which
+// meet in LDS twice per chunk (groups from a 16384th of the pairs on), a group's waves get a
+// few dozen list entries each and wait most of the time: boxes of 250,007, 500,009 and 700,001
+// particles ran at 0.92, 0.89 and 1.05 pairs per ps against 1.96 in the 256^3 box.
 constexpr int kClassifyItems = 8;
 constexpr int kCostBuckets = 64;
 constexpr uint32_t kHeavyCost = 17;
-constexpr uint32_t kMinSplit = 12;
+constexpr uint32_t kMinPiece = 13;
+constexpr uint32_t kPieceShift = 13;
 constexpr int kBins = kXcds * kCostBuckets;
 
 // t of the box: pairs = its interactions.
-__device__ __forceinline__ uint32_t split_log2(unsigned long long pairs)
+__device__ __forceinline__ uint32_t piece_log2(unsigned long long pairs)
 {
     const uint32_t lg = 63u - (uint32_t)__clzll((long long)(pairs | 1ull));
-    return lg > kMinSplit + 14u ? lg - 14u : kMinSplit;
+    return lg > kMinPiece + kPieceShift ? lg - kPieceShift : kMinPiece;
 }
 
+// Segments of a chunk of n_c particles against a list of L entries, about 2^t pairs each.
+__device__ __forceinline__ uint32_t chunk_segs(uint32_t n_c, uint32_t L, uint32_t t)
+{
+    const uint64_t m = ((uint64_t)n_c * L + (1ull << t) - 1) >> t;
+    const uint32_t segs = m < 1 ? 1u : m < kMaxSegs ? (uint32_t)m : kMaxSegs;
+    const uint32_t per = piece_entries(L, segs);
+    return per ? (L + per - 1) / per : 1u;
+}
+
+// The pieces of a group: its chunks, all alike but the last, in segments.
+struct Pieces {
+    uint32_t chunks, segs, last_n, last_segs;
+    __device__ __forceinline__ Pieces(uint32_t n_g, uint32_t L, uint32_t t)
+        : chunks((n_g + kPieceChunk - 1) / kPieceChunk), segs(chunk_segs(kPieceChunk, L, t)),
+          last_n(n_g - (chunks - 1) * kPieceChunk), last_segs(chunk_segs(last_n, L, t))
+    {
+    }
+    __device__ __forceinline__ uint32_t items() const { return (chunks - 1) * segs + last_segs; }
+    __device__ __forceinline__ uint32_t rows() const
+    {
+        return (segs > 1 ? (chunks - 1) * kPieceChunk * segs : 0u) +
+               (last_segs > 1 ? last_n * last_segs : 0u);
+    }
+    __device__ __forceinline__ void write(uint32_t g, ForceItem *out, uint32_t base) const
+    {
+        for (uint32_t c = 0; c < chunks; ++c) {
+            const bool last = c + 1 == chunks;
+            const uint32_t m = last ? last_segs : segs;
+            for (uint32_t q = 0; q < m; ++q) *out++ = ForceItem{g, c, q | m << 16, base};
+            if (m > 1) base += (last ? last_n : kPieceChunk) * m;
+        }
+    }
+};
+
+// Bucket 0 of a part counts pieces.
 __device__ __forceinline__ uint32_t cost_bin(uint32_t g, uint32_t n_groups, uint32_t n_g,
                                              uint32_t L_g, uint32_t t)
 {
     const uint32_t part = (uint32_t)(((uint64_t)g * kXcds) / n_groups);
     const uint64_t cost = (uint64_t)n_g * L_g;
     const uint32_t lg = 63u - (uint32_t)__clzll((long long)(cost | 1ull));
-    const uint32_t least = t < kHeavyCost ? t : kHeavyCost;
-    return part * kCostBuckets + (kCostBuckets - 1 - (lg >= least ? lg : 0u));
+    const uint32_t least = t - 3 < kHeavyCost ? t - 3 : kHeavyCost;
+    const uint32_t bucket =
+        cost > 1ull << t ? 0u : kCostBuckets - 1 - (lg >= least ? lg : 0u);
+    return part * kCostBuckets + bucket;
 }
+__device__ __forceinline__ bool in_pieces(uint32_t bin) { return bin % kCostBuckets == 0; }
 
 __global__ __launch_bounds__(256) void k_class_count(GroupArrays gr, uint32_t n_groups,
                                                      const uint32_t *__restrict__ len,
-                                                     const unsigned long long *pairs,
+                                                     const unsigned long long *stats,
                                                      uint32_t *hist)
 {
     __shared__ uint32_t s_cnt[kBins];
     for (int i = threadIdx.x; i < kBins; i += 256) s_cnt[i] = 0;
     __syncthreads();
-    const uint32_t t = split_log2(*pairs);
+    const uint32_t t = piece_log2(stats[2]);
     const uint32_t base = blockIdx.x * (256u * kClassifyItems);
 #pragma unroll
     for (int r = 0; r < kClassifyItems; ++r) {
         const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
-        if (g < n_groups) atomicAdd(&s_cnt[cost_bin(g, n_groups, gr.count[g], len[g], t)], 1u);
+        if (g >= n_groups) continue;
+        const uint32_t n_g = gr.count[g], L = len[g], bin = cost_bin(g, n_groups, n_g, L, t);
+        atomicAdd(&s_cnt[bin], in_pieces(bin) ? Pieces(n_g, L, t).items() : 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += 256)
@@ -384,65 +430,123 @@ __global__ __launch_bounds__(256) void k_class_count(GroupArrays gr, uint32_t n_
 }
 
 // By one wave, lane = cost bucket: the bins' counts to cursors (in place; bins in global memory
-// or LDS), part starts and the ends of the parts' split runs into cls.
-__device__ __forceinline__ void scan_bins(uint32_t *bins, uint32_t *cls, uint32_t t)
+// or LDS), the part starts of the whole groups and the number of pieces into cls.  Returns the
+// latter.
+__device__ __forceinline__ uint32_t scan_bins(uint32_t *bins, uint32_t *cls)
 {
     static_assert(kCostBuckets == 64, "one lane per bucket");
     const int lane = __lane_id();
-    uint32_t pos = kClsLists;
+    uint32_t pos = kClsLists, items = 0;
     uint32_t c[kXcds];
 #pragma unroll
     for (int p = 0; p < (int)kXcds; ++p) c[p] = bins[p * kCostBuckets + lane];
 #pragma unroll
     for (int p = 0; p < (int)kXcds; ++p) {
-        uint32_t v = c[p];
+        const uint32_t mine = lane ? c[p] : 0u;
+        uint32_t v = mine;
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) {
             const uint32_t u = __shfl_up(v, d, 64);
             if (lane >= d) v += u;
         }
-        bins[p * kCostBuckets + lane] = pos + v - c[p];
-        // bucket lane holds lg = 63 - lane: split for lg >= t
+        bins[p * kCostBuckets + lane] = lane ? pos + v - mine : items;
         if (lane == 0) cls[kClsStarts + p] = pos;
-        if (lane == 63 - (int)t) cls[kClsHeavyEnd + p] = pos + v;
-        if (lane == 63 - (int)(t + kCoarser16)) cls[kClsEnd16 + p] = pos + v;
         pos += (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+        items += (uint32_t)__builtin_amdgcn_readfirstlane((int)c[p]);
     }
-    if (lane == 0) cls[kClsStarts + kXcds] = pos;
+    if (lane == 0) {
+        cls[kClsStarts + kXcds] = pos;
+        cls[kClsItems] = items;
+    }
+    return items;
 }
-__global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, const unsigned long long *pairs)
+__global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, unsigned long long *stats)
 {
-    scan_bins(cls + kClsBins, cls, split_log2(*pairs));
+    const uint32_t items = scan_bins(cls + kClsBins, cls);
+    if (threadIdx.x == 0) stats[5] = items;
 }
 
 __global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t n_groups,
                                                        const uint32_t *__restrict__ len,
-                                                       const unsigned long long *pairs,
-                                                       uint32_t *cls)
+                                                       unsigned long long *stats, uint32_t *cls,
+                                                       ForceItem *__restrict__ items)
 {
-    __shared__ uint32_t s_cnt[kBins];
+    __shared__ uint32_t s_cnt[kBins], s_rows, s_base;
     for (int i = threadIdx.x; i < kBins; i += 256) s_cnt[i] = 0;
+    if (threadIdx.x == 0) s_rows = 0;
     __syncthreads();
-    const uint32_t t = split_log2(*pairs);
+    const uint32_t t = piece_log2(stats[2]);
     const uint32_t base = blockIdx.x * (256u * kClassifyItems);
-    uint32_t bin[kClassifyItems], loc[kClassifyItems];
+    uint32_t bin[kClassifyItems], loc[kClassifyItems], row[kClassifyItems];
 #pragma unroll
     for (int r = 0; r < kClassifyItems; ++r) {
         const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
         bin[r] = ~0u;
+        row[r] = 0;
         if (g < n_groups) {
-            bin[r] = cost_bin(g, n_groups, gr.count[g], len[g], t);
-            loc[r] = atomicAdd(&s_cnt[bin[r]], 1u);
+            const uint32_t n_g = gr.count[g], L = len[g];
+            bin[r] = cost_bin(g, n_groups, n_g, L, t);
+            if (in_pieces(bin[r])) {
+                const Pieces p(n_g, L, t);
+                loc[r] = atomicAdd(&s_cnt[bin[r]], p.items());
+                row[r] = atomicAdd(&s_rows, p.rows());
+            } else
+                loc[r] = atomicAdd(&s_cnt[bin[r]], 1u);
         }
     }
     __syncthreads();
-    // this block's run of each bin
+    // this block's run of each bin, and of the rows
     for (int i = threadIdx.x; i < kBins; i += 256)
         if (s_cnt[i]) s_cnt[i] = atomicAdd(&cls[kClsBins + i], s_cnt[i]);
+    if (threadIdx.x == 0 && s_rows)
+        s_base = (uint32_t)atomicAdd(&stats[4], (unsigned long long)s_rows);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kClassifyItems; ++r)
-        if (bin[r] != ~0u) cls[s_cnt[bin[r]] + loc[r]] = base + (uint32_t)r * 256u + threadIdx.x;
+    for (int r = 0; r < kClassifyItems; ++r) {
+        if (bin[r] == ~0u) continue;
+        const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
+        if (in_pieces(bin[r]))
+            Pieces(gr.count[g], len[g], t).write(g, items + s_cnt[bin[r]] + loc[r], s_base + row[r]);
+        else
+            cls[s_cnt[bin[r]] + loc[r]] = g;
+    }
+}
+
+// Adds up the rows of the chunks whose list was taken in segments, a wave per chunk (that of its
+// first segment), in the order of the segments, and stores the particles' records.
+__device__ __forceinline__ void force_merge(const ForceBox &B, uint32_t k)
+{
+    if (k >= B.n_items) return;
+    const ForceItem f = B.items[k];
+    const uint32_t segs = f.seg_segs >> 16;
+    if ((f.seg_segs & 0xffffu) != 0 || segs < 2) return;
+    const uint32_t n_g = B.gr.count[f.g], i0 = f.chunk * kPieceChunk;
+    const uint32_t n_c = n_g - i0 < kPieceChunk ? n_g - i0 : kPieceChunk;
+    const uint32_t first = B.gr.first[f.g] + i0;
+    for (uint32_t i = __lane_id(); i < n_c; i += 64) {
+        const uint32_t o = B.pidx[first + i];
+        const double *r = B.rows + 3 * ((uint64_t)f.base + i);
+        double x = 0.0, y = 0.0, z = 0.0;
+#pragma unroll 4
+        for (uint32_t q = 0; q < segs; ++q) {
+            const double *p = r + 3 * (uint64_t)q * n_c;
+            x += p[0];
+            y += p[1];
+            z += p[2];
+        }
+        if (B.rec64)
+            store_rec<1, false>(B.rec, o, x, y, z);
+        else
+            store_rec<0, false>(B.rec, o, x, y, z);
+    }
+}
+__global__ __launch_bounds__(256) void k_force_merge(ForceBox box)
+{
+    force_merge(box, blockIdx.x * 4 + (threadIdx.x >> 6));
+}
+__global__ __launch_bounds__(256) void k_force_merge_multi(const ForceBox *__restrict__ bx)
+{
+    force_merge(bx[blockIdx.y], blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
 // The records in the caller's order, split into three arrays or applied as a kick (modes as
@@ -509,7 +613,8 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
 {
     constexpr int kThreads = 1024, kWaves = kThreads / 64;
     __shared__ uint32_t bin[kBins];
-    __shared__ unsigned long long part[4][kWaves], tot[4];
+    __shared__ unsigned long long part[4][kWaves], tot[6];
+    __shared__ uint32_t s_rows;
     const uint32_t tid = threadIdx.x, G = B.n_groups;
     const int lane = tid & 63, wave = tid >> 6;
     unsigned long long v[4] = {0, 0, 0, 0}; // cells, particles, pairs, longest list
@@ -529,6 +634,7 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
     if (lane == 0)
         for (int k = 0; k < 4; ++k) part[k][wave] = v[k];
     for (uint32_t i = tid; i < kBins; i += kThreads) bin[i] = 0;
+    if (tid == 0) s_rows = 0;
     __syncthreads();
     if (tid < 4) {
         unsigned long long t = 0;
@@ -538,19 +644,36 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
         B.stats[tid] = t;
     }
     __syncthreads();
-    const uint32_t t = split_log2(tot[2]);
-    for (uint32_t g = tid; g < G; g += kThreads)
-        atomicAdd(&bin[cost_bin(g, G, B.gr.count[g], B.len[g], t)], 1u);
+    const uint32_t t = piece_log2(tot[2]);
+    for (uint32_t g = tid; g < G; g += kThreads) {
+        const uint32_t n_g = B.gr.count[g], L = B.len[g], k = cost_bin(g, G, n_g, L, t);
+        atomicAdd(&bin[k], in_pieces(k) ? Pieces(n_g, L, t).items() : 1u);
+    }
     __syncthreads();
-    if (wave == 0) scan_bins(bin, B.cls, t);
+    if (wave == 0) {
+        const uint32_t items = scan_bins(bin, B.cls);
+        if (lane == 0) tot[5] = items;
+    }
     __syncthreads();
-    for (uint32_t g = tid; g < G; g += kThreads)
-        B.cls[atomicAdd(&bin[cost_bin(g, G, B.gr.count[g], B.len[g], t)], 1u)] = g;
+    for (uint32_t g = tid; g < G; g += kThreads) {
+        const uint32_t n_g = B.gr.count[g], L = B.len[g], k = cost_bin(g, G, n_g, L, t);
+        if (in_pieces(k)) {
+            const Pieces p(n_g, L, t);
+            const uint32_t at = atomicAdd(&bin[k], p.items());
+            p.write(g, B.items + at, atomicAdd(&s_rows, p.rows()));
+        } else
+            B.cls[atomicAdd(&bin[k], 1u)] = g;
+    }
+    __syncthreads();
+    if (tid == 0) {
+        B.stats[4] = tot[4] = s_rows;
+        B.stats[5] = tot[5];
+    }
     if (tid == 0 && B.mailbox) {
         uint32_t *m = B.mailbox;
         __hip_atomic_store(&m[1], *(volatile unsigned *)B.overflow, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_SYSTEM);
-        for (int k = 0; k < 4; ++k) {
+        for (int k = 0; k < 6; ++k) {
             __hip_atomic_store(&m[2 + 2 * k], (uint32_t)tot[k], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
             __hip_atomic_store(&m[3 + 2 * k], (uint32_t)(tot[k] >> 32), __ATOMIC_RELAXED,
@@ -568,7 +691,7 @@ __global__ __launch_bounds__(1024) void k_walk_results_multi(const WalkBox *__re
 __device__ __forceinline__ void force_prep(const ForceBox &B, uint32_t b, uint32_t nb)
 {
     const uint32_t i = b * 256u + threadIdx.x;
-    if (i < 4 * kXcds) B.cls[kClsQueue + i * kQueueStride] = 0;
+    if (i < 2 * kXcds) B.cls[kClsQueue + i * kQueueStride] = 0;
     if (i == 0) *B.pair_sum = 0;
     for (uint32_t k = i; k < B.n_groups; k += nb * 256u) B.fp.pairs[k] = 0;
 }
@@ -584,30 +707,41 @@ __global__ __launch_bounds__(256) void k_force_prep_multi(const ForceBox *__rest
 } // namespace
 
 void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
-                     const unsigned long long *pairs, uint32_t *cls, hipStream_t s)
+                     unsigned long long *stats, uint32_t *cls, ForceItem *items, hipStream_t s)
 {
     if (!n_groups) return;
     const unsigned b = (n_groups + 256u * kClassifyItems - 1) / (256u * kClassifyItems);
-    k_class_count<<<b, 256, 0, s>>>(gr, n_groups, len, pairs, cls + kClsBins);
-    k_class_scan<<<1, 64, 0, s>>>(cls, pairs);
-    k_class_scatter<<<b, 256, 0, s>>>(gr, n_groups, len, pairs, cls);
+    k_class_count<<<b, 256, 0, s>>>(gr, n_groups, len, stats, cls + kClsBins);
+    k_class_scan<<<1, 64, 0, s>>>(cls, stats);
+    k_class_scatter<<<b, 256, 0, s>>>(gr, n_groups, len, stats, cls, items);
+}
+
+void launch_force_merge(const ForceBox &box, hipStream_t s)
+{
+    if (box.n_items) k_force_merge<<<(box.n_items + 3) / 4, 256, 0, s>>>(box);
+}
+
+void launch_force_merge_multi(const ForceBox *boxes, int nb, uint32_t most_items, hipStream_t s)
+{
+    if (most_items) k_force_merge_multi<<<dim3((most_items + 3) / 4, nb), 256, 0, s>>>(boxes);
 }
 
 // Two workgroups of eight waves per CU (four waves per SIMD, 92 of the 160 KB of LDS).
-void launch_force_f32(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s)
+static unsigned force_blocks(uint32_t n_work, uint32_t cap) { return n_work < cap ? n_work : cap; }
+
+void launch_force_f32(const ForceBox &box, int n_cu, hipStream_t s)
 {
-    if (!n_groups) return;
-    const uint32_t cap = 2u * (uint32_t)n_cu;
-    k_force_f32<<<n_groups < cap ? n_groups : cap, 64 * kForceWaves, kForceLds, s>>>(box);
+    if (!box.n_groups) return;
+    k_force_f32<<<force_blocks(box.n_groups + box.n_items, 2u * (uint32_t)n_cu), 64 * kForceWaves,
+                  kForceLds, s>>>(box);
 }
 
-void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_groups, int n_cu,
+void launch_force_f32_multi(const ForceBox *boxes, int nb, uint32_t n_work, int n_cu,
                             hipStream_t s)
 {
-    if (!n_groups) return;
-    const uint32_t cap = 2u * (uint32_t)n_cu;
-    k_force_f32_multi<<<n_groups < cap ? n_groups : cap, 64 * kForceWaves, kForceLds, s>>>(boxes,
-                                                                                          nb);
+    if (!n_work) return;
+    k_force_f32_multi<<<force_blocks(n_work, 2u * (uint32_t)n_cu), 64 * kForceWaves, kForceLds,
+                        s>>>(boxes, nb);
 }
 
 void launch_force_prep(const ForceBox &box, hipStream_t s)

@@ -220,7 +220,7 @@ template <bool TABLE>
 struct Policy64 {
     static constexpr int kWaves = 16, kTilesAt = TABLE ? (int)kTable64 : 0,
                          kTileBytes = kTile64 * 32;
-    static constexpr uint32_t kQueueAt = kClsQueue, kSplitEnd = kClsEnd16;
+    static constexpr uint32_t kQueueAt = kClsQueue;
     static constexpr bool kAdd = false;
     static constexpr uint32_t kLds = kTilesAt + kWaves * kTileBytes;
     using Frame = Frame64;
@@ -253,14 +253,17 @@ struct Policy64 {
         const int J = 64 / S, lgJ = 31 - __builtin_clz(J);
         const int slot = lane & (S - 1), stream = lane / S;
         uint32_t kept = 0;
+        uint32_t ent[kRounds64];
+        if (j0 < j1) fetch_entries<kRounds64>(list, j0, j1, ent);
+        double4 pos[K];
+        load_chunk<K>(ps, f, n_i, slot, S, pos);
         double xi[K], yi[K], zi[K];
         ChunkBox C;
         {
             float fx[K], fy[K], fz[K];
 #pragma unroll
             for (int k = 0; k < K; ++k) {
-                const uint32_t i = slot + S * k;
-                const double4 v = rel_f64(ps[f + (i < n_i ? i : 0)], F); // idle: the first again
+                const double4 v = rel_f64(pos[k], F);
                 xi[k] = v.x;
                 yi[k] = v.y;
                 zi[k] = v.z;
@@ -274,8 +277,6 @@ struct Policy64 {
         // the table's first edge, kept in a vector register
         uint32_t base = (uint32_t)(1023 - kTab64Oct + kTab64Exp) << 20;
         asm("" : "+v"(base));
-        uint32_t ent[kRounds64];
-        if (j0 < j1) fetch_entries<kRounds64>(list, j0, j1, ent);
         for (uint32_t jb = j0; jb < j1; jb += kTile64) {
             const int nt = load_tile_f64(tile, ent, jb, j1, J, B.nd, F, C);
             kept += (uint32_t)nt;
@@ -290,34 +291,31 @@ struct Policy64 {
                                                ay, az);
             wave_lds_sync();
         }
-        add_streams<K>(ax, ay, az, S);
         return kept;
     }
 
-    static __device__ __forceinline__ void group(char *tiles, int wave, bool split,
-                                                 const ForceBox &B, uint32_t g)
+    static __device__ __forceinline__ void group(char *tile, const ForceBox &B, const Piece &w)
     {
-        const GroupRead R(B, g);
-        const uint32_t node = B.gr.node[g];
+        const GroupRead R(B, w.g);
+        const uint32_t node = B.gr.node[w.g];
         const ForceParams &fp = B.fp;
-        const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
-        constexpr double c = 1.0 / (1u << kTab64Oct);
+        const ForceUnits &U = B.units;
         Frame F;
-        F.wrap = R.wraps(fp);
+        F.wrap = R.wraps(B);
         const double half_side = 0.5 * ldexp(fp.L, -(int)uni((uint32_t)B.nd.level[node]));
         F.pair_wrap = __ballot(!(half_side + fp.rc < 0.5 * fp.L)) != 0;
         F.L = fp.L;
         F.xg0 = uni(R.xg[0]);
         F.xg1 = uni(R.xg[1]);
         F.xg2 = uni(R.xg[2]);
-        F.k2 = uni(kTop64 * (1.0 - c) * inv_len * inv_len);
-        F.c = kTop64 * c;
+        F.k2 = U.k2;
+        F.c = kTop64 / (1u << kTab64Oct);
         F.eps2 = fp.eps2;
         F.inv_eta = fp.inv_eta;
-        F.inv = uni((float)inv_len);
-        F.len = uni((float)(fp.L * inv_len));
-        F.scale = TABLE ? uni(inv_len * inv_len * inv_len) : 1.0;
-        finish_group<Policy64>(tiles, wave, split, B, g, R, F);
+        F.inv = U.inv_f;
+        F.len = U.len_f;
+        F.scale = U.scale;
+        finish_group<Policy64>(tile, B, w, R, F);
     }
 };
 
@@ -329,11 +327,11 @@ __global__ __launch_bounds__(64 * Policy64<TABLE>::kWaves, 4) void k_force_f64(F
 
 } // namespace
 
-void launch_force_f64(const ForceBox &box, uint32_t n_groups, int n_cu, hipStream_t s)
+void launch_force_f64(const ForceBox &box, int n_cu, hipStream_t s)
 {
-    if (!n_groups) return;
-    const uint32_t cap = (uint32_t)n_cu;
-    const uint32_t blocks = n_groups < cap ? n_groups : cap;
+    if (!box.n_groups) return;
+    const uint32_t cap = (uint32_t)n_cu, work = box.n_groups + box.n_items;
+    const uint32_t blocks = work < cap ? work : cap;
     constexpr int threads = 64 * Policy64<true>::kWaves;
     if (box.tab64_hi)
         k_force_f64<true><<<blocks, threads, Policy64<true>::kLds, s>>>(box);

@@ -41,31 +41,57 @@ __device__ __forceinline__ void node_second_moments(const NodeArrays &nd,
     const double X = cu.x, Y = cu.y, Z = cu.z;
     double q[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
     const uint32_t nch = nd.nchild[u];
+    // as for the moments, everything is read before any of it is added (in order, zeros for what
+    // there is not)
     if (nch == 0) {
-        const uint32_t f = nd.first[u], e = f + nd.count[u];
-        for (uint32_t k = f; k < e; ++k) {
-            const double4 r = ps[k];
-            const double dx = r.x - X, dy = r.y - Y, dz = r.z - Z;
-            q[0] += r.w * dx * dx;
-            q[1] += r.w * dy * dy;
-            q[2] += r.w * dz * dz;
-            q[3] += r.w * dx * dy;
-            q[4] += r.w * dx * dz;
-            q[5] += r.w * dy * dz;
+        const uint32_t f = nd.first[u], n = nd.count[u];
+        for (uint32_t k = 0; k < n; k += 4) {
+            double4 r[4];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                r[j] = ps[f + (k + j < n ? k + j : k)];
+                if (k + j >= n) r[j].w = 0.0;
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const double dx = r[j].x - X, dy = r[j].y - Y, dz = r[j].z - Z, m = r[j].w;
+                q[0] += m * dx * dx;
+                q[1] += m * dy * dy;
+                q[2] += m * dz * dz;
+                q[3] += m * dx * dy;
+                q[4] += m * dx * dz;
+                q[5] += m * dy * dz;
+            }
         }
     } else {
         const uint32_t cf = nd.child_first[u];
-        for (uint32_t c = cf; c < cf + nch; ++c) {
-            const double4 cc = nd.nsrc[c];
-            const double m = cc.w;
-            const double dx = cc.x - X, dy = cc.y - Y, dz = cc.z - Z;
-            const double *qc = Q + 6 * (size_t)c;
-            q[0] += qc[0] + m * dx * dx;
-            q[1] += qc[1] + m * dy * dy;
-            q[2] += qc[2] + m * dz * dz;
-            q[3] += qc[3] + m * dx * dy;
-            q[4] += qc[4] + m * dx * dz;
-            q[5] += qc[5] + m * dy * dz;
+#pragma unroll
+        for (uint32_t h = 0; h < 8; h += 4) {
+            double4 cc[4];
+            double qc[4][6];
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const bool there = h + j < nch;
+                const uint32_t c = cf + (there ? h + j : 0);
+                cc[j] = nd.nsrc[c];
+#pragma unroll
+                for (int a = 0; a < 6; ++a) qc[j][a] = Q[6 * (size_t)c + a];
+                if (!there) {
+                    cc[j].w = 0.0;
+#pragma unroll
+                    for (int a = 0; a < 6; ++a) qc[j][a] = 0.0;
+                }
+            }
+#pragma unroll
+            for (uint32_t j = 0; j < 4; ++j) {
+                const double dx = cc[j].x - X, dy = cc[j].y - Y, dz = cc[j].z - Z, m = cc[j].w;
+                q[0] += qc[j][0] + m * dx * dx;
+                q[1] += qc[j][1] + m * dy * dy;
+                q[2] += qc[j][2] + m * dz * dz;
+                q[3] += qc[j][3] + m * dx * dy;
+                q[4] += qc[j][4] + m * dx * dz;
+                q[5] += qc[j][5] + m * dy * dz;
+            }
         }
     }
     for (int a = 0; a < 6; ++a) Q[6 * (size_t)u + a] = q[a];
@@ -170,7 +196,7 @@ __device__ __forceinline__ void quad_pairs(const QuadCell &s, const float *xi, c
 struct PolicyQuad {
     static constexpr int kWaves = kQuadWaves, kTilesAt = 0,
                          kTileBytes = kQuadTile * (int)sizeof(QuadCell);
-    static constexpr uint32_t kQueueAt = kClsQuadQueue, kSplitEnd = kClsEnd16;
+    static constexpr uint32_t kQueueAt = kClsQuadQueue;
     static constexpr bool kAdd = true;
     using Frame = FrameF32;
 
@@ -205,21 +231,22 @@ struct PolicyQuad {
         const int lane = __lane_id();
         const int J = 64 / S, lgJ = 31 - __builtin_clz(J);
         const int slot = lane & (S - 1), stream = lane / S;
+        constexpr uint32_t kRound = 64 * kQuadFetch;
+        uint32_t ent[kQuadFetch];
+        uint32_t jb = j0, nq = 0;
+        if (j0 < j1) fetch_entries<kQuadFetch>(list, j0, j1, ent);
+        double4 pos[K];
+        load_chunk<K>(ps, f, n_i, slot, S, pos);
         float xi[K], yi[K], zi[K];
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            const uint32_t i = slot + S * k;
-            const float4 v = rel_f32(ps[f + (i < n_i ? i : 0)], F); // idle slots repeat the first
+            const float4 v = rel_f32(pos[k], F);
             xi[k] = v.x;
             yi[k] = v.y;
             zi[k] = v.z;
             ax[k] = ay[k] = az[k] = 0.0;
         }
         const ChunkBox C = chunk_box<K>(xi, yi, zi, S);
-        constexpr uint32_t kRound = 64 * kQuadFetch;
-        uint32_t ent[kQuadFetch];
-        uint32_t jb = j0, nq = 0;
-        if (j0 < j1) fetch_entries<kQuadFetch>(list, j0, j1, ent);
         for (;;) {
             while (nq < 64 && jb < j1) {
 #pragma unroll
@@ -287,15 +314,13 @@ struct PolicyQuad {
                 az[k] += (double)tz[k];
             }
         }
-        add_streams<K>(ax, ay, az, S);
         return 0;
     }
 
-    static __device__ __forceinline__ void group(char *tiles, int wave, bool split,
-                                                 const ForceBox &B, uint32_t g)
+    static __device__ __forceinline__ void group(char *tile, const ForceBox &B, const Piece &w)
     {
-        const GroupRead R(B, g);
-        finish_group<PolicyQuad>(tiles, wave, split, B, g, R, frame_f32(B, R));
+        const GroupRead R(B, w.g);
+        finish_group<PolicyQuad>(tile, B, w, R, frame_f32(B, R));
     }
 };
 static_assert(kQuadTile % 16 == 0, "J divides a tile");
@@ -600,12 +625,13 @@ void build_quad_table(double eps_over_rcut, double c, std::vector<float> &coef, 
     }
 }
 
-void launch_quad(const ForceBox &box, uint32_t n_groups, int fp64, int n_cu, hipStream_t s)
+void launch_quad(const ForceBox &box, int fp64, int n_cu, hipStream_t s)
 {
+    const uint32_t n_groups = box.n_groups;
     if (!n_groups) return;
     if (!fp64) {
-        const uint32_t cap = (uint32_t)n_cu;
-        k_quad_f32<<<n_groups < cap ? n_groups : cap, 64 * kQuadWaves, kQuadLds, s>>>(box);
+        const uint32_t cap = (uint32_t)n_cu, work = n_groups + box.n_items;
+        k_quad_f32<<<work < cap ? work : cap, 64 * kQuadWaves, kQuadLds, s>>>(box);
     } else if (box.rec64)
         k_quad_f64<1><<<n_groups, 64, 0, s>>>(box.nd, box.gr, n_groups, box.off, box.len,
                                               box.entries, box.ps, box.pidx, box.moments, box.fp,

@@ -80,6 +80,9 @@ struct treepm_ctx {
     uint32_t n_groups = 0;
     unsigned min_group_level = 0, max_group = 0;
     // lists
+    Buf items, rows; // pieces of the groups too long for a wave, and their sums
+    uint32_t n_items = 0;
+    uint64_t n_rows = 0;
     Buf off, glen, wctr, scan64, entries, wstats, overflow, gcells, cls, kept, kept_sum, out[3], bnd, runs;
     int last_force_prec = -1;
     uint64_t n_entries = 0;
@@ -856,6 +859,8 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
         return hip_fail(c, e, "group stats");
     if ((e = reserve(c->cls, (kClsLists + (size_t)G + 1) * 4)) != hipSuccess)
         return hip_fail(c, e, "group classes");
+    if ((e = reserve(c->items, max_force_items((uint64_t)c->n, G) * sizeof(ForceItem))) != hipSuccess)
+        return hip_fail(c, e, "group pieces");
     const treepm_params &P = c->prm;
     const bool open = P.opening == TREEPM_OPEN_DISTANCE;
     const double th_lo = std::min(P.theta_max, P.theta / std::sqrt(0.46));
@@ -931,6 +936,7 @@ WalkBox walk_box(treepm_ctx *c, const BoxWalk &bw, uint32_t g0)
     w.slots = bw.slots;
     w.stats = c->wstats.as<unsigned long long>();
     w.cls = c->cls.as<uint32_t>();
+    w.items = c->items.as<ForceItem>();
     return w;
 }
 
@@ -964,7 +970,7 @@ int walk_two_pass(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, bool ahead)
 
 // Statistics and force classes of the lists, queued with the flags for the host.
 struct WalkResults {
-    unsigned long long hs[4] = {};
+    unsigned long long hs[6] = {};
     unsigned hov = 0;
     uint32_t seq = 0;
 };
@@ -992,7 +998,8 @@ int post_walk_results(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResul
     GroupArrays gr = groups_view(c);
     uint32_t *len = c->glen.as<uint32_t>(), *cls = c->cls.as<uint32_t>();
     launch_walk_stats(gr, G, len, c->gcells.as<uint32_t>(), c->wstats.as<unsigned long long>(), s);
-    launch_classify(gr, G, len, c->wstats.as<unsigned long long>() + 2, cls, s);
+    launch_classify(gr, G, len, c->wstats.as<unsigned long long>(), cls,
+                    c->items.as<ForceItem>(), s);
     return fetch_post(c, s, &wr.seq, {&wr.hov, c->overflow.p, sizeof wr.hov},
                       {wr.hs, c->wstats.p, sizeof wr.hs});
 }
@@ -1023,6 +1030,8 @@ int settle_walk(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr
     c->n_entries = wr.hs[0] + wr.hs[1];
     c->walk_hint = c->n_entries;
     c->walk_hint_max = wr.hs[3];
+    c->n_rows = wr.hs[4];
+    c->n_items = (uint32_t)wr.hs[5];
     c->walk_hint_groups = bw.G;
     for (int i = 0; i < 3; ++i) c->st[i] = wr.hs[i];
     return TREEPM_OK;
@@ -1096,7 +1105,7 @@ size_t treepm_internal_ctx_bytes(const treepm_ctx *c)
                         &c->g_cg[2], &c->g_hg[0], &c->g_hg[1], &c->g_hg[2], &c->g_xg[0],
                         &c->g_xg[1], &c->g_xg[2], &c->g_lo[0], &c->g_lo[1], &c->g_lo[2],
                         &c->g_hi[0], &c->g_hi[1], &c->g_hi[2], &c->g_misc, &c->off, &c->glen, &c->wctr, &c->scan64,
-                        &c->entries, &c->wstats, &c->overflow, &c->gcells, &c->cls,
+                        &c->items, &c->rows, &c->entries, &c->wstats, &c->overflow, &c->gcells, &c->cls,
                         &c->kept, &c->kept_sum, &c->out[0], &c->out[1], &c->out[2], &c->bnd, &c->runs,
                         &c->tab, &c->tab64};
     size_t t = 0;
@@ -1232,7 +1241,7 @@ TREEPM_API int treepm_destroy(treepm_ctx *c)
                   &c->g_cg[1], &c->g_cg[2], &c->g_hg[0], &c->g_hg[1], &c->g_hg[2], &c->g_xg[0],
                   &c->g_xg[1], &c->g_xg[2], &c->g_lo[0], &c->g_lo[1], &c->g_lo[2], &c->g_hi[0],
                   &c->g_hi[1], &c->g_hi[2], &c->g_misc, &c->off, &c->glen, &c->wctr, &c->scan64, &c->entries,
-                  &c->wstats, &c->overflow, &c->rec, &c->kept, &c->kept_sum, &c->gcells, &c->cls, &c->out[0],
+                  &c->items, &c->rows, &c->wstats, &c->overflow, &c->rec, &c->kept, &c->kept_sum, &c->gcells, &c->cls, &c->out[0],
                   &c->out[1], &c->out[2], &c->bnd, &c->runs, &c->pm_mass, &c->pm_grid,
                   &c->pm_green, &c->pm_tw, &c->pm_mx, &c->pm_stage, &c->pm_cells, &c->pm_slots,
                   &c->n_q, &c->step_min, &c->tab, &c->tab64, &c->bdesc};
@@ -1441,10 +1450,26 @@ ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
     F.moments = c->n_q.as<double>();
     F.rec = rec;
     F.rec64 = rec64;
+    F.items = c->items.as<ForceItem>();
+    F.n_items = c->n_items;
+    F.rows = c->rows.as<double>();
     if (c->prm.precision == TREEPM_FP64 && c->tab64_ok) {
         F.tab64_hi = c->tab64.as<double>();
         F.tab64_lo = reinterpret_cast<const float *>(F.tab64_hi +
                                                      (size_t)kTab64F64 * kTab64Entries);
+    }
+    const double inv_len = 0.5 * fp.inv_eta; // 1 / r_cut
+    F.units.inv_L = 1.0 / fp.L;
+    F.units.rc_wrap = fp.rc * (1.0 + 0x1p-10);
+    F.units.inv_f = (float)inv_len;
+    F.units.len_f = (float)(fp.L * inv_len);
+    if (c->prm.precision == TREEPM_FP32) {
+        const double lam = std::sqrt(1.0 - (double)c->ftab.c);
+        F.units.inv = inv_len * lam;
+        F.units.scale = inv_len * inv_len / lam;
+    } else {
+        F.units.k2 = std::ldexp(1.0, kTab64Exp) * (1.0 - std::ldexp(1.0, -kTab64Oct)) * inv_len * inv_len;
+        F.units.scale = F.tab64_hi ? inv_len * inv_len * inv_len : 1.0;
     }
     F.n_groups = c->n_groups;
     F.pair_sum = c->kept_sum.as<unsigned long long>();
@@ -1496,6 +1521,7 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     {
         hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
         if (e == hipSuccess) e = reserve(c->kept_sum, 64);
+        if (e == hipSuccess && c->n_rows) e = reserve(c->rows, c->n_rows * 24);
         if (e != hipSuccess) return hip_fail(c, e, "force statistics");
     }
     ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
@@ -1507,11 +1533,14 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     const ForceBox F = force_box(c, fp, rec, rec64);
     launch_force_prep(F, s);
     if (P.precision == TREEPM_FP32) {
-        launch_force_f32(F, c->n_groups, c->n_cu, s);
+        launch_force_f32(F, c->n_cu, s);
     } else
-        launch_force_f64(F, c->n_groups, c->n_cu, s);
-    if (P.quadrupole)
-        launch_quad(F, c->n_groups, P.precision == TREEPM_FP64, c->n_cu, s);
+        launch_force_f64(F, c->n_cu, s);
+    // the FP32 quadrupole kernel adds to the rows of pieces, the FP64 one to whole records
+    const bool quad64 = P.quadrupole && P.precision == TREEPM_FP64;
+    if (P.quadrupole && !quad64) launch_quad(F, 0, c->n_cu, s);
+    launch_force_merge(F, s);
+    if (quad64) launch_quad(F, 1, c->n_cu, s);
     launch_force_out(rec, out_prec, (int64_t)c->n, dst[0], dst[1], dst[2], kick_dt, c->n_groups,
                      fp.pairs, F.pair_sum, s);
     HIPCHK(c, hipGetLastError());
@@ -1736,6 +1765,7 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         if ((rc = ensure_table(c, s))) return rc;
         hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
         if (e == hipSuccess) e = reserve(c->kept_sum, 64);
+        if (e == hipSuccess && c->n_rows) e = reserve(c->rows, c->n_rows * 24);
         if (e != hipSuccess) return hip_fail(c, e, "force statistics");
         dst[b] = {ax[b], ay[b], az[b]};
         if (mem_kind == TREEPM_HOST)
@@ -1764,20 +1794,23 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         int k1 = k;
         uint32_t groups = 0;
         for (; k1 < nb && cs[order[k1]]->tab_key == cs[order[k]]->tab_key; ++k1)
-            groups += cs[order[k1]]->n_groups;
+            groups += cs[order[k1]]->n_groups + cs[order[k1]]->n_items;
         launch_force_f32_multi(dev + k, k1 - k, groups, lead->n_cu, s);
         k = k1;
     }
     int64_t most = 0;
+    uint32_t most_items = 0;
     for (int b = 0; b < nb; ++b) {
         treepm_ctx *c = cs[b];
         const ForceBox &F = fb[b];
         if (c->prm.quadrupole)
-            launch_quad(F, c->n_groups, 0, c->n_cu, s);
+            launch_quad(F, 0, c->n_cu, s);
         most = std::max(most, c->n);
+        most_items = std::max(most_items, c->n_items);
         c->last_force_prec = TREEPM_FP32;
         c->ev_valid[1] = c->ev_valid[2] = false;
     }
+    launch_force_merge_multi(dev, nb, most_items, s);
     launch_force_out_multi(dev, nb, most, s);
     HIPCHK(lead, hipGetLastError());
     if (mem_kind == TREEPM_HOST)
