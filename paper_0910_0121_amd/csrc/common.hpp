@@ -313,18 +313,14 @@ constexpr uint32_t kClsLists = kClsBins + kXcds * 64;
 // one segment go straight to the records, those of several to rows of three doubles, base +
 // seg (particles of the chunk) + i.
 struct ForceItem {
-    uint32_t g, chunk, seg_segs, base; // seg_segs: segment, and from bit 16 their number
+    uint32_t g, chunk, seg_segs, base; // seg_segs: segment, from bit 8 their number, from 16 s
 };
 constexpr uint32_t kPieceChunk = 128;
 constexpr uint32_t kMaxSegs = 64;
-// Entries per segment of a list of L in `segs` segments (whole rounds of 64).
-__host__ __device__ __forceinline__ uint32_t piece_entries(uint32_t L, uint32_t segs)
-{
-    return ((L + segs - 1) / segs + 63) / 64 * 64;
-}
+constexpr uint32_t kSegMin = 64; // a segment is kSegMin 2^s entries
 // An upper bound on the pieces of a box of n particles in G groups: a group in pieces has more
-// than a 2^14th of the pairs, and its chunks are pieces of at least 2^t pairs but for the last of
-// each list and one per chunk.
+// than a 2^14th of the pairs, and its chunks are pieces of at least 2^(t-1) pairs but for the last
+// of each list.
 __host__ __device__ __forceinline__ size_t max_force_items(uint64_t n, uint64_t G)
 {
     const uint64_t by_pairs = (1ull << 17) + n / kPieceChunk;
@@ -334,14 +330,15 @@ __host__ __device__ __forceinline__ size_t max_force_items(uint64_t n, uint64_t 
 // Parts and longest-first order of the groups (len: list lengths; stats: the walk's, of which the
 // third is the box's interactions) into cls (kClsLists + n_groups words), and the pieces of long
 // ones into items (max_force_items); the rows they need and their number into stats[4] and [5].
-// The bins and those two have been cleared (launch_walk_init).
+// The bins and stats have been cleared (launch_walk_init).
 void launch_classify(GroupArrays gr, uint32_t n_groups, const uint32_t *len,
                      unsigned long long *stats, uint32_t *cls, ForceItem *items, hipStream_t s);
 // launch_walk_stats and launch_classify in one launch of a workgroup (boxes of at most
 // kOneBlockGroups groups), which then publishes the overflow word and the six statistics to
 // the box's mailbox.
 void launch_walk_results_one(const WalkBox &box, hipStream_t s);
-void launch_walk_results_multi(const WalkBox *boxes, int nb, hipStream_t s); // device array
+// (boxes in device memory; most: the most groups of one)
+void launch_walk_results_multi(const WalkBox *boxes, int nb, uint32_t most, hipStream_t s);
 // A box's units in the force kernels, from the host so that no wave works them out (and holds them in
 // vector registers): FP32, x' = x inv, sums times scale; FP64, u = r^2 k2 + c, sums times scale
 // (1 without a table), and inv_f = 1 / r_cut and len_f = L / r_cut for the cull; 1 / L; r_cut with

@@ -346,7 +346,7 @@ __device__ __forceinline__ float pair_u(const float4 s, float xi, float yi, floa
 struct Piece {
     uint32_t g;
     bool whole;
-    uint32_t chunk, seg, segs, base; // see ForceItem
+    uint32_t chunk, seg, segs, log2_per, base; // see ForceItem
 };
 
 // The piece once its group's frame is known.
@@ -360,7 +360,7 @@ __device__ __forceinline__ void finish_group(char *tile, const ForceBox &B, cons
     if (!w.whole) {
         i0 = w.chunk * kPieceChunk;
         i1 = n_g - i0 < kPieceChunk ? n_g : i0 + kPieceChunk;
-        const uint32_t per = piece_entries(Lg, w.segs);
+        const uint32_t per = kSegMin << w.log2_per;
         j0 = w.seg * per;
         j1 = j0 + per < Lg ? j0 + per : Lg;
         if (w.segs > 1) rows = B.rows + 3 * ((uint64_t)w.base + (uint64_t)w.seg * (i1 - i0));
@@ -478,7 +478,7 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
     uint32_t *const ctr = bx[0].cls + P::kQueueAt;
     uint32_t size = 0, part = xcd, have = kXcds, next = 0;
     for (;;) { // one place where a group is taken, whichever way it was found
-        Piece w{0, false, 0, 0, 1, 0};
+        Piece w{0, false, 0, 0, 1, 0, 0};
         Item it{0, at};
         bool dealt = false;
         if (pieces && at >= hi) {
@@ -514,8 +514,9 @@ __device__ __forceinline__ void force_body(const ForceBox *bx, int n_boxes)
         const ForceBox &B = MULTI ? bx[uni(it.box)] : bx[0];
         if (pieces) {
             const ForceItem f = B.items[it.k];
-            w = Piece{uni(f.g), false, uni(f.chunk), uni(f.seg_segs & 0xffffu),
-                      uni(f.seg_segs >> 16), uni(f.base)};
+            const uint32_t ss = uni(f.seg_segs);
+            w = Piece{uni(f.g), false, uni(f.chunk), ss & 0xffu, ss >> 8 & 0xffu, ss >> 16,
+                      uni(f.base)};
             at += blocks * P::kWaves;
         } else {
             w.g = uni(B.cls[B.cls[kClsStarts + (dealt ? xcd : part)] + it.k]);

@@ -331,7 +331,7 @@ __global__ __launch_bounds__(256) void k_pairwise_f32(int64_t n_i, const double 
     }
 }
 
-// Queues of the force.  Group g belongs to XCD part p = floor(8 g / G) (contiguous key ranges) and,
+// Queues of the force.  Group g belongs to XCD part p, about 8 g / G (contiguous key ranges), and,
 // unless it is taken in pieces (more than 2^t pairs, see ForceItem), to a cost bucket: the octave
 // of its pairs n_g L_g if it has at least 2^kHeavyCost of them or an eighth of 2^t, one bucket for
 // all others.  The bins (p, bucket) are laid out with the costliest first, so each part lists its
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(256) void k_pairwise_f32(int64_t n_i, const double 
 // before them.  Three passes: count the bins, scan them into cursors and part starts, scatter.
 // Blocks take kClassifyItems * 256 consecutive groups and aggregate their bins in LDS first.
 //
-// Why pieces, and of 2^t: a wave alone would hold up the end of the launch, and a device of 4096
-// waves needs several items for each.  Shared by the eight waves of a workgroup instead, which
+// Why pieces: a wave alone would hold up the end of the launch, and a device of 4096 waves needs
+// several items for each.  Shared by the eight waves of a workgroup instead, which
 // meet in LDS twice per chunk (groups from a 16384th of the pairs on), a group's waves get a
 // few dozen list entries each and wait most of the time: boxes of 250,007, 500,009 and 700,001
 // particles ran at 0.92, 0.89 and 1.05 pairs per ps against 1.96 in the 256^3 box.
@@ -349,31 +349,49 @@ constexpr int kClassifyItems = 8;
 constexpr int kCostBuckets = 64;
 constexpr uint32_t kHeavyCost = 17;
 constexpr uint32_t kMinPiece = 13;
-constexpr uint32_t kPieceShift = 13;
 constexpr int kBins = kXcds * kCostBuckets;
+// Up to this many groups, one per thread, k_walk_results writes the queues itself; for more a
+// launch of many workgroups follows, which the host does not wait for (one workgroup took 57 us to
+// write the 20,000 pieces of a box of 700,001).
+constexpr uint32_t kWriteHere = 1024;
 
-// t of the box: pairs = its interactions.
+// t of the box (pairs: its interactions): 6,550 to 13,100 times 2^t in all.  Pieces of half of that
+// to that many pairs each are two to four for every wave.  Force calls of 250,007, 700,001 and, with
+// quadrupoles, 1,000,003 particles (12,100, 15,300 and 13,700 times 2^t): 1.17, 1.31 and 0.71
+// pairs per ps, with 2^t doubled 1.07, 1.53 and 0.82.
 __device__ __forceinline__ uint32_t piece_log2(unsigned long long pairs)
 {
-    const uint32_t lg = 63u - (uint32_t)__clzll((long long)(pairs | 1ull));
-    return lg > kMinPiece + kPieceShift ? lg - kPieceShift : kMinPiece;
+    const unsigned long long v = (pairs >> 13) + (pairs >> 15);
+    const uint32_t lg = 63u - (uint32_t)__clzll((long long)(v | 1ull));
+    return lg > kMinPiece ? lg : kMinPiece;
 }
 
-// Segments of a chunk of n_c particles against a list of L entries, about 2^t pairs each.
-__device__ __forceinline__ uint32_t chunk_segs(uint32_t n_c, uint32_t L, uint32_t t)
+// ceil(log2(v)), v >= 1.
+__device__ __forceinline__ uint32_t log2_up(uint32_t v) { return v > 1 ? 32u - (uint32_t)__clz((int)(v - 1)) : 0u; }
+
+// s of the segments of a chunk of n_c particles against a list of L entries: the longest of at most
+// 2^t pairs, but not so short that there are more than kMaxSegs.  (Powers of two: the queues of a
+// box are made by one compute unit or a few, and integer divisions were most of it.)
+__device__ __forceinline__ uint32_t seg_log2(uint32_t n_c, uint32_t L, uint32_t t)
 {
-    const uint64_t m = ((uint64_t)n_c * L + (1ull << t) - 1) >> t;
-    const uint32_t segs = m < 1 ? 1u : m < kMaxSegs ? (uint32_t)m : kMaxSegs;
-    const uint32_t per = piece_entries(L, segs);
-    return per ? (L + per - 1) / per : 1u;
+    const uint32_t by_pairs = log2_up(n_c) + 6u, rounds = (L + kSegMin - 1) / kSegMin;
+    const uint32_t few = log2_up((rounds + kMaxSegs - 1) / kMaxSegs);
+    const uint32_t s = t > by_pairs ? t - by_pairs : 0u;
+    return s > few ? (s < 24u ? s : 24u) : few;
+}
+__device__ __forceinline__ uint32_t seg_count(uint32_t L, uint32_t s)
+{
+    const uint32_t rounds = (L + kSegMin - 1) / kSegMin;
+    return rounds ? (rounds - 1 >> s) + 1 : 1u;
 }
 
 // The pieces of a group: its chunks, all alike but the last, in segments.
 struct Pieces {
-    uint32_t chunks, segs, last_n, last_segs;
+    uint32_t chunks, s, segs, last_n, last_s, last_segs;
     __device__ __forceinline__ Pieces(uint32_t n_g, uint32_t L, uint32_t t)
-        : chunks((n_g + kPieceChunk - 1) / kPieceChunk), segs(chunk_segs(kPieceChunk, L, t)),
-          last_n(n_g - (chunks - 1) * kPieceChunk), last_segs(chunk_segs(last_n, L, t))
+        : chunks((n_g + kPieceChunk - 1) / kPieceChunk), s(seg_log2(kPieceChunk, L, t)),
+          segs(seg_count(L, s)), last_n(n_g - (chunks - 1) * kPieceChunk),
+          last_s(seg_log2(last_n, L, t)), last_segs(seg_count(L, last_s))
     {
     }
     __device__ __forceinline__ uint32_t items() const { return (chunks - 1) * segs + last_segs; }
@@ -386,8 +404,8 @@ struct Pieces {
     {
         for (uint32_t c = 0; c < chunks; ++c) {
             const bool last = c + 1 == chunks;
-            const uint32_t m = last ? last_segs : segs;
-            for (uint32_t q = 0; q < m; ++q) *out++ = ForceItem{g, c, q | m << 16, base};
+            const uint32_t m = last ? last_segs : segs, ss = m << 8 | (last ? last_s : s) << 16;
+            for (uint32_t q = 0; q < m; ++q) *out++ = ForceItem{g, c, q | ss, base};
             if (m > 1) base += (last ? last_n : kPieceChunk) * m;
         }
     }
@@ -397,7 +415,9 @@ struct Pieces {
 __device__ __forceinline__ uint32_t cost_bin(uint32_t g, uint32_t n_groups, uint32_t n_g,
                                              uint32_t L_g, uint32_t t)
 {
-    const uint32_t part = (uint32_t)(((uint64_t)g * kXcds) / n_groups);
+    // any rounding will do, as long as the parts follow the groups' order
+    const uint32_t p = (uint32_t)((float)g * ((float)kXcds / (float)n_groups));
+    const uint32_t part = p < kXcds ? p : kXcds - 1;
     const uint64_t cost = (uint64_t)n_g * L_g;
     const uint32_t lg = 63u - (uint32_t)__clzll((long long)(cost | 1ull));
     const uint32_t least = t - 3 < kHeavyCost ? t - 3 : kHeavyCost;
@@ -409,11 +429,11 @@ __device__ __forceinline__ bool in_pieces(uint32_t bin) { return bin % kCostBuck
 
 __global__ __launch_bounds__(256) void k_class_count(GroupArrays gr, uint32_t n_groups,
                                                      const uint32_t *__restrict__ len,
-                                                     const unsigned long long *stats,
-                                                     uint32_t *hist)
+                                                     unsigned long long *stats, uint32_t *hist)
 {
-    __shared__ uint32_t s_cnt[kBins];
+    __shared__ uint32_t s_cnt[kBins], s_rows;
     for (int i = threadIdx.x; i < kBins; i += 256) s_cnt[i] = 0;
+    if (threadIdx.x == 0) s_rows = 0;
     __syncthreads();
     const uint32_t t = piece_log2(stats[2]);
     const uint32_t base = blockIdx.x * (256u * kClassifyItems);
@@ -422,11 +442,17 @@ __global__ __launch_bounds__(256) void k_class_count(GroupArrays gr, uint32_t n_
         const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
         if (g >= n_groups) continue;
         const uint32_t n_g = gr.count[g], L = len[g], bin = cost_bin(g, n_groups, n_g, L, t);
-        atomicAdd(&s_cnt[bin], in_pieces(bin) ? Pieces(n_g, L, t).items() : 1u);
+        if (in_pieces(bin)) {
+            const Pieces p(n_g, L, t);
+            atomicAdd(&s_cnt[bin], p.items());
+            atomicAdd(&s_rows, p.rows());
+        } else
+            atomicAdd(&s_cnt[bin], 1u);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += 256)
         if (s_cnt[i]) atomicAdd(&hist[i], s_cnt[i]);
+    if (threadIdx.x == 0 && s_rows) atomicAdd(&stats[4], (unsigned long long)s_rows);
 }
 
 // By one wave, lane = cost bucket: the bins' counts to cursors (in place; bins in global memory
@@ -466,20 +492,22 @@ __global__ __launch_bounds__(64) void k_class_scan(uint32_t *cls, unsigned long 
     if (threadIdx.x == 0) stats[5] = items;
 }
 
-__global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t n_groups,
-                                                       const uint32_t *__restrict__ len,
-                                                       unsigned long long *stats, uint32_t *cls,
-                                                       ForceItem *__restrict__ items)
+// Block b's groups, ITEMS per thread; rows are handed out through stats[6].
+template <int ITEMS>
+__device__ __forceinline__ void class_scatter(const GroupArrays &gr, uint32_t n_groups,
+                                              const uint32_t *__restrict__ len,
+                                              unsigned long long *stats, uint32_t *cls,
+                                              ForceItem *__restrict__ items, uint32_t b)
 {
     __shared__ uint32_t s_cnt[kBins], s_rows, s_base;
     for (int i = threadIdx.x; i < kBins; i += 256) s_cnt[i] = 0;
-    if (threadIdx.x == 0) s_rows = 0;
+    if (threadIdx.x == 0) s_rows = s_base = 0;
     __syncthreads();
     const uint32_t t = piece_log2(stats[2]);
-    const uint32_t base = blockIdx.x * (256u * kClassifyItems);
-    uint32_t bin[kClassifyItems], loc[kClassifyItems], row[kClassifyItems];
+    const uint32_t base = b * (256u * ITEMS);
+    uint32_t bin[ITEMS], loc[ITEMS], row[ITEMS];
 #pragma unroll
-    for (int r = 0; r < kClassifyItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
         bin[r] = ~0u;
         row[r] = 0;
@@ -499,10 +527,10 @@ __global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t 
     for (int i = threadIdx.x; i < kBins; i += 256)
         if (s_cnt[i]) s_cnt[i] = atomicAdd(&cls[kClsBins + i], s_cnt[i]);
     if (threadIdx.x == 0 && s_rows)
-        s_base = (uint32_t)atomicAdd(&stats[4], (unsigned long long)s_rows);
+        s_base = (uint32_t)atomicAdd(&stats[6], (unsigned long long)s_rows);
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < kClassifyItems; ++r) {
+    for (int r = 0; r < ITEMS; ++r) {
         if (bin[r] == ~0u) continue;
         const uint32_t g = base + (uint32_t)r * 256u + threadIdx.x;
         if (in_pieces(bin[r]))
@@ -511,6 +539,24 @@ __global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t 
             cls[s_cnt[bin[r]] + loc[r]] = g;
     }
 }
+__global__ __launch_bounds__(256) void k_class_scatter(GroupArrays gr, uint32_t n_groups,
+                                                       const uint32_t *__restrict__ len,
+                                                       unsigned long long *stats, uint32_t *cls,
+                                                       ForceItem *__restrict__ items)
+{
+    class_scatter<kClassifyItems>(gr, n_groups, len, stats, cls, items, blockIdx.x);
+}
+// After k_walk_results, for boxes whose groups it has only counted.
+__global__ __launch_bounds__(256) void k_walk_scatter(WalkBox B)
+{
+    class_scatter<1>(B.gr, B.n_groups, B.len, B.stats, B.cls, B.items, blockIdx.x);
+}
+__global__ __launch_bounds__(256) void k_walk_scatter_multi(const WalkBox *__restrict__ bx)
+{
+    const WalkBox &B = bx[blockIdx.y];
+    if (B.n_groups > kWriteHere && blockIdx.x * 256u < B.n_groups)
+        class_scatter<1>(B.gr, B.n_groups, B.len, B.stats, B.cls, B.items, blockIdx.x);
+}
 
 // Adds up the rows of the chunks whose list was taken in segments, a wave per chunk (that of its
 // first segment), in the order of the segments, and stores the particles' records.
@@ -518,8 +564,8 @@ __device__ __forceinline__ void force_merge(const ForceBox &B, uint32_t k)
 {
     if (k >= B.n_items) return;
     const ForceItem f = B.items[k];
-    const uint32_t segs = f.seg_segs >> 16;
-    if ((f.seg_segs & 0xffffu) != 0 || segs < 2) return;
+    const uint32_t segs = f.seg_segs >> 8 & 0xffu;
+    if ((f.seg_segs & 0xffu) != 0 || segs < 2) return;
     const uint32_t n_g = B.gr.count[f.g], i0 = f.chunk * kPieceChunk;
     const uint32_t n_c = n_g - i0 < kPieceChunk ? n_g - i0 : kPieceChunk;
     const uint32_t first = B.gr.first[f.g] + i0;
@@ -607,7 +653,7 @@ __global__ __launch_bounds__(256) void k_force_out_multi(const ForceBox *__restr
         sum_pairs(B.n_groups, B.fp.pairs, B.pair_sum, blockIdx.x - nb, stat_blocks);
 }
 
-// Statistics, queue bins, queues and their publication by one workgroup (see the class kernels
+// Statistics, queue bins, queues (kWriteHere) and their publication by one workgroup (see the class kernels
 // and launch_walk_stats for each part).
 __device__ __forceinline__ void walk_results(const WalkBox &B)
 {
@@ -618,12 +664,27 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
     const uint32_t tid = threadIdx.x, G = B.n_groups;
     const int lane = tid & 63, wave = tid >> 6;
     unsigned long long v[4] = {0, 0, 0, 0}; // cells, particles, pairs, longest list
-    for (uint32_t g = tid; g < G; g += kThreads) {
-        const unsigned long long l = B.len[g], c = B.gcells[g];
-        v[0] += c;
-        v[1] += l - c;
-        v[2] += l * B.gr.count[g];
-        v[3] = l > v[3] ? l : v[3];
+    // all of a thread's groups at once, kept for the two passes below: one memory latency
+    constexpr int kPer = (int)(kOneBlockGroups / kThreads);
+    // neighbouring lanes take groups an eighth of the box apart, of different parts: atomics of
+    // a wave on one bin in LDS are served one by one
+    const uint32_t eighth = (G + 7) / 8, g0 = (tid & 7) * eighth, g_end = min(G, g0 + eighth);
+    auto group = [&](int r) { return g0 + (tid >> 3) + (uint32_t)r * (kThreads / 8); };
+    uint32_t n_g[kPer], len[kPer], cells[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const uint32_t g = group(r), at = g < g_end ? g : 0u;
+        n_g[r] = B.gr.count[at];
+        len[r] = B.len[at];
+        cells[r] = B.gcells[at];
+    }
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        if (group(r) >= g_end) continue;
+        v[0] += cells[r];
+        v[1] += len[r] - cells[r];
+        v[2] += (unsigned long long)len[r] * n_g[r];
+        v[3] = len[r] > v[3] ? len[r] : v[3];
     }
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) {
@@ -645,29 +706,45 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
     }
     __syncthreads();
     const uint32_t t = piece_log2(tot[2]);
-    for (uint32_t g = tid; g < G; g += kThreads) {
-        const uint32_t n_g = B.gr.count[g], L = B.len[g], k = cost_bin(g, G, n_g, L, t);
-        atomicAdd(&bin[k], in_pieces(k) ? Pieces(n_g, L, t).items() : 1u);
+    uint32_t rows = 0;
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const uint32_t g = group(r);
+        if (g >= g_end) continue;
+        const uint32_t k = cost_bin(g, G, n_g[r], len[r], t);
+        if (in_pieces(k)) {
+            const Pieces p(n_g[r], len[r], t);
+            atomicAdd(&bin[k], p.items());
+            rows += p.rows();
+        } else
+            atomicAdd(&bin[k], 1u);
     }
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) rows += __shfl_xor(rows, d, 64);
+    if (lane == 0 && rows) atomicAdd(&s_rows, rows);
     __syncthreads();
     if (wave == 0) {
         const uint32_t items = scan_bins(bin, B.cls);
-        if (lane == 0) tot[5] = items;
+        if (lane == 0) {
+            B.stats[4] = tot[4] = s_rows;
+            B.stats[5] = tot[5] = items;
+            s_rows = 0;
+        }
     }
     __syncthreads();
-    for (uint32_t g = tid; g < G; g += kThreads) {
-        const uint32_t n_g = B.gr.count[g], L = B.len[g], k = cost_bin(g, G, n_g, L, t);
-        if (in_pieces(k)) {
-            const Pieces p(n_g, L, t);
-            const uint32_t at = atomicAdd(&bin[k], p.items());
-            p.write(g, B.items + at, atomicAdd(&s_rows, p.rows()));
-        } else
-            B.cls[atomicAdd(&bin[k], 1u)] = g;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        B.stats[4] = tot[4] = s_rows;
-        B.stats[5] = tot[5];
+    if (G <= kWriteHere) {
+        const uint32_t g = group(0); // kWriteHere groups: one each
+        if (g < g_end) {
+            const uint32_t k = cost_bin(g, G, n_g[0], len[0], t);
+            if (in_pieces(k)) {
+                const Pieces p(n_g[0], len[0], t);
+                const uint32_t at = atomicAdd(&bin[k], p.items());
+                p.write(g, B.items + at, atomicAdd(&s_rows, p.rows()));
+            } else
+                B.cls[atomicAdd(&bin[k], 1u)] = g;
+        }
+    } else { // the cursors for the launch that follows
+        for (uint32_t i = tid; i < kBins; i += kThreads) B.cls[kClsBins + i] = bin[i];
     }
     if (tid == 0 && B.mailbox) {
         uint32_t *m = B.mailbox;
@@ -758,11 +835,15 @@ void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s)
 void launch_walk_results_one(const WalkBox &box, hipStream_t s)
 {
     k_walk_results<<<1, 1024, 0, s>>>(box);
+    if (box.n_groups > kWriteHere)
+        k_walk_scatter<<<(box.n_groups + 255) / 256, 256, 0, s>>>(box);
 }
 
-void launch_walk_results_multi(const WalkBox *boxes, int nb, hipStream_t s)
+void launch_walk_results_multi(const WalkBox *boxes, int nb, uint32_t most, hipStream_t s)
 {
-    if (nb) k_walk_results_multi<<<nb, 1024, 0, s>>>(boxes);
+    if (!nb) return;
+    k_walk_results_multi<<<nb, 1024, 0, s>>>(boxes);
+    if (most > kWriteHere) k_walk_scatter_multi<<<dim3((most + 255) / 256, nb), 256, 0, s>>>(boxes);
 }
 
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,

@@ -566,10 +566,10 @@ __global__ __launch_bounds__(256) void k_walk_stats(GroupArrays gr, uint32_t n_g
 __device__ __forceinline__ void walk_init(const WalkBox &B)
 {
     for (uint32_t i = threadIdx.x; i < kClsLists; i += blockDim.x) B.cls[i] = 0u;
-    if (threadIdx.x < 6) B.stats[threadIdx.x] = 0ull;
-    if (threadIdx.x == 6) *B.overflow = 0u;
-    if (threadIdx.x == 7) B.off[B.n_groups] = 0ull;
-    if (threadIdx.x == 8 && B.slots.size) *B.slots.next = 0ull;
+    if (threadIdx.x < 8) B.stats[threadIdx.x] = 0ull;
+    if (threadIdx.x == 8) *B.overflow = 0u;
+    if (threadIdx.x == 9) B.off[B.n_groups] = 0ull;
+    if (threadIdx.x == 10 && B.slots.size) *B.slots.next = 0ull;
 }
 __global__ __launch_bounds__(512) void k_walk_init(WalkBox box) { walk_init(box); }
 __global__ __launch_bounds__(512) void k_walk_init_multi(const WalkBox *__restrict__ bx)

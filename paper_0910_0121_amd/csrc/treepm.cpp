@@ -1735,7 +1735,9 @@ int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
                 ++k;
             }
         if ((rc = upload(lead, s, small, 3 * kRun, &dev))) return rc;
-        launch_walk_results_multi(dev, (int)small.size(), s);
+        uint32_t most = 0;
+        for (const WalkBox &w : small) most = std::max(most, w.n_groups);
+        launch_walk_results_multi(dev, (int)small.size(), most, s);
     }
     for (int b = 0; b < nb; ++b)
         if (!results_by_one(cs[b]) && (rc = post_walk_results(cs[b], s, bw[b], wr[b]))) return rc;
