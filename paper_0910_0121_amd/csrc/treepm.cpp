@@ -664,23 +664,40 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     int run_bits = c->sort_wide ? 24 : sort_run_bits(n);
     sort_high(run_bits);
     unsigned fl[6] = {};
-    if ((rc = fetch(c, s, {fl, flags, sizeof fl}))) return rc;
-    if (fl[0] & kFlagNonFinite)
-        return fail(c, TREEPM_ERR_ARG, "non-finite position or mass, or a mass <= 0");
-    if (fl[0] & kFlagRange)
-        return fail(c, TREEPM_ERR_RANGE, "a position lies outside [0, L); wrap it first");
-    while (fl[5]) {
-        if (run_bits == 24) {
-            radix_sort(n, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
-                       c->key_alt.as<uint64_t>(), c->idx_alt.as<uint32_t>(),
-                       c->hist.as<uint32_t>(), scan_tmp, s);
-            break;
+    auto check_input = [&]() -> int {
+        if (fl[0] & kFlagNonFinite)
+            return fail(c, TREEPM_ERR_ARG, "non-finite position or mass, or a mass <= 0");
+        if (fl[0] & kFlagRange)
+            return fail(c, TREEPM_ERR_RANGE, "a position lies outside [0, L); wrap it first");
+        return TREEPM_OK;
+    };
+    auto complete_sort = [&]() -> int {
+        while (fl[5]) {
+            if (run_bits == 24) {
+                radix_sort(n, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
+                           c->key_alt.as<uint64_t>(), c->idx_alt.as<uint32_t>(),
+                           c->hist.as<uint32_t>(), scan_tmp, s);
+                fl[5] = 0;
+                break;
+            }
+            c->sort_wide = true;
+            run_bits = 24;
+            fill_u32(sflags, 2, 0u, s);
+            sort_high(run_bits);
+            const int r = fetch(c, s, {fl, flags, sizeof fl});
+            if (r) return r;
         }
-        c->sort_wide = true;
-        run_bits = 24;
-        fill_u32(sflags, 2, 0u, s);
-        sort_high(run_bits);
+        return TREEPM_OK;
+    };
+    // A smaller box does not wait for these: its gather and its octree's counting pass follow at
+    // once (they stay in bounds on whatever order the sort has left), the flags come with the
+    // counts, and if the sort was not complete both are launched again.
+    const bool flat = n >= 1 && P.n_leaf - 1 <= kTreeWin;
+    const bool ahead = flat && n < kSideGather;
+    if (!ahead) {
         if ((rc = fetch(c, s, {fl, flags, sizeof fl}))) return rc;
+        if ((rc = check_input())) return rc;
+        if ((rc = complete_sort())) return rc;
     }
     // The gather into key order reads only the sort's indices, and the octree passes only the
     // keys: the gather runs on a side stream beside them, and the moments wait for it.
@@ -711,7 +728,6 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     uint32_t *cnt_total = cnt + (N + 1);
     uint32_t *cnt_tmp = cnt_total + 16;
     NodeArrays nd{};
-    const bool flat = n >= 1 && P.n_leaf - 1 <= kTreeWin;
     if (flat) {
         const uint32_t nblk = tree_blocks(n);
         hipError_t e = reserve(c->tree_sl, (size_t)n * sizeof(uint32_t));
@@ -720,11 +736,24 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
         if (e != hipSuccess) return hip_fail(c, e, "tree build buffers");
         uint32_t *blk = c->tree_blk.as<uint32_t>();
         uint32_t *tot = blk + (size_t)nblk * (kMaxLevel + 1);
-        launch_tree_levels(c->key.as<uint64_t>(), (uint32_t)n, P.n_leaf,
-                           c->tree_sl.as<uint32_t>(), blk, tot, c->gstart.as<uint32_t>(),
-                           c->gflag.as<uint32_t>(), s);
         uint32_t per_level[kMaxLevel + 1] = {};
-        if ((rc = fetch(c, s, {per_level, tot, sizeof per_level}))) return rc;
+        for (;;) {
+            launch_tree_levels(c->key.as<uint64_t>(), (uint32_t)n, P.n_leaf,
+                               c->tree_sl.as<uint32_t>(), blk, tot, c->gstart.as<uint32_t>(),
+                               c->gflag.as<uint32_t>(), s);
+            if (!ahead) {
+                if ((rc = fetch(c, s, {per_level, tot, sizeof per_level}))) return rc;
+                break;
+            }
+            if ((rc = fetch(c, s, {per_level, tot, sizeof per_level}, {fl, flags, sizeof fl})))
+                return rc;
+            if ((rc = check_input())) return rc;
+            if (!fl[5]) break;
+            if ((rc = complete_sort())) return rc;
+            fill_u32(sflags, 2, 0u, s);
+            launch_permute(n, c->idx.as<uint32_t>(), c->rec.as<double4>(), c->psrc.as<double4>(),
+                           c->pm_mx.as<unsigned long long>(), s);
+        }
         TreeOffsets to{};
         uint64_t acc = 0;
         c->max_level = 0;
