@@ -26,16 +26,17 @@ METRIC = "particles/s + interactions/s at θ=0.5, FP32 vs FP64 path; ensemble p5
 K_PP = 38  # flops per pair interaction (FMA = 2, add/mul/rsqrt/sqrt = 1, selects = 0)
 FP32_VECTOR_PEAK_TFLOPS = 157.3
 HBM_PEAK_GBS = 8000.0
-# Algorithmic HBM bytes of one particle-mesh call: per mesh point, clearing and filling the
-# fixed-point mass mesh (8 + 8), five FFT passes (16 + 16 + 16 + 16 + 12), the differences
-# (4 read + 16 written) and one read of the force mesh (16); per particle, the key-ordered
-# record read by the max-mass pass, the assignment and the interpolation (3 x 32), its index
-# (4) and three FP32 outputs (12).
-PM_BYTES_PER_POINT = 8 + 8 + 16 + 16 + 16 + 16 + 12 + 4 + 16 + 16
-PM_BYTES_PER_PARTICLE = 3 * 32 + 4 + 12
+# Algorithmic HBM bytes of one particle-mesh call: per mesh point, the fixed-point mass written
+# (8), five FFT passes over the half spectrum (8 + 4, 4 + 4, 4 + 4, 4 + 4, 4 + 4) and one read of
+# the potential (4); per particle, the key-ordered record read by the assignment and the
+# interpolation (2 x 32), its index (4), the record of its force written and read (2 x 16) and
+# three FP32 outputs (12).
+PM_BYTES_PER_POINT = 8 + 12 + 8 + 8 + 8 + 8 + 4
+PM_BYTES_PER_PARTICLE = 2 * 32 + 4 + 2 * 16 + 12
 FP64_VECTOR_PEAK_TFLOPS = 78.6
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "force_f32_traffic.json")
-FORCE_SRC = os.path.join(ROOT, "paper_0910_0121_amd", "csrc", "k_force.hip")
+FORCE_SRC = [os.path.join(ROOT, "paper_0910_0121_amd", "csrc", f)
+             for f in ("k_force.hip", "force_common.hpp")]
 
 
 def log(msg):
@@ -95,8 +96,11 @@ def measured_traffic(n_crit, workload):
     try:
         with open(TRAFFIC_FILE) as f:
             t = json.load(f)
-        with open(FORCE_SRC, "rb") as f:
-            sha = hashlib.sha1(f.read()).hexdigest()
+        h = hashlib.sha1()
+        for name in FORCE_SRC:
+            with open(name, "rb") as f:
+                h.update(f.read())
+        sha = h.hexdigest()
         for run in [t] + t.get("other_runs", []):
             if (run.get("source_sha1") == sha and run.get("n_crit") == n_crit
                     and run.get("workload", "").startswith(workload)):

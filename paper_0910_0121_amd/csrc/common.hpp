@@ -130,8 +130,8 @@ void launch_emit(NodeArrays nd, const uint32_t *bnd, uint32_t lo, uint32_t hi, i
                  uint32_t base, const uint32_t *cnt, double L, hipStream_t s);
 // The octree straight from the sorted keys (n >= 1, n_leaf - 1 <= kTreeWin): the same nodes in
 // the same order as the level-by-level split.  launch_tree_levels writes per particle the
-// levels of the nodes that start there and its leaf's count (sl, n words), per block of tree_blocks(n) the counts
-// per level (blk, kMaxLevel + 1 rows of tree_blocks(n) words, left as exclusive prefixes) and
+// levels of the nodes that start there and its leaf's count (sl, n words), per block of
+// tree_blocks(n) the counts per level (blk, kMaxLevel + 1 rows of tree_blocks(n) words, left as exclusive prefixes) and
 // the nodes per level into tot (kMaxLevel + 1 words).  With off[] from tot, launch_tree_emit
 // writes every node but nchild and the internal counts (left to the moments with derive = 1).
 constexpr int kTreeWin = 256;
@@ -192,8 +192,8 @@ void launch_walk_emit(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, Wal
                       const Slots &slots, unsigned *overflow, uint32_t *gcells, hipStream_t s);
 // One pass: n_waves waves write the lists into chunks of `chunk` entries taken from the
 // pool entries[0, pool_cap); a group is walked into the wave's current chunk if at least
-// `reserve` entries are left there, else (or if it did not fit) into a fresh chunk.  Sets bit 4 of *overflow if a list or the pool ran out of room
-// (the lists are then incomplete).  counters holds kWalkCounterWords words (8-byte aligned).
+// `reserve` entries are left there, else (or if it did not fit) into a fresh chunk.  Sets bit 4 of
+// *overflow if a list or the pool ran out of room (the lists are then incomplete).  counters holds kWalkCounterWords words (8-byte aligned).
 constexpr uint32_t kWalkCounterWords = (kXcds + 1) * kQueueStride;
 void launch_walk_pool(const WalkNode *wn, GroupArrays gr, uint32_t n_groups, WalkParams wp,
                       uint32_t n_waves, uint64_t pool_cap, uint64_t chunk, uint64_t reserve,
@@ -299,8 +299,8 @@ void build_quad_table(double eps_over_rcut, double c, std::vector<float> &coef, 
 // Layout of the queue buffer (u32 words): the kXcds + 1 part starts of the whole groups (absolute
 // word positions in the buffer), the number of pieces, the queue counters of the force kernel and
 // of the quadrupole kernel (every wave reads the starts for each group: on the first counter's
-// line they cost the 256^3 box 5 % of its force), the (part, cost bucket) cursors, then the group ids, each part's
-// longest first.
+// line they cost the 256^3 box 5 % of its force), the (part, cost bucket) cursors, then the group
+// ids, each part's longest first.
 constexpr uint32_t kClsStarts = 0;
 constexpr uint32_t kClsItems = kClsStarts + kXcds + 1;
 constexpr uint32_t kClsQueue = kQueueStride;
@@ -373,11 +373,11 @@ struct ForceBox {
     int64_t n;
     void *out[3]; // launch_force_out_multi: the float outputs
 };
-// Empties a box's force and quadrupole queues and zeroes its pairs (which split groups add to) and *pair_sum
-// (which the output pass adds to).
+// Empties a box's force and quadrupole queues and zeroes its pairs (which the pieces add to) and
+// *pair_sum (which the output pass adds to).
 void launch_force_prep(const ForceBox &box, hipStream_t s);
 void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s); // device array
-// A persistent launch of at most two workgroups per CU over the box's queues.
+// A persistent launch of at most two workgroups per CU over the box's pieces and queues.
 void launch_force_f32(const ForceBox &box, int n_cu, hipStream_t s);
 // The same over nb <= kMaxBatch boxes with equal tables (descriptors in device memory; the
 // queues of all boxes are taken as one, through the first box's counters; n_work: groups and

@@ -1,5 +1,5 @@
 // Parts shared by the FP32 and FP64 force kernels: the persistent workgroups and their queues,
-// the split of a group into chunks of particles, and the reduction and output of their sums.
+// the split of a group into chunks of particles, its pieces, and the output of their sums.
 // A kernel is a policy P: kWaves (waves per workgroup), kTilesAt and kTileBytes (the waves' LDS
 // tiles), kQueueAt (its queue counters), kAdd (sums are added to the records and no pairs are
 // counted), Frame (a group's origin and units, with `scale`, the factor of the sums), load_table,

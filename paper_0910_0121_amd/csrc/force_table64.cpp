@@ -3,12 +3,12 @@
 // As in the FP32 table, G(s) = g(2 sqrt(s)) / (s + e2)^(3/2), s = (r / r_cut)^2, is the fifth
 // power of p, given in polynomial pieces over u = c + (1 - c) s, 64 per octave, in t = u - a with
 // a the piece's lower edge; here of degree 6, and with u and t scaled by 2^18, so that the floats
-// among the coefficients stay in range for the narrowest pieces and the widest.  Per piece p is expanded about the middle as a
-// power series (s = s_m + h x, x in [-1, 1]): R = 2 sqrt(s), eq. (2) as a polynomial of R, split
+// among the coefficients stay in range for the narrowest pieces and the widest.  Per piece p is expanded
+// about the middle as a power series (s = s_m + h x, x in [-1, 1]): R = 2 sqrt(s), eq. (2) as a polynomial of R, split
 // into even and odd powers (R^2 = 4 s is linear in x), and the fractional powers from their
 // differential equation; the series of degree 9 is brought to degree 6 by subtracting Chebyshev
-// polynomials, which leaves a relative error below 1e-17 in p.  c = 2^-24: g carries (8/5) R^3 = 12.8 s^(3/2), which no polynomial follows
-// at s = 0, and a first piece of width 2^-30 keeps what is missed there below 1e-16.
+// polynomials, which leaves a relative error below 1e-17 in p.  c = 2^-24: g carries
+// (8/5) R^3 = 12.8 s^(3/2), which no polynomial follows at s = 0, and a first piece of width 2^-30 keeps what is missed there below 1e-16.
 // The three highest coefficients are rounded to float, from the top down, each time putting the
 // rounding error times the best lower-degree approximation of that power back into the lower
 // coefficients: what remains is below 2e-18 of p.

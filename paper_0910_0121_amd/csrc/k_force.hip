@@ -3,21 +3,21 @@
 //
 //   a_i += m_j d g(|d| / eta) / (|d|^2 + eps^2)^(3/2),   d = x_j - x_i.
 //
-// One 64-lane wavefront per group (or, in the FP32 path, eight of them for a group that would
-// hold up the launch): the group's i-particles sit in registers and its list is streamed
-// through LDS in tiles; lanes of one stream read the same tile entry (an LDS broadcast) and
-// accumulate in registers.  List entries whose source lies at least r_cut from the group's
-// bounding box are dropped while a tile is loaded (every pair they form adds exactly zero).
+// One 64-lane wavefront takes a group, or a piece of a long one (some of its particles by a
+// segment of its list): the i-particles sit in registers, a chunk of them at a time, and the list
+// is streamed through LDS in tiles; lanes of one stream read the same tile entry (an LDS
+// broadcast) and accumulate in registers.  List entries whose source lies at least r_cut from the
+// chunk's bounding box are dropped while a tile is loaded (every pair they form adds exactly zero).
 //
 // FP32 path (Section 3.1.1): positions are passed relative to the group's cube centre x_g,
 // x_i - x_g and wrap(x_j - x_g), each difference taken in FP64 and then rounded to FP32, so
 // the rounding error of the subtraction scales with the group size, not the box.  The pair
 // law is read from a per-box table of quadratic pieces (see the FP32 section).  The per-tile
-// FP32 partial sums are added up in FP64.  Persistent workgroups take the groups from per-XCD
-// queues, the heaviest groups first.  Each particle's result
-// leaves the kernels as one record in the caller's order, which a last pass splits into the
-// output arrays or applies as a kick.
-// The FP64 kernel is in k_force64.hip; the queues and the reduction, which they share, in
+// FP32 partial sums are added up in FP64.  The waves of persistent workgroups take the pieces,
+// dealt beforehand, and then the whole groups from per-XCD queues, the heaviest first.  Each
+// particle's result leaves the kernels as one record in the caller's order, which a last pass
+// splits into the output arrays or applies as a kick.
+// The FP64 kernel is in k_force64.hip; what they share (chunks, pieces and queues) in
 // force_common.hpp.
 #include "force_common.hpp"
 
@@ -27,7 +27,6 @@
 
 namespace tpm {
 namespace {
-
 
 // FP32 path.  Lengths are in units of r_cut / lam, lam = sqrt(1 - c), and the pair law is
 //   a_i = 1/(r_cut^2 lam) sum_j m_j d'_ij G(s),  G(s) = g(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2),
@@ -234,10 +233,10 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
 }
 
 // What bounds it (256^3 clustered box, n_crit 256): the LDS pipe is busy 93 % of the time and
-// the vector units 80 %; without the table reads the call takes 8.7 ms, with conflict-free ones
-// 10.2, as it is 10.4 (12.4 with a kernel per blocking factor, a table of 16-byte entries and
-// queue counters side by side: 311,000 groups taken through counters in one cache line alone
-// cost about 12 ms, at 40 ns each).  700,001 particles: the whole step 3.41 -> 1.53 ms.
+// the vector units 80 %.  The call takes 10.2 ms, 1.9 pairs per ps (12.4 with a kernel per blocking
+// factor, a table of 16-byte entries and queue counters side by side: 311,000 groups taken
+// through counters in one cache line alone cost about 12 ms, at 40 ns each); without the table
+// reads it would be 8.7.  700,001 particles, build, walk and force: 3.44 -> 1.06 ms.
 struct PolicyF32 {
     static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
     static constexpr uint32_t kQueueAt = kClsQueue;
@@ -341,10 +340,10 @@ __global__ __launch_bounds__(256) void k_pairwise_f32(int64_t n_i, const double 
 // Blocks take kClassifyItems * 256 consecutive groups and aggregate their bins in LDS first.
 //
 // Why pieces: a wave alone would hold up the end of the launch, and a device of 4096 waves needs
-// several items for each.  Shared by the eight waves of a workgroup instead, which
-// meet in LDS twice per chunk (groups from a 16384th of the pairs on), a group's waves get a
-// few dozen list entries each and wait most of the time: boxes of 250,007, 500,009 and 700,001
-// particles ran at 0.92, 0.89 and 1.05 pairs per ps against 1.96 in the 256^3 box.
+// several items for each.  Shared by the eight waves of a workgroup instead, which meet in LDS
+// twice per chunk, a group's waves get a few dozen list entries each and wait most of the time:
+// boxes of 250,007, 500,009 and 700,001 particles ran at 0.92, 0.89 and 1.05 pairs per ps against
+// 1.14, 1.18 and 1.47 with pieces (1.9 in the 256^3 box).
 constexpr int kClassifyItems = 8;
 constexpr int kCostBuckets = 64;
 constexpr uint32_t kHeavyCost = 17;
@@ -653,8 +652,8 @@ __global__ __launch_bounds__(256) void k_force_out_multi(const ForceBox *__restr
         sum_pairs(B.n_groups, B.fp.pairs, B.pair_sum, blockIdx.x - nb, stat_blocks);
 }
 
-// Statistics, queue bins, queues (kWriteHere) and their publication by one workgroup (see the class kernels
-// and launch_walk_stats for each part).
+// Statistics, queue bins, queues (kWriteHere) and their publication by one workgroup (see the
+// class kernels and launch_walk_stats for each part).
 __device__ __forceinline__ void walk_results(const WalkBox &B)
 {
     constexpr int kThreads = 1024, kWaves = kThreads / 64;

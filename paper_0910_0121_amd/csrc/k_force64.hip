@@ -3,8 +3,8 @@
 // relative to x_g are FP64 differences (nearest image once per entry, or per pair when the
 // group's cube plus r_cut reaches half the box), and the pair law is
 //   * read from a table (force_table64.cpp) where the softening allows one: G(s) = p^5 with p a
-//     polynomial of degree 6 in t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the piece's lower
-//     edge, which is u with its low mantissa bits cleared, so t is exact; or
+//     polynomial of degree 6 in t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the
+//     piece's lower edge, which is u with its low mantissa bits cleared, so t is exact; or
 //   * evaluated pair by pair for smaller eps: (r^2 + eps^2)^(-1/2) and r^(-1) from the hardware
 //     estimate refined by two Newton steps, and eq. (2) in a form with no cancellation: for R < 1,
 //     g = 1 + R^3 (-8/5 + R^2 (8/5 + R (-1/2 + R (-12/35 + 3R/20)))), and for R >= 1,
@@ -16,8 +16,8 @@
 // 16-byte read costs two to three times as much per byte once the lanes spread over pieces),
 // and the three highest, whose share of p is at most 7e-9, are floats and are summed in FP32: 26
 // cycles of LDS time a pair against 32, and two conversions less.  Measured on the 128^3 clustered
-// box (2.1 million particles): 3.4 ms, LDS and vector units both busy three quarters of it; pair by
-// pair, with one group a wave, it was 8.2 ms.
+// box (2.1 million particles): 3.0 ms, LDS and vector units both busy three quarters of it or more;
+// pair by pair, with one group a wave, it was 8.2 ms.
 #include "force_common.hpp"
 
 namespace tpm {

@@ -82,8 +82,8 @@ constexpr int kAssignThreads = 256;
 
 // Particles per workgroup at most.  250,007 clustered particles on a 64^3 mesh are 570 workgroups
 // of up to 4096, whose fullest decide: assignment and interpolation take 28 us each, 17 with
-// workgroups of up to 1024; 16.8 million have
-// enough with 4096, and halves of that only add slots to the gather (0.16 to 0.18 ms).
+// workgroups of up to 1024; 16.8 million have enough with 4096, and halves of that only add slots
+// to the gather (0.16 to 0.18 ms).
 static uint32_t cell_chunk(int64_t n) { return n < (1 << 22) ? 1024u : 4096u; }
 
 __device__ __forceinline__ uint32_t spread3_10(uint32_t v) // 10 bits -> every third bit

@@ -129,9 +129,9 @@ __global__ __launch_bounds__(1024) void k_second_moments_levels(NodeArrays nd,
 // Each wave first collects its range's cell entries in an LDS queue, 128 list entries at a
 // time, and gathers centre and moments for 64 cells at once: on the lists of a clustered box most
 // entries are particles, and a tile per 64 list entries would be mostly empty.  Measured on
-// 1,000,003 particles (theta 0.7, groups of up to 256): 0.67 ms, of which instruction issue is
-// 0.3 and the rest waits for cells (80 bytes each, gathered) and for the launch's end; with a
-// workgroup of one wave per group and the laws evaluated, 1.54 ms.
+// 1,000,003 particles (theta 0.7, groups of up to 256): 0.54 ms, of which instruction issue is
+// 0.3 and the rest waits for cells (80 bytes each, gathered); with a workgroup of one wave per
+// group and the laws evaluated, 1.54 ms.
 constexpr int kQuadWaves = 16; // per workgroup: one workgroup, four waves per SIMD
 constexpr int kQuadFetch = 2;  // list entries fetched per lane and round
 struct QuadCell {

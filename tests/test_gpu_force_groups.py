@@ -1,6 +1,6 @@
 """FP32 force at the edges of its work split: groups of every size at which the kernel's chunks
-of particles change (1, 4, 8, 16, ... up to groups of several chunks), shared by a workgroup or
-run by single waves, and pair-law tables from the smallest to the largest softening.
+of particles change (1, 4, 8, 16, ... up to groups of several chunks), in pieces or run by
+single waves, and pair-law tables from the smallest to the largest softening.
 
 Boxes are isolated clumps, one per level-2 cell, so the groups are exactly the clumps.  Bound per
 particle as in the parity suite: |da_i| <= 8 u B_i (rounding of the FP32 relative positions and

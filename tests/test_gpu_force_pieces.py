@@ -1,4 +1,4 @@
-"""Groups that are taken in pieces (more than a 2^15th of the box's pairs, at least 2^12): chunks of
+"""Groups that are taken in pieces (about a 2^13th of the box's pairs or more, at least 2^13): chunks of
 128 particles by segments of 64 list entries or more, at the edges of both: groups of one chunk and
 of dozens, lists shorter than a round and of many segments, for the FP32, FP64 and quadrupole
 kernels, alone and through shared launches.  Bounds as in the parity suite.
