@@ -640,8 +640,8 @@ __global__ __launch_bounds__(256) void k_pm_green(int N, double L, double eta,
 //     F_a = -[(2/3)(phi(i+1) - phi(i-1)) - (1/12)(phi(i+2) - phi(i-2))] / h,
 // and each particle's 27 points come from that.  The weights and the order of the sums are those
 // of a plain per-particle gather.
-// 256^3 mesh, 16.8 million clustered particles: 0.59 ms, of which the boxes take 0.2 and the
-// particles 0.39, half of that for scattering their 16-byte records (with the records in key
+// 256^3 mesh, 16.8 million clustered particles: 0.55 ms, of which the boxes take 0.2 and the
+// particles 0.35, half of that for scattering their 16-byte records (with the records in key
 // order 0.39 in all; stored around the caches 0.92); with the force mesh written out and read
 // back, 0.77.  The three components are arrays of their own: a 16-byte read per lane takes
 // two to three times the LDS time of three 4-byte ones once the lanes spread over points.
@@ -656,9 +656,11 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
     __shared__ float lds[3 * kBoxWords];
     static_assert(3 * kBoxWords >= kPhi * kPhi * kPhi, "the potential fits");
     float *const pot = lds, *const fx = lds, *const fy = lds + kBoxWords, *const fz = fy + kBoxWords;
-    // each XCD takes a contiguous run of chunks (cells in Morton order): the chunks of one
-    // cell and its neighbours then read their boxes through one L2
-    const uint32_t item = xcd_block(blockIdx.x, gridDim.x);
+    // an XCD takes runs of 32 chunks (cells in Morton order): the chunks of one cell and its
+    // neighbours then read their boxes through one L2.  With one run per XCD over the whole grid,
+    // whose end has no chunks, the XCDs' shares differ: 578 us at 256^3 against 549 (557 in plain
+    // order, 562 with one run each over the chunks alone, 558 with runs of 8).
+    const uint32_t item = xcd_run(blockIdx.x, gridDim.x);
     if (item >= item_start[ncells]) return; // the same for the whole workgroup
     const uint32_t m = item_cell(item_start, ncells, item);
     const uint32_t first = cell_start[m] + (item - item_start[m]) * chunk;
