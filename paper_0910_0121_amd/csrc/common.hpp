@@ -64,15 +64,15 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n)
     const uint32_t q = n / kXcds, r = n % kXcds, x = b % kXcds;
     return x * q + (x < r ? x : r) + b / kXcds;
 }
-// The same within every kXcds * kXcdRun blocks: an XCD takes runs of kXcdRun neighbours, dealt in
-// turn, for work that is uneven along the order or ends before the grid does.  The blocks past the
-// last whole deal keep their numbers.
-constexpr uint32_t kXcdRun = 32;
+// The same within every kXcds * RUN blocks: an XCD takes runs of RUN neighbours, dealt in turn, for
+// work that is uneven along the order or ends before the grid does.  The blocks past the last
+// whole deal keep their numbers.
+template <uint32_t RUN>
 __device__ __forceinline__ uint32_t xcd_run(uint32_t b, uint32_t n)
 {
-    constexpr uint32_t kDeal = kXcds * kXcdRun;
+    constexpr uint32_t kDeal = kXcds * RUN;
     if (b >= n / kDeal * kDeal) return b;
-    return b / kDeal * kDeal + b % kXcds * kXcdRun + b % kDeal / kXcds;
+    return b / kDeal * kDeal + b % kXcds * RUN + b % kDeal / kXcds;
 }
 
 // Work counters that many waves share lie kQueueStride words (256 bytes) apart: atomics on one

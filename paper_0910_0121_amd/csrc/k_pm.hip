@@ -660,7 +660,7 @@ __global__ __launch_bounds__(kAssignThreads) void k_pm_interp(
     // neighbours then read their boxes through one L2.  With one run per XCD over the whole grid,
     // whose end has no chunks, the XCDs' shares differ: 578 us at 256^3 against 549 (557 in plain
     // order, 562 with one run each over the chunks alone, 558 with runs of 8).
-    const uint32_t item = xcd_run(blockIdx.x, gridDim.x);
+    const uint32_t item = xcd_run<32>(blockIdx.x, gridDim.x);
     if (item >= item_start[ncells]) return; // the same for the whole workgroup
     const uint32_t m = item_cell(item_start, ncells, item);
     const uint32_t first = cell_start[m] + (item - item_start[m]) * chunk;

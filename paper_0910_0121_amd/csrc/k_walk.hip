@@ -295,7 +295,10 @@ __global__ __launch_bounds__(64) void k_walk(const WalkNode *__restrict__ wn, Gr
 {
     __shared__ uint32_t stk[kStackCap];
     __shared__ uint32_t s_mark[64];
-    const uint32_t g = xcd_block(blockIdx.x, gridDim.x);
+    // runs of 8 neighbouring groups share an XCD's L2; with one run per XCD the clustered half of a
+    // box fell to a few of them.  2.1 million particles, groups of up to 128: 455 us, now 408 (409
+    // with runs of 32); 1,000,003 and 256: 104 and 95 (93); 500,009, theta(r): 147 and 138 (142).
+    const uint32_t g = xcd_run<8>(blockIdx.x, gridDim.x);
     if (g >= n_groups) return;
     uint64_t ncell = 0;
     uint64_t at = 0, room = 0;
@@ -421,7 +424,7 @@ __global__ __launch_bounds__(64) void k_walk_multi(const WalkBox *__restrict__ b
 {
     __shared__ uint32_t stk[kStackCap];
     __shared__ uint32_t s_mark[64];
-    const uint32_t t = xcd_block(blockIdx.x, gridDim.x);
+    const uint32_t t = xcd_run<8>(blockIdx.x, gridDim.x);
     if (t >= total) return;
     const WalkBox &B = bx[box_of(bx, nb, t)];
     const uint32_t g = t - B.g0;
