@@ -350,8 +350,8 @@ constexpr uint32_t kHeavyCost = 17;
 constexpr uint32_t kMinPiece = 13;
 constexpr int kBins = kXcds * kCostBuckets;
 // Up to this many groups, one per thread, k_walk_results writes the queues itself; for more a
-// launch of many workgroups follows, which the host does not wait for (one workgroup took 57 us to
-// write the 20,000 pieces of a box of 700,001).
+// launch of many workgroups follows, and one that publishes the results (one workgroup took 57 us
+// to write the 20,000 pieces of a box of 700,001).
 constexpr uint32_t kWriteHere = 1024;
 
 // t of the box (pairs: its interactions): 6,550 to 13,100 times 2^t in all.  Pieces of half of that
@@ -652,13 +652,31 @@ __global__ __launch_bounds__(256) void k_force_out_multi(const ForceBox *__restr
         sum_pairs(B.n_groups, B.fp.pairs, B.pair_sum, blockIdx.x - nb, stat_blocks);
 }
 
+// The overflow word and the six statistics to the box's mailbox, from word 1 on, and then its
+// sequence number: the host may go on, on any stream, as soon as it sees that, so whatever else
+// the walk leaves has to be complete.
+__device__ __forceinline__ void publish_results(const WalkBox &B)
+{
+    uint32_t *m = B.mailbox;
+    __hip_atomic_store(&m[1], *(volatile unsigned *)B.overflow, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+    for (int k = 0; k < 6; ++k) {
+        const unsigned long long v = *(volatile unsigned long long *)&B.stats[k];
+        __hip_atomic_store(&m[2 + 2 * k], (uint32_t)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&m[3 + 2 * k], (uint32_t)(v >> 32), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    __hip_atomic_store(&m[0], B.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Statistics, queue bins, queues (kWriteHere) and their publication by one workgroup (see the
 // class kernels and launch_walk_stats for each part).
 __device__ __forceinline__ void walk_results(const WalkBox &B)
 {
     constexpr int kThreads = 1024, kWaves = kThreads / 64;
     __shared__ uint32_t bin[kBins];
-    __shared__ unsigned long long part[4][kWaves], tot[6];
+    __shared__ unsigned long long part[4][kWaves], tot[4];
     __shared__ uint32_t s_rows;
     const uint32_t tid = threadIdx.x, G = B.n_groups;
     const int lane = tid & 63, wave = tid >> 6;
@@ -725,8 +743,8 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
     if (wave == 0) {
         const uint32_t items = scan_bins(bin, B.cls);
         if (lane == 0) {
-            B.stats[4] = tot[4] = s_rows;
-            B.stats[5] = tot[5] = items;
+            B.stats[4] = s_rows;
+            B.stats[5] = items;
             s_rows = 0;
         }
     }
@@ -745,23 +763,27 @@ __device__ __forceinline__ void walk_results(const WalkBox &B)
     } else { // the cursors for the launch that follows
         for (uint32_t i = tid; i < kBins; i += kThreads) B.cls[kClsBins + i] = bin[i];
     }
-    if (tid == 0 && B.mailbox) {
-        uint32_t *m = B.mailbox;
-        __hip_atomic_store(&m[1], *(volatile unsigned *)B.overflow, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_SYSTEM);
-        for (int k = 0; k < 6; ++k) {
-            __hip_atomic_store(&m[2 + 2 * k], (uint32_t)tot[k], __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
-            __hip_atomic_store(&m[3 + 2 * k], (uint32_t)(tot[k] >> 32), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
-        }
-        __hip_atomic_store(&m[0], B.seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (G <= kWriteHere && B.mailbox) { // every thread's writes before the publication
+        __threadfence();
+        __syncthreads();
+        if (tid == 0) publish_results(B);
     }
 }
 __global__ __launch_bounds__(1024) void k_walk_results(WalkBox box) { walk_results(box); }
 __global__ __launch_bounds__(1024) void k_walk_results_multi(const WalkBox *__restrict__ bx)
 {
     walk_results(bx[blockIdx.x]);
+}
+
+// For boxes whose queues k_walk_scatter has written.
+__global__ void k_walk_publish(WalkBox box)
+{
+    if (threadIdx.x == 0) publish_results(box);
+}
+__global__ void k_walk_publish_multi(const WalkBox *__restrict__ bx)
+{
+    const WalkBox &B = bx[blockIdx.x];
+    if (threadIdx.x == 0 && B.n_groups > kWriteHere && B.mailbox) publish_results(B);
 }
 
 __device__ __forceinline__ void force_prep(const ForceBox &B, uint32_t b, uint32_t nb)
@@ -833,16 +855,25 @@ void launch_force_prep_multi(const ForceBox *boxes, int nb, hipStream_t s)
 
 void launch_walk_results_one(const WalkBox &box, hipStream_t s)
 {
-    k_walk_results<<<1, 1024, 0, s>>>(box);
-    if (box.n_groups > kWriteHere)
-        k_walk_scatter<<<(box.n_groups + 255) / 256, 256, 0, s>>>(box);
+    if (box.n_groups <= kWriteHere) {
+        k_walk_results<<<1, 1024, 0, s>>>(box);
+        return;
+    }
+    WalkBox quiet = box;
+    quiet.mailbox = nullptr;
+    k_walk_results<<<1, 1024, 0, s>>>(quiet);
+    k_walk_scatter<<<(box.n_groups + 255) / 256, 256, 0, s>>>(box);
+    if (box.mailbox) k_walk_publish<<<1, 64, 0, s>>>(box);
 }
 
 void launch_walk_results_multi(const WalkBox *boxes, int nb, uint32_t most, hipStream_t s)
 {
     if (!nb) return;
     k_walk_results_multi<<<nb, 1024, 0, s>>>(boxes);
-    if (most > kWriteHere) k_walk_scatter_multi<<<dim3((most + 255) / 256, nb), 256, 0, s>>>(boxes);
+    if (most > kWriteHere) {
+        k_walk_scatter_multi<<<dim3((most + 255) / 256, nb), 256, 0, s>>>(boxes);
+        k_walk_publish_multi<<<nb, 64, 0, s>>>(boxes);
+    }
 }
 
 void launch_pairwise_f32(int64_t n_i, const double *xi, int64_t n_j, const double *xj,

@@ -1,0 +1,260 @@
+// A stand-in for the HIP runtime that runs the library's host code without a device: memory is
+// host memory, a launch is written to the log and only does what the host reads back (counts,
+// statistics, publications).  Linked into an executable, these definitions come before the
+// runtime's own.  Each command runs one sequence of calls and prints what happened.
+#include <cxxabi.h>
+#include <sys/mman.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <mutex>
+#include <string>
+#include <thread>
+#include <unordered_map>
+#include <vector>
+
+#include "common.hpp"
+#include "treepm.h"
+
+namespace {
+
+std::mutex mu;
+std::map<void *, size_t> live;
+size_t live_bytes = 0;
+int mallocs = 0, fail_at = -1; // fail_at: the first allocation that fails, counted from 0
+// (registered before this file's own objects are constructed)
+std::unordered_map<const void *, std::string> &names()
+{
+    static std::unordered_map<const void *, std::string> n;
+    return n;
+}
+std::vector<std::string> trace;
+
+// What the device would report for every box.
+struct Report {
+    uint32_t nodes1 = 8, groups = 2000;
+    uint64_t cells = 100000, parts = 100000, pairs = 1000000, longest = 300, rows = 0, items = 0;
+} rep;
+
+void note(const std::string &s) { trace.push_back(s); }
+
+bool has(const std::string &s, const char *what) { return s.find(what) != std::string::npos; }
+
+void set_stats(unsigned long long *st)
+{
+    const unsigned long long v[6] = {rep.cells, rep.parts, rep.pairs, rep.longest, rep.rows, rep.items};
+    memcpy(st, v, sizeof v);
+}
+
+template <typename T>
+T arg(void **args, int i)
+{
+    return *static_cast<T *>(args[i]);
+}
+
+// Called with mu held.
+void run_kernel(const std::string &k, void **args)
+{
+    note(k);
+    if (has(k, "::k_publish(")) {
+        uint32_t *m = arg<uint32_t *>(args, 6), at = 1;
+        for (int r = 0; r < 3; ++r) {
+            const uint32_t n = arg<uint32_t>(args, 2 * r + 1);
+            if (n) memcpy(m + at, arg<const uint32_t *>(args, 2 * r), 4 * n);
+            at += n;
+        }
+        __atomic_store_n(&m[0], arg<uint32_t>(args, 7), __ATOMIC_RELEASE);
+        note("published");
+    } else if (has(k, "k_set<unsigned int>")) {
+        uint32_t *p = arg<uint32_t *>(args, 0);
+        for (size_t i = 0; i < arg<size_t>(args, 1); ++i) p[i] = arg<uint32_t>(args, 2);
+    } else if (has(k, "k_set<unsigned long>")) {
+        uint64_t *p = arg<uint64_t *>(args, 0);
+        for (size_t i = 0; i < arg<size_t>(args, 1); ++i) p[i] = arg<uint64_t>(args, 2);
+    } else if (has(k, "k_build_init")) {
+        memset(arg<unsigned *>(args, 0), 0, 24);
+    } else if (has(k, "k_tree_scan")) {
+        uint32_t *tot = arg<uint32_t *>(args, 2);
+        memset(tot, 0, (tpm::kMaxLevel + 1) * 4);
+        tot[0] = 1;
+        tot[1] = rep.nodes1;
+    } else if (has(k, "k_scan_one<") || has(k, "k_scan_tile<")) {
+        void *total = arg<void *>(args, has(k, "k_scan_one<") ? 2 : 3);
+        if (total && has(k, "<unsigned int>")) *static_cast<uint32_t *>(total) = rep.groups;
+        if (total && has(k, "<unsigned long>"))
+            *static_cast<uint64_t *>(total) = rep.cells + rep.parts;
+    } else if (has(k, "k_group_compact") || has(k, "k_group_bbox")) {
+        const bool bbox = has(k, "k_group_bbox");
+        const uint32_t cap = arg<uint32_t>(args, 3);
+        const tpm::GroupArrays gr = bbox ? arg<tpm::GroupArrays>(args, 1) : tpm::GroupArrays{};
+        const void *need[] = {gr.node, gr.first, gr.count, gr.cgx, gr.cgy, gr.cgz, gr.hgx,
+                              gr.hgy, gr.hgz, gr.xgx, gr.xgy, gr.xgz, gr.lox, gr.loy,
+                              gr.loz, gr.hix, gr.hiy, gr.hiz};
+        const size_t size[] = {4, 4, 4, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8};
+        if (bbox)
+            for (int a = 0; a < 18; ++a) {
+                const auto it = live.find(const_cast<void *>(need[a]));
+                if (it == live.end() || it->second < cap * size[a])
+                    note("group array " + std::to_string(a) + " too small for " + std::to_string(cap));
+            }
+    } else if (has(k, "k_walk_results(") || has(k, "k_walk_publish(")) {
+        const tpm::WalkBox B = arg<tpm::WalkBox>(args, 0);
+        set_stats(B.stats);
+        if (B.mailbox) {
+            B.mailbox[1] = 0;
+            memcpy(B.mailbox + 2, B.stats, 48);
+            __atomic_store_n(&B.mailbox[0], B.seq, __ATOMIC_RELEASE);
+            note("published");
+        }
+    } else if (has(k, "k_walk_stats")) {
+        set_stats(arg<unsigned long long *>(args, 4));
+    }
+}
+
+} // namespace
+
+extern "C" {
+static dim3 cfg_grid, cfg_block;
+void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
+void __hipUnregisterFatBinary(void **) {}
+void __hipRegisterFunction(void **, const void *host, char *, const char *name, unsigned, void *,
+                           void *, void *, void *, int *)
+{
+    int st;
+    char *d = abi::__cxa_demangle(name, nullptr, nullptr, &st);
+    names()[host] = st == 0 ? d : name;
+    free(d);
+}
+void __hipRegisterVar(void **, void *, char *, const char *, int, size_t, int, int) {}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t)
+{
+    cfg_grid = g;
+    cfg_block = b;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *sh, hipStream_t *s)
+{
+    *g = cfg_grid;
+    *b = cfg_block;
+    *sh = 0;
+    *s = nullptr;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *f, dim3, dim3, void **args, size_t, hipStream_t)
+{
+    std::lock_guard<std::mutex> lk(mu);
+    run_kernel(names()[f], args);
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n)
+{
+    std::lock_guard<std::mutex> lk(mu);
+    if (mallocs++ >= fail_at && fail_at >= 0) return hipErrorOutOfMemory;
+    *p = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    live[*p] = n;
+    live_bytes += n;
+    return hipSuccess;
+}
+hipError_t hipFree(void *p)
+{
+    std::lock_guard<std::mutex> lk(mu);
+    const auto it = live.find(p);
+    if (it == live.end()) return hipErrorInvalidValue;
+    munmap(p, it->second);
+    live_bytes -= it->second;
+    live.erase(it);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = calloc(1, n); return hipSuccess; }
+hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { memcpy(d, s, n); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t)
+{
+    memcpy(d, s, n);
+    return hipSuccess;
+}
+hipError_t hipMemGetInfo(size_t *f, size_t *t) { *f = *t = (size_t)288 << 30; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t *e) { *e = (hipEvent_t)malloc(1); return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { free(e); return hipSuccess; }
+hipError_t hipEventElapsedTime(float *t, hipEvent_t, hipEvent_t) { *t = 0; return hipSuccess; }
+hipError_t hipEventQuery(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+const char *hipGetErrorString(hipError_t) { return "error"; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipPeekAtLastError() { return hipSuccess; }
+hipError_t hipGetSymbolAddress(void **, const void *) { return hipErrorInvalidValue; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *) { return hipErrorInvalidValue; }
+hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)malloc(1); return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) { free(s); return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+}
+
+namespace {
+
+treepm_params params(int precision)
+{
+    treepm_params p{};
+    p.L = 1.0;
+    p.mesh = 1.0 / 64;
+    p.r_cut = 3.0 / 64;
+    p.eps = p.mesh / 20;
+    p.theta = 0.5;
+    p.n_leaf = 10;
+    p.n_crit = 64;
+    p.precision = precision;
+    return p;
+}
+
+struct Arrays {
+    std::vector<double> v;
+    explicit Arrays(int64_t n) : v((size_t)n * 4, 0.25) {}
+    const double *at(int a) const { return v.data() + v.size() / 4 * a; }
+};
+
+int build(treepm_ctx *c, const Arrays &a)
+{
+    return treepm_build(c, (int64_t)a.v.size() / 4, a.at(0), a.at(1), a.at(2), a.at(3), TREEPM_DEVICE,
+                        nullptr);
+}
+
+int number(int argc, char **argv, int i, int def) { return i < argc ? atoi(argv[i]) : def; }
+
+// What was launched from trace[from] on.
+void print(size_t from)
+{
+    for (size_t i = from; i < trace.size(); ++i) printf("%s\n", trace[i].c_str());
+}
+
+} // namespace
+
+int main(int argc, char **argv)
+{
+    const std::string cmd = argc > 1 ? argv[1] : "";
+    treepm_ctx *c = nullptr;
+    if (cmd == "walk") { // groups: the launches of a walk, and its return
+        rep.groups = (uint32_t)number(argc, argv, 2, 2000);
+        const treepm_params p = params(TREEPM_FP32);
+        const Arrays a(200000);
+        if (treepm_create(&p, 0, &c) || build(c, a)) return 1;
+        const size_t from = trace.size();
+        treepm_stats st{};
+        if (treepm_walk(c, nullptr, &st)) return 1;
+        print(from);
+        printf("returned %lld\n", (long long)st.interactions);
+        treepm_destroy(c);
+    } else {
+        return 2;
+    }
+    return 0;
+}

@@ -1,0 +1,44 @@
+"""The library's host code on a stand-in for the HIP runtime (tests/fake_hip.cpp): no device, no
+kernels, but the allocations that the calls make and the launches that they queue, in order."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.dirname(os.path.abspath(__file__))
+PKG = os.path.join(ROOT, "paper_0910_0121_amd")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("no g++")
+    import paper_0910_0121_amd as t
+    t.lib()  # built
+    exe = str(tmp_path_factory.mktemp("fake") / "fake_hip")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    subprocess.run([gxx, "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", "-rdynamic",
+                    "-I", os.path.join(rocm, "include"), "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(PKG, "csrc"), os.path.join(HERE, "fake_hip.cpp"),
+                    os.path.join(PKG, "libtreepm.so"), f"-Wl,-rpath,{PKG}",
+                    f"-Wl,-rpath,{rocm}/lib", f"-L{rocm}/lib", "-lpthread", "-o", exe], check=True)
+
+    def call(*args):
+        r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=120)
+        assert r.returncode == 0, (args, r.returncode, r.stdout[-2000:], r.stderr[-2000:])
+        return r.stdout.splitlines()
+    return call
+
+
+@pytest.mark.parametrize("groups", [1, 1024, 1025, 16384, 16385, 200000])
+def test_walk_returns_after_its_last_launch(run, groups):
+    """The walk's results reach the host only once everything that it leaves for the force has
+    been written: whatever publishes them is the last launch."""
+    lines = run("walk", groups)
+    assert lines[-1] == "returned 1000000"
+    assert lines[-2] == "published"
+    assert sum("k_walk_results" in l or "k_class_scatter" in l for l in lines) == 1
