@@ -466,6 +466,7 @@ int ensure_groups(treepm_ctx *c, size_t need)
 {
     if (need <= c->group_cap && c->g_node.p) return TREEPM_OK;
     size_t cap = need + need / 8 + 64;
+    c->group_cap = 0; // until all of them are held: a build launches for as many as this says
     Buf *u32s[] = {&c->g_node, &c->g_first, &c->g_count};
     for (Buf *b : u32s) {
         hipError_t e = reserve(*b, cap * 4);

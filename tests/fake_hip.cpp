@@ -253,6 +253,22 @@ int main(int argc, char **argv)
         print(from);
         printf("returned %lld\n", (long long)st.interactions);
         treepm_destroy(c);
+    } else if (cmd == "groups") { // k: a build whose k-th group array fails, and the next one
+        treepm_params p = params(TREEPM_FP32);
+        const Arrays a((1 << 20) + 1);
+        rep.groups = 1000;
+        if (treepm_create(&p, 0, &c) || build(c, a)) return 1;
+        // more groups: the arrays grow, the other buffers do not
+        rep.groups = 400000;
+        treepm_release_cached(0);
+        fail_at = mallocs + number(argc, argv, 2, 0);
+        printf("failed %d\n", build(c, a));
+        fail_at = -1;
+        const size_t from = trace.size();
+        if (build(c, a)) return 1;
+        print(from);
+        printf("built\n");
+        treepm_destroy(c);
     } else {
         return 2;
     }

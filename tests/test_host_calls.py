@@ -42,3 +42,14 @@ def test_walk_returns_after_its_last_launch(run, groups):
     assert lines[-1] == "returned 1000000"
     assert lines[-2] == "published"
     assert sum("k_walk_results" in l or "k_class_scatter" in l for l in lines) == 1
+
+
+@pytest.mark.parametrize("more", range(18))
+def test_a_failed_allocation_of_the_groups_leaves_no_half_of_them(run, more):
+    """A build whose group arrays cannot all be allocated fails; the same build afterwards
+    launches the group kernels on whole arrays."""
+    lines = run("groups", more)
+    assert lines[0] == "failed -3"  # TREEPM_ERR_OOM
+    assert lines[-1] == "built"
+    assert any("k_group_bbox" in l for l in lines)
+    assert not [l for l in lines if "too small" in l]
