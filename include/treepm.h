@@ -158,8 +158,9 @@ int treepm_set_timing(treepm_ctx *ctx, int enable);
  * (the default): once an earlier walk has sized the device memory, in one pass; boxes of at
  * least 98,304 groups (16 per wave of that launch: below that it cannot fill the device) into a
  * pool, smaller ones a wave per group into a slot for each list (of twice the earlier walk's
- * longest list if that takes at most 1 GiB, else of four times its mean list, with room for
- * longer ones behind); in two passes otherwise.  TREEPM_WALK_ONE_PASS: into a pool whenever an
+ * longest list if that takes at most four times its lists' memory, else four times that memory
+ * in equal slots with room for longer lists behind; a server's box less, if it was admitted with
+ * less); in two passes otherwise.  TREEPM_WALK_ONE_PASS: into a pool whenever an
  * earlier walk sized it.  TREEPM_WALK_TWO_PASS: always in two passes.  The lists are the same in
  * every mode.  ERR_ARG for another mode. */
 enum { TREEPM_WALK_AUTO = 0, TREEPM_WALK_ONE_PASS = 1, TREEPM_WALK_TWO_PASS = 2 };
@@ -178,7 +179,7 @@ int treepm_build(treepm_ctx *ctx, int64_t n, const double *x, const double *y, c
  * build (ERR_STATE).  Fills *stats if non-NULL.  The first walk on a context counts the lists
  * and then writes them (two passes); later walks (see treepm_set_walk_passes) write them in one
  * pass into device memory sized from the previous walk (a pool of about 1.25x its lists plus a
- * chunk per wave, or a slot per list) and fall back to two passes if that is too small, so the
+ * chunk per wave, or a slot per list, at most about 4x) and fall back to two passes if that is too small, so the
  * lists never depend on the estimate.  ERR_OVERFLOW if a group's traversal stack would exceed
  * its capacity (see last_error). */
 int treepm_walk(treepm_ctx *ctx, void *hip_stream, treepm_stats *stats);

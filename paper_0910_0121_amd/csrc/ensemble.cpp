@@ -35,6 +35,8 @@
 // Device bytes a context currently holds, and the parameter checks of treepm_create, without
 // a device (treepm.cpp).
 size_t treepm_internal_ctx_bytes(const treepm_ctx *c);
+// What the context's walks may let it grow to.
+void treepm_internal_set_room(treepm_ctx *c, size_t bytes);
 int treepm_internal_check_params(const treepm_params *p);
 
 namespace {
@@ -209,7 +211,9 @@ size_t box_need(const treepm_ens *e, const Request &r)
 
 // With e->mu held: evict idle boxes (least recently used first) until `need` more bytes fit;
 // their contexts go to `gone`, for the caller to destroy after releasing the lock (destroying
-// waits for the context's last work).  Returns false if they cannot be made to fit now.
+// waits for the context's last work).  Returns false if they cannot be made to fit now.  A
+// resident box that turned out larger than its estimate, and than the budget, may still run
+// when it is the only one left: waiting would not make it fit.
 bool make_room(treepm_ens *e, size_t need, uint64_t keep_box, std::vector<treepm_ctx *> &gone)
 {
     while (e->resident + need > e->budget) {
@@ -222,7 +226,7 @@ bool make_room(treepm_ens *e, size_t need, uint64_t keep_box, std::vector<treepm
                 victim = kv.first;
                 found = true;
             }
-        if (!found) return false;
+        if (!found) return need == 0 && e->boxes.size() == 1 && e->boxes.count(keep_box);
         Box &b = e->boxes[victim];
         if (b.ctx) gone.push_back(b.ctx);
         e->resident -= std::min(e->resident, b.bytes);
@@ -267,6 +271,7 @@ int build_request(treepm_ens *e, Worker &w, Request &r, Box &b)
         if (rc) return rc;
         b.prm = r.prm;
     }
+    treepm_internal_set_room(b.ctx, b.bytes); // what the box has been admitted with
     const double *x = static_cast<const double *>(r.in.p), *y = x + r.n, *z = y + r.n,
                  *m = z + r.n;
     // returns once the inputs have been copied and the tree is built

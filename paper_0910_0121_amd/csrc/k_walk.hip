@@ -32,8 +32,8 @@
 //     list or the pool runs out of room, the pass reports it and the caller falls back to
 //     two passes, so the result never depends on those sizes;
 //   * slots: a wave per group writes its list to a slot of its own, sized from an earlier walk's
-//     longest list (or, for many groups, its mean list, with room elsewhere for longer ones),
-//     with the same fallback.  It halves the walk of boxes too small for the pool: 700,001
+//     longest list (or, where that takes too much memory, about twice its mean list, with room
+//     elsewhere for longer ones), with the same fallback.  It halves the walk of boxes too small for the pool: 700,001
 //     clustered particles 0.23 -> 0.12 ms.
 // All layouts also run over the groups of several boxes in one launch (k_walk_multi,
 // k_walk_pool_multi: per-box descriptors in device memory, each box's own lists and flags).

@@ -97,6 +97,7 @@ struct treepm_ctx {
     // A sort of this context found runs too long for sort_run_bits: start from 24 bits.
     bool sort_wide = false;
     int walk_passes = TREEPM_WALK_AUTO; // treepm_set_walk_passes
+    size_t room = 0; // device bytes that the context's owner has for it (0: it does not say)
     uint64_t st[3] = {0, 0, 0};
     // FP32 pair-law table: device copy, and the eps / eta it was built for (0: none)
     Buf tab;
@@ -123,6 +124,8 @@ struct treepm_ctx {
     int pm_n = 0; // mesh size, box and eta the table was built for
     double pm_L = 0.0, pm_eta = 0.0;
 };
+
+size_t treepm_internal_ctx_bytes(const treepm_ctx *c); // below
 
 namespace {
 
@@ -859,8 +862,21 @@ uint32_t pool_waves(uint32_t G) { return std::max(1u, std::min(6144u, (G + 15) /
 // of that); at 153,000 groups 1.87 against 2.34 ms for the two passes.
 constexpr uint32_t kOnePassMinGroups = 16 * 6144;
 
-// Room that slots of twice the longest list may take.
-constexpr uint64_t kSlotBytes = 1ull << 30;
+// Slots and the room behind them, in multiples of the last walk's lists.  On clustered boxes the
+// longest list is three to four times the mean (n_crit 64 and 256), so four times the lists hold
+// nearly all of them in equal slots; slots of twice the longest list took six to seven times.
+// With three times, and 2 % of the lists walked again, the longest of them last, a pass over
+// 700,001 particles took 66 us more (of 1042), a time step of 250,007 70 (of 807).
+constexpr uint64_t kSlotRoom = 4;
+
+// Entries that the lists of c may grow to within what its owner has for the context (reserve
+// takes an eighth more than it is asked for, in whole blocks).
+uint64_t list_room(const treepm_ctx *c)
+{
+    if (!c->room) return ~0ull;
+    const size_t others = treepm_internal_ctx_bytes(c) - c->entries.bytes + ((size_t)2 << 20);
+    return c->room > others ? (c->room - others) / 9 * 8 / 4 : 0;
+}
 
 // One box's walk in parts, shared by treepm_walk and the shared launches of several boxes.
 struct BoxWalk {
@@ -919,27 +935,33 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
         bw.pool = c->walk_hint + c->walk_hint / 4 + (uint64_t)bw.waves * bw.chunk;
         bw.pooled = reserve(c->entries, bw.pool * 4) == hipSuccess;
     } else if (c->walk_hint && G && c->walk_passes == TREEPM_WALK_AUTO) {
-        // Slots of twice the last walk's longest list if they fit kSlotBytes; else of four times
-        // its mean list, and for longer ones, which are walked twice, room of half of the
-        // packed lists.  Somewhat less is taken as it is: lists that grow a little from call to
-        // call do not mean an allocation each time.
+        // Room of kSlotRoom times the last walk's lists, or what the context's owner has for it
+        // (list_room): slots of twice the longest list if that fits, else equal ones, with a
+        // quarter (half, if the owner has less) of the lists behind them for the longer ones,
+        // which are walked twice.  Slots near the mean list would walk most lists twice, as the
+        // two passes do.
         Slots sl{};
-        const uint64_t have = c->entries.bytes / 4, longest = c->walk_hint_max;
-        uint64_t need = 0;
+        const uint64_t have = c->entries.bytes / 4, longest = c->walk_hint_max, all = c->walk_hint;
+        const uint64_t mean = all / std::max<uint32_t>(c->walk_hint_groups, 1);
+        const uint64_t room =
+            std::min(kSlotRoom * std::max(all, mean * G), std::max(list_room(c), have));
+        uint64_t behind = 0;
         sl.size = (2 * longest + 63) / 64 * 64;
-        if (sl.size * G * 4 <= kSlotBytes) {
-            const uint64_t fit = have / G / 64 * 64;
-            if (fit >= longest + longest / 4 + 16) sl.size = std::min(sl.size, fit);
-        } else {
-            sl.size = (4 * c->walk_hint / std::max<uint32_t>(c->walk_hint_groups, 1) + 63) / 64 * 64;
-            need = c->walk_hint / 2 + 16 * longest;
-            if (have >= sl.size * G + need / 2) need = std::min(need, have - sl.size * G);
+        if (sl.size * G > room) {
+            behind = std::max(room < kSlotRoom * all ? all / 2 : all / 4, 2 * longest);
+            sl.size = room > behind ? (room - behind) / G / 64 * 64 : 0;
         }
-        sl.spill_at = sl.size * G;
-        sl.spill_end = sl.spill_at + need;
-        sl.next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() +
-                                                         kXcds * kQueueStride);
-        if (reserve(c->entries, sl.spill_end * 4) == hipSuccess) bw.slots = sl;
+        // somewhat less is taken as it is: lists that grow a little from call to call do not mean
+        // an allocation each time
+        const uint64_t fit = have > behind ? (have - behind) / G / 64 * 64 : 0;
+        if (fit < sl.size && fit >= sl.size - sl.size / 8) sl.size = fit;
+        if (sl.size && sl.size >= mean + mean / 4) {
+            sl.spill_at = sl.size * G;
+            sl.spill_end = sl.spill_at + behind;
+            sl.next = reinterpret_cast<unsigned long long *>(c->wctr.as<uint32_t>() +
+                                                             kXcds * kQueueStride);
+            if (reserve(c->entries, sl.spill_end * 4) == hipSuccess) bw.slots = sl;
+        }
     }
     return TREEPM_OK;
 }
@@ -1142,6 +1164,9 @@ size_t treepm_internal_ctx_bytes(const treepm_ctx *c)
     for (const Buf *b : all) t += b->bytes;
     return t;
 }
+
+// What the walk may let the context grow to for speed (the server's admission; 0: no limit).
+void treepm_internal_set_room(treepm_ctx *c, size_t bytes) { c->room = bytes; }
 
 TREEPM_API const char *treepm_version(void) { return "treepm-mi355x 0.1"; }
 

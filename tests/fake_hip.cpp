@@ -93,6 +93,10 @@ void run_kernel(const std::string &k, void **args)
                               gr.hgy, gr.hgz, gr.xgx, gr.xgy, gr.xgz, gr.lox, gr.loy,
                               gr.loz, gr.hix, gr.hiy, gr.hiz};
         const size_t size[] = {4, 4, 4, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8, 8};
+        if (bbox) {
+            *arg<unsigned *>(args, 5) = 6;
+            *arg<unsigned *>(args, 6) = 64;
+        }
         if (bbox)
             for (int a = 0; a < 18; ++a) {
                 const auto it = live.find(const_cast<void *>(need[a]));
@@ -269,6 +273,49 @@ int main(int argc, char **argv)
         print(from);
         printf("built\n");
         treepm_destroy(c);
+    } else if (cmd == "slots") { // groups, longest and mean list: the memory held after 3 walks
+        rep.groups = (uint32_t)number(argc, argv, 2, 0);
+        rep.longest = (uint64_t)number(argc, argv, 3, 0);
+        rep.cells = (uint64_t)rep.groups * (uint64_t)number(argc, argv, 4, 0);
+        rep.parts = 0;
+        const treepm_params p = params(TREEPM_FP32);
+        const Arrays a(1000000);
+        if (treepm_create(&p, 0, &c)) return 1;
+        const size_t from = trace.size();
+        for (int k = 0; k < 3; ++k) {
+            if (build(c, a)) return 1;
+            treepm_stats st{};
+            if (treepm_walk(c, nullptr, &st)) return 1;
+            treepm_release_cached(0); // what the context does not hold is not counted
+            printf("held %zu\n", live_bytes);
+        }
+        print(from);
+        treepm_destroy(c);
+    } else if (cmd == "server") { // n, groups, longest and mean list, requests, budget
+        const int64_t n = number(argc, argv, 2, 0);
+        rep.groups = (uint32_t)number(argc, argv, 3, 0);
+        rep.longest = (uint64_t)number(argc, argv, 4, 0);
+        rep.cells = (uint64_t)rep.groups * (uint64_t)number(argc, argv, 5, 0);
+        rep.parts = 0;
+        rep.nodes1 = (uint32_t)(n / 2);
+        const treepm_params p = params(TREEPM_FP32);
+        const Arrays a(n);
+        std::vector<float> out((size_t)n * 3);
+        treepm_ens *e = nullptr;
+        if (treepm_ens_create(0, (size_t)atoll(argv[7]), 2, &e)) return 1;
+        for (int k = 0; k < number(argc, argv, 6, 1); ++k) {
+            uint64_t t = 0;
+            if (treepm_ensemble_submit(e, 7, &p, n, a.at(0), a.at(1), a.at(2), a.at(3), &t)) return 1;
+            int rc = TREEPM_PENDING;
+            for (int w = 0; w < 5000 && rc == TREEPM_PENDING; ++w) {
+                std::this_thread::sleep_for(std::chrono::milliseconds(1));
+                rc = treepm_ensemble_poll(e, t, out.data(), out.data() + n, out.data() + 2 * n, nullptr);
+            }
+            int64_t bytes = 0;
+            treepm_ens_info(e, nullptr, nullptr, &bytes, nullptr);
+            printf("served %d\nresident %lld\n", rc, (long long)bytes);
+        }
+        treepm_ens_destroy(e);
     } else {
         return 2;
     }

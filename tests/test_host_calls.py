@@ -53,3 +53,42 @@ def test_a_failed_allocation_of_the_groups_leaves_no_half_of_them(run, more):
     assert lines[-1] == "built"
     assert any("k_group_bbox" in l for l in lines)
     assert not [l for l in lines if "too small" in l]
+
+
+def _field(lines, name):
+    return [int(l.split()[1]) for l in lines if l.startswith(name + " ")]
+
+
+@pytest.mark.parametrize("groups,longest,mean", [(1500, 3700, 1170), (14197, 3940, 1180),
+                                                 (64, 310, 280), (60000, 5000, 1250)])
+def test_slots_take_about_four_times_the_lists(run, groups, longest, mean):
+    """From its second walk on a context holds at most about four times the packed lists of the
+    first (with the eighth that every allocation adds, and blocks of 2 MiB)."""
+    lines = run("slots", groups, longest, mean)
+    packed, held = 4 * groups * mean, _field(lines, "held")
+    assert len(held) == 3
+    for h in held[1:]:
+        assert h - held[0] <= 3 * packed * 9 // 8 + (4 << 20)
+    assert held[1] == held[2]
+    # and they are slots: one traversal
+    assert sum("k_walk<0, 0>" in l for l in lines) == 1
+
+
+@pytest.mark.parametrize("n,groups,longest,mean", [(200000, 4000, 4000, 1000),
+                                                   (400000, 7781, 4600, 1190),
+                                                   (30000, 500, 4000, 1200)])
+def test_a_server_keeps_a_box_within_what_it_admitted(run, n, groups, longest, mean):
+    """Repeated requests on one box of ordinary lists: the server holds no more than its estimate
+    for the box (320 bytes a particle and 64 MiB), which is what it asked its budget for."""
+    lines = run("server", n, groups, longest, mean, 4, n * 320 + (64 << 20))
+    resident = _field(lines, "resident")
+    assert sum(l == "served 0" for l in lines) == 4 and len(resident) == 4 and max(resident) <= n * 320 + (64 << 20)
+
+
+def test_a_server_serves_a_box_that_outgrew_its_budget(run):
+    """Lists several times as long as the estimate allows for: the box counts more than the
+    budget after its first request, and its later requests are still served."""
+    n = 100000
+    lines = run("server", n, 20000, 9000, 3000, 3, n * 330 + (64 << 20))
+    assert max(_field(lines, "resident")) > n * 330 + (64 << 20)
+    assert sum(l == "served 0" for l in lines) == 3
