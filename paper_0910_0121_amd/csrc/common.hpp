@@ -279,12 +279,12 @@ struct ForceTable {
 // pointer; false if eps / r_cut is not in [2^-13, 8).
 bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTable &ft);
 
-// The FP64 kernel's table: pieces of p = G^(1/5) of degree kTab64Deg in t, 64 per octave over
-// kTab64Oct octaves of u = c + (1 - c) s, c = 2^-kTab64Oct (see force_table64.cpp); the entry of
-// u = 1 is zero.  The coefficients of powers 0 .. kTab64F64 - 1 are doubles, the others floats,
-// each power an array of kTab64Entries.
+// The FP64 kernel's table: pieces of G = G_a (1 + r(t))^5, r a polynomial of degree kTab64Deg
+// without a constant, 64 per octave over kTab64Oct octaves of u = c + (1 - c) s, c = 2^-kTab64Oct
+// (see force_table64.cpp); the entry of u = 1 is zero.  G_a and the coefficients of powers 1 ..
+// kTab64F64 - 1 are doubles, the others floats, each power an array of kTab64Entries.
 constexpr int kTab64Exp = 18;
-constexpr int kTab64Deg = 6, kTab64Oct = 24, kTab64F64 = 4;
+constexpr int kTab64Deg = 6, kTab64Oct = 24, kTab64F64 = 5;
 constexpr uint32_t kTab64Entries = (uint32_t)kTab64Oct * 64u + 1u;
 // False if (eps / r_cut)^2 is below 2^(1 - kTab64Oct) (the first pieces would not resolve it) or
 // above 64: the kernel then evaluates eq. (2) pair by pair.

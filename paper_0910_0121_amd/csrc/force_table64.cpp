@@ -1,17 +1,19 @@
 // The FP64 force kernel's table of the pair law, built on the host in extended precision.
 //
-// As in the FP32 table, G(s) = g(2 sqrt(s)) / (s + e2)^(3/2), s = (r / r_cut)^2, is the fifth
-// power of p, given in polynomial pieces over u = c + (1 - c) s, 64 per octave, in t = u - a with
-// a the piece's lower edge; here of degree 6, and with u and t scaled by 2^18, so that the floats
-// among the coefficients stay in range for the narrowest pieces and the widest.  Per piece p is expanded
-// about the middle as a power series (s = s_m + h x, x in [-1, 1]): R = 2 sqrt(s), eq. (2) as a polynomial of R, split
-// into even and odd powers (R^2 = 4 s is linear in x), and the fractional powers from their
-// differential equation; the series of degree 9 is brought to degree 6 by subtracting Chebyshev
-// polynomials, which leaves a relative error below 1e-17 in p.  c = 2^-24: g carries
-// (8/5) R^3 = 12.8 s^(3/2), which no polynomial follows at s = 0, and a first piece of width 2^-30 keeps what is missed there below 1e-16.
-// The three highest coefficients are rounded to float, from the top down, each time putting the
+// G(s) = g(2 sqrt(s)) / (s + e2)^(3/2), s = (r / r_cut)^2, is given in pieces over u = c + (1 - c) s,
+// 64 per octave, in t = u - a with a the piece's lower edge, as G = G_a (1 + r(t))^5: G_a its value
+// at the edge and r a polynomial of degree 6 without a constant, so that only one rounding, G_a's,
+// and not five times that of a fifth root, is left in G.  u and t are scaled by 2^18, so that the
+// floats among the coefficients stay in range for the narrowest pieces and the widest.  Per piece
+// p = G^(1/5) is expanded about the middle as a power series (s = s_m + h x, x in [-1, 1]): R = 2
+// sqrt(s), eq. (2) as a polynomial of R, split into even and odd powers (R^2 = 4 s is linear in x),
+// and the fractional powers from their differential equation; the series of degree 9 is brought to
+// degree 6 by subtracting Chebyshev polynomials, which leaves a relative error below 1e-17 in p.
+// c = 2^-24: g carries (8/5) R^3 = 12.8 s^(3/2), which no polynomial follows at s = 0, and a first
+// piece of width 2^-30 keeps what is missed there below 1e-16.
+// The two highest coefficients are rounded to float, from the top down, each time putting the
 // rounding error times the best lower-degree approximation of that power back into the lower
-// coefficients: what remains is below 2e-18 of p.
+// coefficients: what remains is below 1e-19 of p.
 #include "common.hpp"
 
 #include <cmath>
@@ -196,13 +198,16 @@ bool build_force_table64(double eps_over_rcut, std::vector<double> &hi, std::vec
         iw[0] = 1;
         for (int i = 1; i <= kKeep; ++i) iw[i] = iw[i - 1] / std::ldexp(w, kTab64Exp);
         for (int n = kKeep; n >= kTab64F64; --n) {
-            const float v = (float)(b[n] * iw[n]);
+            const float v = (float)(b[n] / b[0] * iw[n]);
             lo[(size_t)(n - kTab64F64) * kTab64Entries + k] = v;
-            const real off = b[n] - (real)v / iw[n]; // this much of tau^n is left over
+            const real off = b[n] - (real)v * b[0] / iw[n]; // this much of tau^n is left over
             for (int i = 0; i < n; ++i) b[i] -= off * Ts[n][i] / Ts[n][n];
         }
-        for (int n = 0; n < kTab64F64; ++n)
-            hi[(size_t)n * kTab64Entries + k] = (double)(b[n] * iw[n]);
+        // p / b[0] = 1 + r
+        const real p2 = b[0] * b[0];
+        hi[k] = (double)(p2 * p2 * b[0]);
+        for (int n = 1; n < kTab64F64; ++n)
+            hi[(size_t)n * kTab64Entries + k] = (double)(b[n] / b[0] * iw[n]);
     }
     return true;
 }

@@ -2,22 +2,26 @@
 // softening of Section 2.4), in the work split of the FP32 kernel (force_common.hpp): positions
 // relative to x_g are FP64 differences (nearest image once per entry, or per pair when the
 // group's cube plus r_cut reaches half the box), and the pair law is
-//   * read from a table (force_table64.cpp) where the softening allows one: G(s) = p^5 with p a
-//     polynomial of degree 6 in t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the
+//   * read from a table (force_table64.cpp) where the softening allows one: G(s) = G_a (1 + r)^5
+//     with r a polynomial of degree 6 in t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the
 //     piece's lower edge, which is u with its low mantissa bits cleared, so t is exact; or
 //   * evaluated pair by pair for smaller eps: (r^2 + eps^2)^(-1/2) and r^(-1) from the hardware
 //     estimate refined by two Newton steps, and eq. (2) in a form with no cancellation: for R < 1,
 //     g = 1 + R^3 (-8/5 + R^2 (8/5 + R (-1/2 + R (-12/35 + 3R/20)))), and for R >= 1,
 //     g = max(2 - R, 0)^5 (7R^3 + 22R^2 + 10R + 4) / 140.
 //
-// A pair from the table is 22 FP64 and 10 other vector instructions (about 125 cycles of issue at
-// 4.4 per FP64 instruction) and 44 bytes from LDS; evaluated, it is about 50 FP64 instructions, two
-// of them 17-cycle estimates.  The coefficients are read power by power (4- and 8-byte reads: a
-// 16-byte read costs two to three times as much per byte once the lanes spread over pieces),
-// and the three highest, whose share of p is at most 7e-9, are floats and are summed in FP32: 26
-// cycles of LDS time a pair against 32, and two conversions less.  Measured on the 128^3 clustered
-// box (2.1 million particles): 3.0 ms, LDS and vector units both busy three quarters of it or more;
-// pair by pair, with one group a wave, it was 8.2 ms.
+// A pair from the table is 26 FP64 and 9 other vector instructions (about 140 cycles of issue at
+// 4.4 per FP64 instruction) and 48 bytes from LDS; evaluated, it is about 50 FP64 instructions, two
+// of them 17-cycle estimates.  |r| is at most 0.008 but for the last pieces before the cutoff, so
+// its coefficients need not be as exact as G_a: the two highest, whose share of G is at most 6e-10,
+// are floats and are summed in FP32 (an error of 3e-17).  A pair's error, of 300,000 each at eps /
+// r_cut from 2^-11 to 3 and without that of u: RMS 0.8e-16 for R < 1.9, largest 3.7e-16; as p^5
+// with three coefficients in FP32 it was 2.4 to 4.6e-16 and 2.3e-15 below R = 1, and pair by pair
+// it is 1.6 to 2.7e-16 and 1.3e-15.  The coefficients are read power by power (4- and 8-byte reads:
+// a 16-byte read costs two to three times as much per byte once the lanes spread over pieces).
+// Measured on the 128^3 clustered box (2.1 million particles, kernel trace): 3.2 ms, LDS and vector
+// units both busy three quarters of it or more; as p^5 it was 3.0, pair by pair, with one group a
+// wave, 8.2.
 #include "force_common.hpp"
 
 namespace tpm {
@@ -29,7 +33,7 @@ constexpr uint32_t kPlaneHi = (kTab64Entries * 8u + 15u) / 16u * 16u;
 constexpr uint32_t kPlaneLo = (kTab64Entries * 4u + 15u) / 16u * 16u;
 constexpr uint32_t kLoAt = kTab64F64 * kPlaneHi;
 constexpr uint32_t kTable64 = kLoAt + (kTab64Deg + 1 - kTab64F64) * kPlaneLo;
-static_assert(kTab64Deg == 6 && kTab64F64 == 4, "the Horner steps below");
+static_assert(kTab64Deg == 6 && kTab64F64 == 5, "the Horner steps below");
 static_assert(kTable64 <= 81920, "LDS: the table below half of a compute unit's 160 KB");
 
 constexpr double kTop64 = 1 << kTab64Exp; // u at s = 1
@@ -153,8 +157,8 @@ __device__ __forceinline__ void pairs_f64(const double4 s, const double *xi, con
         r2[k] = fma(dx[k], dx[k], fma(dy[k], dy[k], dz[k] * dz[k]));
     }
     if (TABLE) {
-        double t[NP], q0[NP], q1[NP], q2[NP], q3[NP];
-        float q4[NP], q5[NP], q6[NP];
+        double t[NP], q0[NP], q1[NP], q2[NP], q3[NP], q4[NP];
+        float q5[NP], q6[NP];
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
             const double u = fmin(fma(r2[k], F.k2, F.c), kTop64);
@@ -166,19 +170,19 @@ __device__ __forceinline__ void pairs_f64(const double4 s, const double *xi, con
             q1[k] = *(lds_d)(h + kPlaneHi);
             q2[k] = *(lds_d)(h + 2 * kPlaneHi);
             q3[k] = *(lds_d)(h + 3 * kPlaneHi);
-            q4[k] = *(lds_f)(l + kLoAt);
-            q5[k] = *(lds_f)(l + kLoAt + kPlaneLo);
-            q6[k] = *(lds_f)(l + kLoAt + 2 * kPlaneLo);
+            q4[k] = *(lds_d)(h + 4 * kPlaneHi);
+            q5[k] = *(lds_f)(l + kLoAt);
+            q6[k] = *(lds_f)(l + kLoAt + kPlaneLo);
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
-            const float tf = (float)t[k];
-            const double z = (double)fmaf(fmaf(q6[k], tf, q5[k]), tf, q4[k]);
-            const double p =
-                fma(fma(fma(fma(z, t[k], q3[k]), t[k], q2[k]), t[k], q1[k]), t[k], q0[k]);
-            const double p2 = p * p;
-            const double f = (p2 * p2) * (p * s.w);
+            const double z = (double)fmaf(q6[k], (float)t[k], q5[k]);
+            const double r =
+                fma(fma(fma(fma(z, t[k], q4[k]), t[k], q3[k]), t[k], q2[k]), t[k], q1[k]) * t[k];
+            // (1 + r)^5 - 1
+            const double y = r * fma(r, fma(r, fma(r, r + 5.0, 10.0), 10.0), 5.0);
+            const double f = fma(q0[k], y, q0[k]) * s.w;
             ax[k] = fma(f, dx[k], ax[k]);
             ay[k] = fma(f, dy[k], ay[k]);
             az[k] = fma(f, dz[k], az[k]);
