@@ -187,9 +187,10 @@ int treepm_walk(treepm_ctx *ctx, void *hip_stream, treepm_stats *stats);
 /* Short-range force on every particle from its group's list (eq. 1, 2), written in the
  * caller's original particle order.  TREEPM_FP32 boxes work in lengths of r_cut, relative to
  * the group's cube centre: with s = (r / r_cut)^2 the pair law
- * G(s) = g_P3M(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) is G = p(u)^5, u = min(c + (1 - c) s, 1),
- * c a power of two at most (eps/r_cut)^2 / 2, and p comes from a table of quadratic pieces built
- * on the host for the box (64 per octave of u, relative least-squares fits, zero at u = 1);
+ * G(s) = g_P3M(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) is G = G_a (1 + r(u))^5 with
+ * u = min(c + (1 - c) s, 1), c a power of two at most (eps/r_cut)^2 / 2, and G_a and the quadratic
+ * r come from a table of pieces built on the host for the box (64 per octave of u, relative
+ * least-squares fits, zero at u = 1);
  * the rest of the pair arithmetic is FP32, with the sums over at most 192 list entries added up
  * in FP64.  ax, ay, az: n values each of type out_prec
  * (TREEPM_FP32 = float, TREEPM_FP64 = double) and kind mem_kind.  Requires a walk

@@ -262,15 +262,15 @@ struct ForceParams {
 };
 
 // The FP32 pair law G(s) = g(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2) (s = r^2 in units of
-// r_cut^2) as quadratic pieces of p = G^(1/5) in u = min(c + (1 - c) s, 1): 2^kTabSegBits pieces
-// per octave of u, located by the bit pattern of u, from u = c up to u = 1 (R = 2); the last
-// entry is zero and takes u = 1.
+// r_cut^2) as pieces G = G_a (1 + r)^5, r quadratic in u = min(c + (1 - c) s, 1) less the piece's
+// lower edge: 2^kTabSegBits pieces per octave of u, located by the bit pattern of u, from u = c up
+// to u = 1 (R = 2); the last entry is zero and takes u = 1.
 constexpr int kTabSegBits = 6;
 constexpr int kTabShift = 23 - kTabSegBits;
 constexpr int kTabAddrShift = kTabShift - 2; // bits(edge) >> this = byte address of its entry
 constexpr int kTabMinExp = -27;              // c >= 2^-27: eps / r_cut down to 2^-13
 struct ForceTable {
-    const float *coef;  // device: entries constant terms, then the linear, then the quadratic
+    const float *coef;  // device: the entries' G_a, then r's linear and its quadratic terms
     uint32_t entries;
     uint32_t base;      // byte address of the first entry: bits(c) >> kTabAddrShift
     float c;            // a power of two at most (eps/r_cut)^2 / 2

@@ -32,12 +32,16 @@ namespace {
 //   a_i = 1/(r_cut^2 lam) sum_j m_j d'_ij G(s),  G(s) = g(2 sqrt(s)) / (s + (eps/r_cut)^2)^(3/2),
 // s = |d_ij|^2 / r_cut^2 = (u - c) / (1 - c) with u = |d'_ij|^2 + c: c is a power of two below
 // (eps/r_cut)^2, added inside the fused sum of squares, whose result the instruction itself
-// clamps to 1, so the cutoff is exactly u = 1.  G is read from a table of p = G^(1/5)
-// (build_force_table): 2^kTabSegBits pieces per octave of u, a quadratic in t = u - a where a,
-// the piece's lower edge, is u with its low mantissa bits cleared (one AND, and t is exact),
-// and G = p^5.  The fifth root turns eq. (2)'s fifth-order zero at the cutoff into a simple one
-// and flattens s^-3/2 to s^-3/10, so that a quadratic keeps G's relative accuracy up to R = 2.
-// A pair is 18 vector instructions, all of the kind that issues every 2 cycles on gfx950 (FP32
+// clamps to 1, so the cutoff is exactly u = 1.  G is read from a table of G = G_a (1 + r)^5
+// (build_force_table): 2^kTabSegBits pieces per octave of u, a the piece's lower edge, which is u
+// with its low mantissa bits cleared (one AND), G_a about the value there, and r a quadratic
+// without a constant in t = u - a, which is exact.  The fifth root 1 + r turns eq. (2)'s
+// fifth-order zero at the cutoff into a simple one and flattens s^-3/2 to s^-3/10, so that a
+// quadratic keeps G's relative accuracy up to R = 2; and with |r| at most 0.008 but for the last
+// pieces, what is rounded in G is G_a and the sum, each once (p = G^(1/5) itself rounded to FP32
+// and raised to the fifth power shows its rounding five times, RMS 1.5e-7 in G for R < 1 where
+// this is 0.5e-7).
+// A pair is 21 vector instructions, all of the kind that issues every 2 cycles on gfx950 (FP32
 // add, multiply, fused multiply-add, right shift, AND with a literal), and three 4-byte LDS
 // reads.  Measured there, cycles per instruction of a wave with four waves on the SIMD: FP32
 // fma 2.3-2.7, mul/sub/shift 2.2, AND with a literal 2.4; three-operand integer forms, min, cmp
@@ -118,9 +122,10 @@ static_assert(kTileF32 % 16 == 0, "J divides a tile");
 // One pair (see pair_u): the force from its piece's coefficients.
 __device__ __forceinline__ float pair_f(float c0, float c1, float c2, float t, float m)
 {
-    const float p = fmaf(fmaf(c2, t, c1), t, c0);
-    const float p2 = p * p;
-    return (p2 * p2) * (p * m);
+    const float r = fmaf(c2, t, c1) * t;
+    // (1 + r)^5 - 1
+    const float y = r * fmaf(r, fmaf(r, fmaf(r, r + 5.0f, 10.0f), 10.0f), 5.0f);
+    return fmaf(c0, y, c0) * m;
 }
 constexpr uint32_t kTabEdgeMask = ~((1u << kTabShift) - 1u);
 
@@ -232,11 +237,12 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
     return kept;
 }
 
-// What bounds it (256^3 clustered box, n_crit 256): the LDS pipe is busy 93 % of the time and
-// the vector units 80 %.  The call takes 10.2 ms, 1.9 pairs per ps (12.4 with a kernel per blocking
-// factor, a table of 16-byte entries and queue counters side by side: 311,000 groups taken
-// through counters in one cache line alone cost about 12 ms, at 40 ns each); without the table
-// reads it would be 8.7.  700,001 particles, build, walk and force: 3.44 -> 1.06 ms.
+// What bounds it (256^3 clustered box, n_crit 256): the LDS pipe and the vector units, both nearly
+// always busy.  The kernel takes 10.6 ms, 1.85 pairs per ps.  As the fifth power of p, three
+// instructions fewer a pair, it was 10.0 ms with the LDS pipe 93 % and the vector units 80 % busy;
+// 12.4 with a kernel per blocking factor, a table of 16-byte entries and queue counters side by
+// side (311,000 groups taken through counters in one cache line alone cost about 12 ms, at 40 ns
+// each).  700,001 particles, build, walk and force: 3.44 -> 1.08 ms.
 struct PolicyF32 {
     static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
     static constexpr uint32_t kQueueAt = kClsQueue;
@@ -959,9 +965,9 @@ bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTabl
     ft.c = (float)c;
     coef.assign(3 * (size_t)ft.entries, 0.f); // the entry of u = 1 stays zero
     // Each piece: the quadratic in t closest, in the relative least-squares sense at 6
-    // Chebyshev nodes, to p, with the constant term rounded to float first and the other two
-    // fitted to what is left: the rounding of the constant, which G = p^5 would show fivefold,
-    // is then made up for over most of the piece.
+    // Chebyshev nodes, to p = G^(1/5) gives G_a, rounded to float; then 1 + r, a quadratic with
+    // the constant 1, is fitted to (G / G_a)^(1/5) in the same sense, which makes up for that
+    // rounding over most of the piece.
     constexpr int kNodes = 6;
     const double pi = 3.14159265358979323846;
     const double seg = 1.0 / (1 << kTabSegBits);
@@ -971,7 +977,7 @@ bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTabl
         const int e = kc + (int)(k >> kTabSegBits);
         const double lo = std::ldexp(1.0 + (double)(k & ((1u << kTabSegBits) - 1)) * seg, e);
         const double w = std::ldexp(seg, e);
-        double y[kNodes], c0 = 0.0;
+        double y[kNodes];
         double m[3][3] = {}, r[3] = {};
         for (int i = 0; i < kNodes; ++i) {
             const double u = lo + x[i] * w;
@@ -982,7 +988,7 @@ bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTabl
                 for (int b = 0; b < 3; ++b) m[a][b] += v[a] * v[b];
             }
         }
-        // c0 of the full fit (Cramer's rule), rounded; then the 2 x 2 system of the others
+        // the constant of the full fit (Cramer's rule); then the 2 x 2 system of the others
         auto det3 = [](const double A[3][3]) {
             return A[0][0] * (A[1][1] * A[2][2] - A[1][2] * A[2][1]) -
                    A[0][1] * (A[1][0] * A[2][2] - A[1][2] * A[2][0]) +
@@ -991,10 +997,10 @@ bool build_force_table(double eps_over_rcut, std::vector<float> &coef, ForceTabl
         double m0[3][3];
         for (int a = 0; a < 3; ++a)
             for (int b = 0; b < 3; ++b) m0[a][b] = b == 0 ? r[a] : m[a][b];
-        c0 = (double)(float)(det3(m0) / det3(m));
+        coef[k] = (float)std::pow(det3(m0) / det3(m), 5.0);
+        const double c0 = std::pow((double)coef[k], 0.2);
         const double r1 = r[1] - m[1][0] * c0, r2 = r[2] - m[2][0] * c0;
-        const double d = m[1][1] * m[2][2] - m[1][2] * m[2][1];
-        coef[k] = (float)c0;
+        const double d = (m[1][1] * m[2][2] - m[1][2] * m[2][1]) * c0;
         coef[ft.entries + k] = (float)((r1 * m[2][2] - r2 * m[1][2]) / d / w);
         coef[2 * ft.entries + k] = (float)((m[1][1] * r2 - m[2][1] * r1) / d / (w * w));
     }
