@@ -416,7 +416,7 @@ void launch_force_f64(const ForceBox &box, int n_cu, hipStream_t s);
 
 // Particle-mesh long-range force (k_pm.hip), mesh N^3 with N a power of two in [16, 1024].
 // Octant table of the Green's function ((N/2+1)^3 floats) and N/2 twiddles.
-void launch_pm_green(int N, double L, double eta, float *green, float2 *tw, hipStream_t s);
+void launch_pm_green(int N, double L, double eta, float *green, double2 *tw, hipStream_t s);
 // Fills the fixed-point mass mesh (N^3 words, every word written) from the key-ordered records
 // and their sorted keys; mx holds the largest mass.  Scratch: cell_start (cells + 1 words),
 // item_start (cells + 1 words), scan_tmp (scan_tmp_elems(cells) words) and slots
@@ -433,7 +433,7 @@ void launch_pm_assign(const double4 *ps, const uint64_t *key, int64_t n, int N, 
 size_t pm_grid_points(int N);
 void launch_pm_potential(const unsigned long long *mass, const unsigned long long *mx,
                          int64_t n, int N, float2 *grid, float *phi, const float *green,
-                         const float2 *tw, hipStream_t s);
+                         const double2 *tw, hipStream_t s);
 // Interpolated force of key-ordered particle k (ps[k]) into stage[idx[k]] = (ax, ay, az, 0),
 // i.e. in the caller's order (idx is the sort permutation).  cell_start and item_start as
 // launch_pm_assign left them for the same particles.

@@ -25,12 +25,20 @@
 namespace tpm {
 namespace {
 
-__device__ __forceinline__ float2 cmul(float2 a, float2 b)
+__device__ __forceinline__ double2 cmul(double2 a, double2 b)
 {
-    return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
+    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
-__device__ __forceinline__ float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ float2 csub(float2 a, float2 b) { return make_float2(a.x - b.x, a.y - b.y); }
+__device__ __forceinline__ double2 cadd(double2 a, double2 b)
+{
+    return make_double2(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ double2 csub(double2 a, double2 b)
+{
+    return make_double2(a.x - b.x, a.y - b.y);
+}
+__device__ __forceinline__ double2 wide(float2 a) { return make_double2(a.x, a.y); }
+__device__ __forceinline__ float2 narrow(double2 a) { return make_float2((float)a.x, (float)a.y); }
 
 // Nearest mesh point of coordinate x for inv_h = N / L.  The product is rounded on its own
 // (no contraction into the add), so every kernel finds the same point for the same x.
@@ -284,8 +292,13 @@ __global__ __launch_bounds__(kCellPts * kCellPts * kCellPts) void k_pm_gather(
 // steps the points change places through LDS once.  Step s with radix R after steps of product
 // NS: butterfly j takes points j + r N / R, times exp(-2 pi i r (j mod NS) / (NS R)), to points
 // (j / NS) NS R + (j mod NS) + r NS.
-// N = 256, five passes from the masses to the potential: 0.14 ms for 0.75 GB read and written;
-// with radix-2 stages through LDS on the full complex mesh 0.59 ms.
+// The points are double in registers, and float wherever they are stored (in LDS between the steps,
+// in memory between the passes): with float butterflies the half spectrum's rounding, which no
+// longer averages over k and -k, made the force of a uniform box on a fine mesh 8 % less exact
+// than the full complex transform had it; as it is, that is twice as exact (300,007 particles,
+// 256^3 mesh: 3.3e-7 RMS against 6.8e-7, and 6.4e-7 for the full one).
+// N = 256, five passes from the masses to the potential: 0.152 ms for 0.75 GB read and written,
+// 0.140 with float butterflies; with radix-2 stages through LDS on the full complex mesh 0.59.
 
 template <int LOGN>
 struct Radix; // the steps' radices, 0 where there is none
@@ -308,15 +321,15 @@ struct Lines {
 
 // Times exp(-+ i pi / 2).
 template <bool INV>
-__device__ __forceinline__ float2 quarter(float2 v)
+__device__ __forceinline__ double2 quarter(double2 v)
 {
-    return INV ? make_float2(-v.y, v.x) : make_float2(v.y, -v.x);
+    return INV ? make_double2(-v.y, v.x) : make_double2(v.y, -v.x);
 }
 
 template <bool INV>
-__device__ __forceinline__ void dft4(float2 &a, float2 &b, float2 &c, float2 &d)
+__device__ __forceinline__ void dft4(double2 &a, double2 &b, double2 &c, double2 &d)
 {
-    const float2 s = cadd(a, c), m = csub(a, c), t = cadd(b, d), u = quarter<INV>(csub(b, d));
+    const double2 s = cadd(a, c), m = csub(a, c), t = cadd(b, d), u = quarter<INV>(csub(b, d));
     a = cadd(s, t);
     b = cadd(m, u);
     c = csub(s, t);
@@ -325,22 +338,22 @@ __device__ __forceinline__ void dft4(float2 &a, float2 &b, float2 &c, float2 &d)
 
 // Discrete Fourier transform of R points in registers, natural order in and out.
 template <int R, bool INV>
-__device__ __forceinline__ void dft(float2 *v)
+__device__ __forceinline__ void dft(double2 *v)
 {
-    constexpr float kH = 0.70710678118654752440f; // cos(pi / 4)
-    constexpr float sg = INV ? 1.0f : -1.0f;
+    constexpr double kH = 0.70710678118654752440; // cos(pi / 4)
+    constexpr double sg = INV ? 1.0 : -1.0;
     if (R == 4) {
         dft4<INV>(v[0], v[1], v[2], v[3]);
     } else if (R == 8) {
-        float2 e[4], o[4];
+        double2 e[4], o[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             e[i] = cadd(v[i], v[i + 4]);
             o[i] = csub(v[i], v[i + 4]);
         }
-        o[1] = cmul(o[1], make_float2(kH, sg * kH));
+        o[1] = cmul(o[1], make_double2(kH, sg * kH));
         o[2] = quarter<INV>(o[2]);
-        o[3] = cmul(o[3], make_float2(-kH, sg * kH));
+        o[3] = cmul(o[3], make_double2(-kH, sg * kH));
         dft4<INV>(e[0], e[1], e[2], e[3]);
         dft4<INV>(o[0], o[1], o[2], o[3]);
 #pragma unroll
@@ -349,11 +362,11 @@ __device__ __forceinline__ void dft(float2 *v)
             v[2 * i + 1] = o[i];
         }
     } else {
-        constexpr float c1 = 0.92387953251128675613f, s1 = 0.38268343236508977173f; // pi / 8
-        const float2 w[10] = {{1.f, 0.f},   {c1, sg * s1},  {kH, sg * kH}, {s1, sg * c1},
-                              {0.f, sg},    {-s1, sg * c1}, {-kH, sg * kH}, {-c1, sg * s1},
-                              {-1.f, 0.f},  {-c1, -sg * s1}};
-        float2 y[4][4]; // y[i][k]: over points i, i + 4, i + 8, i + 12
+        constexpr double c1 = 0.92387953251128675613, s1 = 0.38268343236508977173; // pi / 8
+        const double2 w[10] = {{1.0, 0.0},   {c1, sg * s1},  {kH, sg * kH}, {s1, sg * c1},
+                              {0.0, sg},    {-s1, sg * c1}, {-kH, sg * kH}, {-c1, sg * s1},
+                              {-1.0, 0.0},  {-c1, -sg * s1}};
+        double2 y[4][4]; // y[i][k]: over points i, i + 4, i + 8, i + 12
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -375,7 +388,7 @@ __device__ __forceinline__ void dft(float2 *v)
 // Calls f(e, v) for the thread's points as a step of radix R reads them (and the last one leaves
 // them), or as a step of radix R after NS leaves them.
 template <int LOGN, int R, class F>
-__device__ __forceinline__ void for_inputs(float2 *v, int jt, F f)
+__device__ __forceinline__ void for_inputs(double2 *v, int jt, F f)
 {
 #pragma unroll
     for (int q = 0; q < 16 / R; ++q)
@@ -384,7 +397,7 @@ __device__ __forceinline__ void for_inputs(float2 *v, int jt, F f)
             f(jt + q * Lines<LOGN>::T + r * (Lines<LOGN>::N / R), v[q * R + r]);
 }
 template <int LOGN, int R, int NS, class F>
-__device__ __forceinline__ void for_outputs(float2 *v, int jt, F f)
+__device__ __forceinline__ void for_outputs(double2 *v, int jt, F f)
 {
 #pragma unroll
     for (int q = 0; q < 16 / R; ++q) {
@@ -395,7 +408,7 @@ __device__ __forceinline__ void for_outputs(float2 *v, int jt, F f)
 }
 
 template <int LOGN, int R, int NS, bool INV>
-__device__ __forceinline__ void step(float2 *v, int jt, const float2 *tw)
+__device__ __forceinline__ void step(double2 *v, int jt, const double2 *tw)
 {
     constexpr int N = 1 << LOGN;
 #pragma unroll
@@ -404,7 +417,7 @@ __device__ __forceinline__ void step(float2 *v, int jt, const float2 *tw)
         if (NS > 1) {
 #pragma unroll
             for (int r = 1; r < R; ++r) {
-                float2 w = tw[r * k * (N / (NS * R))];
+                double2 w = tw[r * k * (N / (NS * R))];
                 if (INV) w.y = -w.y;
                 v[q * R + r] = cmul(v[q * R + r], w);
             }
@@ -416,18 +429,19 @@ __device__ __forceinline__ void step(float2 *v, int jt, const float2 *tw)
 // The points through LDS (at(e): where point e of the thread's line lies), from the order in which
 // the step of radix R after NS leaves them to that in which one of radix R2 reads them.
 template <int LOGN, int R, int NS, int R2, class AT>
-__device__ __forceinline__ void exchange(float2 *v, int jt, float2 *buf, AT at)
+__device__ __forceinline__ void exchange(double2 *v, int jt, float2 *buf, AT at)
 {
-    for_outputs<LOGN, R, NS>(v, jt, [&](int e, float2 &x) { buf[at(e)] = x; });
+    for_outputs<LOGN, R, NS>(v, jt, [&](int e, double2 &x) { buf[at(e)] = narrow(x); });
     __syncthreads();
-    for_inputs<LOGN, R2>(v, jt, [&](int e, float2 &x) { x = buf[at(e)]; });
+    for_inputs<LOGN, R2>(v, jt, [&](int e, double2 &x) { x = wide(buf[at(e)]); });
     __syncthreads();
 }
 
 // The whole line: v as a step of radix A (C from the back with REV) reads it; left as the last
 // step leaves it.  REV takes the radices in reverse, so it can follow a plain one in registers.
 template <int LOGN, bool INV, bool REV, class AT>
-__device__ __forceinline__ void fft_line(float2 *v, int jt, float2 *buf, const float2 *tw, AT at)
+__device__ __forceinline__ void fft_line(double2 *v, int jt, float2 *buf, const double2 *tw,
+                                         AT at)
 {
     using X = Radix<LOGN>;
     constexpr int n = X::c ? 3 : X::b ? 2 : 1;
@@ -452,12 +466,12 @@ struct Ends { // radices of the first and the last step
 
 // exp(-2 pi i k / N), k < N, from the table's first half.
 template <int LOGN>
-__device__ __forceinline__ void load_twiddles(float2 *tw_s, const float2 *tw)
+__device__ __forceinline__ void load_twiddles(double2 *tw_s, const double2 *tw)
 {
     constexpr int N = 1 << LOGN;
     for (int k = threadIdx.x; k < N; k += blockDim.x) {
-        const float2 w = tw[k & (N / 2 - 1)];
-        tw_s[k] = k < N / 2 ? w : make_float2(-w.x, -w.y);
+        const double2 w = tw[k & (N / 2 - 1)];
+        tw_s[k] = k < N / 2 ? w : make_double2(-w.x, -w.y);
     }
 }
 
@@ -467,26 +481,26 @@ __device__ __forceinline__ void load_twiddles(float2 *tw_s, const float2 *tw)
 template <int LOGN>
 __global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_forward(
     const unsigned long long *__restrict__ mass, const unsigned long long *__restrict__ mx,
-    int64_t n_part, float2 *__restrict__ grid, const float2 *__restrict__ tw)
+    int64_t n_part, float2 *__restrict__ grid, const double2 *__restrict__ tw)
 {
     using D = Lines<LOGN>;
     constexpr int N = D::N, P = D::P;
     __shared__ float2 buf[D::kRows * P];
-    __shared__ float2 tw_s[N];
+    __shared__ double2 tw_s[N];
     load_twiddles<LOGN>(tw_s, tw);
     const int l = threadIdx.x % P, jt = threadIdx.x / P;
     const int y = blockIdx.x / (N / (2 * P)), z0 = (blockIdx.x % (N / (2 * P))) * 2 * P;
     const double inv_s = 1.0 / pm_scale(*mx, n_part);
     auto at = [&](int e) { return (e + (e >> 4)) * P + l; };
-    float2 v[16];
-    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) {
+    double2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, double2 &x) {
         const ulonglong2 m2 =
             *reinterpret_cast<const ulonglong2 *>(mass + ((size_t)e * N + y) * N + z0 + 2 * l);
-        x = make_float2((float)((double)m2.x * inv_s), (float)((double)m2.y * inv_s));
+        x = make_double2((double)m2.x * inv_s, (double)m2.y * inv_s);
     });
     __syncthreads();
     fft_line<LOGN, false, false>(v, jt, buf, tw_s, at);
-    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) { buf[at(e)] = x; });
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, double2 &x) { buf[at(e)] = narrow(x); });
     __syncthreads();
     for (int k = jt; k <= N / 2; k += D::T) {
         const float2 c = buf[at(k)], d = buf[at((N - k) & (N - 1))];
@@ -499,12 +513,12 @@ __global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_forwar
 // Inverse along x, from the half spectrum to the real potential, two lines at a time again.
 template <int LOGN>
 __global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_inverse(
-    const float2 *__restrict__ grid, float *__restrict__ phi, const float2 *__restrict__ tw)
+    const float2 *__restrict__ grid, float *__restrict__ phi, const double2 *__restrict__ tw)
 {
     using D = Lines<LOGN>;
     constexpr int N = D::N, P = D::P;
     __shared__ float2 buf[D::kRows * P];
-    __shared__ float2 tw_s[N];
+    __shared__ double2 tw_s[N];
     load_twiddles<LOGN>(tw_s, tw);
     const int l = threadIdx.x % P, jt = threadIdx.x / P;
     const int y = blockIdx.x / (N / (2 * P)), z0 = (blockIdx.x % (N / (2 * P))) * 2 * P;
@@ -520,36 +534,36 @@ __global__ __launch_bounds__(Lines<LOGN>::P *Lines<LOGN>::T) void k_fft_x_invers
         }
     }
     __syncthreads();
-    float2 v[16];
-    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { x = buf[at(e)]; });
+    double2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, double2 &x) { x = wide(buf[at(e)]); });
     __syncthreads();
     fft_line<LOGN, true, false>(v, jt, buf, tw_s, at);
-    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) {
-        *reinterpret_cast<float2 *>(phi + ((size_t)e * N + y) * N + z0 + 2 * l) = x;
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, double2 &x) {
+        *reinterpret_cast<float2 *>(phi + ((size_t)e * N + y) * N + z0 + 2 * l) = narrow(x);
     });
 }
 
 // Along y in the plane of one kx, B neighbouring lines in z.
 template <int LOGN, bool INV>
 __global__ __launch_bounds__(Lines<LOGN>::B *Lines<LOGN>::T) void k_fft_y(
-    float2 *__restrict__ grid, const float2 *__restrict__ tw)
+    float2 *__restrict__ grid, const double2 *__restrict__ tw)
 {
     using D = Lines<LOGN>;
     constexpr int N = D::N, B = D::B;
     __shared__ float2 buf[D::kRows * B];
-    __shared__ float2 tw_s[N];
+    __shared__ double2 tw_s[N];
     load_twiddles<LOGN>(tw_s, tw);
     const int l = threadIdx.x % B, jt = threadIdx.x / B;
     float2 *const line =
         grid + (size_t)(blockIdx.x / (N / B)) * N * N + (blockIdx.x % (N / B)) * B + l;
     auto at = [&](int e) { return (e + (e >> 4)) * B + l; };
-    float2 v[16];
+    double2 v[16];
     for_inputs<LOGN, Ends<LOGN>::first>(v, jt,
-                                        [&](int e, float2 &x) { x = line[(size_t)e * N]; });
+                                        [&](int e, double2 &x) { x = wide(line[(size_t)e * N]); });
     __syncthreads();
     fft_line<LOGN, INV, false>(v, jt, buf, tw_s, at);
     for_inputs<LOGN, Ends<LOGN>::last>(v, jt,
-                                       [&](int e, float2 &x) { line[(size_t)e * N] = x; });
+                                       [&](int e, double2 &x) { line[(size_t)e * N] = narrow(x); });
 }
 
 // z forward, times the Green's function, z inverse, for B rows (kx, ky = q0 + l).  The forward
@@ -557,29 +571,29 @@ __global__ __launch_bounds__(Lines<LOGN>::B *Lines<LOGN>::T) void k_fft_y(
 // them.  green is the octant table, index (fx H + fy) H + fz with f = min(k, N - k), H = N/2 + 1.
 template <int LOGN>
 __global__ __launch_bounds__(Lines<LOGN>::B *Lines<LOGN>::T) void k_fft_z_green(
-    float2 *__restrict__ grid, const float2 *__restrict__ tw, const float *__restrict__ green)
+    float2 *__restrict__ grid, const double2 *__restrict__ tw, const float *__restrict__ green)
 {
     using D = Lines<LOGN>;
     constexpr int N = D::N, B = D::B, H = N / 2 + 1;
     __shared__ float2 buf[D::kRows * B];
-    __shared__ float2 tw_s[N];
+    __shared__ double2 tw_s[N];
     load_twiddles<LOGN>(tw_s, tw);
     const int l = threadIdx.x / D::T, jt = threadIdx.x % D::T;
     const int kx = blockIdx.x / (N / B), ky = (blockIdx.x % (N / B)) * B + l;
     float2 *const line = grid + ((size_t)kx * N + ky) * N;
     const float *const g = green + ((size_t)kx * H + (ky <= N / 2 ? ky : N - ky)) * H;
     auto at = [&](int e) { return l * D::kRows + e + (e >> 4); };
-    float2 v[16];
-    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { x = line[e]; });
+    double2 v[16];
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, double2 &x) { x = wide(line[e]); });
     __syncthreads();
     fft_line<LOGN, false, false>(v, jt, buf, tw_s, at);
-    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, float2 &x) {
-        const float gk = g[e <= N / 2 ? e : N - e];
+    for_inputs<LOGN, Ends<LOGN>::last>(v, jt, [&](int e, double2 &x) {
+        const double gk = g[e <= N / 2 ? e : N - e];
         x.x *= gk;
         x.y *= gk;
     });
     fft_line<LOGN, true, true>(v, jt, buf, tw_s, at);
-    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, float2 &x) { line[e] = x; });
+    for_inputs<LOGN, Ends<LOGN>::first>(v, jt, [&](int e, double2 &x) { line[e] = narrow(x); });
 }
 
 // Fourier transform of the S2 cloud of radius eta at x = k eta (Hockney & Eastwood's shape):
@@ -603,14 +617,14 @@ __device__ __forceinline__ double s2_hat(double x)
 // tw[k] = exp(-2 pi i k / N), k < N/2.
 __global__ __launch_bounds__(256) void k_pm_green(int N, double L, double eta,
                                                   float *__restrict__ green,
-                                                  float2 *__restrict__ tw)
+                                                  double2 *__restrict__ tw)
 {
     const int H = N / 2 + 1;
     const size_t t = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
     if (t < (size_t)N / 2) {
         double sn, cs;
         sincospi(2.0 * (double)t / N, &sn, &cs);
-        tw[t] = make_float2((float)cs, (float)-sn);
+        tw[t] = make_double2(cs, -sn);
     }
     if (t >= (size_t)H * H * H) return;
     const int fz = (int)(t % H), fy = (int)((t / H) % H), fx = (int)(t / ((size_t)H * H));
@@ -782,7 +796,7 @@ __global__ __launch_bounds__(256) void k_pm_split(const float4 *__restrict__ sta
 
 } // namespace
 
-void launch_pm_green(int N, double L, double eta, float *green, float2 *tw, hipStream_t s)
+void launch_pm_green(int N, double L, double eta, float *green, double2 *tw, hipStream_t s)
 {
     const size_t H = N / 2 + 1;
     const size_t work = H * H * H > (size_t)N / 2 ? H * H * H : (size_t)N / 2;
@@ -819,7 +833,7 @@ size_t pm_grid_points(int N) { return (size_t)(N / 2 + 1) * N * N; }
 
 template <int LOGN>
 static void pm_potential(const unsigned long long *mass, const unsigned long long *mx, int64_t n,
-                         float2 *grid, float *phi, const float *green, const float2 *tw,
+                         float2 *grid, float *phi, const float *green, const double2 *tw,
                          hipStream_t s)
 {
     using D = Lines<LOGN>;
@@ -833,7 +847,7 @@ static void pm_potential(const unsigned long long *mass, const unsigned long lon
 
 void launch_pm_potential(const unsigned long long *mass, const unsigned long long *mx,
                          int64_t n, int N, float2 *grid, float *phi, const float *green,
-                         const float2 *tw, hipStream_t s)
+                         const double2 *tw, hipStream_t s)
 {
     switch (N) {
     case 16: return pm_potential<4>(mass, mx, n, grid, phi, green, tw, s);

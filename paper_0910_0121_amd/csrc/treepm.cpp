@@ -1978,7 +1978,7 @@ TREEPM_API int treepm_force_long(treepm_ctx *c, void *ax, void *ay, void *az, in
         hipError_t e = reserve(c->pm_mass, pts * 8);
         if (e == hipSuccess) e = reserve(c->pm_grid, pm_grid_points((int)N) * 8);
         if (e == hipSuccess) e = reserve(c->pm_green, H * H * H * 4);
-        if (e == hipSuccess) e = reserve(c->pm_tw, (size_t)N / 2 * 8);
+        if (e == hipSuccess) e = reserve(c->pm_tw, (size_t)N / 2 * 16);
         if (e == hipSuccess) e = reserve(c->pm_stage, (size_t)c->n * 16);
         const size_t cells = pm_assign_cells((int)N);
         if (e == hipSuccess)
@@ -1990,7 +1990,7 @@ TREEPM_API int treepm_force_long(treepm_ctx *c, void *ax, void *ay, void *az, in
     }
     const double eta = 0.5 * P.r_cut;
     if (c->pm_n != (int)N || c->pm_L != P.L || c->pm_eta != eta) {
-        launch_pm_green((int)N, P.L, eta, c->pm_green.as<float>(), c->pm_tw.as<float2>(), s);
+        launch_pm_green((int)N, P.L, eta, c->pm_green.as<float>(), c->pm_tw.as<double2>(), s);
         c->pm_n = (int)N;
         c->pm_L = P.L;
         c->pm_eta = eta;
@@ -2020,7 +2020,7 @@ TREEPM_API int treepm_force_long(treepm_ctx *c, void *ax, void *ay, void *az, in
                      c->pm_mx.as<unsigned long long>(), cell_start, item_start, scan_tmp,
                      c->pm_slots.as<unsigned long long>(), mass, s);
     launch_pm_potential(mass, c->pm_mx.as<unsigned long long>(), c->n, (int)N, grid, phi,
-                        c->pm_green.as<float>(), c->pm_tw.as<float2>(), s);
+                        c->pm_green.as<float>(), c->pm_tw.as<double2>(), s);
     launch_pm_interp(ps, c->n, (int)N, P.L, phi, c->idx.as<uint32_t>(), c->pm_stage.as<float4>(),
                      cell_start, item_start, s);
     launch_pm_split(c->pm_stage.as<float4>(), c->n, dst[0], dst[1], dst[2],
