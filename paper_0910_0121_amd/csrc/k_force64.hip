@@ -2,10 +2,11 @@
 // softening of Section 2.4), in the work split of the FP32 kernel (force_common.hpp): positions
 // relative to x_g are FP64 differences (nearest image once per entry, or per pair when the
 // group's cube plus r_cut reaches half the box), and the pair law is
-//   * read from a table (force_table64.cpp) where the softening allows one: G(s) = G_a (1 + r)^5
-//     with r a polynomial of degree 6 in t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the
-//     piece's lower edge, which is u with its low mantissa bits cleared, so t is exact; or
-//   * evaluated pair by pair for smaller eps: (r^2 + eps^2)^(-1/2) and r^(-1) from the hardware
+//   * read from a table (force_table64.cpp) where the softening allows one and the box is large
+//     enough to be worth making it: G(s) = G_a (1 + r)^5 with r a polynomial of degree 6 in
+//     t = u - a, u = 2^18 (c + (1 - c) s) clamped to 2^18, a the piece's lower edge, which is u with
+//     its low mantissa bits cleared, so t is exact; or
+//   * evaluated pair by pair otherwise: (r^2 + eps^2)^(-1/2) and r^(-1) from the hardware
 //     estimate refined by two Newton steps, and eq. (2) in a form with no cancellation: for R < 1,
 //     g = 1 + R^3 (-8/5 + R^2 (8/5 + R (-1/2 + R (-12/35 + 3R/20)))), and for R >= 1,
 //     g = max(2 - R, 0)^5 (7R^3 + 22R^2 + 10R + 4) / 140.

@@ -1465,11 +1465,22 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
     return TREEPM_OK;
 }
 
+// From this many interactions on the FP64 kernel reads a table.  Force calls of 3.4e7, 1.2e8, 2.0e8,
+// 3.2e8, 5.5e8 and 8.6e8 interactions take 156, 369, 562, 823, 1317 and 2208 us pair by pair and
+// 133, 291, 408, 568, 936 and 1700 from the table, which costs a context 0.15 ms for each new
+// eps / r_cut, and the process 1.1 ms the first time.
+constexpr uint64_t kTable64Pairs = 1ull << 28;
+
+bool wants_table64(const treepm_ctx *c)
+{
+    return c->prm.precision == TREEPM_FP64 && c->st[2] >= kTable64Pairs;
+}
+
 // The same for the FP64 kernel; a softening too small for a table is no error.
 int ensure_table64(treepm_ctx *c, hipStream_t s)
 {
     const double key = c->prm.eps / c->prm.r_cut;
-    if (c->tab64_key == key) return TREEPM_OK;
+    if (c->tab64_key == key || !wants_table64(c)) return TREEPM_OK;
     std::vector<double> hi;
     std::vector<float> lo;
     c->tab64_ok = false;
@@ -1508,7 +1519,7 @@ ForceBox force_box(treepm_ctx *c, const ForceParams &fp, void *rec, int rec64)
     F.items = c->items.as<ForceItem>();
     F.n_items = c->n_items;
     F.rows = c->rows.as<double>();
-    if (c->prm.precision == TREEPM_FP64 && c->tab64_ok) {
+    if (wants_table64(c) && c->tab64_ok) {
         F.tab64_hi = c->tab64.as<double>();
         F.tab64_lo = reinterpret_cast<const float *>(F.tab64_hi +
                                                      (size_t)kTab64F64 * kTab64Entries);

@@ -273,6 +273,26 @@ int main(int argc, char **argv)
         print(from);
         printf("built\n");
         treepm_destroy(c);
+    } else if (cmd == "force") { // precision, interactions, rows: a force call after a walk
+        const int prec = number(argc, argv, 2, 0);
+        rep.pairs = strtoull(argv[3], nullptr, 10);
+        rep.rows = strtoull(argv[4], nullptr, 10);
+        rep.items = rep.rows ? 4 : 0;
+        const treepm_params p = params(prec ? TREEPM_FP64 : TREEPM_FP32);
+        const Arrays a(200000);
+        treepm_stats st{};
+        void *out = nullptr;
+        if (treepm_create(&p, 0, &c) || build(c, a) || treepm_walk(c, nullptr, &st) ||
+            hipMalloc(&out, 3 * 200000 * 8) != hipSuccess)
+            return 1;
+        const size_t from = trace.size();
+        const int before = mallocs;
+        double *o = static_cast<double *>(out);
+        if (treepm_force_short(c, o, o + 200000, o + 400000, p.precision, TREEPM_DEVICE, nullptr))
+            return 1;
+        print(from);
+        printf("allocations %d\n", mallocs - before);
+        treepm_destroy(c);
     } else if (cmd == "slots") { // groups, longest and mean list: the memory held after 3 walks
         rep.groups = (uint32_t)number(argc, argv, 2, 0);
         rep.longest = (uint64_t)number(argc, argv, 3, 0);

@@ -92,3 +92,13 @@ def test_a_server_serves_a_box_that_outgrew_its_budget(run):
     lines = run("server", n, 20000, 9000, 3000, 3, n * 330 + (64 << 20))
     assert max(_field(lines, "resident")) > n * 330 + (64 << 20)
     assert sum(l == "served 0" for l in lines) == 3
+
+
+@pytest.mark.parametrize("pairs,table", [(34_000_000, False), ((1 << 28) - 1, False),
+                                         (1 << 28, True), (1 << 33, True)])
+def test_fp64_table_only_where_it_pays(run, pairs, table):
+    """A small box's first FP64 force does not make a table on the host, which takes longer than
+    all of its call."""
+    lines = run("force", 1, pairs, 0)
+    assert [l for l in lines if f"k_force_f64<{str(table).lower()}>" in l]
+    assert not [l for l in lines if f"k_force_f64<{str(not table).lower()}>" in l]
