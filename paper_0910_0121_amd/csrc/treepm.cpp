@@ -1067,6 +1067,35 @@ int wait_walk_results(treepm_ctx *c, hipStream_t s, WalkResults &wr)
     return TREEPM_OK;
 }
 
+// From this many interactions on the FP64 kernel reads a table.  Force calls of 3.4e7, 1.2e8, 2.0e8,
+// 3.2e8, 5.5e8 and 8.6e8 interactions take 156, 369, 562, 823, 1317 and 2208 us pair by pair and
+// 133, 291, 408, 568, 936 and 1700 from the table, which costs a context 0.15 ms for each new
+// eps / r_cut, and the process 1.1 ms the first time.
+constexpr uint64_t kTable64Pairs = 1ull << 28;
+
+bool wants_table64(const treepm_ctx *c)
+{
+    return c->prm.precision == TREEPM_FP64 && c->st[2] >= kTable64Pairs;
+}
+
+// Device memory that the force of a walked box needs beside its outputs.  All of it is held when
+// the walk returns, so that the force itself takes none.
+constexpr size_t kTabBytes = 96 << 10; // the FP32 pair law's table and the quadrupole's
+constexpr size_t kTab64Bytes =
+    kTab64Entries * (kTab64F64 * sizeof(double) + (kTab64Deg + 1 - kTab64F64) * sizeof(float));
+static_assert(((3 << kTabSegBits) + (4 << kQuadSegBits)) * -kTabMinExp * 4 + 28 <= (int)kTabBytes,
+              "the largest of both");
+
+int reserve_force(treepm_ctx *c)
+{
+    hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
+    if (e == hipSuccess) e = reserve(c->kept_sum, 64);
+    if (e == hipSuccess && c->n_rows) e = reserve(c->rows, c->n_rows * 24);
+    if (e == hipSuccess && c->prm.precision == TREEPM_FP32) e = reserve(c->tab, kTabBytes);
+    if (e == hipSuccess && wants_table64(c)) e = reserve(c->tab64, kTab64Bytes);
+    return e == hipSuccess ? TREEPM_OK : hip_fail(c, e, "force buffers");
+}
+
 // Until the results show complete lists: a pool or a slot that was too small (bit 4) means two
 // passes, then the statistics again.
 int settle_walk(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr)
@@ -1086,7 +1115,7 @@ int settle_walk(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, WalkResults &wr
     c->n_items = (uint32_t)wr.hs[5];
     c->walk_hint_groups = bw.G;
     for (int i = 0; i < 3; ++i) c->st[i] = wr.hs[i];
-    return TREEPM_OK;
+    return reserve_force(c);
 }
 
 int do_walk(treepm_ctx *c, hipStream_t s)
@@ -1439,7 +1468,7 @@ double table_key(const treepm_params &P)
 int ensure_table(treepm_ctx *c, hipStream_t s)
 {
     const double key = table_key(c->prm);
-    if (c->tab.p && c->tab_key == key && (!c->prm.quadrupole || c->qtab.entries))
+    if (c->tab_key == key && (!c->prm.quadrupole || c->qtab.entries))
         return TREEPM_OK;
     std::vector<float> coef;
     ForceTable ft{};
@@ -1452,8 +1481,7 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
         build_quad_table(key, (double)ft.c, quad, qt);
         coef.insert(coef.end(), quad.begin(), quad.end());
     }
-    hipError_t e = reserve(c->tab, coef.size() * sizeof(float));
-    if (e != hipSuccess) return hip_fail(c, e, "pair-law table");
+    c->tab_key = 0.0; // until it is there
     HIPCHK(c, hipMemcpyAsync(c->tab.p, coef.data(), coef.size() * sizeof(float),
                              hipMemcpyHostToDevice, s));
     HIPCHK(c, hipStreamSynchronize(s)); // coef is a host temporary
@@ -1465,17 +1493,6 @@ int ensure_table(treepm_ctx *c, hipStream_t s)
     return TREEPM_OK;
 }
 
-// From this many interactions on the FP64 kernel reads a table.  Force calls of 3.4e7, 1.2e8, 2.0e8,
-// 3.2e8, 5.5e8 and 8.6e8 interactions take 156, 369, 562, 823, 1317 and 2208 us pair by pair and
-// 133, 291, 408, 568, 936 and 1700 from the table, which costs a context 0.15 ms for each new
-// eps / r_cut, and the process 1.1 ms the first time.
-constexpr uint64_t kTable64Pairs = 1ull << 28;
-
-bool wants_table64(const treepm_ctx *c)
-{
-    return c->prm.precision == TREEPM_FP64 && c->st[2] >= kTable64Pairs;
-}
-
 // The same for the FP64 kernel; a softening too small for a table is no error.
 int ensure_table64(treepm_ctx *c, hipStream_t s)
 {
@@ -1484,9 +1501,8 @@ int ensure_table64(treepm_ctx *c, hipStream_t s)
     std::vector<double> hi;
     std::vector<float> lo;
     c->tab64_ok = false;
+    c->tab64_key = -1.0;
     if (build_force_table64(key, hi, lo)) {
-        hipError_t e = reserve(c->tab64, hi.size() * 8 + lo.size() * 4);
-        if (e != hipSuccess) return hip_fail(c, e, "pair-law table");
         HIPCHK(c, hipMemcpyAsync(c->tab64.p, hi.data(), hi.size() * 8, hipMemcpyHostToDevice, s));
         HIPCHK(c, hipMemcpyAsync(c->tab64.as<double>() + hi.size(), lo.data(), lo.size() * 4,
                                  hipMemcpyHostToDevice, s));
@@ -1584,12 +1600,6 @@ int do_force_short(treepm_ctx *c, void *ax, void *ay, void *az, int out_prec, in
     NodeArrays nd = nodes_view(c);
     GroupArrays gr = groups_view(c);
     double eta = 0.5 * P.r_cut;
-    {
-        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
-        if (e == hipSuccess) e = reserve(c->kept_sum, 64);
-        if (e == hipSuccess && c->n_rows) e = reserve(c->rows, c->n_rows * 24);
-        if (e != hipSuccess) return hip_fail(c, e, "force statistics");
-    }
     ForceParams fp{P.L, P.eps * P.eps, 1.0 / eta, eta, P.r_cut * P.r_cut, P.r_cut,
                    c->kept.as<unsigned long long>()};
     const int rec64 = out_prec != TREEPM_FP32;
@@ -1831,14 +1841,10 @@ int batch_force(treepm_ctx *const *cs, int nb, float *const *ax, float *const *a
         Bind bind(c, s);
         const treepm_params &P = c->prm;
         if ((rc = ensure_table(c, s))) return rc;
-        hipError_t e = reserve(c->kept, ((size_t)c->n_groups + 1) * 8);
-        if (e == hipSuccess) e = reserve(c->kept_sum, 64);
-        if (e == hipSuccess && c->n_rows) e = reserve(c->rows, c->n_rows * 24);
-        if (e != hipSuccess) return hip_fail(c, e, "force statistics");
         dst[b] = {ax[b], ay[b], az[b]};
         if (mem_kind == TREEPM_HOST)
             for (int a = 0; a < 3; ++a) {
-                e = reserve(c->out[a], (size_t)c->n * 4);
+                hipError_t e = reserve(c->out[a], (size_t)c->n * 4);
                 if (e != hipSuccess) return hip_fail(c, e, "output staging");
                 dst[b][a] = c->out[a].as<float>();
             }

@@ -102,3 +102,10 @@ def test_fp64_table_only_where_it_pays(run, pairs, table):
     lines = run("force", 1, pairs, 0)
     assert [l for l in lines if f"k_force_f64<{str(table).lower()}>" in l]
     assert not [l for l in lines if f"k_force_f64<{str(not table).lower()}>" in l]
+
+
+@pytest.mark.parametrize("precision,pairs,rows", [(0, 1000000, 0), (0, 1000000, 300000),
+                                                  (1, 1000000, 300000), (1, 1 << 30, 0)])
+def test_force_takes_no_memory(run, precision, pairs, rows):
+    """With device outputs the force uses what the build and the walk allocated."""
+    assert "allocations 0" in run("force", precision, pairs, rows)
