@@ -1455,12 +1455,14 @@ TREEPM_API int treepm_walk(treepm_ctx *c, void *hip_stream, treepm_stats *stats)
 namespace {
 
 // eps / r_cut to 36 bits: boxes of the same ratio get the same table whatever the rounding of
-// the two lengths, and a change of 2^-36 in eps is far below the table's own rounding.
+// the two lengths, and a change of 2^-36 in eps is far below the table's own rounding.  A ratio
+// below the table's limit of 8 stays below it.
 double table_key(const treepm_params &P)
 {
     int e;
-    const double f = std::frexp(P.eps / P.r_cut, &e);
-    return std::ldexp(std::nearbyint(std::ldexp(f, 36)), e - 36);
+    const double ratio = P.eps / P.r_cut, f = std::frexp(ratio, &e);
+    const double key = std::ldexp(std::nearbyint(std::ldexp(f, 36)), e - 36);
+    return ratio < 8.0 ? std::min(key, 8.0 - 0x1p-33) : key;
 }
 
 // The FP32 pair-law table of the context's eps / r_cut (and the quadrupole's behind it), built on the host and copied to the

@@ -273,12 +273,13 @@ int main(int argc, char **argv)
         print(from);
         printf("built\n");
         treepm_destroy(c);
-    } else if (cmd == "force") { // precision, interactions, rows: a force call after a walk
+    } else if (cmd == "force") { // precision, interactions, rows, eps / r_cut: a force call after a walk
         const int prec = number(argc, argv, 2, 0);
         rep.pairs = strtoull(argv[3], nullptr, 10);
         rep.rows = strtoull(argv[4], nullptr, 10);
         rep.items = rep.rows ? 4 : 0;
-        const treepm_params p = params(prec ? TREEPM_FP64 : TREEPM_FP32);
+        treepm_params p = params(prec ? TREEPM_FP64 : TREEPM_FP32);
+        if (argc > 5) p.eps = p.r_cut * atof(argv[5]);
         const Arrays a(200000);
         treepm_stats st{};
         void *out = nullptr;
@@ -288,8 +289,8 @@ int main(int argc, char **argv)
         const size_t from = trace.size();
         const int before = mallocs;
         double *o = static_cast<double *>(out);
-        if (treepm_force_short(c, o, o + 200000, o + 400000, p.precision, TREEPM_DEVICE, nullptr))
-            return 1;
+        printf("force %d\n",
+               treepm_force_short(c, o, o + 200000, o + 400000, p.precision, TREEPM_DEVICE, nullptr));
         print(from);
         printf("allocations %d\n", mallocs - before);
         treepm_destroy(c);

@@ -109,3 +109,11 @@ def test_fp64_table_only_where_it_pays(run, pairs, table):
 def test_force_takes_no_memory(run, precision, pairs, rows):
     """With device outputs the force uses what the build and the walk allocated."""
     assert "allocations 0" in run("force", precision, pairs, rows)
+
+
+@pytest.mark.parametrize("ratio,rc", [("0.0001220703125", 0), ("0.016666666666666666", 0), ("1", 0),
+                                      ("7.9", 0), ("7.9999999999999", 0),
+                                      ("7.99999999999999911", 0), ("8", -1), ("9", -1)])
+def test_fp32_softening_range(run, ratio, rc):
+    """FP32 boxes have a table for every eps / r_cut in [2^-13, 8), to the last bit."""
+    assert f"force {rc}" in run("force", 0, 1000000, 0, ratio)
