@@ -105,16 +105,17 @@ void launch_keys(int64_t n, const double *x, const double *y, const double *z, c
 size_t sort_hist_elems(int64_t n);
 void radix_sort(int64_t n, uint64_t *key, uint32_t *idx, uint64_t *key_alt, uint32_t *idx_alt,
                 uint32_t *hist, uint32_t *scan_tmp, hipStream_t s);
-// The sort in two steps: stable passes over bits [run_bits, 64) only, then each run of equal
-// high bits sorted by (key, index) in place.  Returns true if the result is in key_alt /
-// idx_alt (an odd number of passes).  long_runs holds long_cap entries; flags (device, two
-// words, zeroed by the caller) ends with flags[1] != 0 if a run could not be sorted this way:
+// The sort in two steps: stable passes over bits [run_bits, 63) only, 63 - run_bits a multiple of 8,
+// then each run of equal high bits sorted by (key, index) in place.  Returns true if the result is
+// in key_alt / idx_alt (an odd number of passes).  long_runs holds long_cap entries; flags (device,
+// two words, zeroed by the caller) ends with flags[1] != 0 if a run could not be sorted this way:
 // the order is then incomplete, and a sort with fewer run_bits (or radix_sort) on the returned
 // arrays must follow (equal keys are still in index order).
-// sort_run_bits: the run_bits to try first, 40, 32 and 24 up to 2^16, 2^21 and more particles
-// (three, four or five passes; cells of level 8, 10.7 or 13.3).  In a clustered box the fullest
-// cell grows about as the square of its side: 43 particles at level 13.3 of the 256^3 box, and
-// so a few hundred at most at these limits, below kLongRun.
+// sort_run_bits: the run_bits to try first, 39, 31 and 23 up to 2^16, 2^21 and more particles
+// (three, four or five passes; cells of level 8, 10.7 and 13.3).  The fullest cells of clustered
+// boxes at those limits hold 451, 168 and, of 256^3 particles, 43; a pass less would meet runs of
+// 1,601 at 2^19 particles and of 3,774, more than kLongRun, at 2^21.
+constexpr int kLeastRunBits = 23;
 int sort_run_bits(int64_t n);
 constexpr uint32_t kShortRun = 64; // sorted within a tile of k_fix_runs
 constexpr uint32_t kLongRun = 2048;

@@ -1143,14 +1143,14 @@ size_t sort_hist_elems(int64_t n) { return (size_t)(n > 0 ? sort_tiles(n) : 1) *
 
 int sort_run_bits(int64_t n)
 {
-    return n <= (1 << 16) ? 40 : n <= (1 << 21) ? 32 : 24;
+    return n <= (1 << 16) ? 39 : n <= (1 << 21) ? 31 : kLeastRunBits;
 }
 
 // Up to this many tiles the scatter adds up the tiles' digit counts itself: every block then
 // reads tiles x 1 KB, and two to four launches of a pass fall away.
 constexpr uint32_t kSortFusedTiles = 256;
 
-// Stable LSD passes over bits [lo_bit, 64) of the keys, 8 bits per pass; an even number of
+// Stable LSD passes over bits [lo_bit, 63) of the keys, 8 bits per pass; an even number of
 // passes leaves the result in key / idx.
 static void radix_passes(int64_t n, int lo_bit, uint64_t *key, uint32_t *idx, uint64_t *key_alt,
                          uint32_t *idx_alt, uint32_t *hist, uint32_t *scan_tmp, hipStream_t s)
@@ -1159,7 +1159,7 @@ static void radix_passes(int64_t n, int lo_bit, uint64_t *key, uint32_t *idx, ui
     const bool small = sort_items(n) == 4, fused = nb <= kSortFusedTiles;
     uint64_t *kin = key, *kout = key_alt;
     uint32_t *iin = idx, *iout = idx_alt;
-    for (int shift = lo_bit; shift < 64; shift += kSortBits) {
+    for (int shift = lo_bit; shift < 63; shift += kSortBits) { // bit 63 is clear
         if (small) { // 2^18 keys are 256 tiles
             k_hist<4, true><<<nb, kSortThreads, 0, s>>>(kin, n, shift, hist, nb);
             k_scatter<4, true><<<nb, kSortThreads, 0, s>>>(kin, iin, n, shift, hist, nb, kout,
@@ -1185,7 +1185,7 @@ bool radix_sort_high(int64_t n, int run_bits, uint64_t *key, uint32_t *idx, uint
 {
     if (n <= 1) return false;
     radix_passes(n, run_bits, key, idx, key_alt, idx_alt, hist, scan_tmp, s);
-    const bool odd = ((64 - run_bits) / kSortBits) % 2 == 1;
+    const bool odd = ((63 - run_bits) / kSortBits) % 2 == 1;
     uint64_t *k = odd ? key_alt : key;
     uint32_t *v = odd ? idx_alt : idx;
     k_fix_runs<<<grid_for(n, kFixTile), 256, 0, s>>>(n, run_bits, k, v, long_runs, long_cap, flags,

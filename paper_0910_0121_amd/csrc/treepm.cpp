@@ -94,7 +94,7 @@ struct treepm_ctx {
     uint32_t *mbox_h = nullptr, *mbox_d = nullptr;
     uint32_t mseq = 0;
     uint32_t walk_hint_groups = 0;
-    // A sort of this context found runs too long for sort_run_bits: start from 24 bits.
+    // A sort of this context found runs too long for sort_run_bits: start from kLeastRunBits.
     bool sort_wide = false;
     int walk_passes = TREEPM_WALK_AUTO; // treepm_set_walk_passes
     size_t room = 0; // device bytes that the context's owner has for it (0: it does not say)
@@ -665,7 +665,7 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     // The input checks of k_keys and the sort's fallback flag (sorting invalid input first is
     // harmless: keys are clamped).  A run too long to be sorted in place means more high bits,
     // and in the end all of them.
-    int run_bits = c->sort_wide ? 24 : sort_run_bits(n);
+    int run_bits = c->sort_wide ? kLeastRunBits : sort_run_bits(n);
     sort_high(run_bits);
     unsigned fl[6] = {};
     auto check_input = [&]() -> int {
@@ -677,7 +677,7 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
     };
     auto complete_sort = [&]() -> int {
         while (fl[5]) {
-            if (run_bits == 24) {
+            if (run_bits == kLeastRunBits) {
                 radix_sort(n, c->key.as<uint64_t>(), c->idx.as<uint32_t>(),
                            c->key_alt.as<uint64_t>(), c->idx_alt.as<uint32_t>(),
                            c->hist.as<uint32_t>(), scan_tmp, s);
@@ -685,7 +685,7 @@ int do_build(treepm_ctx *c, int64_t n, const double *x, const double *y, const d
                 break;
             }
             c->sort_wide = true;
-            run_bits = 24;
+            run_bits = kLeastRunBits;
             fill_u32(sflags, 2, 0u, s);
             sort_high(run_bits);
             const int r = fetch(c, s, {fl, flags, sizeof fl});
