@@ -68,7 +68,8 @@ enum { TREEPM_OPEN_FIXED = 0, TREEPM_OPEN_DISTANCE = 1 }; /* opening criterion  
  *   n_crit   groups are the maximal nodes holding <= n_crit particles (or leaves); >= 1;
  *            0 selects the library default (128).
  *   precision TREEPM_FP32: pair force in FP32 on positions relative to the group's cube
- *            centre with compensated accumulation (Section 3.1.1); TREEPM_FP64: plain FP64.
+ *            centre, its sums over tiles of the list added up in FP64 (Section 3.1.1);
+ *            TREEPM_FP64: plain FP64.
  *            The tree, moments and every walk decision are FP64 in both cases.
  *   opening  TREEPM_OPEN_FIXED (0, the default of a zeroed struct): theta as above.
  *            TREEPM_OPEN_DISTANCE: the distance-dependent angle of Section 4.1, eq. (12),
@@ -116,9 +117,9 @@ typedef struct {
                                0 unless timing is enabled with treepm_set_timing          */
     int64_t evaluated;      /* pairs the last force call evaluated: both force kernels
                                skip list entries whose source lies at least r_cut from
-                               the bounding box of the group (FP32: of the run of its
-                               particles that is evaluated together; every pair they
-                               form adds exactly zero), so this is at most interactions  */
+                               the bounding box of the run of the group's particles that
+                               is evaluated together (every pair they form adds exactly
+                               zero), so this is at most interactions                    */
     double latency_ms;      /* ensemble results only: completion minus submission (ms)    */
     double queue_ms;        /* ensemble results only: start of service minus submission,
                                the part of latency_ms spent queued (ms)                  */

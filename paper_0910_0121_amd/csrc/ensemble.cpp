@@ -9,7 +9,7 @@
 // switched on (treepm_ens_set_batching) a built box instead waits in a ready list, and
 // whenever no batch is running the next free worker takes every ready box (up to kMaxBatch)
 // and runs their walks and forces together (treepm_force_short_batch: one traversal launch
-// and one launch per size class for all of them) while the other workers build the next
+// and one force launch per eps / r_cut) while the other workers build the next
 // boxes.  A box's context (its device buffers: particles, tree, lists) stays resident between
 // requests until evicted.  poll() is non-blocking.
 #include <algorithm>

@@ -360,10 +360,12 @@ constexpr int kBins = kXcds * kCostBuckets;
 // to write the 20,000 pieces of a box of 700,001).
 constexpr uint32_t kWriteHere = 1024;
 
-// t of the box (pairs: its interactions): 6,550 to 13,100 times 2^t in all.  Pieces of half of that
-// to that many pairs each are two to four for every wave.  Force calls of 250,007, 700,001 and, with
-// quadrupoles, 1,000,003 particles (12,100, 15,300 and 13,700 times 2^t): 1.17, 1.31 and 0.71
-// pairs per ps, with 2^t doubled 1.07, 1.53 and 0.82.
+// t of the box: its interactions (pairs) are 6,554 to 13,107 times 2^t.  Pieces of half of 2^t to 2^t
+// pairs each are two to four for every wave.  A force call's time over the best of all rows, geometric
+// mean over 68 boxes of 100,003 to 2,000,003 particles (four octaves of pairs; clustered and uniform,
+// groups of up to 64 and 256, with and without quadrupoles), by the least multiple of 2^t:
+//   3,277  4,096  4,681  5,461  6,554  8,192  13,107
+//   1.100  1.078  1.063  1.047  1.043  1.057   1.093
 __device__ __forceinline__ uint32_t piece_log2(unsigned long long pairs)
 {
     const unsigned long long v = (pairs >> 13) + (pairs >> 15);

@@ -369,8 +369,7 @@ __device__ __forceinline__ void g_derivs140_far(double R, double &g, double &g1,
 __device__ __forceinline__ double rsqrt_f64q(double x) { return 1.0 / sqrt(x); }
 
 // A cell as the kernel uses it: centre of mass relative to the group's cube centre, half the
-// trace of the moments, and the six moments, in the arithmetic type (three 16-byte LDS reads
-// in FP32).
+// trace of the moments, and the six moments.
 struct alignas(32) QuadCell64 {
     double x, y, z, htr, q0, q1, q2, q3, q4, q5, pad0, pad1;
 };

@@ -904,7 +904,7 @@ int prepare_walk(treepm_ctx *c, hipStream_t s, BoxWalk &bw)
     if ((e = reserve(c->gcells, ((size_t)G + 1) * 4)) != hipSuccess)
         return hip_fail(c, e, "group stats");
     if ((e = reserve(c->cls, (kClsLists + (size_t)G + 1) * 4)) != hipSuccess)
-        return hip_fail(c, e, "group classes");
+        return hip_fail(c, e, "force queues");
     if ((e = reserve(c->items, max_force_items((uint64_t)c->n, G) * sizeof(ForceItem))) != hipSuccess)
         return hip_fail(c, e, "group pieces");
     const treepm_params &P = c->prm;
@@ -1020,7 +1020,7 @@ int walk_two_pass(treepm_ctx *c, hipStream_t s, const BoxWalk &bw, bool ahead)
     return TREEPM_OK;
 }
 
-// Statistics and force classes of the lists, queued with the flags for the host.
+// Statistics of the lists and the force's queues, with the flags for the host.
 struct WalkResults {
     unsigned long long hs[6] = {};
     unsigned hov = 0;
@@ -1288,7 +1288,7 @@ TREEPM_API int treepm_create(const treepm_params *params, int device, treepm_ctx
     for (int i = 0; subs_ok && i < treepm_ctx::kSubStreams; ++i)
         subs_ok = hipStreamCreateWithFlags(&c->sub[i], hipStreamNonBlocking) == hipSuccess &&
                   hipEventCreateWithFlags(&c->join[i], hipEventDisableTiming) == hipSuccess;
-    if (!subs_ok) { // run the classes one after another on the call's stream
+    if (!subs_ok) { // the gather runs on the call's stream
         for (int i = 0; i < treepm_ctx::kSubStreams; ++i) {
             if (c->sub[i]) (void)hipStreamDestroy(c->sub[i]);
             if (c->join[i]) (void)hipEventDestroy(c->join[i]);
@@ -1697,8 +1697,8 @@ int upload(treepm_ctx *lead, hipStream_t s, const std::vector<T> &v, size_t at, 
 
 // The walk of boxes cs[0 .. nb) with shared launches: the boxes whose last walk sizes a pool
 // in one pass together, those whose last walk sizes slots likewise, the others in two passes
-// together (one host wait for all their list lengths); then every box's statistics and classes, and one wait for all of them.  A
-// box whose pool or slots were too small is walked again alone.  Each box ends exactly as treepm_walk
+// together (one host wait for all their list lengths); then every box's statistics and queues, and
+// one wait for all of them.  A box whose pool or slots were too small is walked again alone.  Each box ends exactly as treepm_walk
 // would leave it.
 int batch_walk(treepm_ctx *const *cs, int nb, hipStream_t s)
 {
