@@ -237,12 +237,12 @@ __device__ __forceinline__ uint32_t chunk_sums_f32(float4 *tile, int S, uint32_t
     return kept;
 }
 
-// What bounds it (256^3 clustered box, n_crit 256): the LDS pipe and the vector units, both nearly
-// always busy.  The kernel takes 10.6 ms, 1.85 pairs per ps.  As the fifth power of p, three
-// instructions fewer a pair, it was 10.0 ms with the LDS pipe 93 % and the vector units 80 % busy;
-// 12.4 with a kernel per blocking factor, a table of 16-byte entries and queue counters side by
-// side (311,000 groups taken through counters in one cache line alone cost about 12 ms, at 40 ns
-// each).  700,001 particles, build, walk and force: 3.44 -> 1.08 ms.
+// What bounds it (256^3 clustered box, n_crit 256): the LDS pipe is busy 91 % of the time and the
+// vector units 90 %.  The kernel takes 10.6 ms, 1.85 pairs per ps.  As the fifth power of p, three
+// instructions fewer a pair, it was 10.0 ms (93 and 80 %; 8.7 without the table reads); 12.4 with a
+// kernel per blocking factor, a table of 16-byte entries and queue counters side by side (311,000
+// groups taken through counters in one cache line alone cost about 12 ms, at 40 ns each).
+// 700,001 particles, build, walk and force: 3.44 -> 1.06 ms.
 struct PolicyF32 {
     static constexpr int kWaves = kForceWaves, kTilesAt = 0, kTileBytes = kTileF32 * 16;
     static constexpr uint32_t kQueueAt = kClsQueue;
